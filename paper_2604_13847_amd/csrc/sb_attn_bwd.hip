@@ -102,7 +102,6 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(2))) void 
       lse2 = P.lse[(int64_t)h * P.T + tq] * 1.4426950408889634f;
     }
     dr = part + __shfl_xor(part, 32, 64);
-    if (pos == 0 && blockIdx.y == 0 && tid == 0) P.lse2[(int64_t)P.Hq * P.T] = __builtin_inff();  // read by the key-major kernel in place of the LSE of rows that do not exist
   }
   stage_indices(0);
   // everything loaded so far must have landed before the tile loads start (see the forward kernel)
@@ -322,22 +321,24 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(2))) void 
 // in base 2 and Dr) of the query blocks that kept j are double-buffered in LDS by asynchronous
 // loads; both are read row-wise (S = Q K^T, dP = dO V^T) and through the transposing LDS read
 // (dV += P^T dO, dK += dS^T Q).
-// A tile is processed as two halves of 32 queries, software-pipelined so that the exponentials of
-// one half run under the matrix instructions of the other:
-//   S,dP(half 0);  S,dP(half 1) | P,dS(half 0);  dV,dK(half 0) | P,dS(half 1);  dV,dK(half 1)
-// Tiles that need a mask (the diagonal block, a ragged last query block) take a separate
-// instantiation of the tile body, so the common path has no per-element selects or branches.
 // The column's tiles are visited query block by query block, from the sequence's last query block
 // down to the diagonal, all query heads of the KV group at one query block before the next:
 // concurrent columns of one KV head (same XCD) start at the same query block, advance at a similar
 // pace and so ask for the same Q/dO tiles at about the same time and meet them in that XCD's L2.
+// What bounds it: one wavefront per SIMD (it needs more than 256 registers), so every wait is idle time of the matrix cores, and
+// under matrix load the chip runs at 1.6 - 1.8 GHz of its 2.4.  Hence the software pipeline over half tiles (32 queries) below:
+// every matrix instruction carries the same share of vector work and LDS reads, fenced step by step, results are used two
+// stages after they were started, and the tile loads are issued two at a time between matrix instructions instead of 17 in a
+// row.  The scores are kept out of the accumulation registers (mfma32_first).  32768-token batch, 32/8 heads, D = 128:
+// 3.66 -> 3.24 ms (matrix cores busy 48 -> 56 % of the cycles), block 256 at D = 64: 3.7 -> 3.35 ms, the 262144-token batch,
+// whose gathers come through the fabric at 6 TB/s: 36.7 -> 34.9 ms.
 template <int D, bool OUT_F32>
 __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void attn_bwd_dkv_kernel(AttnParams P) {
   constexpr int TILE_B = 64 * D * 2;  // bytes of one Q or dO tile
   constexpr int BUF_B = 2 * TILE_B;   // bytes of one buffer (Q tile, dO tile)
   constexpr int ROW_B = D * 2;
   __shared__ __attribute__((aligned(1024))) bf16 tiles[2][2][64 * D];  // [buffer][Q, dO]
-  __shared__ __attribute__((aligned(256))) float rowstat[2][2][64];    // [buffer][LSE * log2(e), Dr]
+  __shared__ __attribute__((aligned(256))) float rowstat[4][2][64];    // [buffer, half][LSE * log2(e), Dr]: 32 rows each, the other 32 unused
   constexpr int kCW = 16;            // bitmap words (32 query blocks each) handled per chunk
   __shared__ uint32_t bm_s[8][kCW];  // bitmap words of up to 8 selection heads
   __shared__ uint16_t tl_s[kCW * 32 * 8];  // the chunk's tiles in processing order
@@ -394,80 +395,75 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void a
   auto lds16 = [](unsigned a) __attribute__((always_inline)) { return *(const bf16x8 __attribute__((address_space(3)))*)a; };
   auto lds_f4 = [](unsigned a) __attribute__((always_inline)) { return *(const f32x4 __attribute__((address_space(3)))*)a; };
   constexpr int NOP = D / 16;  // operands (and matrix instructions) per pipeline stage
-  // A operands of S = Q K^T / dP = dO V^T: rows 32qt + lane%32 of the tile at byte offset `off`, all of d
-  auto ld_rows = [&](bf16x8* dst, unsigned off) __attribute__((always_inline)) {
-#pragma unroll
-    for (int ks = 0; ks < NOP; ++ks) dst[ks] = lds16(row_a[ks] + off);
-  };
-  // B operands of dV += P^T dO / dK += dS^T Q for the query steps kk0, kk0+1: contraction slots =
-  // queries 16kk + 8(e/4) + 4hf + e%4, column = d (32dt + lane%32), through the transposing read
-  auto ld_tr = [&](bf16x8* dst, unsigned off, int kk0) __attribute__((always_inline)) {
-#pragma unroll
-    for (int q = 0; q < 2; ++q)
-#pragma unroll
-      for (int dt = 0; dt < D / 32; ++dt) {
-        const unsigned o = off + (kk0 + q) * 16 * ROW_B;
-        bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((bf16x4 __attribute__((address_space(3)))*)(tr_a[dt][0] + o));
-        bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((bf16x4 __attribute__((address_space(3)))*)(tr_a[dt][1] + o));
-        dst[q * (D / 32) + dt] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-      }
+  // A operand ks of S = Q K^T / dP = dO V^T: rows lane%32 of the half tile at byte offset `off`, d 16ks + 8hf + (0..7)
+  auto ld_row = [&](int ks, unsigned off) __attribute__((always_inline)) { return lds16(row_a[ks] + off); };
+  // B operand x = kk * D/32 + dt of dV += P^T dO / dK += dS^T Q: contraction slots = queries 16kk + 8(e/4) + 4hf + e%4 of the
+  // half tile at byte offset `off`, column = d (32dt + lane%32), through the transposing read
+  auto ld_tr = [&](int x, unsigned off) __attribute__((always_inline)) {
+    const int kk = x / (D / 32), dt = x % (D / 32);
+    const unsigned o = off + kk * 16 * ROW_B;
+    bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((bf16x4 __attribute__((address_space(3)))*)(tr_a[dt][0] + o));
+    bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((bf16x4 __attribute__((address_space(3)))*)(tr_a[dt][1] + o));
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
   };
 
-  TileLoader<D> loader;
-  loader.init(P.Hq, wave, lane);
-  constexpr int kLoadsPerTile = 2 * TileLoader<D>::LPT + 1;  // asynchronous loads one wavefront issues per tile
-  auto issue = [&](int buf, int i, int h) __attribute__((always_inline)) {
-    const int64_t q0 = seq0 + (int64_t)i * 64;
-    const int qv = min(64, L - i * 64);
-    loader.issue(tiles[buf][0], P.q, q0, qv, P.Hq, h);
-    loader.issue(tiles[buf][1], P.d_o, q0, qv, P.Hq, h);
-    // 64 LSE and 64 Dr values: one 4-byte load per lane, wavefront 0 takes LSE and wavefront 1 Dr
-    // (rows past the end of the sequence read the +inf stored behind the LSE array: their P becomes 0)
-    const float* src = wave == 0 ? (lane < qv ? P.lse2 + (int64_t)h * P.T + q0 + lane : P.lse2 + (int64_t)P.Hq * P.T)
-                                 : P.drow + (int64_t)h * P.T + q0 + min(lane, qv - 1);
-    dma4(src, lds_offset(rowstat[buf][wave]));
+  // A half tile is 32 query rows: wavefront 0 loads its Q rows, wavefront 1 its dO rows, and each 32 of the rows' statistics
+  // (wavefront 0 the LSE, wavefront 1 Dr).  Rows past the end of the sequence arrive as zeros: their P is 1 and their dS 0,
+  // and both meet zero rows of dO and Q.
+  using Loader = RowLoader<D>;
+  Loader loader;
+  loader.init(P.Hq, lane);
+  constexpr int kLoadsPerHalf = Loader::LPS + 1;  // asynchronous loads one wavefront issues per half tile
+  const int pitch = P.Hq * D * 2;
+  const char* const src0 = (const char*)((wave == 0 ? P.q : P.d_o) + seq0 * P.Hq * D);
+  const float* const stat0 = (wave == 0 ? P.lse2 : P.drow) + seq0;
+  const unsigned dst0 = lds_offset(tiles[0][wave]), sdst0 = lds_offset(rowstat[0][wave]);
+  // where rows 32 half .. +31 of query block i, head h come from, and where they go
+  struct Half { Strip rows; unsigned long long stat; unsigned stat_bytes, stat_slot; };
+  auto half_of = [&](int buf, int half, int i, int h) __attribute__((always_inline)) {
+    const int r0 = i * 64 + half * 32;
+    Half x;
+    x.rows = Loader::strip(dst0 + buf * BUF_B + half * 32 * ROW_B, src0 + ((int64_t)r0 * P.Hq + h) * (D * 2), L - r0, pitch);
+    x.stat = uniform((unsigned long long)(stat0 + (int64_t)h * P.T + r0));
+    x.stat_bytes = uniform((unsigned)max(L - r0, 0) * 4u);
+    x.stat_slot = sdst0 + (2 * buf + half) * 512;
+    return x;
+  };
+  auto issue_half = [&](Half x) __attribute__((always_inline)) {
+    load_floats(x.stat_slot, x.stat, x.stat_bytes, lane);
+    loader.issue(x.rows);
   };
 
-  f32x16 sacc[2], dpacc[2];
-  bf16x8 pa[4], dsa[4];
-  bf16x8 opA[NOP], opB[NOP];
-  // causal mask inside the diagonal tile (raw scores of queries 32qt .. 32qt+31)
-  auto mask_diag = [&](int qt) __attribute__((always_inline)) {
-#pragma unroll
-    for (int v = 0; v < 16; ++v)
-      if (kloc > 32 * qt + c_row(v, hf)) sacc[qt][v] = -__builtin_inff();
-  };
-  // P = exp2(S c - lse2), dS = P (dP - Dr), both to bf16, for registers 4vg .. 4vg+3 = query rows
-  // 32qt + 8vg + 4hf + (0..3).  The rows' statistics are fetched from LDS one stage ahead (ld_stat)
-  // so that no stage has to wait for them.
-  f32x4 st_ls[2], st_dd[2];
-  auto ld_stat = [&](int slot, unsigned so, int qt, int vg) __attribute__((always_inline)) {
-    st_ls[slot] = lds_f4(stat_a + so + (32 * qt + 8 * vg) * 4);
-    st_dd[slot] = lds_f4(stat_a + so + 256 + (32 * qt + 8 * vg) * 4);
-  };
-  auto pointwise = [&](int slot, int qt, int vg) __attribute__((always_inline)) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int v = 4 * vg + c;
-      const float pv = fast_exp2(__builtin_fmaf(sacc[qt][v], P.scale_log2e, -st_ls[slot][c]));
-      pa[2 * qt + (v >> 3)][v & 7] = (bf16)pv;
-      dsa[2 * qt + (v >> 3)][v & 7] = (bf16)(pv * (dpacc[qt][v] - st_dd[slot][c]));
+  f32x16 sacc[2], dpacc[2];  // [half]: scores, then (in place) probabilities; dP
+  bf16x8 pa[2][2], dsa[2];   // P [half][16 queries] and dS [16 queries] as operands
+  bf16x8 op[NOP];  // one rotating operand set: a register is refilled for the next stage right after the matrix instruction that used it
+  f32x4 st_l[2], st_d[2];    // LSE and Dr of the rows 8vg + 4hf + (0..3) of a half tile, vg even / odd
+  auto ld_stat = [&](unsigned so, int vg) __attribute__((always_inline)) { return lds_f4(stat_a + so + 32 * vg); };
+  // P = exp2(S c - lse2) of register v of a half tile (query row 32 half + 8(v/4) + 4hf + v%4), in place, and to bf16 in pairs;
+  // once the last row of a group of four has been used, the statistics two groups on are fetched in its place
+  auto prob = [&](auto diag_c, int half, int v, unsigned so) __attribute__((always_inline)) {
+    float pv = fast_exp2(__builtin_fmaf(sacc[half][v], P.scale_log2e, -st_l[(v >> 2) & 1][v & 3]));
+    if (decltype(diag_c)::value && kloc > 32 * half + c_row(v, hf)) pv = 0.f;  // causal mask inside the diagonal tile
+    sacc[half][v] = pv;
+    if (v & 1) {
+      pa[half][v >> 3][(v & 7) - 1] = (bf16)sacc[half][v - 1];
+      pa[half][v >> 3][v & 7] = (bf16)pv;
     }
+    if ((v & 3) == 3 && v < 8) st_l[(v >> 2) & 1] = ld_stat(so, (v >> 2) + 2);
   };
-#define SB_STAGE_FENCE() __builtin_amdgcn_sched_barrier(0)
-// scheduling groups for one stage: NOP x (1 matrix instruction, nds LDS reads, nvalu vector ALU instructions)
-#define SB_PIPE(nds, nvalu)                                                     \
-  _Pragma("unroll") for (int i_ = 0; i_ < NOP; ++i_) {                          \
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                          \
-    if ((nds) > 0) __builtin_amdgcn_sched_group_barrier(0x100, (nds), 0);       \
-    if ((nvalu) > 0) __builtin_amdgcn_sched_group_barrier(0x002, (nvalu), 0);   \
-  }
+  auto dscore = [&](int half, int v, unsigned so) __attribute__((always_inline)) {  // dS = P (dP - Dr), likewise
+    dpacc[half][v] = sacc[half][v] * (dpacc[half][v] - st_d[(v >> 2) & 1][v & 3]);
+    if (v & 1) {
+      dsa[v >> 3][(v & 7) - 1] = (bf16)dpacc[half][v - 1];
+      dsa[v >> 3][v & 7] = (bf16)dpacc[half][v];
+    }
+    if ((v & 3) == 3 && v < 8) st_d[(v >> 2) & 1] = ld_stat(so + 256, (v >> 2) + 2);
+  };
 
   const int words = (n + 31) >> 5;
   const bool per_qhead = P.mode == SB_SELECT_PER_QHEAD;
   const int nsel = per_qhead ? P.G : 1;      // bitmap columns (selection heads) of this KV head
   const int hpe = per_qhead ? 1 : P.G;       // query heads each set bit stands for
-  int tt = 0;                                // tiles of the chunk processed so far: tile tt lives in buffer tt & 1
   for (int sel0 = 0; sel0 < nsel; sel0 += 8) {                  // selection heads in groups of 8
     const int ns8 = min(8, nsel - sel0);
     for (int wend = whi, w0; wend > wlo; wend = w0) {  // chunks of up to kCW bitmap words, last first
@@ -520,151 +516,147 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void a
         nd = __builtin_amdgcn_readfirstlane(nd);
       }
 #pragma unroll
-      for (int ks = 0; ks < D / 16; ++ks) asm volatile("" : "+v"(kf[ks]), "+v"(vf[ks]));
+      for (int ks = 0; ks < D / 16; ++ks) asm volatile("" : "+a"(kf[ks]), "+a"(vf[ks]));
       auto entry = [&](int t, int& i, int& h) __attribute__((always_inline)) {
         const int e = __builtin_amdgcn_readfirstlane((int)tl_s[ntl - 1 - t]);
         i = 32 * w0 + (e >> 3);
         h = g * P.G + sel0 + (e & 7);
       };
-      // ---- prologue: tiles 0 and 1 in flight, the first operands of tile 0 on their way to registers
-      tt = 0;  // every chunk starts in buffer 0 (the barrier above has drained the loads and reads of the previous one)
+      // ---- software pipeline over half tiles u = 0, 1, ...: four stages of NOP matrix instructions each,
+      //   S(u), dP(u), dV(u-1), dK(u-1)
+      // with P(u) spread under the last two and dS(u-1) under the first two, so that every matrix instruction has the same
+      // share of vector work beside it and nothing waits for a result of the stage before.  The operands of a stage are
+      // fetched from LDS while the previous one computes.  Half tile u-1 has been read when stage dK(u-1) begins: after a
+      // barrier its buffer takes the loads of half tile u+3, two at a time.
+      int i1, h1;  // the newest tile that loads have been issued for
       {
         int i0, h0;
         entry(0, i0, h0);
-        issue(tt & 1, i0, h0);
-        if (ntl > 1) {
-          entry(1, i0, h0);
-          issue((tt + 1) & 1, i0, h0);
-          wait_vmcnt<kLoadsPerTile>();
-        } else {
-          wait_vmcnt<0>();
-        }
+        issue_half(half_of(0, 0, i0, h0));
+        issue_half(half_of(0, 1, i0, h0));
       }
+      entry(min(1, ntl - 1), i1, h1);
+      Half nxt = half_of(1, 0, i1, h1);
+      issue_half(nxt);
+      wait_vmcnt<2 * kLoadsPerHalf>();
       __builtin_amdgcn_s_barrier();
-      ld_rows(opA, 0);
-      // ---- one tile per iteration, eight stages of NOP matrix instructions each; the operands of a
-      // stage are fetched from LDS while the previous stage computes, and the pointwise work of one half
-      // tile is spread under the matrix instructions of the next stages.  The instruction mix of every
-      // stage is pinned with scheduling groups: one matrix instruction, then its share of the LDS reads
-      // and of the vector arithmetic.
-      // BUF = 0 / 1: the tile's buffer is known at compile time and is an immediate offset of every LDS read;
-      // BUF = -1: it is tt & 1 and the offsets are added per tile
-      auto tile = [&](auto diag_c, auto buf_c, int t) __attribute__((always_inline)) {
-          constexpr bool DIAG = decltype(diag_c)::value;
-          constexpr int BUF = decltype(buf_c)::value;
-          const int buf = BUF >= 0 ? BUF : (tt & 1);
-          const unsigned BO = buf * BUF_B, NBO = (1 - buf) * BUF_B, SO = buf * 512;
-          const int e2 = t + 2 < ntl ? (int)tl_s[ntl - 3 - t] : 0;
-          // stage 0: S(queries 0..31)
-          ld_rows(opB, BO + TILE_B);
-          sacc[0] = zero16();
 #pragma unroll
-          for (int ks = 0; ks < NOP; ++ks) sacc[0] = mfma32(opA[ks], kf[ks], sacc[0]);
-          SB_PIPE(1, 0);
-          SB_STAGE_FENCE();
-          // stage 1: dP(queries 0..31)
-          ld_rows(opA, BO + 32 * ROW_B);
-          ld_stat(0, SO, 0, 0);
-          ld_stat(1, SO, 0, 1);
-          dpacc[0] = zero16();
+      for (int ks = 0; ks < NOP; ++ks) op[ks] = ld_row(ks, 0);
+      // one half tile: HALF of tile t, whose buffer is `buf`.  FIRST: nothing precedes it; LAST: there is no half tile u any
+      // more, only dV and dK of u-1 are left.  Loads are issued past the chunk's last tile too (its last tile once more, never
+      // read), so that their number in flight is the same everywhere.
+      auto half_tile = [&](auto first_c, auto last_c, auto diag_c, auto half_c, int buf, int t) __attribute__((always_inline)) {
+        constexpr bool FIRST = decltype(first_c)::value, LAST = decltype(last_c)::value;
+        constexpr int HALF = decltype(half_c)::value, PREV = 1 - HALF, LPS = Loader::LPS;
+        const unsigned CO = buf * BUF_B + HALF * 32 * ROW_B;                               // half tile u
+        const unsigned PO = (HALF ? buf : 1 - buf) * BUF_B + PREV * 32 * ROW_B;             // u - 1
+        const unsigned NO = (HALF ? 1 - buf : buf) * BUF_B + PREV * 32 * ROW_B;             // u + 1
+        const unsigned SO = (2 * buf + HALF) * 512, PSO = (HALF ? 2 * buf : 2 * (1 - buf) + 1) * 512;
+        int e2 = 0;
+        constexpr int EPS = 8 / NOP;  // rows (accumulator registers) of the pointwise work per matrix instruction
+        // Every step is fenced: one matrix instruction, the refill of its operand, its share of the vector work.
+#define SB_FENCE() __builtin_amdgcn_sched_barrier(0)
+        SB_FENCE();
+        if (!LAST && HALF == 1) e2 = (int)tl_s[max(ntl - 3 - t, 0)];
 #pragma unroll
-          for (int ks = 0; ks < NOP; ++ks) dpacc[0] = mfma32(opB[ks], vf[ks], dpacc[0]);
-          SB_PIPE(2, 0);
-          SB_STAGE_FENCE();
-          // stage 2: S(queries 32..63) | first half of the pointwise work of queries 0..31
-          if (DIAG) mask_diag(0);
-          ld_rows(opB, BO + TILE_B + 32 * ROW_B);
-          sacc[1] = zero16();
-#pragma unroll
-          for (int ks = 0; ks < NOP; ++ks) sacc[1] = mfma32(opA[ks], kf[ks], sacc[1]);
-          pointwise(0, 0, 0);
-          pointwise(1, 0, 1);
-          SB_PIPE(1, 8);
-          SB_STAGE_FENCE();
-          ld_stat(0, SO, 0, 2);
-          ld_stat(1, SO, 0, 3);
-          SB_STAGE_FENCE();
-          // stage 3: dP(queries 32..63) | second half
-          ld_tr(opA, BO + TILE_B, 0);
-          dpacc[1] = zero16();
-#pragma unroll
-          for (int ks = 0; ks < NOP; ++ks) dpacc[1] = mfma32(opB[ks], vf[ks], dpacc[1]);
-          pointwise(0, 0, 2);
-          pointwise(1, 0, 3);
-          SB_PIPE(2, 8);
-          SB_STAGE_FENCE();
-          ld_stat(0, SO, 1, 0);
-          ld_stat(1, SO, 1, 1);
-          SB_STAGE_FENCE();
-          // stage 4: dV += P^T dO over queries 0..31 | first half of the pointwise work of queries 32..63
-          if (DIAG) mask_diag(1);
-          ld_tr(opB, BO, 0);
-#pragma unroll
-          for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int dt = 0; dt < D / 32; ++dt) dvacc[dt] = mfma32(pa[q], opA[q * (D / 32) + dt], dvacc[dt]);
-          pointwise(0, 1, 0);
-          pointwise(1, 1, 1);
-          SB_PIPE(2, 8);
-          SB_STAGE_FENCE();
-          ld_stat(0, SO, 1, 2);
-          ld_stat(1, SO, 1, 3);
-          SB_STAGE_FENCE();
-          // stage 5: dK += dS^T Q over queries 0..31 | second half
-          ld_tr(opA, BO + TILE_B, 2);
-#pragma unroll
-          for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int dt = 0; dt < D / 32; ++dt) dkacc[dt] = mfma32(dsa[q], opB[q * (D / 32) + dt], dkacc[dt]);
-          pointwise(0, 1, 2);
-          pointwise(1, 1, 3);
-          SB_PIPE(2, 8);
-          SB_STAGE_FENCE();
-          // stage 6: dV over queries 32..63
-          ld_tr(opB, BO, 2);
-#pragma unroll
-          for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int dt = 0; dt < D / 32; ++dt) dvacc[dt] = mfma32(pa[2 + q], opA[q * (D / 32) + dt], dvacc[dt]);
-          SB_PIPE(2, 0);
-          SB_STAGE_FENCE();
-          // stage 7: dK over queries 32..63.  Its operands are the last LDS reads of this tile: once they
-          // have arrived the buffer is free, and once the next tile has landed everywhere (barrier) its
-          // first operands can be fetched under this stage's matrix instructions.
-          asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-          __builtin_amdgcn_s_barrier();
-          if (t + 2 < ntl) {
-            const int e = __builtin_amdgcn_readfirstlane(e2);
-            issue(buf, 32 * w0 + (e >> 3), g * P.G + sel0 + (e & 7));
+        for (int k = 0; k < NOP; ++k) {
+          if (!LAST) {
+            if (k == 0) mfma32_first(sacc[HALF], op[k], kf[k]);
+            else mfma32_more(sacc[HALF], op[k], kf[k]);
+            op[k] = ld_row(k, CO + TILE_B);
           }
-          SB_STAGE_FENCE();
-          ld_rows(opA, NBO);  // (after the last tile of the chunk this reads a stale buffer and is not used)
+          if (!FIRST)
 #pragma unroll
-          for (int q = 0; q < 2; ++q)
+            for (int e = 0; e < EPS; ++e) dscore(PREV, EPS * k + e, PSO);
+          SB_FENCE();
+        }
+        if constexpr (!FIRST && !LAST && LPS > 4) loader.template issue2<LPS - 4>(nxt.rows);
+        if (!LAST) { st_l[0] = ld_stat(SO, 0); st_l[1] = ld_stat(SO, 1); }
+        SB_FENCE();
 #pragma unroll
-            for (int dt = 0; dt < D / 32; ++dt) dkacc[dt] = mfma32(dsa[2 + q], opB[q * (D / 32) + dt], dkacc[dt]);
-          SB_PIPE(1, 0);
-          SB_STAGE_FENCE();
-          ++tt;
+        for (int k = 0; k < NOP; ++k) {
+          if (!LAST) {
+            if (k == 0) mfma32_first(dpacc[HALF], op[k], vf[k]);
+            else mfma32_more(dpacc[HALF], op[k], vf[k]);
+          }
+          if (!FIRST) {
+            op[k] = ld_tr(k, PO + TILE_B);
+#pragma unroll
+            for (int e = 0; e < EPS; ++e) dscore(PREV, 8 + EPS * k + e, PSO);
+          }
+          SB_FENCE();
+        }
+        if constexpr (!FIRST && !LAST) loader.template issue2<LPS - 2>(nxt.rows);
+        SB_FENCE();
+#pragma unroll
+        for (int k = 0; k < NOP; ++k) {
+          if (!FIRST) {
+            dvacc[k % (D / 32)] = mfma32(pa[PREV][k / (D / 32)], op[k], dvacc[k % (D / 32)]);
+            op[k] = ld_tr(k, PO);
+          }
+          if (!LAST)
+#pragma unroll
+            for (int e = 0; e < EPS; ++e) prob(diag_c, HALF, EPS * k + e, SO);
+          if (!LAST && k == NOP / 2) {  // scalar work for the loads below, while matrix instructions run
+            if (HALF == 1) {
+              const int e = __builtin_amdgcn_readfirstlane(e2);
+              i1 = 32 * w0 + (e >> 3);
+              h1 = g * P.G + sel0 + (e & 7);
+            }
+            nxt = half_of(HALF == 0 ? 1 - buf : buf, PREV, i1, h1);
+          }
+          SB_FENCE();
+        }
+        if (!LAST) {
+          // half tile u - 1 has been read by this wavefront and its part of u + 1 has landed
+          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(kLoadsPerHalf) : "memory");
+          __builtin_amdgcn_s_barrier();
+          st_d[0] = ld_stat(SO + 256, 0);
+          st_d[1] = ld_stat(SO + 256, 1);
+          load_floats(nxt.stat_slot, nxt.stat, nxt.stat_bytes, lane);
+          SB_FENCE();
+        }
+#pragma unroll
+        for (int k = 0; k < NOP; ++k) {
+          if (!FIRST) dkacc[k % (D / 32)] = mfma32(dsa[k / (D / 32)], op[k], dkacc[k % (D / 32)]);
+          if (!LAST) {
+            op[k] = ld_row(k, NO);  // (after the last half tile of the chunk this reads a stale buffer and is not used)
+#pragma unroll
+            for (int e = 0; e < EPS; ++e) prob(diag_c, HALF, 8 + EPS * k + e, SO);
+          }
+          SB_FENCE();
+          if constexpr (!LAST) {
+            if (k == 0) loader.template issue2<0>(nxt.rows);
+            if constexpr (LPS > 4) { if (k == NOP / 2) loader.template issue2<2>(nxt.rows); }
+            SB_FENCE();
+          }
+        }
+#undef SB_FENCE
       };
       {
-        using B0 = std::integral_constant<int, 0>;
-        using B1 = std::integral_constant<int, 1>;
-        using BR = std::integral_constant<int, -1>;
-        const int nn = ntl - nd;  // tiles without a mask: in pairs, the chunk starts in buffer 0
-        int t = 0;
+        using std::true_type;
+        using std::false_type;
+        using H0 = std::integral_constant<int, 0>;
+        using H1 = std::integral_constant<int, 1>;
+        const int nn = ntl - nd;  // tiles without a mask
+        auto tile = [&](auto first_c, auto diag_c, int buf, int t) __attribute__((always_inline)) {
+          half_tile(first_c, false_type(), diag_c, H0(), buf, t);
+          half_tile(false_type(), false_type(), diag_c, H1(), buf, t);
+        };
+        int t = 1;
+        if (nn > 0) tile(true_type(), false_type(), 0, 0);
+        else tile(true_type(), true_type(), 0, 0);
         for (; t + 2 <= nn; t += 2) {
-          tile(std::false_type(), B0(), t);
-          tile(std::false_type(), B1(), t + 1);
+          tile(false_type(), false_type(), 1, t);
+          tile(false_type(), false_type(), 0, t + 1);
         }
-        if (t < nn) tile(std::false_type(), B0(), t++);
-        for (; t < ntl; ++t) tile(std::true_type(), BR(), t);  // the diagonal tiles
+        if (t < nn) { tile(false_type(), false_type(), 1, t); ++t; }
+        for (; t < ntl; ++t) tile(false_type(), true_type(), t & 1, t);  // the diagonal tiles
+        half_tile(false_type(), true_type(), false_type(), H0(), ntl & 1, ntl);
+        wait_vmcnt<0>();  // the loads past the last tile
       }
-
     }
   }
-#undef SB_PIPE
-#undef SB_STAGE_FENCE
   // C layout: column = d (32dt + l32), register v = key row c_row(v, hf) of this wavefront's strip
   if (item.slot >= 0) {  // a part of a split column: leave the fp32 partial sums for the reduction
     float* part = P.partials + (size_t)item.slot * (2 * 64 * D);

@@ -5,7 +5,7 @@
 //   B (16 x 32): col = lane%32, the 8 elements are contraction slots (half, 0..7)
 //   C (32 x 32): col = lane%32, register v is row 8*(v/4) + 4*half + v%4
 // A and B only have to agree on which contraction index sits in slot (half, e); the kernels choose
-// that mapping freely (see key_of_slot below).
+// that mapping freely (see c_row below).
 #pragma once
 
 #include "sb_internal.h"
@@ -17,7 +17,7 @@ struct AttnParams {
   void* o;            // forward output (bf16 or float per out_f32)
   float* lse;         // [Hq][T]
   float* drow;        // [Hq][T] rowsum(dO * O): written by the dQ kernel, read by the dK/dV kernel
-  float* lse2;        // [Hq][T] lse * log2(e), likewise; entry [Hq*T] is +inf (stands in for rows that do not exist)
+  float* lse2;        // [Hq][T] lse * log2(e), likewise
   void* dq; void* dk; void* dv;
   const int32_t* rowptr; const int32_t* idx; const int32_t* work;
   const WorkItem* items;  // descriptors of the query-major items, in work order
@@ -63,6 +63,17 @@ __device__ inline f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+// The same with the accumulator in arithmetic registers and the B operand in accumulation registers: in a kernel that needs more
+// than 256 registers the compiler would put every accumulator into accumulation registers and copy the scores out one by one.
+// It does not see these as matrix instructions: the caller keeps at least 12 wait states (half a stage of matrix instructions)
+// between the last of a chain and the first reader of its result.
+__device__ inline void mfma32_first(f32x16& c, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(c) : "v"(a), "a"(b));
+}
+__device__ inline void mfma32_more(f32x16& c, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "a"(b));
+}
+
 __device__ inline f32x16 zero16() {
   f32x16 z;
 #pragma unroll
@@ -83,60 +94,6 @@ __device__ inline int c_row(int v, int hf) { return 8 * (v >> 2) + 4 * hf + (v &
 // A 64-long contraction axis (keys or queries of one block) is walked in 4 steps of 16; step kk,
 // slot (hf, e) holds element 16*kk + 8*(e/4) + 4*hf + e%4, which is exactly the row of C register
 // 8*(kk%2)+e of the (kk/2)-th 32x32 tile: a C tile converts to an A/B operand without any shuffle.
-// In LDS the transposed tiles keep that element at position 16*kk + 8*hf + e (position_of_quad), so
-// the 8 slots of a lane are one 16-byte read.
-__device__ inline int position_of_quad(int quad) {  // quad = element/4 (0..15) -> position/4
-  return (quad & ~3) | ((quad & 1) << 1) | ((quad >> 1) & 1);
-}
-
-__device__ inline uint4 ld16(const void* p) { return *(const uint4*)p; }
-
-// Cooperative copy of a 64 x D bf16 tile (rows `row0..row0+valid-1` of a [T][H][D] tensor, head h;
-// rows >= valid are zero) into LDS, row-major with padded row length LD.
-template <int D, int LD>
-__device__ inline void load_tile_rowmajor(bf16* dst, const bf16* src, int64_t row0, int valid, int H, int h, int tid, int nthr) {
-  for (int u = tid; u < 64 * (D / 8); u += nthr) {
-    const int r = u / (D / 8), c = u % (D / 8);
-    uint4 x = make_uint4(0, 0, 0, 0);
-    if (r < valid) x = ld16(src + ((row0 + r) * H + h) * D + 8 * c);
-    *(uint4*)(dst + r * LD + 8 * c) = x;
-  }
-}
-
-// Same tile written transposed: dst[d][position(row)] with row length LDT (>= 64), so that a lane
-// reading 8 consecutive elements of a d-row gets its 8 contraction slots.  Optionally also writes
-// the row-major copy (dst_rm != nullptr) from the same loads.
-template <int D, int LD, int LDT>
-__device__ inline void load_tile_transposed(bf16* dst_t, bf16* dst_rm, const bf16* src, int64_t row0, int valid, int H, int h,
-                                            int tid, int nthr) {
-  for (int u = tid; u < 16 * (D / 8); u += nthr) {
-    const int c = u % (D / 8), quad = u / (D / 8);
-    uint4 x[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = 4 * quad + r;
-      x[r] = make_uint4(0, 0, 0, 0);
-      if (row < valid) x[r] = ld16(src + ((row0 + row) * H + h) * D + 8 * c);
-      if (dst_rm) *(uint4*)(dst_rm + row * LD + 8 * c) = x[r];
-    }
-    const int pos = 4 * position_of_quad(quad);
-    const uint32_t* w0 = (const uint32_t*)&x[0];
-    const uint32_t* w1 = (const uint32_t*)&x[1];
-    const uint32_t* w2 = (const uint32_t*)&x[2];
-    const uint32_t* w3 = (const uint32_t*)&x[3];
-#pragma unroll
-    for (int dw = 0; dw < 4; ++dw) {  // dword dw holds d = 8c + 2dw (low half) and 8c + 2dw + 1 (high half)
-      uint2 lo, hi;
-      lo.x = (w0[dw] & 0xffffu) | (w1[dw] << 16);
-      lo.y = (w2[dw] & 0xffffu) | (w3[dw] << 16);
-      hi.x = (w0[dw] >> 16) | (w1[dw] & 0xffff0000u);
-      hi.y = (w2[dw] >> 16) | (w3[dw] & 0xffff0000u);
-      *(uint2*)(dst_t + (8 * c + 2 * dw) * LDT + pos) = lo;
-      *(uint2*)(dst_t + (8 * c + 2 * dw + 1) * LDT + pos) = hi;
-    }
-  }
-}
-
 
 // ---------------------------------------------------------------------------------------------
 // Asynchronous tile staging.  A 64 x D bf16 tile lives in LDS unpadded (row r at byte r*2D), with
@@ -164,11 +121,6 @@ __device__ inline unsigned lds_offset(const void* p) {
 
 __device__ inline void dma16(const void* gptr, unsigned lds_base) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(gptr), "s"(lds_base) : "memory", "m0");
-}
-
-// 4 bytes per lane: the wavefront's 256 bytes land at lds_base + 4*lane
-__device__ inline void dma4(const void* gptr, unsigned lds_base) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" : : "v"(gptr), "s"(lds_base) : "memory", "m0");
 }
 
 // s_waitcnt vmcnt(N) only (the other counters stay unconstrained).  The memory clobber keeps the
@@ -314,35 +266,55 @@ struct StripLoader {
     }
   }
 };
-template <int D>
-constexpr int loads_per_tile() { return D / 16; }
 
-// 8 consecutive elements (chunk c) of row r
-template <int D>
-__device__ inline bf16x8 lds_row8(const bf16* slot, int r, int c) {
-  return *(const bf16x8*)(slot + r * D + 8 * (c ^ chunk_swizzle<D>(r)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+
+// One wavefront copies a strip of 32 rows of one head of a [T][H][D] tensor into LDS (layout as above) with buffer loads: the
+// buffer resource covers the rows that exist, and rows past it arrive as zeros without a branch or a per-lane clamp.
+// The resource is put together by scalar instructions inside the block: a scalar register written by a vector instruction
+// (readfirstlane) must not be read by a vector-memory instruction within 5 wait states, while scalar reads of it are
+// interlocked.  M0 needs one wait state before the load that uses it.
+__device__ inline unsigned uniform(unsigned x) { return (unsigned)__builtin_amdgcn_readfirstlane((int)x); }
+__device__ inline unsigned long long uniform(unsigned long long x) {
+  return ((unsigned long long)uniform((unsigned)(x >> 32)) << 32) | (unsigned long long)uniform((unsigned)(x & 0xffffffffull));
 }
-
-// Transposing read (ds_read_b64_tr_b16): within each group of 16 lanes, lane x supplies the address
-// of 4 consecutive elements of row r0 + x/4 starting at column dbase + 4*(x%4), and receives the 4
-// elements of column dbase + x from rows r0 .. r0+3.
+struct Strip { unsigned long long base; unsigned bytes, slot; };  // first row's head slice, bytes that exist from there, LDS address
 template <int D>
-__device__ inline bf16x4 lds_tr4(const bf16* slot, int r0, int dbase, int lane16) {
-  const int r = r0 + (lane16 >> 2), d = dbase + 4 * (lane16 & 3);
-  const bf16* p = slot + r * D + 8 * ((d >> 3) ^ chunk_swizzle<D>(r)) + (d & 7);
-  return __builtin_amdgcn_ds_read_tr16_b64_v4bf16((bf16x4 __attribute__((address_space(3)))*)p);
+struct RowLoader {
+  static constexpr int C = D / 8, RPI = 64 / C, LPS = 32 / RPI;  // 16-byte chunks per row, rows per load, loads per strip
+  unsigned voff[LPS];
+  __device__ inline void init(int H, int lane) {
+#pragma unroll
+    for (int a = 0; a < LPS; ++a) {
+      const int r = a * RPI + lane / C;
+      voff[a] = (unsigned)(r * H * D * 2 + 16 * ((lane % C) ^ chunk_swizzle<D>(r)));
+    }
+  }
+  // `first`: the first row's head slice (wave-uniform); `valid` rows exist (<= 0: none); `pitch`: bytes from row to row
+  __device__ static inline Strip strip(unsigned slot, const char* first, int valid, int pitch) {
+    return Strip{uniform((unsigned long long)first), uniform(valid > 0 ? (unsigned)((min(valid, 32) - 1) * pitch + D * 2) : 0u), slot};
+  }
+  template <int A>
+  __device__ inline void issue2(Strip x) const {  // loads A, A+1 of the strip
+    asm volatile("s_add_u32 m0, %2, %3\n\ts_mov_b64 s[84:85], %5\n\ts_mov_b32 s86, %6\n\ts_mov_b32 s87, 0x20000\n\t"
+                 "buffer_load_dwordx4 %0, s[84:87], 0 offen lds\n\ts_add_u32 m0, %2, %4\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %1, s[84:87], 0 offen lds"
+                 : : "v"(voff[A]), "v"(voff[A + 1]), "s"(x.slot), "n"(A * 1024), "n"(A * 1024 + 1024), "s"(x.base), "s"(x.bytes)
+                 : "memory", "m0", "scc", "s84", "s85", "s86", "s87");
+  }
+  __device__ inline void issue(Strip x) const {
+    issue2<0>(x);
+    issue2<2>(x);
+    if constexpr (LPS > 4) { issue2<4>(x); issue2<6>(x); }
+  }
+};
+// the first `bytes` of 64 consecutive floats from `src` (both wave-uniform) to LDS, the rest as zeros
+__device__ inline void load_floats(unsigned slot, unsigned long long src, unsigned bytes, int lane) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 s[84:85], %2\n\ts_mov_b32 s86, %3\n\ts_mov_b32 s87, 0x20000\n\t"
+               "buffer_load_dword %0, s[84:87], 0 offen lds"
+               : : "v"(4 * lane), "s"(slot), "s"(src), "s"(bytes)
+               : "memory", "m0", "s84", "s85", "s86", "s87");
 }
-
-// A/B operand whose 8 contraction slots are rows 16*kk + 8*(e/4) + 4*hf + e%4 of the tile and whose
-// MFMA row/column is tile column 32*dt + lane%32.
-template <int D>
-__device__ inline bf16x8 lds_tr_operand(const bf16* slot, int kk, int dt, int lane) {
-  const int hf = lane >> 5, lane16 = lane & 15, dbase = 32 * dt + 16 * ((lane >> 4) & 1);
-  bf16x4 lo = lds_tr4<D>(slot, 16 * kk + 4 * hf, dbase, lane16);
-  bf16x4 hi = lds_tr4<D>(slot, 16 * kk + 8 + 4 * hf, dbase, lane16);
-  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-}
-
 // x * f for an accumulator element that lives in an accumulation register.  Written as one opaque
 // block so that the copies to and from the arithmetic registers stay inside the (rarely taken)
 // branch that needs them instead of being hoisted into the main loop.

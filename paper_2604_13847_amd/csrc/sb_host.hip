@@ -189,7 +189,7 @@ static WsOffsets ws_offsets(const Geo& g, bool bwd) {
   w.oc = o;  o = align_up(o + 0);
   w.doc = o; o = align_up(o + (bwd ? qbytes : 0));
   w.drow = o; o = align_up(o + (bwd ? sizeof(float) * (size_t)g.T * g.Hq : 0));
-  w.lse2 = o; o = align_up(o + (bwd ? sizeof(float) * ((size_t)g.T * g.Hq + 1) : 0));  // + one +inf sentinel
+  w.lse2 = o; o = align_up(o + (bwd ? sizeof(float) * (size_t)g.T * g.Hq : 0));
   w.ticket = o; o = align_up(o + sizeof(int32_t) * 64);
   w.partials = o; o = align_up(o + (bwd ? sizeof(float) * 2 * (size_t)split_extra_max(tile_geo(g)) * 2 * 64 * g.D : 0));  // tile_geo is idempotent
   w.bytes = o;
