@@ -343,8 +343,13 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void a
   __shared__ uint32_t bm_s[8][kCW];  // bitmap words of up to 8 selection heads
   __shared__ uint16_t tl_s[kCW * 32 * 8];  // the chunk's tiles in processing order
   __shared__ int ntl_s;
-  const ColItem item = P.bwd_items[blockIdx.x];
+  const int at = (int)blockIdx.x / P.sub_parts, sub = (int)blockIdx.x - at * P.sub_parts;
+  const ColItem item = P.bwd_items[at];
   if (item.col < 0) return;  // the item lists are padded to their largest possible length
+  const int nsub = P.sub_parts > 1 ? (item.weight + P.sub_weight - 1) / P.sub_weight : 1;  // workgroups that walk this item
+  if (sub >= nsub) return;
+  // this one's run of the item's tiles in walk order
+  const int run0 = (int)((int64_t)item.weight * sub / nsub), run1 = (int)((int64_t)item.weight * (sub + 1) / nsub);
   BusyTimer timer;
   timer.start(P);
   const int tid = threadIdx.x;
@@ -464,6 +469,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void a
   const bool per_qhead = P.mode == SB_SELECT_PER_QHEAD;
   const int nsel = per_qhead ? P.G : 1;      // bitmap columns (selection heads) of this KV head
   const int hpe = per_qhead ? 1 : P.G;       // query heads each set bit stands for
+  int walked = 0;                            // tiles of the item before the current chunk
   for (int sel0 = 0; sel0 < nsel; sel0 += 8) {                  // selection heads in groups of 8
     const int ns8 = min(8, nsel - sel0);
     for (int wend = whi, w0; wend > wlo; wend = w0) {  // chunks of up to kCW bitmap words, last first
@@ -507,18 +513,23 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void a
         }
       }
       __syncthreads();
-      const int ntl = __builtin_amdgcn_readfirstlane(ntl_s);
-      if (ntl == 0) continue;
+      const int nall = __builtin_amdgcn_readfirstlane(ntl_s);
+      // the part of the chunk's tiles that lies in this workgroup's run
+      const int lo = max(run0 - walked, 0), ntl = min(run1 - walked, nall) - lo;
+      walked += nall;
+      if (ntl <= 0) continue;
       // the diagonal tiles (query block j itself) are the first of the list, i.e. the last to be processed: count them
       int nd = 0;
       if (j >= 32 * w0 && j < 32 * (w0 + wn)) {
         for (int sel = 0; sel < ns8; ++sel) nd += (int)((bm_s[sel][(j >> 5) - w0] >> (j & 31)) & 1u) * hpe;
         nd = __builtin_amdgcn_readfirstlane(nd);
+        nd = max(lo + ntl - max(lo, nall - nd), 0);
       }
+      const uint16_t* const list = tl_s + (nall - 1 - lo);  // tile t of the run is list[-t]
 #pragma unroll
       for (int ks = 0; ks < D / 16; ++ks) asm volatile("" : "+a"(kf[ks]), "+a"(vf[ks]));
       auto entry = [&](int t, int& i, int& h) __attribute__((always_inline)) {
-        const int e = __builtin_amdgcn_readfirstlane((int)tl_s[ntl - 1 - t]);
+        const int e = __builtin_amdgcn_readfirstlane((int)list[-t]);
         i = 32 * w0 + (e >> 3);
         h = g * P.G + sel0 + (e & 7);
       };
@@ -557,7 +568,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void a
         // Every step is fenced: one matrix instruction, the refill of its operand, its share of the vector work.
 #define SB_FENCE() __builtin_amdgcn_sched_barrier(0)
         SB_FENCE();
-        if (!LAST && HALF == 1) e2 = (int)tl_s[max(ntl - 3 - t, 0)];
+        if (!LAST && HALF == 1) e2 = (int)list[-min(t + 2, ntl - 1)];
 #pragma unroll
         for (int k = 0; k < NOP; ++k) {
           if (!LAST) {
@@ -658,8 +669,8 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void a
     }
   }
   // C layout: column = d (32dt + l32), register v = key row c_row(v, hf) of this wavefront's strip
-  if (item.slot >= 0) {  // a part of a split column: leave the fp32 partial sums for the reduction
-    float* part = P.partials + (size_t)item.slot * (2 * 64 * D);
+  if (item.slot >= 0 || nsub > 1) {  // a part of a split column, or of an item: leave the fp32 partial sums for the reduction
+    float* part = nsub > 1 ? P.sub_partials + ((size_t)P.sub_base[at] + sub) * (2 * 64 * D) : P.partials + (size_t)item.slot * (2 * 64 * D);
 #pragma unroll
     for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
@@ -690,35 +701,60 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void a
   timer.stop(P);
 }
 
-// dK/dV of the split columns: the parts' fp32 partial sums added in part order (last query blocks first), then the
-// scale and the rounding of the unsplit path.  One workgroup per split column.
+// dK/dV of the columns that more than one workgroup walked: the fp32 partial sums added in walk order (last query blocks first),
+// then the scale and the rounding of the other columns.  Workgroups (x, y): x < extra: split column x; otherwise item x - extra,
+// if it is a whole column walked in sub-parts.  y: 16 rows of the key block.
 template <int D, bool OUT_F32>
-__global__ __launch_bounds__(256) void attn_bwd_dkv_reduce_kernel(AttnParams P) {
-  const int si = blockIdx.x;
-  if (si >= P.counters[1]) return;
-  const int64_t col = P.split_cols[3 * si];
-  const int slot0 = P.split_cols[3 * si + 1], np = P.split_cols[3 * si + 2];
+__global__ __launch_bounds__(256) void attn_bwd_dkv_reduce_kernel(AttnParams P, int extra) {
+  const int x = blockIdx.x;
+  int64_t col;
+  int slot0 = 0, np = 1, at = 0;
+  if (x < extra) {
+    if (x >= P.counters[1]) return;
+    col = P.split_cols[3 * x];
+    slot0 = P.split_cols[3 * x + 1];
+    np = P.split_cols[3 * x + 2];
+  } else {
+    at = x - extra;
+    const ColItem item = P.bwd_items[at];
+    if (item.col < 0 || item.slot >= 0 || item.weight <= P.sub_weight) return;
+    col = item.col;
+  }
   const int g = (int)(col / P.NQB);
   const int qbj = (int)(col - (int64_t)g * P.NQB);
   const int s = P.qb_seq[qbj];
   const int j = qbj - P.qb_off[s];
   const int64_t seq0 = P.cu[s];
   const int rows = min(64, P.cu[s + 1] - P.cu[s] - j * 64);
-  const float* part = P.partials + (size_t)slot0 * (2 * 64 * D);
-  for (int e = threadIdx.x; e < rows * D; e += 256) {
-    float dk = 0.f, dv = 0.f;
+  constexpr int S = 2 * 64 * D;
+  for (int u = threadIdx.x; u < 16 * D / 4; u += 256) {
+    const int e = blockIdx.y * 16 * D + 4 * u;
+    if (e >= rows * D) return;
+    f32x4 dk = {0.f, 0.f, 0.f, 0.f}, dv = dk;
+    auto add = [&](const float* part, int n) {
+      for (int p = 0; p < n; ++p) {
+        dk += *(const f32x4*)(part + (size_t)p * S + e);
+        dv += *(const f32x4*)(part + (size_t)p * S + 64 * D + e);
+      }
+    };
     for (int p = 0; p < np; ++p) {
-      dk += part[(size_t)p * (2 * 64 * D) + e];
-      dv += part[(size_t)p * (2 * 64 * D) + 64 * D + e];
+      const int it = x < extra && P.sub_parts > 1 ? P.part_item[slot0 + p] : at;
+      const int w = P.sub_parts > 1 ? P.bwd_items[it].weight : 0;
+      if (w > P.sub_weight) add(P.sub_partials + (size_t)P.sub_base[it] * S, (w + P.sub_weight - 1) / P.sub_weight);
+      else add(P.partials + (size_t)(slot0 + p) * S, 1);
     }
     const int kr = e / D, d = e % D;
     const int64_t off = ((seq0 + j * 64 + kr) * P.Hkv + g) * D + d;
+    dk *= P.scale;
     if (OUT_F32) {
-      ((float*)P.dk)[off] = dk * P.scale;
-      ((float*)P.dv)[off] = dv;
+      *(f32x4*)((float*)P.dk + off) = dk;
+      *(f32x4*)((float*)P.dv + off) = dv;
     } else {
-      ((bf16*)P.dk)[off] = (bf16)(dk * P.scale);
-      ((bf16*)P.dv)[off] = (bf16)dv;
+      bf16x4 a, b;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) { a[c] = (bf16)dk[c]; b[c] = (bf16)dv[c]; }
+      *(bf16x4*)((bf16*)P.dk + off) = a;
+      *(bf16x4*)((bf16*)P.dv + off) = b;
     }
   }
 }
@@ -743,13 +779,14 @@ template <int D, bool F32>
 static int launch_dkv(const Geo& g, const AttnParams& P, hipStream_t st) {
   const int64_t extra = split_extra_max(g);
   const int64_t n_items = (int64_t)g.Hkv * (g.NQB + extra);
-  if (n_items > 0x7fffffffll) { set_error("too many key-major items for one launch"); return SB_ERR_INVALID_ARG; }
-  dim3 grid((unsigned)n_items), block(128);
+  if (n_items * P.sub_parts > 0x7fffffffll) { set_error("too many key-major items for one launch"); return SB_ERR_INVALID_ARG; }
+  dim3 grid((unsigned)(n_items * P.sub_parts)), block(128);
   KernelTimer kt(K_BWD_DKV, st);
   hipLaunchKernelGGL((attn_bwd_dkv_kernel<D, F32>), grid, block, 0, st, P);
   SB_LAUNCH_CHECK("attn_bwd_dkv_kernel");
-  if (extra > 0) {  // at most `extra` columns are split; workgroups beyond the actual count return at once
-    hipLaunchKernelGGL((attn_bwd_dkv_reduce_kernel<D, F32>), dim3((unsigned)extra), dim3(256), 0, st, P);
+  const int64_t reduced = extra + (P.sub_parts > 1 ? n_items : 0);
+  if (reduced > 0) {  // at most that many columns are cut; workgroups beyond the actual count return at once
+    hipLaunchKernelGGL((attn_bwd_dkv_reduce_kernel<D, F32>), dim3((unsigned)reduced, 4), dim3(256), 0, st, P, (int)extra);
     SB_LAUNCH_CHECK("attn_bwd_dkv_reduce_kernel");
   }
   return SB_OK;
@@ -801,6 +838,11 @@ extern "C" int sb_sparse_attn_bwd(const sb_problem* p, const void* q, const void
   P.split_cols = (const int32_t*)(pb + po.split_cols);
   P.counters = (const int32_t*)(pb + po.counters);
   P.partials = (float*)(wb + wo.partials);
+  P.sub_base = (const int32_t*)(pb + po.sub_base);
+  P.part_item = (const int32_t*)(pb + po.part_item);
+  P.sub_partials = P.partials + 2 * (size_t)split_extra_max(g) * (2 * 64 * g.D);
+  P.sub_parts = sub_parts_max(g);
+  P.sub_weight = sub_weight(g);
   P.cu = t.cu; P.qb_off = t.qb_off; P.qb_seq = t.qb_seq; P.bm_off = t.bm_off;
   P.NQB = g.NQB; P.T = g.T; P.Hq = g.Hq; P.Hkv = g.Hkv; P.G = g.G; P.Hs = g.Hs; P.mode = g.mode;
   P.scale = g.softmax_scale; P.scale_log2e = g.softmax_scale * 1.4426950408889634f;

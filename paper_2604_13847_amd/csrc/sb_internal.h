@@ -109,8 +109,10 @@ struct PlanOffsets {
   size_t work_fwd;   // int32 [Hs*NQB]   row ids, longest first
   size_t colcost;    // int32 [Hkv*NQB]  tiles in each key-major column (summed over the group's heads)
   size_t bwd_items;  // ColItem [Hkv*(NQB+E)]  key-major items: entry r*Hkv + g is the r-th heaviest item of KV head g (col = -1: none)
-  size_t counters;   // int32 [4]  {partial slots in use, split columns}, zeroed by every plan call
+  size_t counters;   // int32 [4]  {partial slots in use, split columns, sub-part slots in use}, zeroed by every plan call
   size_t split_cols; // int32 [3*E]  (column, first partial slot, parts) of every split column
+  size_t sub_base;   // int32 [Hkv*(NQB+E)]  first sub-part slot of every key-major item (see sub_weight), -1: none
+  size_t part_item;  // int32 [2*E]  key-major item (index into bwd_items) of every partial slot
   size_t bitmap;     // uint32 [Hs * bm_words_unit] transpose bitmap: bit i of column (s,hs,j)
   size_t items;      // WorkItem [Hs*NQB]  descriptors of the query-major items, in work_fwd order
   // only for selection blocks larger than a tile (r > 1); everything above is then at tile level
@@ -136,6 +138,27 @@ static_assert(sizeof(ColItem) == 16, "ColItem is loaded as 4 dwords");
 inline int64_t bwd_total_tiles(const Geo& tg) { return (int64_t)tg.Hq * tg.nnz_unit; }  // tg = tile_geo(...)
 inline int split_weight(const Geo& tg) { const int64_t w = (bwd_total_tiles(tg) + 4095) / 4096; return (int)(w < 512 ? 512 : w); }
 inline int split_extra_max(const Geo& tg) { return (int)(bwd_total_tiles(tg) / split_weight(tg)); }
+// Small problems: fewer columns than the chip has workgroup slots (two per CU) leave most of it idle while the heaviest column
+// is walked (37 blocks on 2 KV heads with 8 query heads each: 74 workgroups, up to 88 tiles in a row, 115 us).  Items of more
+// than sub_weight() tiles are then walked by several workgroups, each an equal run of the item's tiles in walk order; they leave
+// fp32 partial sums that the reduction adds in walk order (the same problem: 44 us with the reduction; at least 4 tiles a
+// workgroup: 56 us, 6: 43, 12: 46).  A heaviest column of at most twice the weight is left alone (16 tiles: 21 us whole, 23 us
+// cut), and from kSubMinColumns columns on nothing is cut this way: two rounds of workgroups are there, heaviest first.
+constexpr int64_t kSubMinColumns = 1024, kSubSlots = 512;
+inline int sub_weight(const Geo& tg) {
+  const int64_t w = (bwd_total_tiles(tg) + kSubSlots - 1) / kSubSlots;
+  return (int)(w < 8 ? 8 : w);
+}
+// Most workgroups an item can be cut into (1: nothing is cut): an item has at most all tiles of its column, and less than
+// split_weight() plus one bitmap word's.
+inline int sub_parts_max(const Geo& tg) {
+  if ((int64_t)tg.Hkv * tg.NQB >= kSubMinColumns) return 1;
+  const int64_t w = sub_weight(tg), col = (int64_t)tg.n_max * tg.G, part = (int64_t)split_weight(tg) + 32 * tg.G;
+  const int64_t most = col < part ? col : part;
+  return most <= 2 * w ? 1 : (int)((most + w - 1) / w);
+}
+// slots: an item of t > w tiles takes ceil(t / w) < 2 t / w of them
+inline int64_t sub_slots_max(const Geo& tg) { return sub_parts_max(tg) > 1 ? 2 * bwd_total_tiles(tg) / sub_weight(tg) + 1 : 0; }
 // Everything a query-major workgroup needs to know about its item, so that it starts with one
 // 32-byte load instead of a chain of dependent table lookups.
 struct WorkItem {
@@ -157,7 +180,7 @@ struct WsOffsets {
   size_t drow;       // float [Hq][T]
   size_t lse2;       // float [Hq][T]
   size_t ticket;     // int32 [64] work tickets of the query-major attention kernels (kTicketSlots)
-  size_t partials;   // float [2*E][dK, dV][64][D]  partial sums of the parts of split key-major columns
+  size_t partials;   // float [2*E + sub-parts][dK, dV][64][D]  partial sums of the parts of split key-major columns, then of the sub-parts
   size_t bytes;
 };
 WsOffsets fwd_ws_offsets(const Geo& g);

@@ -133,8 +133,9 @@ struct ColumnWalk {
 __global__ __launch_bounds__(1024) void plan_bwd_order_kernel(const int32_t* __restrict__ colcost, const uint32_t* __restrict__ bitmap,
                                                               const int32_t* __restrict__ qb_off, const int32_t* __restrict__ qb_seq,
                                                               const int64_t* __restrict__ bm_off, int64_t NQB, int Hkv, int Hs, int G,
-                                                              int mode, int wmax, ColItem* __restrict__ items,
-                                                              int32_t* __restrict__ counters, int32_t* __restrict__ split_cols) {
+                                                              int mode, int wmax, int wsub, ColItem* __restrict__ items,
+                                                              int32_t* __restrict__ counters, int32_t* __restrict__ split_cols,
+                                                              int32_t* __restrict__ sub_base, int32_t* __restrict__ part_item) {
   __shared__ int bins[kBwdBins];
   __shared__ int sh[1024];
   const int tid = threadIdx.x;
@@ -151,6 +152,10 @@ __global__ __launch_bounds__(1024) void plan_bwd_order_kernel(const int32_t* __r
     cw.head_stride = (int64_t)n * cw.words;
     cw.bm = bitmap + (int64_t)Hs * bm_off[s] + (hs0 * n + j) * cw.words;
     return cw;
+  };
+  auto emit = [&](int64_t at, ColItem it) {
+    items[at] = it;
+    if (wsub > 0) sub_base[at] = it.weight > wsub ? atomicAdd(&counters[2], (it.weight + wsub - 1) / wsub) : -1;
   };
   for (int b = tid; b < kBwdBins; b += 1024) bins[b] = 0;
   __syncthreads();
@@ -186,7 +191,7 @@ __global__ __launch_bounds__(1024) void plan_bwd_order_kernel(const int32_t* __r
     if (cost[c] > wmax) np = cw.parts(wmax, [](int, int, int) {});
     if (np == 1) {
       const int rank = atomicAdd(&bins[min(cost[c], kBwdBins - 1)], 1);
-      items[(int64_t)rank * Hkv + g] = ColItem{col, cw.wj | (cw.words << 16), -1, cost[c]};
+      emit((int64_t)rank * Hkv + g, ColItem{col, cw.wj | (cw.words << 16), -1, cost[c]});
     } else {
       const int slot0 = atomicAdd(&counters[0], np);
       const int si = atomicAdd(&counters[1], 1);
@@ -194,7 +199,8 @@ __global__ __launch_bounds__(1024) void plan_bwd_order_kernel(const int32_t* __r
       int part = 0;
       cw.parts(wmax, [&](int lo, int hi, int wt) {
         const int rank = atomicAdd(&bins[min(wt, kBwdBins - 1)], 1);
-        items[(int64_t)rank * Hkv + g] = ColItem{col, lo | (hi << 16), slot0 + part, wt};
+        emit((int64_t)rank * Hkv + g, ColItem{col, lo | (hi << 16), slot0 + part, wt});
+        part_item[slot0 + part] = (int32_t)((int64_t)rank * Hkv + g);
         ++part;
       });
     }
@@ -323,7 +329,8 @@ extern "C" int sb_plan_worklist(const sb_problem* p, const int32_t* sel_rowptr, 
   if ((rc = fill_words(bwd_items, sizeof(ColItem) * n_items, 0xffffffffu, st)) != SB_OK) return rc;
   if ((rc = fill_zero(counters, sizeof(int32_t) * 4, st)) != SB_OK) return rc;
   hipLaunchKernelGGL(plan_bwd_order_kernel, dim3((unsigned)g.Hkv), dim3(1024), 0, st, colcost, bitmap, t.qb_off, t.qb_seq, t.bm_off,
-                     g.NQB, g.Hkv, g.Hs, g.G, g.mode, split_weight(g), bwd_items, counters, (int32_t*)(base + po.split_cols));
+                     g.NQB, g.Hkv, g.Hs, g.G, g.mode, split_weight(g), sub_parts_max(g) > 1 ? sub_weight(g) : 0, bwd_items, counters, (int32_t*)(base + po.split_cols),
+                     (int32_t*)(base + po.sub_base), (int32_t*)(base + po.part_item));
   SB_LAUNCH_CHECK("plan_bwd kernels");
   return SB_OK;
 }

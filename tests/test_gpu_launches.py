@@ -1,0 +1,33 @@
+"""Launch shapes that depend on the size of the problem: each at the sizes where the rule changes, against the checker."""
+import numpy as np
+import pytest
+import torch
+
+from helpers import Run
+from paper_2604_13847_amd import binding as sb
+from paper_2604_13847_amd import synth
+from test_gpu_parity import check_attention
+
+pytestmark = pytest.mark.gpu
+
+
+# Key-major columns of a small problem are walked by several workgroups when the heaviest can have more than 16 tiles (twice
+# the least run of 8): a column of the first block has (blocks * query heads per KV head) tiles at full budget.
+@pytest.mark.parametrize("lens,Hq,Hkv,D,mode,ratio", [
+    ([16 * 64], 1, 1, 64, 0, (1.0, 1.0)),                 # 16 tiles: one workgroup
+    ([17 * 64 - 5], 1, 1, 64, 0, (1.0, 1.0)),             # 17 tiles: three workgroups, a ragged last block
+    ([300, 64, 1, 577], 14, 2, 128, 0, (0.4, 1.0)),       # seven heads, ragged short sequences
+    ([300, 64, 1, 577], 8, 2, 128, 1, (0.4, 1.0)),        # one selection for four heads
+    ([2100], 16, 1, 64, 0, (1.0, 1.0)),                   # two rounds of eight selection heads: runs cross the rounds
+    ([64 * 520 - 3], 2, 1, 64, 0, (0.01, 0.01)),          # runs cross the chunks of 512 query blocks
+])
+def test_columns_of_small_problems_walked_by_several_workgroups(lens, Hq, Hkv, D, mode, ratio):
+    w = synth.small_ragged(seed=71, lens=lens, Hq=Hq, Hkv=Hkv, D=D, ratio=ratio)
+    r = Run(w, mode)
+    print(w, check_attention(r), flush=True)
+    dk, dv = r.dk.clone(), r.dv.clone()
+    for _ in range(2):  # the parts are added in walk order, whichever workgroup finishes first
+        sb.sb_sparse_attn_bwd(r.pb, r.q, r.k, r.v, r.o, r.lse, r.do, r.rowptr, r.idx, sb.sb_plan_worklist(r.pb, r.rowptr, r.idx),
+                              dq=r.dq, dk=r.dk, dv=r.dv)
+        torch.cuda.synchronize()
+        assert torch.equal(r.dk.view(torch.int16), dk.view(torch.int16)) and torch.equal(r.dv.view(torch.int16), dv.view(torch.int16))
