@@ -6,6 +6,7 @@
 #include <atomic>
 #include <mutex>
 
+#include "sb_geom.h"
 #include "sb_internal.h"
 
 namespace sb {
@@ -154,13 +155,19 @@ Tables make_tables(const Geo& g, const sb_problem* p, void* base) {
   return r;
 }
 
+GeomArgs make_geom_args(const Geo& g, const sb_problem* p, const Tables& t) {
+  return GeomArgs{p->cu_seqlens_dev, p->topk_dev, t.qb_off, t.row_base, t.kclamp, t.qb_seq, t.sc_off, g.S, g.B};
+}
+
 PlanOffsets plan_offsets(const Geo& gb) {
   const Geo g = tile_geo(gb);  // the plan is laid out for the 64-row tiles the attention kernels work on
   PlanOffsets p{};
   size_t o = 0;
   p.tables = o;   o = align_up(o + table_offsets(g).bytes);
   p.work_fwd = o; o = align_up(o + sizeof(int32_t) * (size_t)(g.Hs * g.NQB + 1));
+  p.counters = o; o = align_up(o + sizeof(int32_t) * 4);  // counters and colcost are cleared as one piece
   p.colcost = o;  o = align_up(o + sizeof(int32_t) * (size_t)(g.Hkv * g.NQB + 1));
+  p.zeros_end = o;
   p.bitmap = o;   o = align_up(o + sizeof(uint32_t) * (size_t)(g.Hs * g.bm_words_unit + 1));
   p.items = o;    o = align_up(o + sizeof(WorkItem) * (size_t)(g.Hs * g.NQB + 1));
   p.blk_tables = p.t_rowptr = p.t_idx = o;
@@ -171,7 +178,6 @@ PlanOffsets plan_offsets(const Geo& gb) {
   }
   const size_t E = (size_t)split_extra_max(g);
   p.bwd_items = o;  o = align_up(o + sizeof(ColItem) * ((size_t)g.Hkv * ((size_t)g.NQB + E) + 1));
-  p.counters = o;   o = align_up(o + sizeof(int32_t) * 4);
   p.split_cols = o; o = align_up(o + sizeof(int32_t) * (3 * E + 1));
   p.sub_base = o;   o = align_up(o + (sub_parts_max(g) > 1 ? sizeof(int32_t) * (size_t)g.Hkv * ((size_t)g.NQB + E) : 0));
   p.part_item = o;  o = align_up(o + sizeof(int32_t) * (2 * E + 1));
@@ -208,81 +214,110 @@ size_t scores_ws_bytes(const Geo& g) {
          align_up(sizeof(float) * (size_t)g.NQB * g.Hkv * g.D);
 }
 
-// One workgroup: prefix sums over sequences, then the query-block -> sequence map.
-__global__ __launch_bounds__(1024) void geom_kernel(const int32_t* __restrict__ cu, const int32_t* __restrict__ topk, int S, int B,
-                                                    int64_t NQB, int32_t* qb_off, int64_t* sc_off, int32_t* row_base,
-                                                    int64_t* bm_off, int32_t* kclamp, int32_t* qb_seq) {
+// Geometry tables, by one workgroup of 1024 threads: prefix sums over sequences, then the query-block -> sequence map.
+struct GeomOut {
+  int B;
+  int64_t NQB;
+  int32_t *qb_off, *row_base, *kclamp, *qb_seq;
+  int64_t *sc_off, *bm_off;
+};
+constexpr int kGeomLdsSeqs = 4096;  // the map's binary search runs in LDS up to this many sequences
+
+__device__ void geom_tables(const int32_t* __restrict__ cu, const int32_t* __restrict__ topk, int S, const GeomOut& o) {
   __shared__ long long wsum[4][16];  // per-wavefront totals of the four scanned columns
-  __shared__ long long carry[4];
+  __shared__ int ends[kGeomLdsSeqs];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid < 4) carry[tid] = 0;
-  if (tid == 0) { qb_off[0] = 0; sc_off[0] = 0; row_base[0] = 0; bm_off[0] = 0; }
-  __syncthreads();
+  long long carry[4] = {0, 0, 0, 0};
+  if (tid == 0) { o.qb_off[0] = 0; o.sc_off[0] = 0; o.row_base[0] = 0; o.bm_off[0] = 0; }
   for (int base = 0; base < S; base += 1024) {
     int s = base + tid;
     long long v[4] = {0, 0, 0, 0};
     if (s < S) {
       long long L = cu[s + 1] - cu[s];
-      long long n = (L + B - 1) / B;
+      long long n = (L + o.B - 1) / o.B;
       long long k = topk[s] < n ? topk[s] : n;
       if (k < 1) k = n > 0 ? 1 : 0;
-      kclamp[s] = (int32_t)k;
+      o.kclamp[s] = (int32_t)k;
       v[0] = n; v[1] = n * n; v[2] = k * n - k * (k - 1) / 2; v[3] = n * ((n + 31) / 32);
     }
     // inclusive scan of the four columns: inside each wavefront by shuffles, then over the 16 wavefront totals
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
+      for (int off = 1; off < 64 && off < S; off <<= 1) {
         const long long t = __shfl_up(v[a], off, 64);
         if (lane >= off) v[a] += t;
       }
       if (lane == 63) wsum[a][wave] = v[a];
     }
     __syncthreads();
+    const int waves = min(16, (S - base + 63) >> 6);  // the others hold nothing
     long long before[4];
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
-      before[a] = 0;
-      for (int w = 0; w < wave; ++w) before[a] += wsum[a][w];
+      before[a] = carry[a];
+      for (int w = 0; w < waves; ++w) {
+        if (w < wave) before[a] += wsum[a][w];
+        carry[a] += wsum[a][w];
+      }
     }
     if (s < S) {
-      qb_off[s + 1] = (int32_t)(carry[0] + before[0] + v[0]);
-      sc_off[s + 1] = carry[1] + before[1] + v[1];
-      row_base[s + 1] = (int32_t)(carry[2] + before[2] + v[2]);
-      bm_off[s + 1] = carry[3] + before[3] + v[3];
-    }
-    __syncthreads();
-    if (tid < 4) {
-      long long total = 0;
-      for (int w = 0; w < 16; ++w) total += wsum[tid][w];
-      carry[tid] += total;
+      o.qb_off[s + 1] = (int32_t)(before[0] + v[0]);
+      if (s < kGeomLdsSeqs) ends[s] = (int)(before[0] + v[0]);
+      o.sc_off[s + 1] = before[1] + v[1];
+      o.row_base[s + 1] = (int32_t)(before[2] + v[2]);
+      o.bm_off[s + 1] = before[3] + v[3];
     }
     __syncthreads();
   }
   __threadfence_block();
   __syncthreads();
-  // query block -> sequence by binary search over qb_off (written above by this workgroup)
-  for (long long qb = tid; qb < NQB; qb += 1024) {
-    int lo = 0, hi = S - 1;  // largest s with qb_off[s] <= qb and n_s > 0  (first s with qb_off[s+1] > qb)
+  // query block -> sequence: the first s with qb_off[s + 1] > qb, by binary search over the table written above
+  const int32_t* const far_ends = o.qb_off + 1;
+  for (long long qb = tid; qb < o.NQB; qb += 1024) {
+    int lo = 0, hi = S - 1;
     while (lo < hi) {
-      int mid = (lo + hi) >> 1;
-      if (qb_off[mid + 1] > qb) hi = mid; else lo = mid + 1;
+      const int mid = (lo + hi) >> 1;
+      const int e = S <= kGeomLdsSeqs ? ends[mid] : far_ends[mid];
+      if (e > qb) hi = mid; else lo = mid + 1;
     }
-    qb_seq[qb] = lo;
+    o.qb_seq[qb] = lo;
   }
 }
 
-int launch_geom(const Geo& g, const sb_problem* p, void* base, hipStream_t st) {
+// Workgroups 0 .. tables-1 fill a set of geometry tables each, the others 16 KiB pieces of the two areas.
+__global__ __launch_bounds__(1024) void geom_kernel(const int32_t* __restrict__ cu, const int32_t* __restrict__ topk, int S, GeomOut o0,
+                                                    GeomOut o1, int tables, uint4* __restrict__ zeros, size_t zero_n,
+                                                    uint4* __restrict__ ones, size_t ones_n) {
+  if ((int)blockIdx.x < tables) {
+    geom_tables(cu, topk, S, blockIdx.x == 0 ? o0 : o1);
+    return;
+  }
+  const size_t i = (size_t)(blockIdx.x - tables) * 1024 + threadIdx.x;
+  if (i < zero_n) zeros[i] = make_uint4(0u, 0u, 0u, 0u);
+  else if (i - zero_n < ones_n) ones[i - zero_n] = make_uint4(~0u, ~0u, ~0u, ~0u);
+}
+
+int launch_geom_and_fills(const Geo& g, void* base, const Geo* g2, void* base2, const sb_problem* p, void* zeros, size_t zero_bytes,
+                          void* ones, size_t ones_bytes, hipStream_t st) {
   if (g.S == 0) return SB_OK;
   if (!p->cu_seqlens_dev || !p->topk_dev) { set_error("cu_seqlens_dev and topk_dev are required"); return SB_ERR_INVALID_ARG; }
-  TableOffsets t = table_offsets(g);
-  char* b = (char*)base;
-  hipLaunchKernelGGL(geom_kernel, dim3(1), dim3(1024), 0, st, p->cu_seqlens_dev, p->topk_dev, g.S, g.B, g.NQB,
-                     (int32_t*)(b + t.qb_off), (int64_t*)(b + t.sc_off), (int32_t*)(b + t.row_base),
-                     (int64_t*)(b + t.bm_off), (int32_t*)(b + t.kclamp), (int32_t*)(b + t.qb_seq));
+  auto out = [](const Geo& x, void* at) {
+    const TableOffsets t = table_offsets(x);
+    char* b = (char*)at;
+    return GeomOut{x.B, x.NQB, (int32_t*)(b + t.qb_off), (int32_t*)(b + t.row_base), (int32_t*)(b + t.kclamp), (int32_t*)(b + t.qb_seq),
+                   (int64_t*)(b + t.sc_off), (int64_t*)(b + t.bm_off)};
+  };
+  const int tables = g2 ? 2 : 1;
+  const size_t zn = zero_bytes / 16, on = ones_bytes / 16, fills = (zn + on + 1023) / 1024;
+  const GeomOut o0 = out(g, base), o1 = g2 ? out(*g2, base2) : o0;
+  hipLaunchKernelGGL(geom_kernel, dim3((unsigned)(tables + fills)), dim3(1024), 0, st, p->cu_seqlens_dev, p->topk_dev, g.S, o0, o1, tables,
+                     (uint4*)zeros, zn, (uint4*)ones, on);
   SB_LAUNCH_CHECK("geom_kernel");
   return SB_OK;
+}
+
+int launch_geom(const Geo& g, const sb_problem* p, void* base, hipStream_t st) {
+  return launch_geom_and_fills(g, base, nullptr, nullptr, p, nullptr, 0, nullptr, 0, st);
 }
 
 __global__ __launch_bounds__(256) void fill_words_kernel(uint32_t* __restrict__ dst, size_t n, uint32_t value) {

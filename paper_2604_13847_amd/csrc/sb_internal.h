@@ -101,13 +101,19 @@ struct Tables {  // device pointers into a tables area
   const int32_t* qb_seq;
 };
 Tables make_tables(const Geo& g, const sb_problem* p, void* base);
+struct GeomArgs;
+GeomArgs make_geom_args(const Geo& g, const sb_problem* p, const Tables& t);
 int launch_geom(const Geo& g, const sb_problem* p, void* base, hipStream_t st);
+// geometry tables of `g` and (unless it is null) of `g2`, and two fills, as one launch; the fills' sizes are multiples of 16 bytes
+int launch_geom_and_fills(const Geo& g, void* base, const Geo* g2, void* base2, const sb_problem* p, void* zeros, size_t zero_bytes,
+                          void* ones, size_t ones_bytes, hipStream_t st);
 
 // Layout of the opaque plan buffer.
 struct PlanOffsets {
   size_t tables;     // TableOffsets area
   size_t work_fwd;   // int32 [Hs*NQB]   row ids, longest first
   size_t colcost;    // int32 [Hkv*NQB]  tiles in each key-major column (summed over the group's heads)
+  size_t zeros_end;  // end of colcost
   size_t bwd_items;  // ColItem [Hkv*(NQB+E)]  key-major items: entry r*Hkv + g is the r-th heaviest item of KV head g (col = -1: none)
   size_t counters;   // int32 [4]  {partial slots in use, split columns, sub-part slots in use}, zeroed by every plan call
   size_t split_cols; // int32 [3*E]  (column, first partial slot, parts) of every split column
@@ -136,7 +142,10 @@ struct ColItem {
 };
 static_assert(sizeof(ColItem) == 16, "ColItem is loaded as 4 dwords");
 inline int64_t bwd_total_tiles(const Geo& tg) { return (int64_t)tg.Hq * tg.nnz_unit; }  // tg = tile_geo(...)
-inline int split_weight(const Geo& tg) { const int64_t w = (bwd_total_tiles(tg) + 4095) / 4096; return (int)(w < 512 ? 512 : w); }
+// Total / 2048: at most an eighth of what each of the 512 workgroup slots has to do.  Half of that cut every second column of the
+// block-256 workloads (each cut costs 128 KiB of partial sums written and read) and made the plan walk them (131072-token sequence:
+// plan 150 -> 77 us, dK/dV the same within 1 %); twice it makes the 65536-token batch with 28/4 heads 4 % slower.
+inline int split_weight(const Geo& tg) { const int64_t w = (bwd_total_tiles(tg) + 2047) / 2048; return (int)(w < 512 ? 512 : w); }
 inline int split_extra_max(const Geo& tg) { return (int)(bwd_total_tiles(tg) / split_weight(tg)); }
 // Small problems: fewer columns than the chip has workgroup slots (two per CU) leave most of it idle while the heaviest column
 // is walked (37 blocks on 2 KV heads with 8 query heads each: 74 workgroups, up to 88 tiles in a row, 115 us).  Items of more

@@ -15,78 +15,155 @@
 
 namespace sb {
 
-__global__ __launch_bounds__(256) void plan_fwd_kernel(const int32_t* __restrict__ qb_off, const int32_t* __restrict__ kclamp,
-                                                       const int32_t* __restrict__ qb_seq, const int32_t* __restrict__ cu,
-                                                       const int32_t* __restrict__ rowptr, int S, int64_t NQB, int Hs,
-                                                       int Hkv, int G, int mode, int32_t* __restrict__ work_fwd,
-                                                       WorkItem* __restrict__ items) {
-  const int64_t row = (int64_t)blockIdx.x * 256 + threadIdx.x;  // row id = hs*NQB + qb
-  if (row >= (int64_t)Hs * NQB) return;
-  const int hs = (int)(row / NQB);
-  const int qb = (int)(row - (int64_t)hs * NQB);
-  const int s = qb_seq[qb];
-  const int i = qb - qb_off[s];
-  const int ks = kclamp[s];
+struct PlanArgs {
+  const int32_t *rowptr, *idx;             // the selection, at block level
+  const int32_t *cu, *qb_off, *kclamp, *qb_seq;  // tile-level tables (for 64-token selection blocks tiles are blocks)
+  const int64_t* bm_off;
+  const int32_t *b_qb_off, *b_kclamp;      // block-level tables
+  int S, Hs, Hkv, G, mode, r;              // r: tiles per selection block
+  int64_t NQB, bNQB, nnzT_unit;            // tiles, blocks, tile-level selection entries of one head
+  int32_t *t_rowptr, *t_idx;               // tile-level selection (r > 1)
+  int32_t* work_fwd;
+  WorkItem* items;
+  uint32_t* bitmap;
+  int32_t* colcost;
+  int64_t row_wgs;                         // workgroups of the query-major part
+  int64_t words;                           // (sequence, 32 query tiles) pairs
+};
+
+// order of the selection heads inside one query block: KV head fastest
+__device__ inline int head_rank(const PlanArgs& A, int hs) { return A.mode == SB_SELECT_PER_QHEAD ? (hs % A.G) * A.Hkv + hs / A.G : hs; }
+
+// Query-major item of selection row `row` (r = 1), one thread per row.
+__device__ inline void plan_row(const PlanArgs& A, int64_t row) {
+  const int hs = (int)(row / A.NQB);
+  const int qb = (int)(row - (int64_t)hs * A.NQB);
+  const int s = A.qb_seq[qb];
+  const int i = qb - A.qb_off[s];
+  const int ks = A.kclamp[s];
   const int c = min(ks, i + 1);
   int64_t pos = 0;
-  for (int t = 0; t < S; ++t) {
-    const int nt = qb_off[t + 1] - qb_off[t], kt = kclamp[t];
+  for (int t = 0; t < A.S; ++t) {
+    const int nt = A.qb_off[t + 1] - A.qb_off[t], kt = A.kclamp[t];
     if (nt == 0) continue;
-    if (kt > c) pos += (int64_t)Hs * (nt - c);                          // items of t with larger cost
-    if (t < s) pos += (int64_t)Hs * (kt == c ? nt - c + 1 : (kt > c ? 1 : 0));  // equal cost, earlier sequence
+    if (kt > c) pos += (int64_t)A.Hs * (nt - c);                          // items of t with larger cost
+    if (t < s) pos += (int64_t)A.Hs * (kt == c ? nt - c + 1 : (kt > c ? 1 : 0));  // equal cost, earlier sequence
   }
-  int hrank;  // order of the selection heads inside one query block: KV head fastest
-  if (mode == SB_SELECT_PER_QHEAD) hrank = (hs % G) * Hkv + hs / G; else hrank = hs;
-  pos += (c < ks) ? hrank : (int64_t)(i - (ks - 1)) * Hs + hrank;
-  work_fwd[pos] = (int32_t)row;
+  const int hrank = head_rank(A, hs);
+  pos += (c < ks) ? hrank : (int64_t)(i - (ks - 1)) * A.Hs + hrank;
+  A.work_fwd[pos] = (int32_t)row;
   WorkItem it;
-  it.row = (int32_t)row; it.seq0 = cu[s]; it.len = cu[s + 1] - cu[s]; it.i = i;
-  it.e0 = rowptr[row]; it.ntiles = rowptr[row + 1] - it.e0; it.hs = hs; it.s = s;
-  items[pos] = it;
+  it.row = (int32_t)row; it.seq0 = A.cu[s]; it.len = A.cu[s + 1] - A.cu[s]; it.i = i;
+  it.e0 = A.rowptr[row]; it.ntiles = A.rowptr[row + 1] - it.e0; it.hs = hs; it.s = s;
+  A.items[pos] = it;
 }
 
-// One workgroup per (selection head, sequence, 32 consecutive query blocks) builds word i/32 of
+// ---- selection blocks larger than a tile (B = 64 r, r > 1) -------------------------------------
+// The attention kernels work on 64-row tiles.  Query tile it of block I = it / r keeps, for every
+// earlier block J its block kept, the r key tiles rJ .. rJ+r-1 (whole blocks in the past), and of
+// its own block the tiles rI .. it (causality inside the diagonal block, at tile granularity; the
+// token-level mask stays inside tile it).  One wavefront per tile row writes the tile-level CSR and the row's
+// query-major item.  The tile count of a row grows with the query tile until the budget
+// saturates, so "later query tiles first" is close to longest-first, keeps the heads of one query
+// tile adjacent (KV head fastest, see plan_row) and is a closed form again: the position of
+// (s, it, hs) counts the rows of all sequences with a larger tile index, then the rows with the same
+// tile index in earlier sequences.
+__device__ inline void plan_tile_row(const PlanArgs& A, int64_t row) {
+  const int lane = threadIdx.x & 63;
+  const int hs = (int)(row / A.NQB);
+  const int64_t qt = row - (int64_t)hs * A.NQB;
+  const int s = A.qb_seq[qt];
+  const int it = (int)(qt - A.qb_off[s]);
+  // the sequences are dealt to the lanes: entries of the earlier ones (one selection head), and this row's rank
+  int64_t base = 0, pos = 0;
+  for (int t = lane; t < A.S; t += 64) {
+    const int nt = A.qb_off[t + 1] - A.qb_off[t];
+    if (t < s) base += tile_entries_before(nt, A.b_kclamp[t], A.r);
+    if (nt > it + 1) pos += (int64_t)A.Hs * (nt - 1 - it);  // rows of t with a larger tile index
+    if (t < s && nt > it) pos += A.Hs;                      // same tile index, earlier sequence
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) { base += __shfl_xor(base, off, 64); pos += __shfl_xor(pos, off, 64); }
+  const int64_t e0 = (int64_t)hs * A.nnzT_unit + base + tile_entries_before(it, A.b_kclamp[s], A.r);
+  const int r = A.r, I = it / r, a = it % r;
+  const int64_t brow = (int64_t)hs * A.bNQB + A.b_qb_off[s] + I;
+  const int be0 = A.rowptr[brow], past = A.rowptr[brow + 1] - be0 - 1;  // kept earlier blocks
+  if (lane == 0) {
+    A.t_rowptr[row] = (int32_t)e0;
+    if (row == (int64_t)A.Hs * A.NQB - 1) A.t_rowptr[row + 1] = (int32_t)(e0 + (int64_t)past * r + a + 1);
+    pos += head_rank(A, hs);
+    A.work_fwd[pos] = (int32_t)row;
+    WorkItem w;
+    w.row = (int32_t)row; w.seq0 = A.cu[s]; w.len = A.cu[s + 1] - A.cu[s]; w.i = it;
+    w.e0 = (int32_t)e0; w.ntiles = past * r + a + 1; w.hs = hs; w.s = s;
+    A.items[pos] = w;
+  }
+  for (int x = lane; x < past * r; x += 64) A.t_idx[e0 + x] = A.idx[be0 + x / r] * r + x % r;
+  for (int x = lane; x <= a; x += 64) A.t_idx[e0 + (int64_t)past * r + x] = I * r + x;
+}
+
+// One workgroup per (selection head, sequence, 32 consecutive query tiles) builds word it/32 of
 // every column of the sequence in LDS (LDS atomics) and then stores it: every bitmap word has one
 // owner, so the bitmap needs neither clearing nor global atomics; the column weights get one global
 // add per non-empty word instead of one per selected tile.
 constexpr int kTrChunk = 8192;  // columns handled per pass (32 KiB of LDS)
-__global__ __launch_bounds__(256) void plan_transpose_kernel(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ idx,
-                                                             const int32_t* __restrict__ qb_off, const int64_t* __restrict__ bm_off,
-                                                             int S, int64_t NQB, int Hs, int G, int mode,
-                                                             uint32_t* __restrict__ bitmap, int32_t* __restrict__ colcost) {
+__device__ inline void plan_transpose(const PlanArgs& A, int64_t word, int hs) {
   __shared__ uint32_t wcol[kTrChunk];
   __shared__ int sh_s, sh_w;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  if (tid == 0) {
-    int x = blockIdx.x, s = 0;
-    for (; s < S; ++s) {
-      const int w = (qb_off[s + 1] - qb_off[s] + 31) >> 5;
-      if (x < w) break;
-      x -= w;
+  if (wave == 0) {  // which sequence: 64 of them at a time
+    int64_t x = word;
+    int s = A.S;
+    for (int base = 0; base < A.S; base += 64) {
+      const int t = base + lane;
+      const int w = t < A.S ? (A.qb_off[t + 1] - A.qb_off[t] + 31) >> 5 : 0;
+      int incl = w;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const int up = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += up;
+      }
+      const unsigned long long hit = __builtin_amdgcn_ballot_w64(x < incl);
+      if (hit) {
+        const int src = __builtin_ctzll(hit);
+        s = base + src;
+        x -= __shfl(incl - w, src, 64);
+        break;
+      }
+      x -= __shfl(incl, 63, 64);
     }
-    sh_s = s; sh_w = x;
+    if (lane == 0) { sh_s = s; sh_w = (int)x; }
   }
   __syncthreads();
   const int s = sh_s, wi = sh_w;
-  if (s >= S) return;
-  const int hs = blockIdx.y;
-  const int n = qb_off[s + 1] - qb_off[s];
+  if (s >= A.S) return;
+  const int n = A.qb_off[s + 1] - A.qb_off[s];
   const int w = (n + 31) >> 5;
-  uint32_t* bm = bitmap + (int64_t)Hs * bm_off[s] + (int64_t)hs * n * w;
-  const int g = mode == SB_SELECT_PER_QHEAD ? hs / G : hs;
-  const int weight = mode == SB_SELECT_PER_QHEAD ? 1 : G;  // query-head tiles an entry stands for
-  int32_t* cost = colcost + (int64_t)g * NQB + qb_off[s];
-  const int64_t row0 = (int64_t)hs * NQB + qb_off[s] + 32 * wi;
-  const int nrows = min(32, n - 32 * wi);
+  uint32_t* bm = A.bitmap + (int64_t)A.Hs * A.bm_off[s] + (int64_t)hs * n * w;
+  const int g = A.mode == SB_SELECT_PER_QHEAD ? hs / A.G : hs;
+  const int weight = A.mode == SB_SELECT_PER_QHEAD ? 1 : A.G;  // query-head tiles an entry stands for
+  int32_t* cost = A.colcost + (int64_t)g * A.NQB + A.qb_off[s];
+  const int nrows = min(32, n - 32 * wi), r = A.r;
+  const int64_t row0 = (int64_t)hs * A.bNQB + A.b_qb_off[s];  // the sequence's first block row
   for (int j0 = 0; j0 < n; j0 += kTrChunk) {
     const int nj = min(kTrChunk, n - j0);
     for (int j = tid; j < nj; j += 256) wcol[j] = 0u;
     __syncthreads();
-    for (int r = wave; r < nrows; r += 4)
-      for (int e = rowptr[row0 + r] + lane; e < rowptr[row0 + r + 1]; e += 64) {
-        const int j = idx[e] - j0;
-        if (j >= 0 && j < nj) atomicOr(&wcol[j], 1u << r);
+    auto mark = [&](int jt, uint32_t bit) {
+      const int j = jt - j0;
+      if (j >= 0 && j < nj) atomicOr(&wcol[j], bit);
+    };
+    for (int y = wave; y < nrows; y += 4) {
+      const int it = 32 * wi + y;
+      const int64_t row = row0 + it / r;
+      const int e1 = A.rowptr[row + 1];
+      for (int e = A.rowptr[row] + lane; e < e1; e += 64) {
+        const int J = A.idx[e];
+        if (r == 1) mark(J, 1u << y);
+        else if (e + 1 == e1) for (int jt = J * r; jt <= it; ++jt) mark(jt, 1u << y);  // the row's own block
+        else for (int u = 0; u < r; ++u) mark(J * r + u, 1u << y);
       }
+    }
     __syncthreads();
     for (int j = tid; j < nj; j += 256) {
       const uint32_t x = wcol[j];
@@ -94,6 +171,22 @@ __global__ __launch_bounds__(256) void plan_transpose_kernel(const int32_t* __re
       if (x) atomicAdd(&cost[j0 + j], weight * __popc(x));
     }
     __syncthreads();
+  }
+}
+
+// the query-major lists and the transpose, side by side: neither needs the other
+__global__ __launch_bounds__(256) void plan_lists_kernel(PlanArgs A) {
+  if ((int64_t)blockIdx.x < A.row_wgs) {
+    if (A.r == 1) {
+      const int64_t row = (int64_t)blockIdx.x * 256 + threadIdx.x;  // row id = hs*NQB + qb
+      if (row < (int64_t)A.Hs * A.NQB) plan_row(A, row);
+    } else {
+      const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);  // hs * NT + global tile
+      if (row < (int64_t)A.Hs * A.NQB) plan_tile_row(A, row);
+    }
+  } else {
+    const int64_t x = (int64_t)blockIdx.x - A.row_wgs;
+    plan_transpose(A, x % A.words, (int)(x / A.words));
   }
 }
 
@@ -137,7 +230,7 @@ __global__ __launch_bounds__(1024) void plan_bwd_order_kernel(const int32_t* __r
                                                               int32_t* __restrict__ counters, int32_t* __restrict__ split_cols,
                                                               int32_t* __restrict__ sub_base, int32_t* __restrict__ part_item) {
   __shared__ int bins[kBwdBins];
-  __shared__ int sh[1024];
+  __shared__ int sh[16];
   const int tid = threadIdx.x;
   const int64_t g = blockIdx.x;
   const int32_t* cost = colcost + g * NQB;
@@ -172,15 +265,16 @@ __global__ __launch_bounds__(1024) void plan_bwd_order_kernel(const int32_t* __r
   int v[per], sum = 0;
 #pragma unroll
   for (int a = 0; a < per; ++a) { v[a] = bins[kBwdBins - 1 - (tid * per + a)]; sum += v[a]; }
-  sh[tid] = sum;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    const int t = tid >= off ? sh[tid - off] : 0;
-    __syncthreads();
-    sh[tid] += t;
-    __syncthreads();
+  int incl = sum;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int t = __shfl_up(incl, off, 64);
+    if ((tid & 63) >= off) incl += t;
   }
-  int run = sh[tid] - sum;
+  if ((tid & 63) == 63) sh[tid >> 6] = incl;
+  __syncthreads();
+  int run = incl - sum;
+  for (int w = 0; w < (tid >> 6); ++w) run += sh[w];
 #pragma unroll
   for (int a = 0; a < per; ++a) { bins[kBwdBins - 1 - (tid * per + a)] = run; run += v[a]; }
   __syncthreads();
@@ -207,68 +301,6 @@ __global__ __launch_bounds__(1024) void plan_bwd_order_kernel(const int32_t* __r
   }
 }
 
-// ---- selection blocks larger than a tile (B = 64 r, r > 1) -------------------------------------
-// The attention kernels work on 64-row tiles.  Query tile it of block I = it / r keeps, for every
-// earlier block J its block kept, the r key tiles rJ .. rJ+r-1 (whole blocks in the past), and of
-// its own block the tiles rI .. it (causality inside the diagonal block, at tile granularity; the
-// token-level mask stays inside tile it).  One wavefront per tile row writes the tile-level CSR.
-__global__ __launch_bounds__(256) void plan_expand_kernel(const int32_t* __restrict__ b_rowptr, const int32_t* __restrict__ b_idx,
-                                                          const int32_t* __restrict__ cu, const int32_t* __restrict__ b_qb_off,
-                                                          const int32_t* __restrict__ kclamp, const int32_t* __restrict__ t_qb_off,
-                                                          const int32_t* __restrict__ t_qb_seq, int S, int64_t NQB, int64_t NT, int Hs,
-                                                          int r, int64_t nnzT_unit, int32_t* __restrict__ t_rowptr,
-                                                          int32_t* __restrict__ t_idx) {
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);  // hs * NT + global tile
-  if (row >= (int64_t)Hs * NT) return;
-  const int lane = threadIdx.x & 63;
-  const int hs = (int)(row / NT);
-  const int64_t qt = row - (int64_t)hs * NT;
-  const int s = t_qb_seq[qt];
-  const int it = (int)(qt - t_qb_off[s]);
-  int64_t base = 0;  // entries of the earlier sequences (one selection head)
-  for (int t = 0; t < s; ++t) base += tile_entries_before(t_qb_off[t + 1] - t_qb_off[t], kclamp[t], r);
-  const int64_t k = kclamp[s];
-  const int64_t e0 = (int64_t)hs * nnzT_unit + base + tile_entries_before(it, k, r);
-  const int I = it / r, a = it % r;
-  const int64_t brow = (int64_t)hs * NQB + b_qb_off[s] + I;
-  const int be0 = b_rowptr[brow], past = b_rowptr[brow + 1] - be0 - 1;  // kept earlier blocks
-  if (lane == 0) {
-    t_rowptr[row] = (int32_t)e0;
-    if (row == (int64_t)Hs * NT - 1) t_rowptr[row + 1] = (int32_t)(e0 + (int64_t)past * r + a + 1);
-  }
-  for (int x = lane; x < past * r; x += 64) t_idx[e0 + x] = b_idx[be0 + x / r] * r + x % r;
-  for (int x = lane; x <= a; x += 64) t_idx[e0 + (int64_t)past * r + x] = I * r + x;
-}
-
-// Query-major items for r > 1.  The tile count of a row grows with the query tile until the budget
-// saturates, so "later query tiles first" is close to longest-first, keeps the heads of one query
-// tile adjacent (KV head fastest, see plan_fwd_kernel) and is a closed form again: the position of
-// (s, it, hs) counts the rows of all sequences with a larger tile index, then the rows with the same
-// tile index in earlier sequences.
-__global__ __launch_bounds__(256) void plan_fwd_tiles_kernel(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ qb_off,
-                                                             const int32_t* __restrict__ qb_seq, const int32_t* __restrict__ cu, int S,
-                                                             int64_t NQB, int Hs, int Hkv, int G, int mode,
-                                                             int32_t* __restrict__ work_fwd, WorkItem* __restrict__ items) {
-  const int64_t row = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (row >= (int64_t)Hs * NQB) return;
-  const int hs = (int)(row / NQB);
-  const int qb = (int)(row - (int64_t)hs * NQB);
-  const int s = qb_seq[qb];
-  const int it = qb - qb_off[s];
-  int64_t pos = 0;
-  for (int t = 0; t < S; ++t) {
-    const int nt = qb_off[t + 1] - qb_off[t];
-    if (nt > it + 1) pos += (int64_t)Hs * (nt - 1 - it);  // rows of t with a larger tile index
-    if (t < s && nt > it) pos += Hs;                      // same tile index, earlier sequence
-  }
-  pos += mode == SB_SELECT_PER_QHEAD ? (hs % G) * Hkv + hs / G : hs;
-  work_fwd[pos] = (int32_t)row;
-  WorkItem w;
-  w.row = (int32_t)row; w.seq0 = cu[s]; w.len = cu[s + 1] - cu[s]; w.i = it;
-  w.e0 = rowptr[row]; w.ntiles = rowptr[row + 1] - w.e0; w.hs = hs; w.s = s;
-  items[pos] = w;
-}
-
 }  // namespace sb
 
 using namespace sb;
@@ -284,50 +316,39 @@ extern "C" int sb_plan_worklist(const sb_problem* p, const int32_t* sel_rowptr, 
   const Geo g = tile_geo(gb);  // everything below is at the granularity of the 64-row tiles
   PlanOffsets po = plan_offsets(gb);
   char* base = (char*)plan_out;
-  rc = launch_geom(g, p, base + po.tables, st);
-  if (rc != SB_OK) return rc;
   Tables t = make_tables(g, p, base + po.tables);
-  int32_t* work_fwd = (int32_t*)(base + po.work_fwd);
+  const Tables tb = gb.r == 1 ? t : make_tables(gb, p, base + po.blk_tables);
   int32_t* colcost = (int32_t*)(base + po.colcost);
   ColItem* bwd_items = (ColItem*)(base + po.bwd_items);
   int32_t* counters = (int32_t*)(base + po.counters);
   uint32_t* bitmap = (uint32_t*)(base + po.bitmap);
-  const int64_t rows = (int64_t)g.Hs * g.NQB, ncol = (int64_t)g.Hkv * g.NQB;
   KernelTimer kt(K_PLAN, st);
-  if ((rc = fill_zero(colcost, sizeof(int32_t) * (size_t)ncol, st)) != SB_OK) return rc;  // the only part of the plan that is accumulated into
-  const int32_t* rowptr = sel_rowptr;
-  const int32_t* idx = sel_idx;
-  if (gb.r == 1) {
-    hipLaunchKernelGGL(plan_fwd_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, st, t.qb_off, t.kclamp, t.qb_seq,
-                       t.cu, sel_rowptr, g.S, g.NQB, g.Hs, g.Hkv, g.G, g.mode, work_fwd, (WorkItem*)(base + po.items));
-    SB_LAUNCH_CHECK("plan_fwd_kernel");
-  } else {
-    rc = launch_geom(gb, p, base + po.blk_tables, st);
-    if (rc != SB_OK) return rc;
-    Tables tb = make_tables(gb, p, base + po.blk_tables);
-    int32_t* t_rowptr = (int32_t*)(base + po.t_rowptr);
-    int32_t* t_idx = (int32_t*)(base + po.t_idx);
-    hipLaunchKernelGGL(plan_expand_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, sel_rowptr, sel_idx, t.cu, tb.qb_off,
-                       tb.kclamp, t.qb_off, t.qb_seq, g.S, gb.NQB, g.NQB, g.Hs, gb.r, g.nnz_unit, t_rowptr, t_idx);
-    SB_LAUNCH_CHECK("plan_expand_kernel");
-    rowptr = t_rowptr;
-    idx = t_idx;
-    hipLaunchKernelGGL(plan_fwd_tiles_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, st, rowptr, t.qb_off, t.qb_seq, t.cu, g.S,
-                       g.NQB, g.Hs, g.Hkv, g.G, g.mode, work_fwd, (WorkItem*)(base + po.items));
-    SB_LAUNCH_CHECK("plan_fwd_tiles_kernel");
-  }
-  int64_t words = 0;  // (sequence, 32 query blocks) pairs
+  // Three launches: tables and fills, lists and transpose, order of the key-major items (each costs 4 - 5 us whatever it does; as
+  // seven to nine launches the plan took 20 us of a 1024-token step and 43 us of a 32768-token one, now 14 and 38 us).
+  // The item lists are padded to their largest possible length; unused entries say "no item".
+  const size_t n_items = (size_t)g.Hkv * ((size_t)g.NQB + (size_t)split_extra_max(g));
+  rc = launch_geom_and_fills(g, base + po.tables, gb.r > 1 ? &gb : nullptr, base + po.blk_tables, p, base + po.counters, po.zeros_end - po.counters,
+                             bwd_items, sizeof(ColItem) * n_items, st);
+  if (rc != SB_OK) return rc;
+  PlanArgs A{};
+  A.rowptr = sel_rowptr; A.idx = sel_idx;
+  A.cu = t.cu; A.qb_off = t.qb_off; A.kclamp = t.kclamp; A.qb_seq = t.qb_seq; A.bm_off = t.bm_off;
+  A.b_qb_off = tb.qb_off; A.b_kclamp = tb.kclamp;
+  A.S = g.S; A.Hs = g.Hs; A.Hkv = g.Hkv; A.G = g.G; A.mode = g.mode; A.r = gb.r;
+  A.NQB = g.NQB; A.bNQB = gb.NQB; A.nnzT_unit = g.nnz_unit;
+  A.t_rowptr = (int32_t*)(base + po.t_rowptr); A.t_idx = (int32_t*)(base + po.t_idx);
+  A.work_fwd = (int32_t*)(base + po.work_fwd); A.items = (WorkItem*)(base + po.items);
+  A.bitmap = bitmap; A.colcost = colcost;
+  const int64_t rows = (int64_t)g.Hs * g.NQB;
+  A.row_wgs = gb.r == 1 ? (rows + 255) / 256 : (rows + 3) / 4;
   for (int s = 0; s < g.S; ++s) {
     const int64_t L = (int64_t)p->cu_seqlens_host[s + 1] - p->cu_seqlens_host[s];
-    words += ((L + g.B - 1) / g.B + 31) / 32;
+    A.words += ((L + g.B - 1) / g.B + 31) / 32;
   }
-  hipLaunchKernelGGL(plan_transpose_kernel, dim3((unsigned)words, (unsigned)g.Hs), dim3(256), 0, st, rowptr, idx, t.qb_off, t.bm_off,
-                     g.S, g.NQB, g.Hs, g.G, g.mode, bitmap, colcost);
-  SB_LAUNCH_CHECK("plan_transpose_kernel");
-  // the item lists are padded to their largest possible length; unused entries say "no item"
-  const size_t n_items = (size_t)g.Hkv * ((size_t)g.NQB + (size_t)split_extra_max(g));
-  if ((rc = fill_words(bwd_items, sizeof(ColItem) * n_items, 0xffffffffu, st)) != SB_OK) return rc;
-  if ((rc = fill_zero(counters, sizeof(int32_t) * 4, st)) != SB_OK) return rc;
+  const int64_t wgs = A.row_wgs + A.words * g.Hs;
+  if (wgs > 0x7fffffffll) { set_error("too many rows for one launch of the plan"); return SB_ERR_UNSUPPORTED; }
+  hipLaunchKernelGGL(plan_lists_kernel, dim3((unsigned)wgs), dim3(256), 0, st, A);
+  SB_LAUNCH_CHECK("plan_lists_kernel");
   hipLaunchKernelGGL(plan_bwd_order_kernel, dim3((unsigned)g.Hkv), dim3(1024), 0, st, colcost, bitmap, t.qb_off, t.qb_seq, t.bm_off,
                      g.NQB, g.Hkv, g.Hs, g.G, g.mode, split_weight(g), sub_parts_max(g) > 1 ? sub_weight(g) : 0, bwd_items, counters, (int32_t*)(base + po.split_cols),
                      (int32_t*)(base + po.sub_base), (int32_t*)(base + po.part_item));

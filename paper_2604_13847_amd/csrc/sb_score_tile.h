@@ -5,6 +5,7 @@
 // order, and every path that selects goes through select_row, so the paths agree bit for bit.
 #pragma once
 
+#include "sb_geom.h"
 #include "sb_internal.h"
 
 namespace sb {
@@ -202,7 +203,7 @@ __device__ inline void select_row(const uint32_t* keys, int* hist, int lane, int
 }
 
 // Pooling of Q and K into the workspace (and kbar_out, if given); qbar/kbar receive the two pooled arrays.
-int launch_pool(const Geo& g, const sb_problem* p, const Tables& t, const void* q, const void* k, float* kbar_out, void* ws,
-                hipStream_t st, float** qbar, float** kbar);
+int launch_pool(const Geo& g, const GeomArgs& ga, const void* q, const void* k, float* kbar_out, void* ws, hipStream_t st, float** qbar,
+                float** kbar);
 
 }  // namespace sb

@@ -2,6 +2,7 @@
 // score = score_scale * <pooled Q block i, pooled K block j> for past blocks j < i.
 // Pooling is HBM-bound (K and Q are read once); the score tiles run on the fp32 matrix cores and
 // write the score matrix once.
+#include "sb_geom.h"
 #include "sb_internal.h"
 #include "sb_score_tile.h"
 
@@ -10,20 +11,25 @@ namespace sb {
 __device__ inline float bf16_bits_to_float(uint32_t b) { return __uint_as_float(b << 16); }
 
 // Mean over the valid tokens of one block, for 8 (bf16) or 4 (float) adjacent columns per thread: 16-byte loads, eight
-// rows in flight per thread.  grid = (NQB, ceil(H*D / (256 * columns per thread))); X is [T][H*D]; out is [NQB][H*D] float.
+// rows in flight per thread.  grid = (NQB, column groups of Q, then column groups of K); X is [T][H*D]; out is [NQB][H*D] float.
+// Q and K share a launch: the second one cost a small batch 4 us, and the K part alone fills only a fifth of the chip.
 template <bool F32>
-__global__ __launch_bounds__(256) void pool_kernel(const void* __restrict__ X, int cols, const int32_t* __restrict__ cu,
-                                                   const int32_t* __restrict__ qb_off, const int32_t* __restrict__ qb_seq,
-                                                   int B, float* __restrict__ out) {
+__global__ __launch_bounds__(256) void pool_kernel(const void* __restrict__ Q, const void* __restrict__ K, int qcols, int kcols, int qgroups,
+                                                   GeomArgs ga, float* __restrict__ qbar, float* __restrict__ kbar) {
   constexpr int CPT = F32 ? 4 : 8;  // columns per thread
+  const bool is_q = (int)blockIdx.y < qgroups;
+  const void* __restrict__ X = is_q ? Q : K;
+  float* __restrict__ out = is_q ? qbar : kbar;
+  const int cols = is_q ? qcols : kcols;
   const int qb = blockIdx.x;
-  const int c0 = (blockIdx.y * 256 + threadIdx.x) * CPT;
+  const int c0 = (((int)blockIdx.y - (is_q ? 0 : qgroups)) * 256 + threadIdx.x) * CPT;
+  const BatchGeom bg(ga);
+  const int s = bg.seq_of(qb);
+  const int j = qb - bg.get(s).qb0;
   if (c0 >= cols) return;
-  const int s = qb_seq[qb];
-  const int j = qb - qb_off[s];
-  const int L = cu[s + 1] - cu[s];
-  const int first = j * B, last = min((j + 1) * B, L);
-  const int64_t row0 = (int64_t)cu[s] + first;
+  const int L = ga.cu[s + 1] - ga.cu[s];
+  const int first = j * ga.B, last = min((j + 1) * ga.B, L);
+  const int64_t row0 = (int64_t)ga.cu[s] + first;
   float a[CPT];
 #pragma unroll
   for (int e = 0; e < CPT; ++e) a[e] = 0.f;
@@ -70,38 +76,27 @@ __host__ __device__ inline int64_t score_items(int64_t nt) {
 }
 
 template <int D>
-__global__ __launch_bounds__(256) void score_kernel(const float* __restrict__ qbar, const float* __restrict__ kbar,
-                                                    const int32_t* __restrict__ qb_off, const int64_t* __restrict__ sc_off,
-                                                    int S, int Hq, int Hkv, int Hs, int G, int mode, float scale,
-                                                    float* __restrict__ scores) {
+__global__ __launch_bounds__(256) void score_kernel(const float* __restrict__ qbar, const float* __restrict__ kbar, GeomArgs ga, int Hq,
+                                                    int Hkv, int Hs, int G, int mode, float scale, float* __restrict__ scores) {
   constexpr int LD = D + 4;  // padded row length (floats) of the LDS tiles
   __shared__ float qs[64 * LD];
   __shared__ float ks[64 * LD];
-  __shared__ int sh_s, sh_it, sh_jc;
   const int tid = threadIdx.x;
-  if (tid == 0) {  // locate (sequence, row tile, column chunk) of this workgroup
-    int64_t x = blockIdx.x;
-    int s = 0, it = 0;
-    for (; s < S; ++s) {
-      const int64_t c = score_items((qb_off[s + 1] - qb_off[s] + 63) >> 6);
-      if (x < c) break;
-      x -= c;
-    }
-    if (s < S)
-      for (;; ++it) {
-        const int c = it / kScChunk + 1;
-        if (x < c) break;
-        x -= c;
-      }
-    sh_s = s; sh_it = it; sh_jc = (int)x;
-  }
-  __syncthreads();
-  const int s = sh_s, it = sh_it, jc = sh_jc;
-  if (s >= S) return;
+  // (sequence, row tile, column chunk) of this workgroup
+  const BatchGeom bg(ga);
+  int64_t x = blockIdx.x;
+  const int s = bg.locate(x, [](int n) { return score_items((n + 63) >> 6); });
+  if (s >= ga.S) return;
+  // row tile `it` starts at item score_items(it), with it / kScChunk + 1 chunks: about sqrt(2 kScChunk x), then corrected
+  int it = (int)sqrtf(2.f * kScChunk * (float)x);
+  while (it > 0 && score_items(it) > x) --it;
+  while (score_items(it + 1) <= x) ++it;
+  const int jc = (int)(x - score_items(it));
   const int hs = blockIdx.y;
-  const int n = qb_off[s + 1] - qb_off[s];
-  const int64_t qb0 = qb_off[s];
-  float* out = scores + (int64_t)Hs * sc_off[s] + (int64_t)hs * n * n;
+  const SeqGeom sg = bg.get(s);
+  const int n = sg.n;
+  const int64_t qb0 = sg.qb0;
+  float* out = scores + (int64_t)Hs * sg.sc_off + (int64_t)hs * n * n;
   const int i0 = it * 64;
   const int rows = min(64, n - i0);
   const int heads = mode == SB_SELECT_PER_QHEAD ? 1 : G;
@@ -186,24 +181,21 @@ __global__ __launch_bounds__(256) void score_kernel(const float* __restrict__ qb
 }
 
 // Mean-pools Q and K into the workspace behind the geometry tables.
-int launch_pool(const Geo& g, const sb_problem* p, const Tables& t, const void* q, const void* k, float* kbar_out, void* ws,
-                hipStream_t st, float** qbar_p, float** kbar_p) {
-  (void)p;
+int launch_pool(const Geo& g, const GeomArgs& ga, const void* q, const void* k, float* kbar_out, void* ws, hipStream_t st, float** qbar_p,
+                float** kbar_p) {
   char* b = (char*)ws + align_up(table_offsets(g).bytes);
   float* qbar = (float*)b;
   float* kbar = (float*)(b + align_up(sizeof(float) * (size_t)g.NQB * g.Hq * g.D));
   const int qcols = g.Hq * g.D, kcols = g.Hkv * g.D;
   const int per_wg = 256 * (g.dtype == SB_F32 ? 4 : 8);  // columns per workgroup (head_dim is a multiple of 8)
-  dim3 gq((unsigned)g.NQB, (unsigned)((qcols + per_wg - 1) / per_wg)), gk((unsigned)g.NQB, (unsigned)((kcols + per_wg - 1) / per_wg));
+  const int qgroups = (qcols + per_wg - 1) / per_wg, kgroups = (kcols + per_wg - 1) / per_wg;
+  dim3 grid((unsigned)g.NQB, (unsigned)(qgroups + kgroups));
   {
     KernelTimer kt(K_POOL, st);
-    if (g.dtype == SB_F32) {
-      hipLaunchKernelGGL(pool_kernel<true>, gq, dim3(256), 0, st, q, qcols, t.cu, t.qb_off, t.qb_seq, g.B, qbar);
-      hipLaunchKernelGGL(pool_kernel<true>, gk, dim3(256), 0, st, k, kcols, t.cu, t.qb_off, t.qb_seq, g.B, kbar);
-    } else {
-      hipLaunchKernelGGL(pool_kernel<false>, gq, dim3(256), 0, st, q, qcols, t.cu, t.qb_off, t.qb_seq, g.B, qbar);
-      hipLaunchKernelGGL(pool_kernel<false>, gk, dim3(256), 0, st, k, kcols, t.cu, t.qb_off, t.qb_seq, g.B, kbar);
-    }
+    if (g.dtype == SB_F32)
+      hipLaunchKernelGGL(pool_kernel<true>, grid, dim3(256), 0, st, q, k, qcols, kcols, qgroups, ga, qbar, kbar);
+    else
+      hipLaunchKernelGGL(pool_kernel<false>, grid, dim3(256), 0, st, q, k, qcols, kcols, qgroups, ga, qbar, kbar);
   }
   SB_LAUNCH_CHECK("pool_kernel");
   if (kbar_out)
@@ -225,11 +217,10 @@ extern "C" int sb_block_scores(const sb_problem* p, const void* q, const void* k
   if (g.S == 0 || g.T == 0 || g.NQB == 0) return SB_OK;
   if (!q || !k || !scores_out || !ws) { set_error("null q, k, scores_out or ws"); return SB_ERR_INVALID_ARG; }
   hipStream_t st = (hipStream_t)stream;
-  rc = launch_geom(g, p, ws, st);
-  if (rc != SB_OK) return rc;
-  Tables t = make_tables(g, p, ws);
+  if (g.S > kLaneSeqs && (rc = launch_geom(g, p, ws, st)) != SB_OK) return rc;
+  const GeomArgs ga = make_geom_args(g, p, make_tables(g, p, ws));
   float *qbar = nullptr, *kbar = nullptr;
-  if ((rc = launch_pool(g, p, t, q, k, kbar_out, ws, st, &qbar, &kbar)) != SB_OK) return rc;
+  if ((rc = launch_pool(g, ga, q, k, kbar_out, ws, st, &qbar, &kbar)) != SB_OK) return rc;
   int64_t items = 0;  // (sequence, row tile, column chunk) triples
   for (int s = 0; s < g.S; ++s) {
     const int64_t L = (int64_t)p->cu_seqlens_host[s + 1] - p->cu_seqlens_host[s];
@@ -240,11 +231,9 @@ extern "C" int sb_block_scores(const sb_problem* p, const void* q, const void* k
   dim3 gs((unsigned)items, (unsigned)g.Hs);
   KernelTimer kt(K_SCORE, st);
   if (g.D == 128)
-    hipLaunchKernelGGL(score_kernel<128>, gs, dim3(256), 0, st, qbar, kbar, t.qb_off, t.sc_off, g.S, g.Hq, g.Hkv, g.Hs, g.G,
-                       g.mode, g.score_scale, scores_out);
+    hipLaunchKernelGGL(score_kernel<128>, gs, dim3(256), 0, st, qbar, kbar, ga, g.Hq, g.Hkv, g.Hs, g.G, g.mode, g.score_scale, scores_out);
   else
-    hipLaunchKernelGGL(score_kernel<64>, gs, dim3(256), 0, st, qbar, kbar, t.qb_off, t.sc_off, g.S, g.Hq, g.Hkv, g.Hs, g.G,
-                       g.mode, g.score_scale, scores_out);
+    hipLaunchKernelGGL(score_kernel<64>, gs, dim3(256), 0, st, qbar, kbar, ga, g.Hq, g.Hkv, g.Hs, g.G, g.mode, g.score_scale, scores_out);
   SB_LAUNCH_CHECK("score_kernel");
   return SB_OK;
 }

@@ -5,6 +5,7 @@
 // threshold key, then an index-ordered compaction, so the result is a pure function of the scores.
 #include <mutex>
 
+#include "sb_geom.h"
 #include "sb_internal.h"
 #include "sb_score_tile.h"
 
@@ -12,25 +13,21 @@ namespace sb {
 
 // One wavefront per row (several rows per workgroup, no workgroup barrier anywhere): keys and a
 // 256-bin histogram in the wavefront's own LDS region.
-__global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ scores, const int32_t* __restrict__ qb_off,
-                                                   const int64_t* __restrict__ sc_off, const int32_t* __restrict__ row_base,
-                                                   const int32_t* __restrict__ kclamp, const int32_t* __restrict__ qb_seq,
-                                                   int64_t NQB, int Hs, int64_t nnz_unit, int region_words,
-                                                   int32_t* __restrict__ rowptr, int32_t* __restrict__ idx) {
+__global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ scores, GeomArgs ga, int64_t NQB, int Hs, int64_t nnz_unit,
+                                                   int region_words, int32_t* __restrict__ rowptr, int32_t* __restrict__ idx) {
   extern __shared__ uint32_t smem[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t row_id = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;  // hs * NQB + query block
   if (row_id >= (int64_t)Hs * NQB) return;
   uint32_t* keys = smem + (size_t)wave * region_words;
   int* hist = (int*)(keys + region_words - 256);
   const int hs = (int)(row_id / NQB);
   const int qb = (int)(row_id - (int64_t)hs * NQB);
-  const int s = qb_seq[qb];
-  const int i = qb - qb_off[s];
-  const int n = qb_off[s + 1] - qb_off[s];
-  const int k = kclamp[s];
+  const BatchGeom bg(ga);
+  const SeqGeom sg = bg.get(bg.seq_of(qb));
+  const int i = qb - sg.qb0, n = sg.n, k = sg.k;
   const int c = min(k, i + 1);
-  const int64_t start = (int64_t)hs * nnz_unit + row_base[s] + sel_rows_before(i, k);
+  const int64_t start = (int64_t)hs * nnz_unit + sg.row_base + sel_rows_before(i, k);
   if (lane == 0) {
     rowptr[row_id] = (int32_t)start;
     if (row_id == (int64_t)Hs * NQB - 1) rowptr[(int64_t)Hs * NQB] = (int32_t)(start + c);
@@ -45,7 +42,7 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ sco
     if (lane == 0) out[0] = i;
     return;
   }
-  const float* row = scores + (int64_t)Hs * sc_off[s] + ((int64_t)hs * n + i) * n;
+  const float* row = scores + (int64_t)Hs * sg.sc_off + ((int64_t)hs * n + i) * n;
   for (int j0 = lane; j0 < m; j0 += 64 * 8) {  // eight independent loads in flight per lane: the row comes from HBM
     float x[8];
 #pragma unroll
@@ -69,14 +66,13 @@ constexpr int kFusedWaves = 16;
 
 template <int D>
 __global__ __launch_bounds__(64 * kFusedWaves) void score_select_kernel(
-    const float* __restrict__ qbar, const float* __restrict__ kbar, const int32_t* __restrict__ qb_off,
-    const int32_t* __restrict__ row_base, const int32_t* __restrict__ kclamp, const int32_t* __restrict__ qb_seq, int64_t NQB,
-    int Hq, int Hkv, int Hs, int G, int mode, float scale, int64_t nnz_unit, int R, int stride, int32_t* __restrict__ rowptr,
-    int32_t* __restrict__ idx) {
+    const float* __restrict__ qbar, const float* __restrict__ kbar, GeomArgs ga, int64_t NQB, int Hq, int Hkv, int Hs, int G, int mode,
+    float scale, int64_t nnz_unit, int R, int stride, int32_t* __restrict__ rowptr, int32_t* __restrict__ idx) {
   extern __shared__ uint32_t smem[];
   uint32_t* keys = smem;                            // [R][stride]
   int* hist = (int*)(smem + (size_t)R * stride);    // [kFusedWaves][256]
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kq = lane >> 4;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, kq = lane >> 4;
+  const BatchGeom bg(ga);
   // Workgroup ids run over the selection heads first and workgroups go to the eight XCDs in turn: head index
   // (x % 8) * (Hs / 8) + x / 8 gives every XCD a contiguous range of heads, i.e. few KV heads, whose pooled keys
   // (n * D floats each) then stay in that XCD's L2.
@@ -89,12 +85,12 @@ __global__ __launch_bounds__(64 * kFusedWaves) void score_select_kernel(
   // rows late in a sequence have the most past blocks: hand out the last groups of blocks first
   const int64_t b0 = (ngroups - 1 - gy) * R, b1 = min(NQB, b0 + R);
   for (int64_t ba = b0; ba < b1;) {
-    const int s = qb_seq[ba];
-    const int64_t qb0 = qb_off[s];
-    const int n = qb_off[s + 1] - (int)qb0;
+    const SeqGeom sg = bg.get(bg.seq_of((int)ba));
+    const int64_t qb0 = sg.qb0;
+    const int n = sg.n;
     const int ia = (int)(ba - qb0), ib = (int)min((int64_t)n, ia + (b1 - ba));  // rows [ia, ib) of sequence s
     const int nrows = ib - ia;
-    const int k = kclamp[s];
+    const int k = sg.k;
     // a row needs its scores only if it keeps some but not all of its past blocks: 2 <= k <= i
     if (k >= 2 && ib - 1 >= k) {
       float a[D / 4];
@@ -120,7 +116,7 @@ __global__ __launch_bounds__(64 * kFusedWaves) void score_select_kernel(
       const int i = ia + wave;
       const int c = min(k, i + 1);
       const int64_t row_id = (int64_t)hs * NQB + ba + wave;
-      const int64_t start = (int64_t)hs * nnz_unit + row_base[s] + sel_rows_before(i, k);
+      const int64_t start = (int64_t)hs * nnz_unit + sg.row_base + sel_rows_before(i, k);
       if (lane == 0) {
         rowptr[row_id] = (int32_t)start;
         if (row_id == (int64_t)Hs * NQB - 1) rowptr[(int64_t)Hs * NQB] = (int32_t)(start + c);
@@ -145,7 +141,7 @@ __global__ __launch_bounds__(64 * kFusedWaves) void score_select_kernel(
 using namespace sb;
 
 // launches the selection on tables that are already in device memory
-static int select_launch(const Geo& g, const Tables& t, const float* scores, int32_t* sel_rowptr_out, int32_t* sel_idx_out,
+static int select_launch(const Geo& g, const GeomArgs& ga, const float* scores, int32_t* sel_rowptr_out, int32_t* sel_idx_out,
                          hipStream_t st) {
   // every wavefront owns a region of n_max keys (rounded up to 64) plus 256 histogram bins; as many rows per workgroup
   // (at most four) as fit in 64 KiB
@@ -169,10 +165,15 @@ static int select_launch(const Geo& g, const Tables& t, const float* scores, int
   const int64_t rows = (int64_t)g.Hs * g.NQB;
   dim3 grid((unsigned)((rows + W - 1) / W));
   KernelTimer kt(K_TOPK, st);
-  hipLaunchKernelGGL(topk_kernel, grid, dim3(64 * W), smem, st, scores, t.qb_off, t.sc_off, t.row_base, t.kclamp, t.qb_seq,
-                     g.NQB, g.Hs, g.nnz_unit, region_words, sel_rowptr_out, sel_idx_out);
+  hipLaunchKernelGGL(topk_kernel, grid, dim3(64 * W), smem, st, scores, ga, g.NQB, g.Hs, g.nnz_unit, region_words, sel_rowptr_out,
+                     sel_idx_out);
   SB_LAUNCH_CHECK("topk_kernel");
   return SB_OK;
+}
+
+// the geometry tables, where the kernels read them
+static int need_tables(const Geo& g, const sb_problem* p, void* ws, hipStream_t st) {
+  return g.S > kLaneSeqs ? launch_geom(g, p, ws, st) : SB_OK;
 }
 
 extern "C" int sb_select_topk(const sb_problem* p, const float* scores, int32_t* sel_rowptr_out, int32_t* sel_idx_out,
@@ -186,13 +187,12 @@ extern "C" int sb_select_topk(const sb_problem* p, const float* scores, int32_t*
     return fill_zero(sel_rowptr_out, sizeof(int32_t), st);
   }
   if (!scores || !sel_idx_out || !ws) { set_error("null scores, sel_idx_out or ws"); return SB_ERR_INVALID_ARG; }
-  rc = launch_geom(g, p, ws, st);
-  if (rc != SB_OK) return rc;
-  return select_launch(g, make_tables(g, p, ws), scores, sel_rowptr_out, sel_idx_out, st);
+  if ((rc = need_tables(g, p, ws, st)) != SB_OK) return rc;
+  return select_launch(g, make_geom_args(g, p, make_tables(g, p, ws)), scores, sel_rowptr_out, sel_idx_out, st);
 }
 
 // launches the kernel that scores and selects; qbar/kbar are the pooled arrays
-static int score_select_launch(const Geo& g, const Tables& t, const float* qbar, const float* kbar, int32_t* sel_rowptr_out,
+static int score_select_launch(const Geo& g, const GeomArgs& ga, const float* qbar, const float* kbar, int32_t* sel_rowptr_out,
                                int32_t* sel_idx_out, hipStream_t st) {
   static std::mutex mu;
   static int lds_of_device[kMaxDevices] = {};  // LDS a workgroup may use, once the kernels' limit has been raised to it
@@ -228,13 +228,11 @@ static int score_select_launch(const Geo& g, const Tables& t, const float* qbar,
   dim3 grid((unsigned)(groups * g.Hs));
   KernelTimer kt(K_SCORE_SELECT, st);
   if (g.D == 128)
-    hipLaunchKernelGGL(score_select_kernel<128>, grid, dim3(64 * kFusedWaves), smem, st, qbar, kbar, t.qb_off, t.row_base, t.kclamp,
-                       t.qb_seq, g.NQB, g.Hq, g.Hkv, g.Hs, g.G, g.mode, g.score_scale, g.nnz_unit, R, stride, sel_rowptr_out,
-                       sel_idx_out);
+    hipLaunchKernelGGL(score_select_kernel<128>, grid, dim3(64 * kFusedWaves), smem, st, qbar, kbar, ga, g.NQB, g.Hq, g.Hkv, g.Hs, g.G,
+                       g.mode, g.score_scale, g.nnz_unit, R, stride, sel_rowptr_out, sel_idx_out);
   else
-    hipLaunchKernelGGL(score_select_kernel<64>, grid, dim3(64 * kFusedWaves), smem, st, qbar, kbar, t.qb_off, t.row_base, t.kclamp,
-                       t.qb_seq, g.NQB, g.Hq, g.Hkv, g.Hs, g.G, g.mode, g.score_scale, g.nnz_unit, R, stride, sel_rowptr_out,
-                       sel_idx_out);
+    hipLaunchKernelGGL(score_select_kernel<64>, grid, dim3(64 * kFusedWaves), smem, st, qbar, kbar, ga, g.NQB, g.Hq, g.Hkv, g.Hs, g.G,
+                       g.mode, g.score_scale, g.nnz_unit, R, stride, sel_rowptr_out, sel_idx_out);
   SB_LAUNCH_CHECK("score_select_kernel");
   return SB_OK;
 }
@@ -250,18 +248,17 @@ extern "C" int sb_score_select(const sb_problem* p, const void* q, const void* k
     return fill_zero(sel_rowptr_out, sizeof(int32_t), st);
   }
   if (!sel_idx_out) { set_error("null sel_idx_out"); return SB_ERR_INVALID_ARG; }
+  if (!q || !k || !ws) { set_error("null q, k or ws"); return SB_ERR_INVALID_ARG; }
+  const GeomArgs ga = make_geom_args(g, p, make_tables(g, p, ws));
   if (scores_out) {  // the caller wants the score matrix: write it, then select from it
     rc = sb_block_scores(p, q, k, kbar_out, scores_out, ws, stream);  // leaves the geometry tables at the start of ws
     if (rc != SB_OK) return rc;
-    return select_launch(g, make_tables(g, p, ws), scores_out, sel_rowptr_out, sel_idx_out, st);
+    return select_launch(g, ga, scores_out, sel_rowptr_out, sel_idx_out, st);
   }
-  if (!q || !k || !ws) { set_error("null q, k or ws"); return SB_ERR_INVALID_ARG; }
-  rc = launch_geom(g, p, ws, st);
-  if (rc != SB_OK) return rc;
-  Tables t = make_tables(g, p, ws);
+  if ((rc = need_tables(g, p, ws, st)) != SB_OK) return rc;
   float *qbar = nullptr, *kbar = nullptr;
-  if ((rc = launch_pool(g, p, t, q, k, kbar_out, ws, st, &qbar, &kbar)) != SB_OK) return rc;
-  return score_select_launch(g, t, qbar, kbar, sel_rowptr_out, sel_idx_out, st);
+  if ((rc = launch_pool(g, ga, q, k, kbar_out, ws, st, &qbar, &kbar)) != SB_OK) return rc;
+  return score_select_launch(g, ga, qbar, kbar, sel_rowptr_out, sel_idx_out, st);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -305,7 +302,6 @@ extern "C" int sb_select_topk_static(const sb_problem* p, const float* scores, i
   void* ws = nullptr;
   if ((rc = static_scratch_ptr(&ws)) != SB_OK) return rc;
   // every table entry the selection reads is rewritten by the geometry kernel of this call: nothing has to start at zero
-  rc = launch_geom(g, p, ws, st);
-  if (rc != SB_OK) return rc;
-  return select_launch(g, make_tables(g, p, ws), scores, sel_rowptr_out, sel_idx_out, st);
+  if ((rc = need_tables(g, p, ws, st)) != SB_OK) return rc;
+  return select_launch(g, make_geom_args(g, p, make_tables(g, p, ws)), scores, sel_rowptr_out, sel_idx_out, st);
 }

@@ -6,7 +6,7 @@ import torch
 from helpers import Run
 from paper_2604_13847_amd import binding as sb
 from paper_2604_13847_amd import synth
-from test_gpu_parity import check_attention
+from test_gpu_parity import check_attention, check_plan, check_scores, check_selection, fused_selection_matches
 
 pytestmark = pytest.mark.gpu
 
@@ -31,3 +31,18 @@ def test_columns_of_small_problems_walked_by_several_workgroups(lens, Hq, Hkv, D
                               dq=r.dq, dk=r.dk, dv=r.dv)
         torch.cuda.synchronize()
         assert torch.equal(r.dk.view(torch.int16), dk.view(torch.int16)) and torch.equal(r.dv.view(torch.int16), dv.view(torch.int16))
+
+
+# Up to 64 sequences the kernels find their place by a scan across the lanes, from 65 on in tables in memory; the plan's work
+# lists and its transpose are one launch for selection blocks of one tile and of several.
+@pytest.mark.parametrize("S", [1, 63, 64, 65, 130])
+@pytest.mark.parametrize("B,mode", [(64, 0), (256, 1)])
+def test_sequence_counts_around_a_wavefront(S, B, mode):
+    lens = [[130, 1, 0, 64, 577][(7 * s) % 5] for s in range(S)]
+    w = synth.small_ragged(seed=80 + S, lens=lens, Hq=4, Hkv=2, D=64, B=B, ratio=(0.3, 0.9))
+    r = Run(w, mode)
+    check_selection(r, check_scores(r))
+    if B == 64:
+        check_plan(r)
+    fused_selection_matches(r)
+    print(w, check_attention(r), flush=True)
