@@ -759,8 +759,6 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_reduce_kernel(AttnParams P, 
   }
 }
 
-int convert_f32_to_bf16(const void* src, void* dst, int64_t n, hipStream_t st);
-
 template <int D, bool F32>
 static int launch_bwd(const Geo& g, const AttnParams& P, hipStream_t st) {
   // query-major dQ: one workgroup per (item, part of the item's query heads); 2 * KS wavefronts per head
@@ -818,10 +816,12 @@ extern "C" int sb_sparse_attn_bwd(const sb_problem* p, const void* q, const void
   const bool f32 = g.dtype == SB_F32;
   if (f32) {
     KernelTimer kt(K_BWD_PREP, st);  // float32 inputs only: the conversions to the kernels' operand type
-    if ((rc = convert_f32_to_bf16(q, wb + wo.qc, (int64_t)g.T * g.Hq * g.D, st)) != SB_OK) return rc;
-    if ((rc = convert_f32_to_bf16(k, wb + wo.kc, (int64_t)g.T * g.Hkv * g.D, st)) != SB_OK) return rc;
-    if ((rc = convert_f32_to_bf16(v, wb + wo.vc, (int64_t)g.T * g.Hkv * g.D, st)) != SB_OK) return rc;
-    if ((rc = convert_f32_to_bf16(d_o, wb + wo.doc, (int64_t)g.T * g.Hq * g.D, st)) != SB_OK) return rc;
+    Conversions c{};
+    c.add(q, wb + wo.qc, (int64_t)g.T * g.Hq * g.D);
+    c.add(k, wb + wo.kc, (int64_t)g.T * g.Hkv * g.D);
+    c.add(v, wb + wo.vc, (int64_t)g.T * g.Hkv * g.D);
+    c.add(d_o, wb + wo.doc, (int64_t)g.T * g.Hq * g.D);
+    if ((rc = convert_f32_to_bf16(c, st)) != SB_OK) return rc;
     P.q = (const bf16*)(wb + wo.qc); P.k = (const bf16*)(wb + wo.kc); P.v = (const bf16*)(wb + wo.vc);
     P.d_o = (const bf16*)(wb + wo.doc);
   } else {

@@ -40,6 +40,14 @@ struct AttnParams {
   int* ticket;        // [kTicketSlots] counters, zero at launch; null: every item is taken by position
   int n_items;        // query-major items
 };
+// float -> bf16 copies of one launch
+struct Conversions {
+  const void* src[4]; void* dst[4]; int64_t n4[4];
+  int n;
+  void add(const void* from, void* to, int64_t elems) { src[n] = from; dst[n] = to; n4[n++] = elems / 4; }
+};
+int convert_f32_to_bf16(const Conversions& c, hipStream_t st);
+
 constexpr int kTicketSlots = 64;    // one counter per head plane of a query-major launch
 
 // Which item does the workgroup at position `pos` of a launch work on?

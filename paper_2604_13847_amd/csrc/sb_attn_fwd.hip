@@ -552,19 +552,27 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void a
   timer.stop(P);
 }
 
-// float -> bf16 (round to nearest even) copy used when the caller's tensors are float
-__global__ __launch_bounds__(256) void f32_to_bf16_kernel(const float* __restrict__ src, bf16* __restrict__ dst, int64_t n4) {
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= n4) return;
-  float4 x = ((const float4*)src)[idx];
-  bf16x4 y;
-  y[0] = (bf16)x.x; y[1] = (bf16)x.y; y[2] = (bf16)x.z; y[3] = (bf16)x.w;
-  ((bf16x4*)dst)[idx] = y;
+// float -> bf16 (round to nearest even) copies used when the caller's tensors are float: up to four tensors, one after the other, as
+// one launch (a launch costs a small problem 4 us; element counts are multiples of head_dim)
+__global__ __launch_bounds__(256) void f32_to_bf16_kernel(Conversions c) {
+  int64_t at = (int64_t)blockIdx.x * 256 + threadIdx.x;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    if (at < c.n4[t]) {
+      const float4 x = ((const float4*)c.src[t])[at];
+      bf16x4 y;
+      y[0] = (bf16)x.x; y[1] = (bf16)x.y; y[2] = (bf16)x.z; y[3] = (bf16)x.w;
+      ((bf16x4*)c.dst[t])[at] = y;
+      return;
+    }
+    at -= c.n4[t];
+  }
 }
 
-int convert_f32_to_bf16(const void* src, void* dst, int64_t n, hipStream_t st) {
-  const int64_t n4 = n / 4;  // element counts are multiples of head_dim
-  hipLaunchKernelGGL(f32_to_bf16_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, (const float*)src, (bf16*)dst, n4);
+int convert_f32_to_bf16(const Conversions& c, hipStream_t st) {
+  const int64_t n4 = c.n4[0] + c.n4[1] + c.n4[2] + c.n4[3], wgs = (n4 + 255) / 256;
+  if (wgs > 0x7fffffffll) { set_error("too many elements for one launch of the conversion"); return SB_ERR_UNSUPPORTED; }
+  hipLaunchKernelGGL(f32_to_bf16_kernel, dim3((unsigned)wgs), dim3(256), 0, st, c);
   SB_LAUNCH_CHECK("f32_to_bf16_kernel");
   return SB_OK;
 }
@@ -590,9 +598,11 @@ extern "C" int sb_sparse_attn_fwd(const sb_problem* p, const void* q, const void
   Tables t = make_tables(g, p, (void*)(pb + po.tables));
   AttnParams P{};
   if (g.dtype == SB_F32) {
-    if ((rc = convert_f32_to_bf16(q, wb + wo.qc, (int64_t)g.T * g.Hq * g.D, st)) != SB_OK) return rc;
-    if ((rc = convert_f32_to_bf16(k, wb + wo.kc, (int64_t)g.T * g.Hkv * g.D, st)) != SB_OK) return rc;
-    if ((rc = convert_f32_to_bf16(v, wb + wo.vc, (int64_t)g.T * g.Hkv * g.D, st)) != SB_OK) return rc;
+    Conversions c{};
+    c.add(q, wb + wo.qc, (int64_t)g.T * g.Hq * g.D);
+    c.add(k, wb + wo.kc, (int64_t)g.T * g.Hkv * g.D);
+    c.add(v, wb + wo.vc, (int64_t)g.T * g.Hkv * g.D);
+    if ((rc = convert_f32_to_bf16(c, st)) != SB_OK) return rc;
     P.q = (const bf16*)(wb + wo.qc); P.k = (const bf16*)(wb + wo.kc); P.v = (const bf16*)(wb + wo.vc);
   } else {
     P.q = (const bf16*)q; P.k = (const bf16*)k; P.v = (const bf16*)v;
