@@ -330,16 +330,20 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(2))) void 
 // every matrix instruction carries the same share of vector work and LDS reads, fenced step by step, results are used two
 // stages after they were started, and the tile loads are issued two at a time between matrix instructions instead of 17 in a
 // row.  The scores are kept out of the accumulation registers (mfma32_first).  32768-token batch, 32/8 heads, D = 128:
-// 3.66 -> 3.24 ms (matrix cores busy 48 -> 56 % of the cycles), block 256 at D = 64: 3.7 -> 3.35 ms, the 262144-token batch,
-// whose gathers come through the fabric at 6 TB/s: 36.7 -> 34.9 ms.
+// 3.66 -> 3.24 ms (matrix cores busy 48 -> 56 % of the cycles), the 262144-token batch, whose gathers come through the fabric at
+// 6 TB/s: 36.7 -> 34.9 ms.
+// D = 64 needs half the registers: there two wavefronts share a SIMD instead, a half tile is computed from start to end, and the
+// shorter tile list (8 bitmap words per chunk) lets four workgroups share a CU's LDS.  Matrix cores busy 39 -> 48 %, at a clock that
+// the chip lowers from 1.9 to 1.6 GHz for it; together with the forward kernel's second wavefront per SIMD a step of 65536 tokens,
+// 14/2 heads, selection blocks of 256: 7.66 -> 6.81 ms.
 template <int D, bool OUT_F32>
-__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void attn_bwd_dkv_kernel(AttnParams P) {
+__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1))) void attn_bwd_dkv_kernel(AttnParams P) {
   constexpr int TILE_B = 64 * D * 2;  // bytes of one Q or dO tile
   constexpr int BUF_B = 2 * TILE_B;   // bytes of one buffer (Q tile, dO tile)
   constexpr int ROW_B = D * 2;
   __shared__ __attribute__((aligned(1024))) bf16 tiles[2][2][64 * D];  // [buffer][Q, dO]
   __shared__ __attribute__((aligned(256))) float rowstat[4][2][64];    // [buffer, half][LSE * log2(e), Dr]: 32 rows each, the other 32 unused
-  constexpr int kCW = 16;            // bitmap words (32 query blocks each) handled per chunk
+  constexpr int kCW = D == 64 ? 8 : 16;  // bitmap words (32 query blocks each) handled per chunk
   __shared__ uint32_t bm_s[8][kCW];  // bitmap words of up to 8 selection heads
   __shared__ uint16_t tl_s[kCW * 32 * 8];  // the chunk's tiles in processing order
   __shared__ int ntl_s;
@@ -527,12 +531,79 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void a
       }
       const uint16_t* const list = tl_s + (nall - 1 - lo);  // tile t of the run is list[-t]
 #pragma unroll
-      for (int ks = 0; ks < D / 16; ++ks) asm volatile("" : "+a"(kf[ks]), "+a"(vf[ks]));
+      for (int ks = 0; ks < D / 16; ++ks) {
+        if constexpr (D == 64) asm volatile("" : "+v"(kf[ks]), "+v"(vf[ks]));
+        else asm volatile("" : "+a"(kf[ks]), "+a"(vf[ks]));
+      }
       auto entry = [&](int t, int& i, int& h) __attribute__((always_inline)) {
         const int e = __builtin_amdgcn_readfirstlane((int)list[-t]);
         i = 32 * w0 + (e >> 3);
         h = g * P.G + sel0 + (e & 7);
       };
+      using H0 = std::integral_constant<int, 0>;
+      using H1 = std::integral_constant<int, 1>;
+      const int nn = ntl - nd;  // tiles without a mask
+      if constexpr (D == 64) {
+        // ---- D = 64: the kernel fits 256 registers, two wavefronts share a SIMD and hide each other's latencies, so a half tile
+        // is computed from start to end.  Half tile u: its loads have landed for everyone and u - 1 has been read by everyone, so
+        // u - 1's buffer takes the loads of u + 3.
+        int i0, h0, i1, h1;
+        entry(0, i0, h0);
+        issue_half(half_of(0, 0, i0, h0));
+        issue_half(half_of(0, 1, i0, h0));
+        entry(min(1, ntl - 1), i1, h1);
+        issue_half(half_of(1, 0, i1, h1));
+        auto half_tile = [&](auto diag_c, auto half_c, int buf, int t) __attribute__((always_inline)) {
+          constexpr bool DIAG = decltype(diag_c)::value;
+          constexpr int HALF = decltype(half_c)::value;
+          const unsigned CO = buf * BUF_B + HALF * 32 * ROW_B, SO = (2 * buf + HALF) * 512;
+          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(2 * kLoadsPerHalf) : "memory");
+          __builtin_amdgcn_s_barrier();
+          if (HALF == 1) entry(min(t + 2, ntl - 1), i1, h1);
+          issue_half(half_of(HALF == 0 ? 1 - buf : buf, 1 - HALF, i1, h1));  // (past the last tile: that tile once more, never read)
+          bf16x8 rows[NOP], tr[NOP];
+          f32x4 sl[4], sd[4];
+#pragma unroll
+          for (int k = 0; k < NOP; ++k) rows[k] = ld_row(k, CO);
+#pragma unroll
+          for (int k = 0; k < NOP; ++k) tr[k] = ld_row(k, CO + TILE_B);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) sl[v] = ld_stat(SO, v);
+          f32x16 s_ = zero16(), dp = zero16();
+#pragma unroll
+          for (int k = 0; k < NOP; ++k) s_ = mfma32(rows[k], kf[k], s_);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) sd[v] = ld_stat(SO + 256, v);
+#pragma unroll
+          for (int k = 0; k < NOP; ++k) dp = mfma32(tr[k], vf[k], dp);
+#pragma unroll
+          for (int k = 0; k < NOP; ++k) tr[k] = ld_tr(k, CO + TILE_B);
+#pragma unroll
+          for (int k = 0; k < NOP; ++k) rows[k] = ld_tr(k, CO);
+          bf16x8 pb[2], ds[2];
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            float pv = fast_exp2(__builtin_fmaf(s_[v], P.scale_log2e, -sl[v >> 2][v & 3]));
+            if (DIAG && kloc > 32 * HALF + c_row(v, hf)) pv = 0.f;  // causal mask inside the diagonal tile
+            pb[v >> 3][v & 7] = (bf16)pv;
+            ds[v >> 3][v & 7] = (bf16)(pv * (dp[v] - sd[v >> 2][v & 3]));
+          }
+#pragma unroll
+          for (int k = 0; k < NOP; ++k) dvacc[k % (D / 32)] = mfma32(pb[k / (D / 32)], tr[k], dvacc[k % (D / 32)]);
+#pragma unroll
+          for (int k = 0; k < NOP; ++k) dkacc[k % (D / 32)] = mfma32(ds[k / (D / 32)], rows[k], dkacc[k % (D / 32)]);
+        };
+        int t = 0;
+        for (; t < nn; ++t) {
+          half_tile(std::false_type(), H0(), t & 1, t);
+          half_tile(std::false_type(), H1(), t & 1, t);
+        }
+        for (; t < ntl; ++t) {  // the diagonal tiles
+          half_tile(std::true_type(), H0(), t & 1, t);
+          half_tile(std::true_type(), H1(), t & 1, t);
+        }
+        wait_vmcnt<0>();  // the loads past the last tile
+      } else {
       // ---- software pipeline over half tiles u = 0, 1, ...: four stages of NOP matrix instructions each,
       //   S(u), dP(u), dV(u-1), dK(u-1)
       // with P(u) spread under the last two and dS(u-1) under the first two, so that every matrix instruction has the same
@@ -647,9 +718,6 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void a
       {
         using std::true_type;
         using std::false_type;
-        using H0 = std::integral_constant<int, 0>;
-        using H1 = std::integral_constant<int, 1>;
-        const int nn = ntl - nd;  // tiles without a mask
         auto tile = [&](auto first_c, auto diag_c, int buf, int t) __attribute__((always_inline)) {
           half_tile(first_c, false_type(), diag_c, H0(), buf, t);
           half_tile(false_type(), false_type(), diag_c, H1(), buf, t);
@@ -665,6 +733,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void a
         for (; t < ntl; ++t) tile(false_type(), true_type(), t & 1, t);  // the diagonal tiles
         half_tile(false_type(), true_type(), false_type(), H0(), ntl & 1, ntl);
         wait_vmcnt<0>();  // the loads past the last tile
+      }
       }
     }
   }

@@ -12,6 +12,9 @@
 // S^T = K Q^T puts a query in a C-matrix column, so the softmax statistics are per lane and the
 // probabilities convert to the B operand of O^T += V^T P^T without any cross-lane movement; V^T is
 // read straight out of the row-major V strip with the transposing LDS read.
+// D = 128 needs more than 256 registers and runs one wavefront per SIMD.  D = 64 is held to 256, so that two share a SIMD and one
+// runs its exponentials (which outlast the matrix instructions there) under the other's matrix instructions: matrix cores busy
+// 28 -> 40 % of the cycles, 2.14 -> 1.75 ms on 65536 tokens, 14/2 heads, selection blocks of 256.
 #include <type_traits>
 
 #include "sb_attn_common.h"
@@ -19,7 +22,7 @@
 namespace sb {
 
 template <int D, bool OUT_F32>
-__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void attn_fwd_kernel(AttnParams P, int n_items, int heads) {
+__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1))) void attn_fwd_kernel(AttnParams P, int n_items, int heads) {
   constexpr int NS = 4;          // strips in a wavefront's ring
   constexpr int SLOT = 32 * D;   // elements per strip
   constexpr int LPS = StripLoader<D>::LPS;
@@ -202,7 +205,10 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void a
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) oacc[dt][b][v] = scale_acc(oacc[dt][b][v], alpha[b]);
+          for (int v = 0; v < 16; ++v) {
+            if constexpr (D == 64) oacc[dt][b][v] *= alpha[b];
+            else oacc[dt][b][v] = scale_acc(oacc[dt][b][v], alpha[b]);
+          }
     }
   };
   auto accumulate = [&]() __attribute__((always_inline)) {  // O^T += V^T P^T with the operands in va and pb
@@ -236,6 +242,9 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void a
     constexpr int PAR = decltype(par_c)::value;  // t % 2
     constexpr bool STEADY = decltype(steady_c)::value;
     constexpr int SV = (2 * PAR + 2) % NS, SK = (2 * PAR + 3) % NS;  // slots of strips 2t+2 (V_t) and 2t+3 (K_{t+2})
+    // max3 in the softmax is inline asm, whose reads of the matrix instructions' results the compiler's hazard recogniser does not
+    // see (at D = 128 it copies the scores out of accumulation registers itself): 12 wait states after an 8-pass instruction
+    if constexpr (D == 64) asm volatile("s_nop 7\n\ts_nop 3" : "+v"(sa[PAR][0]), "+v"(sa[PAR][1]));
     if (STEADY) wait_vmcnt<3 * LPS>(); else wait_strip(2 * t + 2);
     read_v(SV);
     scores(sa[PAR ^ 1]);

@@ -19,7 +19,9 @@ pytestmark = pytest.mark.gpu
     ([300, 64, 1, 577], 14, 2, 128, 0, (0.4, 1.0)),       # seven heads, ragged short sequences
     ([300, 64, 1, 577], 8, 2, 128, 1, (0.4, 1.0)),        # one selection for four heads
     ([2100], 16, 1, 64, 0, (1.0, 1.0)),                   # two rounds of eight selection heads: runs cross the rounds
-    ([64 * 520 - 3], 2, 1, 64, 0, (0.01, 0.01)),          # runs cross the chunks of 512 query blocks
+    ([64 * 520 - 3], 2, 1, 64, 0, (0.01, 0.01)),          # runs cross the chunks of 256 query blocks (512 at D = 128)
+    ([64 * 520 - 3], 2, 1, 128, 0, (0.01, 0.01)),
+    ([64 * 257 - 3], 2, 1, 64, 0, (0.02, 0.02)),          # one query block past a chunk
 ])
 def test_columns_of_small_problems_walked_by_several_workgroups(lens, Hq, Hkv, D, mode, ratio):
     w = synth.small_ragged(seed=71, lens=lens, Hq=Hq, Hkv=Hkv, D=D, ratio=ratio)
