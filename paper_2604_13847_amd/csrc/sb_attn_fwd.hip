@@ -14,7 +14,7 @@
 // read straight out of the row-major V strip with the transposing LDS read.
 // D = 128 needs more than 256 registers and runs one wavefront per SIMD.  D = 64 is held to 256, so that two share a SIMD and one
 // runs its exponentials (which outlast the matrix instructions there) under the other's matrix instructions: matrix cores busy
-// 28 -> 40 % of the cycles, 2.14 -> 1.75 ms on 65536 tokens, 14/2 heads, selection blocks of 256.
+// 28 -> 40 % of the cycles, 2.14 -> 1.67 ms on 65536 tokens, 14/2 heads, selection blocks of 256 (1.56 with the softmax's branch).
 #include <type_traits>
 
 #include "sb_attn_common.h"
@@ -160,44 +160,6 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
       for (int ks = 0; ks < D / 16; ++ks) dst[b] = mfma32(ka[ks], qf[b][ks], dst[b]);
     }
   };
-  // online softmax on raw scores sc: p = exp2(scale*log2e * (s - m)) -> pb, running sums updated
-  auto softmax = [&](const f32x16* sc) __attribute__((always_inline)) {
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      float mx = max3(sc[b][0], sc[b][1], sc[b][2]);
-#pragma unroll
-      for (int v = 3; v < 15; v += 2) mx = max3(mx, sc[b][v], sc[b][v + 1]);
-      mx = max_across_halves(fmaxf(mx, sc[b][15]));
-      // Lazy running maximum: the reference m[b] used in the exponent follows the true maximum only
-      // when that has grown by more than kLazy (in log2 units), so p stays below 2^kLazy and the
-      // accumulated O needs rescaling only then.  The result is the same up to rounding (O and the
-      // row sum carry the same factor), and the rescale branch becomes rare instead of the rule.
-      const bool first = m[b] == -__builtin_inff();  // nothing accumulated yet for this query: nothing to rescale
-      const bool move = first | ((mx - m[b]) * P.scale_log2e > kLazy);
-      const float m_new = move ? fmaxf(m[b], mx) : m[b];
-      // a wavefront may have seen no unmasked key yet for a query (its strip of the diagonal block can
-      // be entirely above the diagonal): keep the exponent finite then
-      const float m_use = m_new == -__builtin_inff() ? 0.f : m_new;
-      alpha[b] = first ? 1.0f : fast_exp2((m[b] - m_use) * P.scale_log2e);
-      const float neg_m = -m_use * P.scale_log2e;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) pb[b][v >> 3][v & 7] = (bf16)fast_exp2(__builtin_fmaf(sc[b][v], P.scale_log2e, neg_m));
-      // the row sum adds up the probabilities as rounded to bf16, i.e. exactly the weights the
-      // accumulation below applies, two per instruction
-      float rs = l[b] * alpha[b];
-#pragma unroll
-      for (int kk = 0; kk < 2; ++kk)
-      {
-        const bf16x8 x = pb[b][kk];
-        rs = sum2(__builtin_shufflevector(x, x, 0, 1), rs);
-        rs = sum2(__builtin_shufflevector(x, x, 2, 3), rs);
-        rs = sum2(__builtin_shufflevector(x, x, 4, 5), rs);
-        rs = sum2(__builtin_shufflevector(x, x, 6, 7), rs);
-      }
-      l[b] = rs;
-      m[b] = m_new;
-    }
-  };
   auto rescale = [&]() __attribute__((always_inline)) {
     if (__builtin_amdgcn_ballot_w64((alpha[0] != 1.0f) | (alpha[1] != 1.0f)) != 0) {
 #pragma unroll
@@ -209,6 +171,67 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
             if constexpr (D == 64) oacc[dt][b][v] *= alpha[b];
             else oacc[dt][b][v] = scale_acc(oacc[dt][b][v], alpha[b]);
           }
+    }
+  };
+  // online softmax on raw scores sc: p = exp2(scale*log2e * (s - m)) -> pb, running sums updated
+  float neg_m[2];
+  auto max_of = [&](const f32x16& x) __attribute__((always_inline)) {  // of this lane's keys
+    float mx = max3(x[0], x[1], x[2]);
+#pragma unroll
+    for (int v = 3; v < 15; v += 2) mx = max3(mx, x[v], x[v + 1]);
+    return fmaxf(mx, x[15]);
+  };
+  auto reference = [&](const float* mx_lane) __attribute__((always_inline)) {  // moves m, sets alpha
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const float mx = max_across_halves(mx_lane[b]);
+      // Lazy running maximum: the reference m[b] used in the exponent follows the true maximum only
+      // when that has grown by more than kLazy (in log2 units), so p stays below 2^kLazy and the
+      // accumulated O needs rescaling only then.  The result is the same up to rounding (O and the
+      // row sum carry the same factor), and the rescale branch becomes rare instead of the rule.
+      const bool first = m[b] == -__builtin_inff();  // nothing accumulated yet for this query: nothing to rescale
+      const bool move = first | ((mx - m[b]) * P.scale_log2e > kLazy);
+      const float m_new = move ? fmaxf(m[b], mx) : m[b];
+      // a wavefront may have seen no unmasked key yet for a query (its strip of the diagonal block can
+      // be entirely above the diagonal): keep the exponent finite then
+      const float m_use = m_new == -__builtin_inff() ? 0.f : m_new;
+      alpha[b] = first ? 1.0f : fast_exp2((m[b] - m_use) * P.scale_log2e);
+      neg_m[b] = -m_use * P.scale_log2e;
+      l[b] *= alpha[b];
+      m[b] = m_new;
+    }
+  };
+  auto softmax = [&](const f32x16* sc) __attribute__((always_inline)) {
+    const float mx[2] = {max_of(sc[0]), max_of(sc[1])};
+    if constexpr (D == 64) {
+      // Whether any lane's own maximum has grown that far is one comparison per lane, so everything else about the reference moves
+      // into a branch that a row takes in its first tiles: the vector work, not the matrix work, bounds this head dimension
+      // (1674 -> 1563 us on 65536 tokens, 14/2 heads, selection blocks of 256).  At D = 128 the branch gains nothing (1946 against
+      // 1941 us on the 32768-token batch, 7420 against 7458 on one 131072-token sequence): its waits are for the strips.
+      if (__builtin_amdgcn_ballot_w64(!((mx[0] - m[0]) * P.scale_log2e <= kLazy) | !((mx[1] - m[1]) * P.scale_log2e <= kLazy)) != 0) {
+        reference(mx);
+        rescale();
+      }
+    } else {
+      reference(mx);
+    }
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) pb[b][v >> 3][v & 7] = (bf16)fast_exp2(__builtin_fmaf(sc[b][v], P.scale_log2e, neg_m[b]));
+      // the row sum adds up the probabilities as rounded to bf16, i.e. exactly the weights the
+      // accumulation below applies, two per instruction
+      float rs = l[b];
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+      {
+        const bf16x8 x = pb[b][kk];
+        rs = sum2(__builtin_shufflevector(x, x, 0, 1), rs);
+        rs = sum2(__builtin_shufflevector(x, x, 2, 3), rs);
+        rs = sum2(__builtin_shufflevector(x, x, 4, 5), rs);
+        rs = sum2(__builtin_shufflevector(x, x, 6, 7), rs);
+      }
+      l[b] = rs;
     }
   };
   auto accumulate = [&]() __attribute__((always_inline)) {  // O^T += V^T P^T with the operands in va and pb
@@ -253,7 +276,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
     // exponentials overlap the score MFMAs; those of the other 16 may sink below it and overlap the
     // first half of the accumulation MFMAs.
     asm volatile("" : "+v"(pb[0][0]), "+v"(pb[1][0]));
-    rescale();
+    if constexpr (D != 64) rescale();
     if (STEADY) {
       wait_vmcnt<2 * LPS>();
       read_k(SK);
@@ -297,7 +320,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
     for (int v = 0; v < 16; ++v)
       if (32 * wave + c_row(v, hf) > 32 * b + l32) sa[0][b][v] = -__builtin_inff();
   softmax(sa[0]);
-  rescale();
+  if constexpr (D != 64) rescale();
   accumulate();
 
   // ---- merge the two key halves: wavefront w finalises query half w and hands the other half over
@@ -440,7 +463,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void a
   f32x16 oacc[D / 32];
 #pragma unroll
   for (int dt = 0; dt < D / 32; ++dt) oacc[dt] = zero16();
-  float m = -__builtin_inff(), l = 0.f;
+  float m = -__builtin_inff(), neg_m = 0.f, l = 0.f;
   bf16x8 op[NOP];
 
   // The diagonal block is always the last tile of a row: it takes its own instantiation of the tile
@@ -481,38 +504,39 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void a
       // and then took a stale value into its running maximum: harmless for the result's accuracy (the softmax does
       // not depend on the reference point) but not bitwise repeatable.
       if (!diag) asm volatile("s_nop 7\n\ts_nop 3" : "+v"(sacc));
-      // online softmax with a lazy running maximum: the reference m follows the true maximum only when
-      // that has grown by more than kLazy (in log2 units), so p stays below 2^kLazy and the accumulated
-      // O is rescaled only then; O and the row sum carry the same factor, so the result is the same
+      // online softmax with a lazy running maximum, the reference moved in a branch that is rarely taken (see the kernel above; two
+      // wavefronts share the SIMD's vector unit here, which is what bounds them: 32768-token batch, 32/8 heads, 1744 -> 1642 us)
       float mx = max3(sacc[0], sacc[1], sacc[2]);
 #pragma unroll
       for (int v = 3; v < 15; v += 2) mx = max3(mx, sacc[v], sacc[v + 1]);
-      mx = max_across_halves(fmaxf(mx, sacc[15]));
-      const bool first = m == -__builtin_inff();  // nothing accumulated yet for this query
-      const bool move = first | ((mx - m) * P.scale_log2e > kLazy);
-      const float m_new = move ? fmaxf(m, mx) : m;
-      const float m_use = m_new == -__builtin_inff() ? 0.f : m_new;  // no unmasked key seen yet: keep the exponent finite
-      const float alpha = first ? 1.0f : fast_exp2((m - m_use) * P.scale_log2e);
-      const float neg_m = -m_use * P.scale_log2e;
+      mx = max3(mx, sacc[15], sacc[15]);
+      if (__builtin_amdgcn_ballot_w64(!((mx - m) * P.scale_log2e <= kLazy)) != 0) {
+        mx = max_across_halves(mx);
+        const bool first = m == -__builtin_inff();  // nothing accumulated yet for this query
+        const bool move = first | ((mx - m) * P.scale_log2e > kLazy);
+        const float m_new = move ? fmaxf(m, mx) : m;
+        const float m_use = m_new == -__builtin_inff() ? 0.f : m_new;  // no unmasked key seen yet: keep the exponent finite
+        const float alpha = first ? 1.0f : fast_exp2((m - m_use) * P.scale_log2e);
+        neg_m = -m_use * P.scale_log2e;
+        m = m_new;
+        if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+          l *= alpha;
+#pragma unroll
+          for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) oacc[dt][v] *= alpha;
+        }
+      }
       bf16x8 pb[2];
 #pragma unroll
       for (int v = 0; v < 16; ++v) pb[v >> 3][v & 7] = (bf16)fast_exp2(__builtin_fmaf(sacc[v], P.scale_log2e, neg_m));
-      float rs = l * alpha;  // the row sum adds the probabilities as rounded to bf16, the weights the accumulation applies
 #pragma unroll
-      for (int kk = 0; kk < 2; ++kk) {
+      for (int kk = 0; kk < 2; ++kk) {  // the row sum adds the probabilities as rounded to bf16, the weights the accumulation applies
         const bf16x8 x = pb[kk];
-        rs = sum2(__builtin_shufflevector(x, x, 0, 1), rs);
-        rs = sum2(__builtin_shufflevector(x, x, 2, 3), rs);
-        rs = sum2(__builtin_shufflevector(x, x, 4, 5), rs);
-        rs = sum2(__builtin_shufflevector(x, x, 6, 7), rs);
-      }
-      l = rs;
-      m = m_new;
-      if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
-#pragma unroll
-        for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) oacc[dt][v] *= alpha;
+        l = sum2(__builtin_shufflevector(x, x, 0, 1), l);
+        l = sum2(__builtin_shufflevector(x, x, 2, 3), l);
+        l = sum2(__builtin_shufflevector(x, x, 4, 5), l);
+        l = sum2(__builtin_shufflevector(x, x, 6, 7), l);
       }
 #pragma unroll
       for (int kk = 0; kk < 2; ++kk)

@@ -48,3 +48,23 @@ def test_sequence_counts_around_a_wavefront(S, B, mode):
         check_plan(r)
     fused_selection_matches(r)
     print(w, check_attention(r), flush=True)
+
+
+class GrowingKeys(synth.Workload):
+    """Keys grow along the sequence, so the softmax's reference point has to move again and again along a row."""
+
+    def tensors(self):
+        t = super().tensors()
+        at = np.concatenate([np.arange(n) / max(n, 1) for n in self.lens])
+        t["k"] = synth.round_to_bf16((t["k"] * (0.5 + 12.0 * at)[:, None, None]).astype(np.float32))
+        return t
+
+
+# The reference moves in a branch at head_dim 64 and in the kernel whose heads share tiles (three or four heads per KV head).
+# O is an average of V with weights rounded to bf16 as their sum is: the bound of the other parity tests holds for any scores.
+@pytest.mark.parametrize("Hq,Hkv,D,mode", [(2, 1, 64, 0), (4, 1, 64, 1), (3, 1, 128, 1), (4, 1, 128, 1), (2, 1, 128, 0)])
+def test_reference_of_the_softmax_moves_along_the_row(Hq, Hkv, D, mode):
+    lens = [1100, 65, 1, 64, 323]
+    w = GrowingKeys("growing", lens, Hq, Hkv, D, keep_ratio=np.full(len(lens), 1.0), seed=90 + D + Hq)
+    r = Run(w, mode, do_bwd=False)
+    print(w, check_attention(r, bwd=False), flush=True)
