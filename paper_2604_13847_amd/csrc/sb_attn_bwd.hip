@@ -316,6 +316,339 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(2))) void 
 }
 
 // ---------------------------------------------------------------------------------------------
+// The same for one query head per item at D = 128 (per-query-head selection, or one query head per KV head): two wavefronts, split
+// by KEYS as in the forward kernel: wavefront w owns keys 32w .. 32w+31 of every tile and all 64 query rows, so an operand read
+// from LDS feeds two matrix instructions (with 32 rows per wavefront LDS reads take as long as the matrix instructions), and it
+// stages its own strips of K and V, two of each, without any barrier in the loop.  It needs the registers of a whole SIMD, so the
+// loop is a software pipeline over half tiles u (32 keys x 32 queries), stages of 8 matrix instructions:
+//   S(u), dP(u), dQ(u-1)
+// with P(u) beside dP(u) and dQ(u-1), and dS(u) beside dQ(u-1) and the next S; every matrix instruction is fenced with its share of
+// the vector work and LDS reads, and nothing waits for a result of the stage before.
+// Against the kernel above (four wavefronts, 32 rows each), the whole backward of: the 262144-token batch 62.2 -> 60.7 ms, 65536
+// tokens with 28/4 heads 13.9 -> 13.4 ms, with selection blocks of 256 10.50 -> 10.21 ms, one 131072-token sequence 19.3 -> 19.0 ms,
+// the 32768-token batch 5.94 -> 5.84 ms; 65536 tokens whose selection is a sink and a window 6.42 against 6.41 ms.  Results are bit
+// for bit the same.
+template <bool OUT_F32>
+__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void attn_bwd_dq_head_kernel(AttnParams P) {
+  constexpr int D = 128, ROW_B = D * 2, STRIP_B = 32 * ROW_B, NOP = D / 16;
+  using Loader = RowLoader<D>;
+  constexpr int LPS = Loader::LPS;
+  constexpr int KV = 6;  // Q, dQ and the dO operands below this one live in accumulation registers, the other dO operands do not fit there
+  __shared__ __attribute__((aligned(1024))) char ring[2][4 * STRIP_B];  // per wavefront: K even, K odd, V even, V odd tiles
+  BusyTimer timer;
+  timer.start(P);
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+  const int pos = claim_item(blockIdx.x, P.n_items, P.ticket);
+  if (pos < 0) return;
+  const WorkItem item = P.items[pos];
+  const int hs = item.hs, i = item.i, L = item.len, e0 = item.e0, ntiles = item.ntiles;
+  const int64_t seq0 = item.seq0;
+  const int h = hs, g = h / P.G;  // one query head per selection head
+
+  // the row's block indices: lane a holds entry jb0 + a (see the forward kernel)
+  int jb0 = 0;
+  int jreg = lane < ntiles ? P.idx[e0 + lane] : 0;
+  auto refill = [&](int first) __attribute__((always_inline)) {
+    jb0 = first;
+    jreg = jb0 + lane < ntiles ? P.idx[e0 + jb0 + lane] : 0;
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), here and not at the join behind the caller's branch
+  };
+  // B operands: column = query 32b + lane%32, slots = d 16ks + 8hf + (0..7)
+  bf16x8 qf[2][NOP], dof[2][NOP];
+  float lse2[2], dr[2];
+  bool qvalid[2];
+  int64_t tq[2];
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    const int qloc = 32 * b + l32;
+    qvalid[b] = i * 64 + qloc < L;
+    tq[b] = seq0 + i * 64 + qloc;
+    const int64_t row = (tq[b] * P.Hq + h) * D + 8 * hf;
+#pragma unroll
+    for (int ks = 0; ks < NOP; ++ks) {
+      qf[b][ks] = qvalid[b] ? *(const bf16x8*)(P.q + row + 16 * ks) : zero_bf16x8();
+      dof[b][ks] = qvalid[b] ? *(const bf16x8*)(P.d_o + row + 16 * ks) : zero_bf16x8();
+    }
+    lse2[b] = __builtin_inff();  // rows that do not exist: P = exp2(x - inf) = 0
+    float part = 0.f;            // Dr: the lane's half of the head dimension, the other half is in lane ^ 32
+    if (qvalid[b]) {
+      if (OUT_F32) {
+        const float* op_ = (const float*)P.o + row;
+#pragma unroll
+        for (int ks = 0; ks < NOP; ++ks) {
+          const float4 x = *(const float4*)(op_ + 16 * ks), y = *(const float4*)(op_ + 16 * ks + 4);
+          const bf16x8 w = dof[b][ks];
+          part += (float)w[0] * x.x + (float)w[1] * x.y + (float)w[2] * x.z + (float)w[3] * x.w;
+          part += (float)w[4] * y.x + (float)w[5] * y.y + (float)w[6] * y.z + (float)w[7] * y.w;
+        }
+      } else {
+        const bf16* op_ = (const bf16*)P.o + row;
+#pragma unroll
+        for (int ks = 0; ks < NOP; ++ks) {
+          const bf16x8 ov = *(const bf16x8*)(op_ + 16 * ks);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) part += (float)dof[b][ks][e] * (float)ov[e];
+        }
+      }
+      lse2[b] = P.lse[(int64_t)h * P.T + tq[b]] * 1.4426950408889634f;
+    }
+    dr[b] = part + __shfl_xor(part, 32, 64);
+  }
+  Loader loader;
+  loader.init(P.Hkv, lane);
+  const int pitch = P.Hkv * D * 2;
+  const char* const k0 = (const char*)(P.k + ((seq0 + 32 * wave) * P.Hkv + g) * D);  // this wavefront's strip of block 0
+  const char* const v0 = (const char*)(P.v + ((seq0 + 32 * wave) * P.Hkv + g) * D);
+  const unsigned block_pitch = 64u * (unsigned)pitch;  // bytes from one key block to the next
+  const unsigned ring0 = lds_offset(&ring[wave][0]);
+  const int Lw = L - 32 * wave;
+  // strip of tile t, rows past the end of the sequence as zeros (they are masked: only the diagonal tile can have such rows)
+  auto strip_of = [&](bool is_v, int t) __attribute__((always_inline)) {
+    const int j = __builtin_amdgcn_readlane(jreg, t - jb0);
+    return Loader::strip(ring0 + ((is_v ? 2 : 0) + (t & 1)) * STRIP_B, (is_v ? v0 : k0) + (unsigned long long)(unsigned)j * block_pitch, Lw - j * 64, pitch);
+  };
+  // everything loaded so far must have landed before the strip loads start: the loop waits for those by count
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+#pragma unroll
+    for (int ks = 0; ks < NOP; ++ks) {
+      asm volatile("" : "+a"(qf[b][ks]));
+      if (ks < KV) asm volatile("" : "+a"(dof[b][ks]));
+      else asm volatile("" : "+v"(dof[b][ks]));
+    }
+    asm volatile("" : "+v"(lse2[b]), "+v"(dr[b]));
+  }
+  asm volatile("" : "+v"(jreg));
+  wait_vmcnt<0>();
+  loader.issue(strip_of(true, 0));
+  loader.issue(strip_of(false, 0));
+  if (ntiles > 1) {
+    loader.issue(strip_of(true, 1));
+    loader.issue(strip_of(false, 1));
+  }
+
+  // LDS byte addresses of this lane's operand reads in the wavefront's first slot
+  unsigned row_a[NOP], tr_a[D / 32][2];
+#pragma unroll
+  for (int ks = 0; ks < NOP; ++ks) row_a[ks] = ring0 + l32 * ROW_B + 16 * ((2 * ks + hf) ^ chunk_swizzle<D>(l32));
+#pragma unroll
+  for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const int r = 8 * half + 4 * hf + ((lane & 15) >> 2), d = 32 * dt + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+      tr_a[dt][half] = ring0 + r * ROW_B + 16 * ((d >> 3) ^ chunk_swizzle<D>(r)) + 2 * (d & 7);
+    }
+  auto ld_row = [&](int ks, unsigned off) __attribute__((always_inline)) {
+    return *(const bf16x8 __attribute__((address_space(3)))*)(row_a[ks] + off);
+  };
+  // A operand x = kk * 4 + dt of dQ^T += K^T dS^T: row = d (32dt + lane%32), slots = keys 16kk + 8(e/4) + 4hf + e%4
+  auto ld_tr = [&](int x, unsigned off) __attribute__((always_inline)) {
+    const int kk = x / (D / 32), dt = x % (D / 32);
+    const unsigned o = off + kk * 16 * ROW_B;
+    bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((bf16x4 __attribute__((address_space(3)))*)(tr_a[dt][0] + o));
+    bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((bf16x4 __attribute__((address_space(3)))*)(tr_a[dt][1] + o));
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
+  bf16x8 ka[NOP], va[NOP], kt[NOP];
+  f32x16 sacc[2], dpacc;
+  bf16x8 dsb[2][2];
+  f32x16 dqacc[D / 32][2];
+#pragma unroll
+  for (int dt = 0; dt < D / 32; ++dt) dqacc[dt][0] = dqacc[dt][1] = zero16();
+#pragma unroll
+  for (int k = 0; k < NOP; ++k) kt[k] = zero_bf16x8();
+  if (ntiles > 1) wait_vmcnt<2 * LPS>(); else wait_vmcnt<0>();
+#pragma unroll
+  for (int k = 0; k < NOP; ++k) { ka[k] = ld_row(k, 0); va[k] = ld_row(k, 2 * STRIP_B); }
+
+  // P = exp2(S c - lse2) of register v of query half b, in place; keys above the diagonal 0
+  auto prob = [&](auto diag_c, int b, int v) __attribute__((always_inline)) {
+    float pv = fast_exp2(__builtin_fmaf(sacc[b][v], P.scale_log2e, -lse2[b]));
+    if (decltype(diag_c)::value && 32 * wave + c_row(v, hf) > 32 * b + l32) pv = 0.f;
+    sacc[b][v] = pv;
+  };
+  float ds_even;
+  auto dscore = [&](int b, int v) __attribute__((always_inline)) {  // dS = P (dP - Dr), to bf16 in pairs
+    const float x = sacc[b][v] * (dpacc[v] - dr[b]);
+    if ((v & 1) == 0) { ds_even = x; return; }
+    dsb[b][v >> 3][(v & 7) - 1] = (bf16)ds_even;
+    dsb[b][v >> 3][v & 7] = (bf16)x;
+  };
+  // Dr of a row that keeps only its own block comes from sum_j P_j dP_j / sum_j P_j, as in the kernel above
+  if (ntiles == 1) {
+    __shared__ float drx[2][2][64];  // [wavefront][query half][sums, normalisers]
+    float num[2], den[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      f32x16 s_ = zero16(), dp = zero16();
+#pragma unroll
+      for (int k = 0; k < NOP; ++k) s_ = mfma32(ka[k], qf[b][k], s_);
+#pragma unroll
+      for (int k = 0; k < NOP; ++k) dp = mfma32(va[k], dof[b][k], dp);
+      num[b] = den[b] = 0.f;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const bool masked = 32 * wave + c_row(v, hf) > 32 * b + l32;
+        const float pv = masked ? 0.f : fast_exp2(__builtin_fmaf(s_[v], P.scale_log2e, -lse2[b]));
+        num[b] = __builtin_fmaf(pv, dp[v], num[b]);
+        den[b] += pv;
+      }
+      num[b] += __shfl_xor(num[b], 32, 64);
+      den[b] += __shfl_xor(den[b], 32, 64);
+      if (hf == 0) { drx[wave][b][l32] = num[b]; drx[wave][b][32 + l32] = den[b]; }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      num[b] += drx[wave ^ 1][b][l32];
+      den[b] += drx[wave ^ 1][b][32 + l32];
+      if (den[b] > 0.f) dr[b] = num[b] / den[b];
+    }
+  }
+
+#define SB_FENCE() __builtin_amdgcn_sched_barrier(0)
+  // half tile u = (tile t, query half B); PAR = t % 2, known at compile time but for the diagonal tile
+  auto half_tile = [&](auto diag_c, auto PAR, auto b_c, int t) __attribute__((always_inline)) {
+    constexpr int B = decltype(b_c)::value;
+    constexpr bool LAST = decltype(diag_c)::value;  // the diagonal tile is the row's last: nothing follows it
+#pragma unroll
+    for (int k = 0; k < NOP; ++k) {
+      asm volatile("" : "+a"(qf[B][k]));
+      if (k < KV) asm volatile("" : "+a"(dof[B][k]));
+      else asm volatile("" : "+v"(dof[B][k]));
+    }
+    const bool more = !LAST && t + 2 < ntiles;  // strips of tile t + 2 follow: V with B = 0, K with B = 1
+    Strip nxt{};
+    if (!LAST && more) nxt = strip_of(B == 0, t + 2);
+    SB_FENCE();
+#pragma unroll
+    for (int k = 0; k < NOP; ++k) {
+      if (k == 0) mfma32_first(sacc[B], ka[k], qf[B][k]);
+      else mfma32_more(sacc[B], ka[k], qf[B][k]);
+      dscore(B ^ 1, 8 + k);  // (before the row's first half tile: zeros)
+      if (B == 1 && !LAST) {
+        // before the operands of tile t + 1 are fetched its strips must have landed (V_{t+2} may still be on its way)
+        if (k == 0) {
+          if (more) wait_vmcnt<LPS>(); else wait_vmcnt<0>();
+        }
+        ka[k] = ld_row(k, (PAR ^ 1) * STRIP_B);
+      }
+      SB_FENCE();
+      // the slot of V_t (its last reads belong to tile t - 1) or, with B = 1, of K_t (before the three reads just issued; LDS reads
+      // complete in order) may be refilled
+      if (!LAST && more) {
+        if (k == 2) {
+          asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(B == 1 ? 3 : 0) : "memory");
+          loader.template issue2<0>(nxt);
+        }
+        if (k == 5) loader.template issue2<2>(nxt);
+      }
+      SB_FENCE();
+    }
+#pragma unroll
+    for (int k = 0; k < NOP; ++k) {
+      if (k == 0) mfma32_first(dpacc, va[k], dof[B][k]);
+      else if (k < KV) mfma32_more(dpacc, va[k], dof[B][k]);
+      else mfma32_more_v(dpacc, va[k], dof[B][k]);
+      if (B == 1 && !LAST) va[k] = ld_row(k, (2 + (PAR ^ 1)) * STRIP_B);
+      if (k > 1) prob(diag_c, B, k - 2);
+      SB_FENCE();
+      if (!LAST && more) {
+        if (k == 1) loader.template issue2<4>(nxt);
+        if (k == 5) loader.template issue2<6>(nxt);
+      }
+      SB_FENCE();
+    }
+#pragma unroll
+    for (int k = 0; k < NOP; ++k) {
+      mfma32_sum(dqacc[k % (D / 32)][B ^ 1], kt[k], dsb[B ^ 1][k / (D / 32)]);
+      if (B == 0) kt[k] = ld_tr(k, PAR * STRIP_B);
+      if (k < 2) { prob(diag_c, B, 6 + 2 * k); prob(diag_c, B, 7 + 2 * k); }
+      else prob(diag_c, B, 8 + k);
+      if (k >= 4) { dscore(B, 2 * (k - 4)); dscore(B, 2 * (k - 4) + 1); }
+      SB_FENCE();
+    }
+    // (the conversions stay where they are: the compiler would carry the floats over the loop's edge and convert them one by one)
+    asm volatile("" : "+v"(dsb[B][0]), "+v"(dsb[B ^ 1][1]));
+  };
+  using std::integral_constant;
+  using std::false_type;
+  using std::true_type;
+  using I0 = integral_constant<int, 0>;
+  using I1 = integral_constant<int, 1>;
+  {
+    // nothing precedes the first half tile: its dQ stage adds zeros
+    sacc[1] = zero16();
+    dpacc = zero16();
+#pragma unroll
+    for (int q = 0; q < 2; ++q) dsb[1][q] = zero_bf16x8();
+    int t = 0;
+    for (; t + 2 < ntiles; t += 2) {
+      if (t + 3 - jb0 >= 64) refill(t);
+      half_tile(false_type(), I0(), I0(), t);
+      half_tile(false_type(), I0(), I1(), t);
+      half_tile(false_type(), I1(), I0(), t + 1);
+      half_tile(false_type(), I1(), I1(), t + 1);
+    }
+    if (t + 2 == ntiles) {
+      half_tile(false_type(), I0(), I0(), t);
+      half_tile(false_type(), I0(), I1(), t);
+      ++t;
+    }
+    half_tile(true_type(), t & 1, I0(), t);
+    half_tile(true_type(), t & 1, I1(), t);
+#pragma unroll
+    for (int v = 8; v < 16; ++v) dscore(1, v);
+    asm volatile("s_nop 3" : "+v"(dsb[1][0]), "+v"(dsb[1][1]));  // two wait states between a vector write and its use as an operand
+#pragma unroll
+    for (int k = 0; k < NOP; ++k) mfma32_sum(dqacc[k % (D / 32)][1], kt[k], dsb[1][k / (D / 32)]);
+    // the compiler does not see these as matrix instructions: their results are read no sooner than this
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt) asm volatile("s_nop 7\n\ts_nop 7" : "+a"(dqacc[dt][0]), "+a"(dqacc[dt][1]));
+  }
+#undef SB_FENCE
+  // the two key halves are added: wavefront w finishes query half w and hands the other half over
+  float* xbuf = (float*)&ring[wave][0];
+  const float* ybuf = (const float*)&ring[wave ^ 1][0];
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+    if (b != wave) {
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) xbuf[(16 * dt + v) * 64 + lane] = dqacc[dt][b][v];
+    }
+  __syncthreads();
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+    if (b == wave && qvalid[b]) {
+      if (hf == 0) {
+        P.drow[(int64_t)h * P.T + tq[b]] = dr[b];
+        P.lse2[(int64_t)h * P.T + tq[b]] = lse2[b];
+      }
+      const int64_t obase = (tq[b] * P.Hq + h) * D;
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+        for (int vg = 0; vg < 4; ++vg) {
+          const int d0 = 32 * dt + 8 * vg + 4 * hf;
+          float x[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[e] = (dqacc[dt][b][4 * vg + e] + ybuf[(16 * dt + 4 * vg + e) * 64 + lane]) * P.scale;
+          if (OUT_F32) {
+            *(float4*)((float*)P.dq + obase + d0) = make_float4(x[0], x[1], x[2], x[3]);
+          } else {
+            bf16x4 y;
+            y[0] = (bf16)x[0]; y[1] = (bf16)x[1]; y[2] = (bf16)x[2]; y[3] = (bf16)x[3];
+            *(bf16x4*)((bf16*)P.dq + obase + d0) = y;
+          }
+        }
+    }
+  timer.stop(P);
+}
+
+// ---------------------------------------------------------------------------------------------
 // Key-major dK/dV kernel: 2 wavefronts, each owns 32 keys of key block (s, g, j) and keeps their
 // K and V rows in registers for the whole launch.  The Q and dO tiles (plus the rows' log-sum-exp
 // in base 2 and Dr) of the query blocks that kept j are double-buffered in LDS by asynchronous
@@ -835,7 +1168,10 @@ static int launch_bwd(const Geo& g, const AttnParams& P, hipStream_t st) {
   const int parts = (heads + 3) / 4, hpp = (heads + parts - 1) / parts;  // heads per workgroup: 1..4
   dim3 grid((unsigned)ticketed_grid(P.n_items, P.ticket != nullptr), (unsigned)parts);
   KernelTimer kt(K_BWD_DQ, st);
-  if (hpp == 1) hipLaunchKernelGGL((attn_bwd_dq_kernel<D, F32, 2, 256>), grid, dim3(256), 0, st, P, heads);
+  if (hpp == 1) {  // figures at attn_bwd_dq_head_kernel, which is for D = 128: D = 64 is better served by two wavefronts per SIMD (see dK/dV)
+    if constexpr (D == 128) hipLaunchKernelGGL((attn_bwd_dq_head_kernel<F32>), grid, dim3(128), 0, st, P);
+    else hipLaunchKernelGGL((attn_bwd_dq_kernel<D, F32, 2, 256>), grid, dim3(256), 0, st, P, heads);
+  }
   else if (hpp == 2) hipLaunchKernelGGL((attn_bwd_dq_kernel<D, F32, 2, 512>), grid, dim3(512), 0, st, P, heads);
   else hipLaunchKernelGGL((attn_bwd_dq_kernel<D, F32, 1, 512>), grid, dim3(128 * hpp), 0, st, P, heads);
   SB_LAUNCH_CHECK("attn_bwd_dq_kernel");

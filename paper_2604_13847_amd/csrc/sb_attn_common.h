@@ -85,6 +85,14 @@ __device__ inline void mfma32_first(f32x16& c, bf16x8 a, bf16x8 b) {
 __device__ inline void mfma32_more(f32x16& c, bf16x8 a, bf16x8 b) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "a"(b));
 }
+__device__ inline void mfma32_more_v(f32x16& c, bf16x8 a, bf16x8 b) {  // all three in arithmetic registers
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
+}
+// The other way round, for a running sum: accumulator in accumulation registers, both operands in arithmetic registers.  The caller
+// keeps two wait states between a vector instruction that wrote an operand and this, and 12 before the accumulator is read.
+__device__ inline void mfma32_sum(f32x16& c, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
 
 __device__ inline f32x16 zero16() {
   f32x16 z;

@@ -68,3 +68,24 @@ def test_reference_of_the_softmax_moves_along_the_row(Hq, Hkv, D, mode):
     w = GrowingKeys("growing", lens, Hq, Hkv, D, keep_ratio=np.full(len(lens), 1.0), seed=90 + D + Hq)
     r = Run(w, mode, do_bwd=False)
     print(w, check_attention(r, bwd=False), flush=True)
+
+
+# dQ of one query head per item at head_dim 128 is a software pipeline over a row's tiles, two tiles per iteration, with the block
+# indices in a window of 64: rows of 1 to 5 tiles, of one less, as many and more than the window holds, and ragged ends in either
+# 32-key half of the last tile.
+@pytest.mark.parametrize("lens,Hq,Hkv,mode,dtype", [
+    ([1, 33, 64, 65, 97, 128, 190, 256, 300], 2, 1, 0, "bf16"),
+    ([1, 33, 64, 65, 97, 128, 190, 256, 300], 2, 2, 1, "bf16"),
+    ([1, 33, 64, 65, 97, 128, 190, 256, 300], 1, 1, 0, "f32"),
+    ([63 * 64, 64 * 64 - 40], 1, 1, 0, "bf16"),
+    ([67 * 64 - 20], 1, 1, 0, "bf16"),
+    ([133 * 64 - 1], 1, 1, 0, "bf16"),
+])
+def test_dq_of_one_head_per_item(lens, Hq, Hkv, mode, dtype):
+    w = synth.small_ragged(seed=95, lens=lens, Hq=Hq, Hkv=Hkv, D=128, ratio=(1.0, 1.0), dtype=dtype)
+    r = Run(w, mode)
+    print(w, check_attention(r), flush=True)
+    dq = r.dq.clone()
+    sb.sb_sparse_attn_bwd(r.pb, r.q, r.k, r.v, r.o, r.lse, r.do, r.rowptr, r.idx, r.plan, dq=r.dq, dk=r.dk, dv=r.dv)
+    torch.cuda.synchronize()
+    assert torch.equal(r.dq, dq)
