@@ -27,7 +27,7 @@ struct PlanArgs {
   WorkItem* items;
   uint32_t* bitmap;
   int32_t* colcost;
-  int64_t row_wgs;                         // workgroups of the query-major part
+  int64_t row_x;                           // grid columns of the query-major part (Hs workgroups each)
   int64_t words;                           // (sequence, 32 query tiles) pairs
 };
 
@@ -174,19 +174,20 @@ __device__ inline void plan_transpose(const PlanArgs& A, int64_t word, int hs) {
   }
 }
 
-// the query-major lists and the transpose, side by side: neither needs the other
+// The query-major lists and the transpose, side by side: neither needs the other.  The selection heads are the grid's second
+// dimension, so that half a million one-token sequences on 32 heads stay below the 2^32 threads of one dimension.
 __global__ __launch_bounds__(256) void plan_lists_kernel(PlanArgs A) {
-  if ((int64_t)blockIdx.x < A.row_wgs) {
+  if ((int64_t)blockIdx.x < A.row_x) {
+    const int64_t wg = (int64_t)blockIdx.x * A.Hs + blockIdx.y;
     if (A.r == 1) {
-      const int64_t row = (int64_t)blockIdx.x * 256 + threadIdx.x;  // row id = hs*NQB + qb
+      const int64_t row = wg * 256 + threadIdx.x;  // row id = hs*NQB + qb
       if (row < (int64_t)A.Hs * A.NQB) plan_row(A, row);
     } else {
-      const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);  // hs * NT + global tile
+      const int64_t row = wg * 4 + (threadIdx.x >> 6);  // hs * NT + global tile
       if (row < (int64_t)A.Hs * A.NQB) plan_tile_row(A, row);
     }
   } else {
-    const int64_t x = (int64_t)blockIdx.x - A.row_wgs;
-    plan_transpose(A, x % A.words, (int)(x / A.words));
+    plan_transpose(A, (int64_t)blockIdx.x - A.row_x, (int)blockIdx.y);
   }
 }
 
@@ -340,14 +341,13 @@ extern "C" int sb_plan_worklist(const sb_problem* p, const int32_t* sel_rowptr, 
   A.work_fwd = (int32_t*)(base + po.work_fwd); A.items = (WorkItem*)(base + po.items);
   A.bitmap = bitmap; A.colcost = colcost;
   const int64_t rows = (int64_t)g.Hs * g.NQB;
-  A.row_wgs = gb.r == 1 ? (rows + 255) / 256 : (rows + 3) / 4;
+  const int64_t row_wgs = gb.r == 1 ? (rows + 255) / 256 : (rows + 3) / 4;
+  A.row_x = (row_wgs + g.Hs - 1) / g.Hs;
   for (int s = 0; s < g.S; ++s) {
     const int64_t L = (int64_t)p->cu_seqlens_host[s + 1] - p->cu_seqlens_host[s];
     A.words += ((L + g.B - 1) / g.B + 31) / 32;
   }
-  const int64_t wgs = A.row_wgs + A.words * g.Hs;
-  if (wgs > 0x7fffffffll) { set_error("too many rows for one launch of the plan"); return SB_ERR_UNSUPPORTED; }
-  hipLaunchKernelGGL(plan_lists_kernel, dim3((unsigned)wgs), dim3(256), 0, st, A);
+  hipLaunchKernelGGL(plan_lists_kernel, dim3((unsigned)(A.row_x + A.words), (unsigned)g.Hs), dim3(256), 0, st, A);
   SB_LAUNCH_CHECK("plan_lists_kernel");
   hipLaunchKernelGGL(plan_bwd_order_kernel, dim3((unsigned)g.Hkv), dim3(1024), 0, st, colcost, bitmap, t.qb_off, t.qb_seq, t.bm_off,
                      g.NQB, g.Hkv, g.Hs, g.G, g.mode, split_weight(g), sub_parts_max(g) > 1 ? sub_weight(g) : 0, bwd_items, counters, (int32_t*)(base + po.split_cols),
