@@ -153,6 +153,8 @@ inline int split_extra_max(const Geo& tg) { return (int)(bwd_total_tiles(tg) / s
 // fp32 partial sums that the reduction adds in walk order (the same problem: 44 us with the reduction; at least 4 tiles a
 // workgroup: 56 us, 6: 43, 12: 46).  A heaviest column of at most twice the weight is left alone (16 tiles: 21 us whole, 23 us
 // cut), and from kSubMinColumns columns on nothing is cut this way: two rounds of workgroups are there, heaviest first.
+// (From 512 on: 30000 tokens with 16/2 heads, one long and many short dense sequences, 2.33 -> 1.95 ms a step, but 16000 tokens with 28/4
+// heads 1.55 -> 1.75, 30000 with 14/2 heads at D = 64 1.12 -> 1.49 and a sink selection of 8000 tokens 0.98 -> 1.36 ms.)
 constexpr int64_t kSubMinColumns = 1024, kSubSlots = 512;
 inline int sub_weight(const Geo& tg) {
   const int64_t w = (bwd_total_tiles(tg) + kSubSlots - 1) / kSubSlots;
