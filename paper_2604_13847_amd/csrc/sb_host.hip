@@ -297,10 +297,16 @@ __global__ __launch_bounds__(1024) void geom_kernel(const int32_t* __restrict__ 
   else if (i - zero_n < ones_n) ones[i - zero_n] = make_uint4(~0u, ~0u, ~0u, ~0u);
 }
 
+int check_device_arrays(const sb_problem* p) {
+  if (!p->cu_seqlens_dev || !p->topk_dev) { set_error("cu_seqlens_dev and topk_dev are required"); return SB_ERR_INVALID_ARG; }
+  return SB_OK;
+}
+
 int launch_geom_and_fills(const Geo& g, void* base, const Geo* g2, void* base2, const sb_problem* p, void* zeros, size_t zero_bytes,
                           void* ones, size_t ones_bytes, hipStream_t st) {
   if (g.S == 0) return SB_OK;
-  if (!p->cu_seqlens_dev || !p->topk_dev) { set_error("cu_seqlens_dev and topk_dev are required"); return SB_ERR_INVALID_ARG; }
+  const int rc = check_device_arrays(p);
+  if (rc != SB_OK) return rc;
   auto out = [](const Geo& x, void* at) {
     const TableOffsets t = table_offsets(x);
     char* b = (char*)at;

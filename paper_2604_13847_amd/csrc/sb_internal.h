@@ -103,6 +103,9 @@ struct Tables {  // device pointers into a tables area
 Tables make_tables(const Geo& g, const sb_problem* p, void* base);
 struct GeomArgs;
 GeomArgs make_geom_args(const Geo& g, const sb_problem* p, const Tables& t);
+// The device arrays that the geometry comes from, whether a kernel works it out itself or reads tables: every call that launches
+// either checks them here first.
+int check_device_arrays(const sb_problem* p);
 int launch_geom(const Geo& g, const sb_problem* p, void* base, hipStream_t st);
 // geometry tables of `g` and (unless it is null) of `g2`, and two fills, as one launch; the fills' sizes are multiples of 16 bytes
 int launch_geom_and_fills(const Geo& g, void* base, const Geo* g2, void* base2, const sb_problem* p, void* zeros, size_t zero_bytes,

@@ -216,6 +216,7 @@ extern "C" int sb_block_scores(const sb_problem* p, const void* q, const void* k
   if (rc != SB_OK) return rc;
   if (g.S == 0 || g.T == 0 || g.NQB == 0) return SB_OK;
   if (!q || !k || !scores_out || !ws) { set_error("null q, k, scores_out or ws"); return SB_ERR_INVALID_ARG; }
+  if ((rc = check_device_arrays(p)) != SB_OK) return rc;
   hipStream_t st = (hipStream_t)stream;
   if (g.S > kLaneSeqs && (rc = launch_geom(g, p, ws, st)) != SB_OK) return rc;
   const GeomArgs ga = make_geom_args(g, p, make_tables(g, p, ws));

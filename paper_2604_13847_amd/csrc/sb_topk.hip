@@ -187,6 +187,7 @@ extern "C" int sb_select_topk(const sb_problem* p, const float* scores, int32_t*
     return fill_zero(sel_rowptr_out, sizeof(int32_t), st);
   }
   if (!scores || !sel_idx_out || !ws) { set_error("null scores, sel_idx_out or ws"); return SB_ERR_INVALID_ARG; }
+  if ((rc = check_device_arrays(p)) != SB_OK) return rc;
   if ((rc = need_tables(g, p, ws, st)) != SB_OK) return rc;
   return select_launch(g, make_geom_args(g, p, make_tables(g, p, ws)), scores, sel_rowptr_out, sel_idx_out, st);
 }
@@ -249,6 +250,7 @@ extern "C" int sb_score_select(const sb_problem* p, const void* q, const void* k
   }
   if (!sel_idx_out) { set_error("null sel_idx_out"); return SB_ERR_INVALID_ARG; }
   if (!q || !k || !ws) { set_error("null q, k or ws"); return SB_ERR_INVALID_ARG; }
+  if ((rc = check_device_arrays(p)) != SB_OK) return rc;
   const GeomArgs ga = make_geom_args(g, p, make_tables(g, p, ws));
   if (scores_out) {  // the caller wants the score matrix: write it, then select from it
     rc = sb_block_scores(p, q, k, kbar_out, scores_out, ws, stream);  // leaves the geometry tables at the start of ws
@@ -299,6 +301,7 @@ extern "C" int sb_select_topk_static(const sb_problem* p, const float* scores, i
               (int)SB_STATIC_SELECT_WS_BYTES);
     return SB_ERR_WORKSPACE_TOO_SMALL;
   }
+  if ((rc = check_device_arrays(p)) != SB_OK) return rc;
   void* ws = nullptr;
   if ((rc = static_scratch_ptr(&ws)) != SB_OK) return rc;
   // every table entry the selection reads is rewritten by the geometry kernel of this call: nothing has to start at zero

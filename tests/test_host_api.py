@@ -84,6 +84,31 @@ def test_invalid_problems_are_rejected(kw, code):
     assert f"error {code}:" in str(e.value) and len(str(e.value)) > 25
 
 
+# The calls that read cu_seqlens and the budgets on the device refuse a problem that has only the host arrays, whether the batch is
+# small enough for the kernels to work its geometry out themselves (64 sequences) or needs tables.  A refused call enqueues nothing
+# and reads none of its buffers, so their addresses do not matter here.
+@pytest.mark.parametrize("S", [1, 64, 65])
+@pytest.mark.parametrize("missing", ["both", "cu_seqlens_dev", "topk_dev"])
+def test_problems_without_device_arrays_are_rejected(S, missing):
+    pb = sb.Problem(np.arange(S + 1) * 100, [1] * S, 4, 2, 64)
+    buf = C.c_void_p(4096)
+    pb.c.cu_seqlens_dev = None if missing != "topk_dev" else 4096
+    pb.c.topk_dev = None if missing != "cu_seqlens_dev" else 4096
+    L, p = sb.lib(), pb.ref()
+    calls = {
+        "sb_block_scores": lambda: L.sb_block_scores(p, buf, buf, None, buf, buf, None),
+        "sb_select_topk": lambda: L.sb_select_topk(p, buf, buf, buf, buf, None),
+        "sb_select_topk_static": lambda: L.sb_select_topk_static(p, buf, buf, buf, None),
+        "sb_score_select": lambda: L.sb_score_select(p, buf, buf, None, buf, buf, buf, buf, None),
+        "sb_score_select without scores": lambda: L.sb_score_select(p, buf, buf, None, None, buf, buf, buf, None),
+        "sb_plan_worklist": lambda: L.sb_plan_worklist(p, buf, buf, buf, None),
+        "sb_score_coverage": lambda: L.sb_score_coverage(p, buf, buf, buf, None),
+    }
+    for name, call in calls.items():
+        assert call() == -1, name                                             # SB_ERR_INVALID_ARG
+        assert b"cu_seqlens_dev and topk_dev are required" in L.sb_last_error(), name
+
+
 def test_empty_problem_layout():
     pb = sb.Problem([0], [], 4, 2, 64)
     assert pb.layout.num_qblocks == 0 and pb.layout.sel_nnz == 0
