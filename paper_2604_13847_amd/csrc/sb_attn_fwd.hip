@@ -586,26 +586,29 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void a
 }
 
 // float -> bf16 (round to nearest even) copies used when the caller's tensors are float: up to four tensors, one after the other, as
-// one launch (a launch costs a small problem 4 us; element counts are multiples of head_dim)
-__global__ __launch_bounds__(256) void f32_to_bf16_kernel(Conversions c) {
-  int64_t at = (int64_t)blockIdx.x * 256 + threadIdx.x;
+// one launch (a launch costs a small problem 4 us; element counts are multiples of head_dim).  The launch ends at kConvertWgs
+// workgroups, a quarter of the threads that one dimension of a launch may have; tensors with more elements than that are strided over.
+constexpr int64_t kConvertWgs = 1 << 22;
+__global__ __launch_bounds__(256) void f32_to_bf16_kernel(Conversions c, int64_t n4) {
+  for (int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x; u < n4; u += (int64_t)gridDim.x * 256) {
+    int64_t at = u;
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    if (at < c.n4[t]) {
-      const float4 x = ((const float4*)c.src[t])[at];
-      bf16x4 y;
-      y[0] = (bf16)x.x; y[1] = (bf16)x.y; y[2] = (bf16)x.z; y[3] = (bf16)x.w;
-      ((bf16x4*)c.dst[t])[at] = y;
-      return;
+    for (int t = 0; t < 4; ++t) {
+      if (at < c.n4[t]) {
+        const float4 x = ((const float4*)c.src[t])[at];
+        bf16x4 y;
+        y[0] = (bf16)x.x; y[1] = (bf16)x.y; y[2] = (bf16)x.z; y[3] = (bf16)x.w;
+        ((bf16x4*)c.dst[t])[at] = y;
+        break;
+      }
+      at -= c.n4[t];
     }
-    at -= c.n4[t];
   }
 }
 
 int convert_f32_to_bf16(const Conversions& c, hipStream_t st) {
   const int64_t n4 = c.n4[0] + c.n4[1] + c.n4[2] + c.n4[3], wgs = (n4 + 255) / 256;
-  if (wgs > 0x7fffffffll) { set_error("too many elements for one launch of the conversion"); return SB_ERR_UNSUPPORTED; }
-  hipLaunchKernelGGL(f32_to_bf16_kernel, dim3((unsigned)wgs), dim3(256), 0, st, c);
+  hipLaunchKernelGGL(f32_to_bf16_kernel, dim3((unsigned)(wgs < kConvertWgs ? wgs : kConvertWgs)), dim3(256), 0, st, c, n4);
   SB_LAUNCH_CHECK("f32_to_bf16_kernel");
   return SB_OK;
 }

@@ -89,3 +89,24 @@ def test_dq_of_one_head_per_item(lens, Hq, Hkv, mode, dtype):
     sb.sb_sparse_attn_bwd(r.pb, r.q, r.k, r.v, r.o, r.lse, r.do, r.rowptr, r.idx, r.plan, dq=r.dq, dk=r.dk, dv=r.dv)
     torch.cuda.synchronize()
     assert torch.equal(r.dq, dq)
+
+
+# The conversion of float32 inputs is one launch of at most 2^22 workgroups (2^32 elements); larger inputs are strided over.  Q, K and
+# V together have 4.9e9 elements here, with values that bf16 holds, so the output is the bf16 call's before its rounding.
+def test_float32_inputs_larger_than_one_launch():
+    T, H, D = 200_000, 64, 128
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v = (torch.randn((T, H, D), generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    n = (T + 63) // 64
+    rowptr = torch.arange(H * n + 1, dtype=torch.int32, device="cuda")    # every query block keeps itself only
+    idx = torch.arange(n, dtype=torch.int32, device="cuda").repeat(H)
+    outs = []
+    for dt in (sb.SB_BF16, sb.SB_F32):
+        pb = sb.Problem([0, T], [1], H, H, D, dtype=dt, device="cuda")
+        x = [t.float() if dt == sb.SB_F32 else t for t in (q, k, v)]
+        nan = torch.full_like(x[0], float("nan"))
+        outs.append(sb.sb_sparse_attn_fwd(pb, *x, rowptr, idx, sb.sb_plan_worklist(pb, rowptr, idx), o=nan))
+        torch.cuda.synchronize()
+        del x
+    (o16, lse16), (o32, lse32) = outs
+    assert torch.equal(o32.to(torch.bfloat16), o16) and torch.equal(lse32, lse16)
