@@ -162,7 +162,7 @@ int sb_plan_worklist(const sb_problem *p, const int32_t *sel_rowptr, const int32
  *   BITMAP   uint32           bit i of word (s, hs, j, i/32): query tile i of head hs kept key tile j
  *   BWD_ITEMS 4 x int32 each  key-major items in launch order: column (or -1: none), bitmap words lo | hi << 16 the item
  *                             covers, partial slot (or -1: the item is the whole column), tiles; BWD_ITEMS_COUNT entries
- *   COUNTERS int32 [2]        partial slots in use, split columns
+ *   COUNTERS int32 [3]        partial slots in use, split columns, further slots in use for items that several workgroups walk
  *   SPLIT_COLS 3 x int32 each column, first partial slot, parts
  *   SPLIT_WEIGHT              a column with more tiles than this is cut into parts of at least this many
  * (NQB counts 64-token tiles, whatever the selection block size.) */

@@ -331,12 +331,12 @@ def plan_views(pb: Problem, plan: torch.Tensor):
     qb_off = view(o["qb_off"], S + 1, np.int32)
     NT = int(qb_off[-1])
     Hs = pb.layout.sel_heads
-    counters = view(o["counters"], 2, np.int32)
+    counters = view(o["counters"], 3, np.int32)
     return {
         "qb_off": qb_off, "bm_off": view(o["bm_off"], S + 1, np.int64), "qb_seq": view(o["qb_seq"], NT, np.int32),
         "work_fwd": view(o["work_fwd"], Hs * NT, np.int32), "colcost": view(o["colcost"], Hkv * NT, np.int32),
         "bitmap": raw[o["bitmap"]:o["bwd_items"]].view(np.uint32),
         "bwd_items": view(o["bwd_items"], 4 * o["bwd_items_count"], np.int32).reshape(-1, 4),
-        "slots_used": int(counters[0]), "split_cols": view(o["split_cols"], 3 * int(counters[1]), np.int32).reshape(-1, 3),
+        "slots_used": int(counters[0]), "sub_slots_used": int(counters[2]), "split_cols": view(o["split_cols"], 3 * int(counters[1]), np.int32).reshape(-1, 3),
         "split_weight": o["split_weight"], "split_max": o["split_max"],
     }

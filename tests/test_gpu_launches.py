@@ -3,12 +3,27 @@ import numpy as np
 import pytest
 import torch
 
-from helpers import Run
+from helpers import MAX_ABS, ULP_BF16, Run, check_close, check_lse, to_host_f32
+from oracle import oracle as orc
 from paper_2604_13847_amd import binding as sb
 from paper_2604_13847_amd import synth
 from test_gpu_parity import check_attention, check_plan, check_scores, check_selection, fused_selection_matches
 
 pytestmark = pytest.mark.gpu
+
+
+def check_backward_repeats(r, new_plan=False):
+    """Two more backward calls into outputs and a workspace full of NaN: the same bits, whichever workgroup finishes first and
+    whatever the workspace held."""
+    first = {n: getattr(r, n).clone() for n in ("dq", "dk", "dv")}
+    for _ in range(2):
+        plan = sb.sb_plan_worklist(r.pb, r.rowptr, r.idx) if new_plan else r.plan
+        again = {n: torch.full_like(x, float("nan")) for n, x in first.items()}
+        ws = torch.full((max(int(r.pb.layout.bwd_ws_bytes), 256),), 0xff, dtype=torch.uint8, device="cuda")
+        sb.sb_sparse_attn_bwd(r.pb, r.q, r.k, r.v, r.o, r.lse, r.do, r.rowptr, r.idx, plan, ws=ws, **again)
+        torch.cuda.synchronize()
+        for n, x in first.items():
+            assert torch.equal(again[n].view(torch.uint8), x.view(torch.uint8)), n
 
 
 # Key-major columns of a small problem are walked by several workgroups when the heaviest can have more than 16 tiles (twice
@@ -27,12 +42,41 @@ def test_columns_of_small_problems_walked_by_several_workgroups(lens, Hq, Hkv, D
     w = synth.small_ragged(seed=71, lens=lens, Hq=Hq, Hkv=Hkv, D=D, ratio=ratio)
     r = Run(w, mode)
     print(w, check_attention(r), flush=True)
-    dk, dv = r.dk.clone(), r.dv.clone()
-    for _ in range(2):  # the parts are added in walk order, whichever workgroup finishes first
-        sb.sb_sparse_attn_bwd(r.pb, r.q, r.k, r.v, r.o, r.lse, r.do, r.rowptr, r.idx, sb.sb_plan_worklist(r.pb, r.rowptr, r.idx),
-                              dq=r.dq, dk=r.dk, dv=r.dv)
-        torch.cuda.synchronize()
-        assert torch.equal(r.dk.view(torch.int16), dk.view(torch.int16)) and torch.equal(r.dv.view(torch.int16), dv.view(torch.int16))
+    check_backward_repeats(r, new_plan=True)  # the parts are added in walk order
+
+
+# A column heavier than the split weight is cut into parts, and in a small problem a heavy part is itself walked by several
+# workgroups: the reduction then adds, in walk order, the sums of whole parts and of parts' parts.  Blocks that every later query
+# block keeps: 300 blocks with four heads (parts of 512, 512 and 176 tiles of a column) and 125 with seven (651 and 224), on one KV
+# head and on several; 128-token blocks have two such tile columns.
+@pytest.mark.parametrize("blocks,B,Hq,Hkv,D,topk,mode", [
+    (300, 64, 4, 1, 64, 4, 0), (300, 64, 4, 1, 128, 4, 0), (300, 64, 4, 1, 64, 4, 1), (300, 64, 4, 1, 128, 4, 1),
+    (125, 64, 28, 4, 64, 24, 0), (125, 64, 28, 4, 128, 24, 0), (125, 64, 28, 4, 128, 24, 1),
+    (150, 128, 4, 1, 128, 4, 0),
+])
+def test_parts_of_split_columns_walked_by_several_workgroups(blocks, B, Hq, Hkv, D, topk, mode):
+    w = synth.Workload("sink", [B * blocks - 9], Hq, Hkv, D, B=B, topk=[topk], seed=72)
+    r = Run(w, mode, sel_override=synth.sink_selection(w.cu, B, w.topk, Hq if mode == 0 else Hkv))
+    if B == 64:
+        check_plan(r)
+    pv = sb.plan_views(r.pb, r.plan)
+    assert len(pv["split_cols"]) >= Hkv * (B // 64) and pv["sub_slots_used"] > len(pv["split_cols"])
+    q, k, v, do = r.oracle_inputs()
+    O, LSE = orc.attn_fwd(r.opb, q, k, v, r.rowptr_h, r.idx_h, r.scale)
+    dQ, dK, dV = orc.attn_bwd(r.opb, q, k, v, do, r.rowptr_h, r.idx_h, r.scale)
+    print(w, check_close("O", to_host_f32(r.o), O), check_lse(r.lse.cpu().numpy(), LSE), check_close("dQ", to_host_f32(r.dq), dQ))
+    # the rows of a split column add up tens of thousands of rounded products: held to the size of the column instead of the element's
+    heavy = np.zeros((w.T, Hkv), dtype=bool)
+    for col in pv["split_cols"][:, 0]:
+        g, tile = divmod(int(col), len(pv["qb_seq"]))
+        at = slice(64 * tile, min(64 * tile + 64, w.T))
+        heavy[at, g] = True
+        for name, got, ref in (("dK", r.dk, dK), ("dV", r.dv, dV)):
+            err = np.abs(to_host_f32(got[at, g]) - ref[at, g]).max()
+            assert err <= MAX_ABS + ULP_BF16 * np.abs(ref[at, g]).max(), (name, col, err)
+    for name, got, ref in (("dK", r.dk, dK), ("dV", r.dv, dV)):
+        check_close(name, to_host_f32(got)[~heavy], ref[~heavy])
+    check_backward_repeats(r, new_plan=True)
 
 
 # Up to 64 sequences the kernels find their place by a scan across the lanes, from 65 on in tables in memory; the plan's work
@@ -85,10 +129,7 @@ def test_dq_of_one_head_per_item(lens, Hq, Hkv, mode, dtype):
     w = synth.small_ragged(seed=95, lens=lens, Hq=Hq, Hkv=Hkv, D=128, ratio=(1.0, 1.0), dtype=dtype)
     r = Run(w, mode)
     print(w, check_attention(r), flush=True)
-    dq = r.dq.clone()
-    sb.sb_sparse_attn_bwd(r.pb, r.q, r.k, r.v, r.o, r.lse, r.do, r.rowptr, r.idx, r.plan, dq=r.dq, dk=r.dk, dv=r.dv)
-    torch.cuda.synchronize()
-    assert torch.equal(r.dq, dq)
+    check_backward_repeats(r)
 
 
 # The conversion of float32 inputs is one launch of at most 2^22 workgroups (2^32 elements); larger inputs are strided over.  Q, K and
