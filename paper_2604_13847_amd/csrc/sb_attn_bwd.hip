@@ -680,11 +680,20 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
   __shared__ uint32_t bm_s[8][kCW];  // bitmap words of up to 8 selection heads
   __shared__ uint16_t tl_s[kCW * 32 * 8];  // the chunk's tiles in processing order
   __shared__ int ntl_s;
-  const int at = (int)blockIdx.x / P.sub_parts, sub = (int)blockIdx.x - at * P.sub_parts;
-  const ColItem item = P.bwd_items[at];
-  if (item.col < 0) return;  // the item lists are padded to their largest possible length
-  const int nsub = P.sub_parts > 1 ? (item.weight + P.sub_weight - 1) / P.sub_weight : 1;  // workgroups that walk this item
-  if (sub >= nsub) return;
+  // workgroups 0 .. sub_slots-1: the sub-parts; then one per item, for those that are walked as a whole
+  const bool sub_part = (int)blockIdx.x < P.sub_slots;
+  ColItem item;
+  int sub = 0;
+  if (sub_part) {
+    item = P.sub_items[blockIdx.x].item;
+    sub = P.sub_items[blockIdx.x].sub;
+  } else {
+    const int at = (int)blockIdx.x - P.sub_slots;
+    item = P.bwd_items[at];
+    if (P.sub_slots > 0 && P.sub_base[at] >= 0) return;
+  }
+  if (item.col < 0) return;  // the lists are padded to their largest possible length
+  const int nsub = sub_part ? (item.weight + P.sub_weight - 1) / P.sub_weight : 1;  // workgroups that walk this item
   // this one's run of the item's tiles in walk order
   const int run0 = (int)((int64_t)item.weight * sub / nsub), run1 = (int)((int64_t)item.weight * (sub + 1) / nsub);
   BusyTimer timer;
@@ -1072,7 +1081,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
   }
   // C layout: column = d (32dt + l32), register v = key row c_row(v, hf) of this wavefront's strip
   if (item.slot >= 0 || nsub > 1) {  // a part of a split column, or of an item: leave the fp32 partial sums for the reduction
-    float* part = nsub > 1 ? P.sub_partials + ((size_t)P.sub_base[at] + sub) * (2 * 64 * D) : P.partials + (size_t)item.slot * (2 * 64 * D);
+    float* part = nsub > 1 ? P.sub_partials + (size_t)blockIdx.x * (2 * 64 * D) : P.partials + (size_t)item.slot * (2 * 64 * D);
 #pragma unroll
     for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
@@ -1119,7 +1128,7 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_reduce_kernel(AttnParams P, 
   } else {
     at = x - extra;
     const ColItem item = P.bwd_items[at];
-    if (item.col < 0 || item.slot >= 0 || item.weight <= P.sub_weight) return;
+    if (item.col < 0 || item.slot >= 0 || P.sub_base[at] < 0) return;
     col = item.col;
   }
   const int g = (int)(col / P.NQB);
@@ -1133,17 +1142,19 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_reduce_kernel(AttnParams P, 
     const int e = blockIdx.y * 16 * D + 4 * u;
     if (e >= rows * D) return;
     f32x4 dk = {0.f, 0.f, 0.f, 0.f}, dv = dk;
-    auto add = [&](const float* part, int n) {
-      for (int p = 0; p < n; ++p) {
-        dk += *(const f32x4*)(part + (size_t)p * S + e);
-        dv += *(const f32x4*)(part + (size_t)p * S + 64 * D + e);
-      }
+    auto add = [&](const float* part) {
+      dk += *(const f32x4*)(part + e);
+      dv += *(const f32x4*)(part + 64 * D + e);
     };
     for (int p = 0; p < np; ++p) {
-      const int it = x < extra && P.sub_parts > 1 ? P.part_item[slot0 + p] : at;
-      const int w = P.sub_parts > 1 ? P.bwd_items[it].weight : 0;
-      if (w > P.sub_weight) add(P.sub_partials + (size_t)P.sub_base[it] * S, (w + P.sub_weight - 1) / P.sub_weight);
-      else add(P.partials + (size_t)(slot0 + p) * S, 1);
+      const int it = x < extra && P.sub_slots > 0 ? P.part_item[slot0 + p] : at;
+      const int sub0 = P.sub_slots > 0 ? P.sub_base[it] : -1;
+      if (sub0 >= 0) {
+        const int n = (P.bwd_items[it].weight + P.sub_weight - 1) / P.sub_weight;
+        for (int u = 0; u < n; ++u) add(P.sub_partials + ((size_t)(sub0 + u) * P.Hkv + g) * S);
+      } else {
+        add(P.partials + (size_t)(slot0 + p) * S);
+      }
     }
     const int kr = e / D, d = e % D;
     const int64_t off = ((seq0 + j * 64 + kr) * P.Hkv + g) * D + d;
@@ -1182,12 +1193,12 @@ template <int D, bool F32>
 static int launch_dkv(const Geo& g, const AttnParams& P, hipStream_t st) {
   const int64_t extra = split_extra_max(g);
   const int64_t n_items = (int64_t)g.Hkv * (g.NQB + extra);
-  if (n_items * P.sub_parts > 0x7fffffffll) { set_error("too many key-major items for one launch"); return SB_ERR_INVALID_ARG; }
-  dim3 grid((unsigned)(n_items * P.sub_parts)), block(128);
+  if (P.sub_slots + n_items > 0x7fffffffll) { set_error("too many key-major items for one launch"); return SB_ERR_INVALID_ARG; }
+  dim3 grid((unsigned)(P.sub_slots + n_items)), block(128);
   KernelTimer kt(K_BWD_DKV, st);
   hipLaunchKernelGGL((attn_bwd_dkv_kernel<D, F32>), grid, block, 0, st, P);
   SB_LAUNCH_CHECK("attn_bwd_dkv_kernel");
-  const int64_t reduced = extra + (P.sub_parts > 1 ? n_items : 0);
+  const int64_t reduced = extra + (P.sub_slots > 0 ? n_items : 0);
   if (reduced > 0) {  // at most that many columns are cut; workgroups beyond the actual count return at once
     hipLaunchKernelGGL((attn_bwd_dkv_reduce_kernel<D, F32>), dim3((unsigned)reduced, 4), dim3(256), 0, st, P, (int)extra);
     SB_LAUNCH_CHECK("attn_bwd_dkv_reduce_kernel");
@@ -1246,7 +1257,8 @@ extern "C" int sb_sparse_attn_bwd(const sb_problem* p, const void* q, const void
   P.sub_base = (const int32_t*)(pb + po.sub_base);
   P.part_item = (const int32_t*)(pb + po.part_item);
   P.sub_partials = P.partials + 2 * (size_t)split_extra_max(g) * (2 * 64 * g.D);
-  P.sub_parts = sub_parts_max(g);
+  P.sub_items = (const SubItem*)(pb + po.sub_items);
+  P.sub_slots = g.Hkv * sub_slots_max(g);
   P.sub_weight = sub_weight(g);
   P.cu = t.cu; P.qb_off = t.qb_off; P.qb_seq = t.qb_seq; P.bm_off = t.bm_off;
   P.NQB = g.NQB; P.T = g.T; P.Hq = g.Hq; P.Hkv = g.Hkv; P.G = g.G; P.Hs = g.Hs; P.mode = g.mode;

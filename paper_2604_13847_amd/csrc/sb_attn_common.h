@@ -26,10 +26,11 @@ struct AttnParams {
   const int32_t* split_cols;   // (column, first partial slot, parts) of the split columns; counters[1] of them
   const int32_t* counters;
   float* partials;             // [slot][dK, dV][64][D] fp32 partial sums of the parts of split columns
-  const int32_t* sub_base;     // first sub-part slot of every key-major item, or -1
+  const int32_t* sub_base;     // of every key-major item of KV head g: its sub-parts have slots Hkv*(sub_base + 0, 1, ...) + g; -1: walked as a whole
   const int32_t* part_item;    // key-major item of every partial slot
   float* sub_partials;         // like partials, of the sub-parts
-  int sub_weight, sub_parts;   // an item of more than sub_weight tiles is walked by up to sub_parts workgroups (1: none is)
+  const SubItem* sub_items;    // the sub-parts, sub_slots entries
+  int sub_weight, sub_slots;   // sub-parts of an item: ceil(tiles / sub_weight); sub_slots = 0: no item has any
   const int32_t* cu; const int32_t* qb_off; const int32_t* qb_seq; const int64_t* bm_off;
   int64_t NQB;
   int T, Hq, Hkv, G, Hs, mode;

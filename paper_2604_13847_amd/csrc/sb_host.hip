@@ -177,9 +177,10 @@ PlanOffsets plan_offsets(const Geo& gb) {
     p.t_idx = o;      o = align_up(o + sizeof(int32_t) * (size_t)(g.Hs * g.nnz_unit + 1));
   }
   const size_t E = (size_t)split_extra_max(g);
+  p.sub_items = o;  o = align_up(o + sizeof(SubItem) * (size_t)g.Hkv * (size_t)sub_slots_max(g));  // filled as one piece with bwd_items
   p.bwd_items = o;  o = align_up(o + sizeof(ColItem) * ((size_t)g.Hkv * ((size_t)g.NQB + E) + 1));
   p.split_cols = o; o = align_up(o + sizeof(int32_t) * (3 * E + 1));
-  p.sub_base = o;   o = align_up(o + (sub_parts_max(g) > 1 ? sizeof(int32_t) * (size_t)g.Hkv * ((size_t)g.NQB + E) : 0));
+  p.sub_base = o;   o = align_up(o + (sub_slots_max(g) > 0 ? sizeof(int32_t) * (size_t)g.Hkv * ((size_t)g.NQB + E) : 0));
   p.part_item = o;  o = align_up(o + sizeof(int32_t) * (2 * E + 1));
   p.bytes = o;
   return p;
@@ -200,7 +201,7 @@ static WsOffsets ws_offsets(const Geo& g, bool bwd) {
   w.lse2 = o; o = align_up(o + (bwd ? sizeof(float) * (size_t)g.T * g.Hq : 0));
   w.ticket = o; o = align_up(o + sizeof(int32_t) * 64);
   const Geo tg = tile_geo(g);  // idempotent
-  w.partials = o; o = align_up(o + (bwd ? sizeof(float) * (2 * (size_t)split_extra_max(tg) + (size_t)sub_slots_max(tg)) * 2 * 64 * g.D : 0));
+  w.partials = o; o = align_up(o + (bwd ? sizeof(float) * (2 * (size_t)split_extra_max(tg) + (size_t)tg.Hkv * (size_t)sub_slots_max(tg)) * 2 * 64 * g.D : 0));
   w.bytes = o;
   return w;
 }

@@ -121,6 +121,7 @@ struct PlanOffsets {
   size_t counters;   // int32 [4]  {partial slots in use, split columns, sub-part slots in use}, zeroed by every plan call
   size_t split_cols; // int32 [3*E]  (column, first partial slot, parts) of every split column
   size_t sub_base;   // int32 [Hkv*(NQB+E)]  first sub-part slot of every key-major item (see sub_weight), -1: none
+  size_t sub_items;  // SubItem [Hkv*sub_slots_max]  the sub-parts: entry r*Hkv + g, those of KV head g's heaviest items first (col = -1: none)
   size_t part_item;  // int32 [2*E]  key-major item (index into bwd_items) of every partial slot
   size_t bitmap;     // uint32 [Hs * bm_words_unit] transpose bitmap: bit i of column (s,hs,j)
   size_t items;      // WorkItem [Hs*NQB]  descriptors of the query-major items, in work_fwd order
@@ -144,6 +145,8 @@ struct ColItem {
   int32_t weight;  // (query block, query head) tiles of the item
 };
 static_assert(sizeof(ColItem) == 16, "ColItem is loaded as 4 dwords");
+struct SubItem { ColItem item; int32_t sub, pad[3]; };  // sub-part `sub` of an item
+static_assert(sizeof(SubItem) == 32, "SubItem is loaded as 8 dwords");
 inline int64_t bwd_total_tiles(const Geo& tg) { return (int64_t)tg.Hq * tg.nnz_unit; }  // tg = tile_geo(...)
 // Total / 2048: at most an eighth of what each of the 512 workgroup slots has to do.  Half of that cut every second column of the
 // block-256 workloads (each cut costs 128 KiB of partial sums written and read) and made the plan walk them (131072-token sequence:
@@ -153,26 +156,29 @@ inline int split_extra_max(const Geo& tg) { return (int)(bwd_total_tiles(tg) / s
 // Small problems: fewer columns than the chip has workgroup slots (two per CU) leave most of it idle while the heaviest column
 // is walked (37 blocks on 2 KV heads with 8 query heads each: 74 workgroups, up to 88 tiles in a row, 115 us).  Items of more
 // than sub_weight() tiles are then walked by several workgroups, each an equal run of the item's tiles in walk order; they leave
-// fp32 partial sums that the reduction adds in walk order (the same problem: 44 us with the reduction; at least 4 tiles a
-// workgroup: 56 us, 6: 43, 12: 46).  A heaviest column of at most twice the weight is left alone (16 tiles: 21 us whole, 23 us
-// cut), and from kSubMinColumns columns on nothing is cut this way: two rounds of workgroups are there, heaviest first.
-// (From 512 on: 30000 tokens with 16/2 heads, one long and many short dense sequences, 2.33 -> 1.95 ms a step, but 16000 tokens with 28/4
-// heads 1.55 -> 1.75, 30000 with 14/2 heads at D = 64 1.12 -> 1.49 and a sink selection of 8000 tokens 0.98 -> 1.36 ms.)
+// fp32 partial sums that the reduction adds in walk order (the same problem: 44 us with the reduction; at least 4, 6 or 12 tiles a
+// workgroup: 44, 43 and 46 us).  A heaviest column of at most twice the weight is left alone (16 tiles: 25 us whole, 24 us cut, and
+// plan and reduction longer by as much), and from kSubMinColumns columns on nothing is cut this way: two rounds of workgroups are there,
+// heaviest first.  (A line at 512 columns is slower on all that lies between: 30000 tokens of one long and many short dense sequences
+// with 16/2 heads 1.56 -> 1.95 ms a step, 16000 tokens with 28/4 heads 0.96 -> 1.10, 30000 with 14/2 heads at D = 64 0.88 -> 1.22.  So
+// is cutting only items above twice the weight: 1.52 -> 1.78, 0.96 -> 1.05 and 0.88 -> 1.10 ms, the step of 37 blocks 120 -> 128 us.)
 constexpr int64_t kSubMinColumns = 1024, kSubSlots = 512;
 inline int sub_weight(const Geo& tg) {
   const int64_t w = (bwd_total_tiles(tg) + kSubSlots - 1) / kSubSlots;
   return (int)(w < 8 ? 8 : w);
 }
-// Most workgroups an item can be cut into (1: nothing is cut): an item has at most all tiles of its column, and less than
-// split_weight() plus one bitmap word's.
-inline int sub_parts_max(const Geo& tg) {
-  if ((int64_t)tg.Hkv * tg.NQB >= kSubMinColumns) return 1;
+// Slots of one KV head's sub-parts (0: nothing is cut).  An item has at most all tiles of its column, and less than split_weight()
+// plus one bitmap word's; one of t > w tiles takes ceil(t / w) < 2 t / w slots, and a KV head has 1 / Hkv of the tiles.  The sub-parts'
+// workgroups lead the key-major launch, one per slot, interleaved by KV head like the items and a multiple of 8 in all, so that item
+// r * Hkv + g behind them is still on KV head g's XCD.
+inline int sub_slots_max(const Geo& tg) {
+  if ((int64_t)tg.Hkv * tg.NQB >= kSubMinColumns) return 0;
   const int64_t w = sub_weight(tg), col = (int64_t)tg.n_max * tg.G, part = (int64_t)split_weight(tg) + 32 * tg.G;
-  const int64_t most = col < part ? col : part;
-  return most <= 2 * w ? 1 : (int)((most + w - 1) / w);
+  if ((col < part ? col : part) <= 2 * w) return 0;
+  int slots = (int)(2 * bwd_total_tiles(tg) / tg.Hkv / w) + 1;
+  while (slots * tg.Hkv % 8 != 0) ++slots;
+  return slots;
 }
-// slots: an item of t > w tiles takes ceil(t / w) < 2 t / w of them
-inline int64_t sub_slots_max(const Geo& tg) { return sub_parts_max(tg) > 1 ? 2 * bwd_total_tiles(tg) / sub_weight(tg) + 1 : 0; }
 // Everything a query-major workgroup needs to know about its item, so that it starts with one
 // 32-byte load instead of a chain of dependent table lookups.
 struct WorkItem {
