@@ -681,21 +681,18 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
   __shared__ uint16_t tl_s[kCW * 32 * 8];  // the chunk's tiles in processing order
   __shared__ int ntl_s;
   // workgroups 0 .. sub_slots-1: the sub-parts; then one per item, for those that are walked as a whole
-  const bool sub_part = (int)blockIdx.x < P.sub_slots;
-  ColItem item;
-  int sub = 0;
-  if (sub_part) {
-    item = P.sub_items[blockIdx.x].item;
-    sub = P.sub_items[blockIdx.x].sub;
-  } else {
     const int at = (int)blockIdx.x - P.sub_slots;
-    item = P.bwd_items[at];
-    if (P.sub_slots > 0 && P.sub_base[at] >= 0) return;
-  }
+  const ColItem item = at < 0 ? P.sub_items[blockIdx.x].item : P.bwd_items[at];
   if (item.col < 0) return;  // the lists are padded to their largest possible length
-  const int nsub = sub_part ? (item.weight + P.sub_weight - 1) / P.sub_weight : 1;  // workgroups that walk this item
-  // this one's run of the item's tiles in walk order
-  const int run0 = (int)((int64_t)item.weight * sub / nsub), run1 = (int)((int64_t)item.weight * (sub + 1) / nsub);
+  int nsub = 1, run0 = 0, run1 = item.weight;  // workgroups that walk the item; this one's run of its tiles in walk order
+  if (at < 0) {
+    const int sub = P.sub_items[blockIdx.x].sub;
+    nsub = (item.weight + P.sub_weight - 1) / P.sub_weight;
+    run0 = (int)((int64_t)item.weight * sub / nsub);
+    run1 = (int)((int64_t)item.weight * (sub + 1) / nsub);
+  } else if (P.sub_slots > 0 && P.sub_base[at] >= 0) {
+    return;
+  }
   BusyTimer timer;
   timer.start(P);
   const int tid = threadIdx.x;
