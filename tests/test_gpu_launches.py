@@ -46,13 +46,13 @@ def test_columns_of_small_problems_walked_by_several_workgroups(lens, Hq, Hkv, D
 
 
 # A column heavier than the split weight is cut into parts, and in a small problem a heavy part is itself walked by several
-# workgroups: the reduction then adds, in walk order, the sums of whole parts and of parts' parts.  Blocks that every later query
-# block keeps: 300 blocks with four heads (parts of 512, 512 and 176 tiles of a column) and 125 with seven (651 and 224), on one KV
-# head and on two; 128-token blocks have two such tile columns.
+# workgroups: the reduction then adds, in walk order, the sums of whole parts and of parts' parts.  Block 0 is kept by every query
+# block: 300 blocks with four heads (parts of 512, 512 and 176 tiles, all of them walked by several), 112 with seven heads on one KV
+# head and on two (560 and 224), 545 with one (513 tiles for 16 workgroups and 32 for one); 128-token blocks have two such columns.
 @pytest.mark.parametrize("blocks,B,Hq,Hkv,D,topk,mode", [
     (300, 64, 4, 1, 64, 4, 0), (300, 64, 4, 1, 128, 4, 0), (300, 64, 4, 1, 64, 4, 1), (300, 64, 4, 1, 128, 4, 1),
-    (125, 64, 14, 2, 64, 24, 0), (125, 64, 7, 1, 128, 24, 0), (125, 64, 7, 1, 64, 24, 1),
-    (150, 128, 4, 1, 128, 4, 0),
+    (112, 64, 14, 2, 64, 8, 0), (112, 64, 7, 1, 64, 8, 1), (545, 64, 1, 1, 64, 31, 0), (545, 64, 1, 1, 128, 31, 0),
+    (150, 128, 4, 1, 64, 4, 0),
 ])
 def test_parts_of_split_columns_walked_by_several_workgroups(blocks, B, Hq, Hkv, D, topk, mode):
     w = synth.Workload("sink", [B * blocks - 9], Hq, Hkv, D, B=B, topk=[topk], seed=72)
