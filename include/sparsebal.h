@@ -120,10 +120,11 @@ int sb_select_topk(const sb_problem *p, const float *scores, int32_t *sel_rowptr
 
 /* sb_select_topk for callers that cannot allocate device memory or bring a workspace: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments minus `ws`, same results bit for bit.  The
- * geometry tables that `ws` holds in sb_select_topk live in a device array built into the library (SB_STATIC_SELECT_WS_BYTES
- * per GPU, held until the process ends); a problem whose tables (select_ws_bytes of sb_layout) do not fit returns
- * SB_ERR_WORKSPACE_TOO_SMALL and enqueues nothing.  The call allocates and frees nothing.  All calls on one GPU share that
- * array: calls on different streams of one GPU that overlap in time race; calls on one stream are ordered.  The first
+ * geometry tables that `ws` holds in sb_select_topk (problems of more than 64 sequences need them) live in a device array built
+ * into the library (SB_STATIC_SELECT_WS_BYTES per GPU, held until the process ends); a problem whose tables (select_ws_bytes of
+ * sb_layout) would not fit returns SB_ERR_WORKSPACE_TOO_SMALL and enqueues nothing, whatever its number of sequences.  The call
+ * allocates and frees nothing.  All calls on one GPU share that array: calls on different streams of one GPU that overlap in time
+ * race unless both have at most 64 sequences; calls on one stream are ordered.  The first
  * call on a device looks up the array's address (a host-side query, no allocation); make it outside graph capture. */
 #define SB_STATIC_SELECT_WS_BYTES (1 << 20)
 int sb_select_topk_static(const sb_problem *p, const float *scores, int32_t *sel_rowptr_out, int32_t *sel_idx_out,
@@ -146,8 +147,8 @@ int sb_score_select(const sb_problem *p, const void *q, const void *k, float *kb
  * selected-block count (longest first, as in balanced partitioning by workload weight, paper
  * section 4.3), the key-major transpose of the selection (for every (s,hs,j) the set of query
  * blocks that kept j) and key-major items ordered by decreasing weight; a column that very many query blocks
- * kept (an attention sink) is cut into several items of bounded weight, so that no single workgroup becomes the
- * straggler the paper's section 3.2 describes.  plan_out: dev, plan_bytes, opaque; it is valid for this problem and
+ * kept (an attention sink) is cut into several items of bounded weight, and in small problems heavy items are walked by
+ * several workgroups, so that no single workgroup becomes the straggler the paper's section 3.2 describes.  plan_out: dev, plan_bytes, opaque; it is valid for this problem and
  * this selection only. */
 int sb_plan_worklist(const sb_problem *p, const int32_t *sel_rowptr, const int32_t *sel_idx, void *plan_out,
                      void *stream);
@@ -192,7 +193,8 @@ int sb_sparse_attn_fwd(const sb_problem *p, const void *q, const void *k, const 
 
 /* Backward of Eq. 2 with the selection held fixed: dQ, dK, dV from dO (dK, dV summed over the
  * query heads of each KV head).  o and lse are the forward's outputs.  Deterministic: every output
- * element is accumulated by one workgroup in a fixed order.  ws: dev, bwd_ws_bytes. */
+ * element is accumulated in a fixed order, by one workgroup or as partial sums of several that are
+ * added in a fixed order.  ws: dev, bwd_ws_bytes. */
 int sb_sparse_attn_bwd(const sb_problem *p, const void *q, const void *k, const void *v, const void *o,
                        const float *lse, const void *d_o, const int32_t *sel_rowptr, const int32_t *sel_idx,
                        const void *plan, void *dq, void *dk, void *dv, void *ws, void *stream);

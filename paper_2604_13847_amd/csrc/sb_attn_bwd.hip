@@ -681,7 +681,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
   __shared__ uint16_t tl_s[kCW * 32 * 8];  // the chunk's tiles in processing order
   __shared__ int ntl_s;
   // workgroups 0 .. sub_slots-1: the sub-parts; then one per item, for those that are walked as a whole
-    const int at = (int)blockIdx.x - P.sub_slots;
+  const int at = (int)blockIdx.x - P.sub_slots;
   const ColItem item = at < 0 ? P.sub_items[blockIdx.x].item : P.bwd_items[at];
   if (item.col < 0) return;  // the lists are padded to their largest possible length
   int nsub = 1, run0 = 0, run1 = item.weight;  // workgroups that walk the item; this one's run of its tiles in walk order
@@ -943,136 +943,136 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
         }
         wait_vmcnt<0>();  // the loads past the last tile
       } else {
-      // ---- software pipeline over half tiles u = 0, 1, ...: four stages of NOP matrix instructions each,
-      //   S(u), dP(u), dV(u-1), dK(u-1)
-      // with P(u) spread under the last two and dS(u-1) under the first two, so that every matrix instruction has the same
-      // share of vector work beside it and nothing waits for a result of the stage before.  The operands of a stage are
-      // fetched from LDS while the previous one computes.  Half tile u-1 has been read when stage dK(u-1) begins: after a
-      // barrier its buffer takes the loads of half tile u+3, two at a time.
-      int i1, h1;  // the newest tile that loads have been issued for
-      {
-        int i0, h0;
-        entry(0, i0, h0);
-        issue_half(half_of(0, 0, i0, h0));
-        issue_half(half_of(0, 1, i0, h0));
-      }
-      entry(min(1, ntl - 1), i1, h1);
-      Half nxt = half_of(1, 0, i1, h1);
-      issue_half(nxt);
-      wait_vmcnt<2 * kLoadsPerHalf>();
-      __builtin_amdgcn_s_barrier();
+        // ---- software pipeline over half tiles u = 0, 1, ...: four stages of NOP matrix instructions each,
+        //   S(u), dP(u), dV(u-1), dK(u-1)
+        // with P(u) spread under the last two and dS(u-1) under the first two, so that every matrix instruction has the same
+        // share of vector work beside it and nothing waits for a result of the stage before.  The operands of a stage are
+        // fetched from LDS while the previous one computes.  Half tile u-1 has been read when stage dK(u-1) begins: after a
+        // barrier its buffer takes the loads of half tile u+3, two at a time.
+        int i1, h1;  // the newest tile that loads have been issued for
+        {
+          int i0, h0;
+          entry(0, i0, h0);
+          issue_half(half_of(0, 0, i0, h0));
+          issue_half(half_of(0, 1, i0, h0));
+        }
+        entry(min(1, ntl - 1), i1, h1);
+        Half nxt = half_of(1, 0, i1, h1);
+        issue_half(nxt);
+        wait_vmcnt<2 * kLoadsPerHalf>();
+        __builtin_amdgcn_s_barrier();
 #pragma unroll
-      for (int ks = 0; ks < NOP; ++ks) op[ks] = ld_row(ks, 0);
-      // one half tile: HALF of tile t, whose buffer is `buf`.  FIRST: nothing precedes it; LAST: there is no half tile u any
-      // more, only dV and dK of u-1 are left.  Loads are issued past the chunk's last tile too (its last tile once more, never
-      // read), so that their number in flight is the same everywhere.
-      auto half_tile = [&](auto first_c, auto last_c, auto diag_c, auto half_c, int buf, int t) __attribute__((always_inline)) {
-        constexpr bool FIRST = decltype(first_c)::value, LAST = decltype(last_c)::value;
-        constexpr int HALF = decltype(half_c)::value, PREV = 1 - HALF, LPS = Loader::LPS;
-        const unsigned CO = buf * BUF_B + HALF * 32 * ROW_B;                               // half tile u
-        const unsigned PO = (HALF ? buf : 1 - buf) * BUF_B + PREV * 32 * ROW_B;             // u - 1
-        const unsigned NO = (HALF ? 1 - buf : buf) * BUF_B + PREV * 32 * ROW_B;             // u + 1
-        const unsigned SO = (2 * buf + HALF) * 512, PSO = (HALF ? 2 * buf : 2 * (1 - buf) + 1) * 512;
-        int e2 = 0;
-        constexpr int EPS = 8 / NOP;  // rows (accumulator registers) of the pointwise work per matrix instruction
-        // Every step is fenced: one matrix instruction, the refill of its operand, its share of the vector work.
+        for (int ks = 0; ks < NOP; ++ks) op[ks] = ld_row(ks, 0);
+        // one half tile: HALF of tile t, whose buffer is `buf`.  FIRST: nothing precedes it; LAST: there is no half tile u any
+        // more, only dV and dK of u-1 are left.  Loads are issued past the chunk's last tile too (its last tile once more, never
+        // read), so that their number in flight is the same everywhere.
+        auto half_tile = [&](auto first_c, auto last_c, auto diag_c, auto half_c, int buf, int t) __attribute__((always_inline)) {
+          constexpr bool FIRST = decltype(first_c)::value, LAST = decltype(last_c)::value;
+          constexpr int HALF = decltype(half_c)::value, PREV = 1 - HALF, LPS = Loader::LPS;
+          const unsigned CO = buf * BUF_B + HALF * 32 * ROW_B;                               // half tile u
+          const unsigned PO = (HALF ? buf : 1 - buf) * BUF_B + PREV * 32 * ROW_B;             // u - 1
+          const unsigned NO = (HALF ? 1 - buf : buf) * BUF_B + PREV * 32 * ROW_B;             // u + 1
+          const unsigned SO = (2 * buf + HALF) * 512, PSO = (HALF ? 2 * buf : 2 * (1 - buf) + 1) * 512;
+          int e2 = 0;
+          constexpr int EPS = 8 / NOP;  // rows (accumulator registers) of the pointwise work per matrix instruction
+          // Every step is fenced: one matrix instruction, the refill of its operand, its share of the vector work.
 #define SB_FENCE() __builtin_amdgcn_sched_barrier(0)
-        SB_FENCE();
-        if (!LAST && HALF == 1) e2 = (int)list[-min(t + 2, ntl - 1)];
-#pragma unroll
-        for (int k = 0; k < NOP; ++k) {
-          if (!LAST) {
-            if (k == 0) mfma32_first(sacc[HALF], op[k], kf[k]);
-            else mfma32_more(sacc[HALF], op[k], kf[k]);
-            op[k] = ld_row(k, CO + TILE_B);
-          }
-          if (!FIRST)
-#pragma unroll
-            for (int e = 0; e < EPS; ++e) dscore(PREV, EPS * k + e, PSO);
           SB_FENCE();
-        }
-        if constexpr (!FIRST && !LAST && LPS > 4) loader.template issue2<LPS - 4>(nxt.rows);
-        if (!LAST) { st_l[0] = ld_stat(SO, 0); st_l[1] = ld_stat(SO, 1); }
-        SB_FENCE();
+          if (!LAST && HALF == 1) e2 = (int)list[-min(t + 2, ntl - 1)];
 #pragma unroll
-        for (int k = 0; k < NOP; ++k) {
-          if (!LAST) {
-            if (k == 0) mfma32_first(dpacc[HALF], op[k], vf[k]);
-            else mfma32_more(dpacc[HALF], op[k], vf[k]);
-          }
-          if (!FIRST) {
-            op[k] = ld_tr(k, PO + TILE_B);
-#pragma unroll
-            for (int e = 0; e < EPS; ++e) dscore(PREV, 8 + EPS * k + e, PSO);
-          }
-          SB_FENCE();
-        }
-        if constexpr (!FIRST && !LAST) loader.template issue2<LPS - 2>(nxt.rows);
-        SB_FENCE();
-#pragma unroll
-        for (int k = 0; k < NOP; ++k) {
-          if (!FIRST) {
-            dvacc[k % (D / 32)] = mfma32(pa[PREV][k / (D / 32)], op[k], dvacc[k % (D / 32)]);
-            op[k] = ld_tr(k, PO);
-          }
-          if (!LAST)
-#pragma unroll
-            for (int e = 0; e < EPS; ++e) prob(diag_c, HALF, EPS * k + e, SO);
-          if (!LAST && k == NOP / 2) {  // scalar work for the loads below, while matrix instructions run
-            if (HALF == 1) {
-              const int e = __builtin_amdgcn_readfirstlane(e2);
-              i1 = 32 * w0 + (e >> 3);
-              h1 = g * P.G + sel0 + (e & 7);
+          for (int k = 0; k < NOP; ++k) {
+            if (!LAST) {
+              if (k == 0) mfma32_first(sacc[HALF], op[k], kf[k]);
+              else mfma32_more(sacc[HALF], op[k], kf[k]);
+              op[k] = ld_row(k, CO + TILE_B);
             }
-            nxt = half_of(HALF == 0 ? 1 - buf : buf, PREV, i1, h1);
-          }
-          SB_FENCE();
-        }
-        if (!LAST) {
-          // half tile u - 1 has been read by this wavefront and its part of u + 1 has landed
-          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(kLoadsPerHalf) : "memory");
-          __builtin_amdgcn_s_barrier();
-          st_d[0] = ld_stat(SO + 256, 0);
-          st_d[1] = ld_stat(SO + 256, 1);
-          load_floats(nxt.stat_slot, nxt.stat, nxt.stat_bytes, lane);
-          SB_FENCE();
-        }
+            if (!FIRST)
 #pragma unroll
-        for (int k = 0; k < NOP; ++k) {
-          if (!FIRST) dkacc[k % (D / 32)] = mfma32(dsa[k / (D / 32)], op[k], dkacc[k % (D / 32)]);
-          if (!LAST) {
-            op[k] = ld_row(k, NO);  // (after the last half tile of the chunk this reads a stale buffer and is not used)
-#pragma unroll
-            for (int e = 0; e < EPS; ++e) prob(diag_c, HALF, 8 + EPS * k + e, SO);
-          }
-          SB_FENCE();
-          if constexpr (!LAST) {
-            if (k == 0) loader.template issue2<0>(nxt.rows);
-            if constexpr (LPS > 4) { if (k == NOP / 2) loader.template issue2<2>(nxt.rows); }
+              for (int e = 0; e < EPS; ++e) dscore(PREV, EPS * k + e, PSO);
             SB_FENCE();
           }
-        }
+          if constexpr (!FIRST && !LAST && LPS > 4) loader.template issue2<LPS - 4>(nxt.rows);
+          if (!LAST) { st_l[0] = ld_stat(SO, 0); st_l[1] = ld_stat(SO, 1); }
+          SB_FENCE();
+#pragma unroll
+          for (int k = 0; k < NOP; ++k) {
+            if (!LAST) {
+              if (k == 0) mfma32_first(dpacc[HALF], op[k], vf[k]);
+              else mfma32_more(dpacc[HALF], op[k], vf[k]);
+            }
+            if (!FIRST) {
+              op[k] = ld_tr(k, PO + TILE_B);
+#pragma unroll
+              for (int e = 0; e < EPS; ++e) dscore(PREV, 8 + EPS * k + e, PSO);
+            }
+            SB_FENCE();
+          }
+          if constexpr (!FIRST && !LAST) loader.template issue2<LPS - 2>(nxt.rows);
+          SB_FENCE();
+#pragma unroll
+          for (int k = 0; k < NOP; ++k) {
+            if (!FIRST) {
+              dvacc[k % (D / 32)] = mfma32(pa[PREV][k / (D / 32)], op[k], dvacc[k % (D / 32)]);
+              op[k] = ld_tr(k, PO);
+            }
+            if (!LAST)
+#pragma unroll
+              for (int e = 0; e < EPS; ++e) prob(diag_c, HALF, EPS * k + e, SO);
+            if (!LAST && k == NOP / 2) {  // scalar work for the loads below, while matrix instructions run
+              if (HALF == 1) {
+                const int e = __builtin_amdgcn_readfirstlane(e2);
+                i1 = 32 * w0 + (e >> 3);
+                h1 = g * P.G + sel0 + (e & 7);
+              }
+              nxt = half_of(HALF == 0 ? 1 - buf : buf, PREV, i1, h1);
+            }
+            SB_FENCE();
+          }
+          if (!LAST) {
+            // half tile u - 1 has been read by this wavefront and its part of u + 1 has landed
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(kLoadsPerHalf) : "memory");
+            __builtin_amdgcn_s_barrier();
+            st_d[0] = ld_stat(SO + 256, 0);
+            st_d[1] = ld_stat(SO + 256, 1);
+            load_floats(nxt.stat_slot, nxt.stat, nxt.stat_bytes, lane);
+            SB_FENCE();
+          }
+#pragma unroll
+          for (int k = 0; k < NOP; ++k) {
+            if (!FIRST) dkacc[k % (D / 32)] = mfma32(dsa[k / (D / 32)], op[k], dkacc[k % (D / 32)]);
+            if (!LAST) {
+              op[k] = ld_row(k, NO);  // (after the last half tile of the chunk this reads a stale buffer and is not used)
+#pragma unroll
+              for (int e = 0; e < EPS; ++e) prob(diag_c, HALF, 8 + EPS * k + e, SO);
+            }
+            SB_FENCE();
+            if constexpr (!LAST) {
+              if (k == 0) loader.template issue2<0>(nxt.rows);
+              if constexpr (LPS > 4) { if (k == NOP / 2) loader.template issue2<2>(nxt.rows); }
+              SB_FENCE();
+            }
+          }
 #undef SB_FENCE
-      };
-      {
-        using std::true_type;
-        using std::false_type;
-        auto tile = [&](auto first_c, auto diag_c, int buf, int t) __attribute__((always_inline)) {
-          half_tile(first_c, false_type(), diag_c, H0(), buf, t);
-          half_tile(false_type(), false_type(), diag_c, H1(), buf, t);
         };
-        int t = 1;
-        if (nn > 0) tile(true_type(), false_type(), 0, 0);
-        else tile(true_type(), true_type(), 0, 0);
-        for (; t + 2 <= nn; t += 2) {
-          tile(false_type(), false_type(), 1, t);
-          tile(false_type(), false_type(), 0, t + 1);
+        {
+          using std::true_type;
+          using std::false_type;
+          auto tile = [&](auto first_c, auto diag_c, int buf, int t) __attribute__((always_inline)) {
+            half_tile(first_c, false_type(), diag_c, H0(), buf, t);
+            half_tile(false_type(), false_type(), diag_c, H1(), buf, t);
+          };
+          int t = 1;
+          if (nn > 0) tile(true_type(), false_type(), 0, 0);
+          else tile(true_type(), true_type(), 0, 0);
+          for (; t + 2 <= nn; t += 2) {
+            tile(false_type(), false_type(), 1, t);
+            tile(false_type(), false_type(), 0, t + 1);
+          }
+          if (t < nn) { tile(false_type(), false_type(), 1, t); ++t; }
+          for (; t < ntl; ++t) tile(false_type(), true_type(), t & 1, t);  // the diagonal tiles
+          half_tile(false_type(), true_type(), false_type(), H0(), ntl & 1, ntl);
+          wait_vmcnt<0>();  // the loads past the last tile
         }
-        if (t < nn) { tile(false_type(), false_type(), 1, t); ++t; }
-        for (; t < ntl; ++t) tile(false_type(), true_type(), t & 1, t);  // the diagonal tiles
-        half_tile(false_type(), true_type(), false_type(), H0(), ntl & 1, ntl);
-        wait_vmcnt<0>();  // the loads past the last tile
-      }
       }
     }
   }

@@ -253,7 +253,7 @@ extern "C" int sb_score_select(const sb_problem* p, const void* q, const void* k
   if ((rc = check_device_arrays(p)) != SB_OK) return rc;
   const GeomArgs ga = make_geom_args(g, p, make_tables(g, p, ws));
   if (scores_out) {  // the caller wants the score matrix: write it, then select from it
-    rc = sb_block_scores(p, q, k, kbar_out, scores_out, ws, stream);  // leaves the geometry tables at the start of ws
+    rc = sb_block_scores(p, q, k, kbar_out, scores_out, ws, stream);  // leaves the geometry tables, where they are needed, at the start of ws
     if (rc != SB_OK) return rc;
     return select_launch(g, ga, scores_out, sel_rowptr_out, sel_idx_out, st);
   }
@@ -304,7 +304,7 @@ extern "C" int sb_select_topk_static(const sb_problem* p, const float* scores, i
   if ((rc = check_device_arrays(p)) != SB_OK) return rc;
   void* ws = nullptr;
   if ((rc = static_scratch_ptr(&ws)) != SB_OK) return rc;
-  // every table entry the selection reads is rewritten by the geometry kernel of this call: nothing has to start at zero
+  // (from kLaneSeqs + 1 sequences on:) every table entry the selection reads is rewritten by this call: nothing has to start at zero
   if ((rc = need_tables(g, p, ws, st)) != SB_OK) return rc;
   return select_launch(g, make_geom_args(g, p, make_tables(g, p, ws)), scores, sel_rowptr_out, sel_idx_out, st);
 }
