@@ -37,10 +37,15 @@ __device__ inline void load_quarter(float (&dst)[D / 4], const float* __restrict
 }
 template <int D>
 __device__ inline void add_quarter(float (&dst)[D / 4], const float* __restrict__ row, int kq) {
+  float4 v[D / 16];
+#pragma unroll
+  for (int u = 0; u < D / 16; ++u) v[u] = *(const float4*)(row + 16 * u + 4 * kq);
+  // all loads in flight at once: to save registers that nothing else could use, the compiler waited for each before the next (scoring and
+  // selection in one kernel, per KV group: 30000 tokens in 85 sequences 65 -> 53 us, 262144 tokens in 109 sequences 252 -> 234 us)
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int u = 0; u < D / 16; ++u) {
-    const float4 v = *(const float4*)(row + 16 * u + 4 * kq);
-    dst[4 * u] += v.x; dst[4 * u + 1] += v.y; dst[4 * u + 2] += v.z; dst[4 * u + 3] += v.w;
+    dst[4 * u] += v[u].x; dst[4 * u + 1] += v[u].y; dst[4 * u + 2] += v[u].z; dst[4 * u + 3] += v[u].w;
   }
 }
 
