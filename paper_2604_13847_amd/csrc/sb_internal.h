@@ -158,13 +158,21 @@ inline int split_extra_max(const Geo& tg) { return (int)(bwd_total_tiles(tg) / s
 // than sub_weight() tiles are then walked by several workgroups, each an equal run of the item's tiles in walk order; they leave
 // fp32 partial sums that the reduction adds in walk order (the same problem: 44 us with the reduction; at least 4, 6 or 12 tiles a
 // workgroup: 44, 43 and 46 us).  A heaviest column of at most twice the weight is left alone (16 tiles: 25 us whole, 24 us cut, and
-// plan and reduction longer by as much), and from kSubMinColumns columns on nothing is cut this way: two rounds of workgroups are there,
-// heaviest first.  (A line at 512 columns is slower on all that lies between: 30000 tokens of one long and many short dense sequences
-// with 16/2 heads 1.56 -> 1.95 ms a step, 16000 tokens with 28/4 heads 0.96 -> 1.10, 30000 with 14/2 heads at D = 64 0.88 -> 1.22.  So
-// is cutting only items above twice the weight: 1.52 -> 1.78, 0.96 -> 1.05 and 0.88 -> 1.10 ms, the step of 37 blocks 120 -> 128 us.)
+// plan and reduction longer by as much).
+// From sub_min_columns() columns on nothing is cut this way.  At D = 128 that is 1024: two rounds of workgroups are there, heaviest
+// first.  (A line at 512 columns is slower on all that lies between: 30000 tokens of one long and many short dense sequences with 16/2
+// heads 1.56 -> 1.95 ms a step, 16000 tokens with 28/4 heads 0.96 -> 1.10, 30000 with 14/2 heads at D = 64 0.88 -> 1.22.  So is cutting
+// only items above twice the weight: 1.52 -> 1.78, 0.96 -> 1.05 and 0.88 -> 1.10 ms, the step of 37 blocks 120 -> 128 us.)
+// At D = 64 a CU holds four workgroups, which with fewer than three rounds of them (3 * 1024 columns) are handed out at once or nearly
+// so, and nothing evens out unequal columns then: uncut, the kernel was slower than with the two workgroups per CU it had when it took
+// more registers.  From 1024 columns on the weight is half, or hardly an item would exceed it.  dK/dV with two workgroups per CU / four
+// and uncut / four and cut: 12500 tokens with 32/8 heads 328 / 367 / 260 us, 40000 tokens of one long and many short dense sequences with
+// 14/2 heads 907 / 986 / 485 us, 40000 tokens with 28/4 heads and a sink 1005 / 1051 / 773 us; at 3250 columns the sink gains 14 %, other
+// selections are equal or 2 % slower.
 constexpr int64_t kSubMinColumns = 1024, kSubSlots = 512;
+inline int64_t sub_min_columns(const Geo& tg) { return (tg.D == 64 ? 3 : 1) * kSubMinColumns; }
 inline int sub_weight(const Geo& tg) {
-  const int64_t w = (bwd_total_tiles(tg) + kSubSlots - 1) / kSubSlots;
+  const int64_t slots = ((int64_t)tg.Hkv * tg.NQB >= kSubMinColumns ? 2 : 1) * kSubSlots, w = (bwd_total_tiles(tg) + slots - 1) / slots;
   return (int)(w < 8 ? 8 : w);
 }
 // Slots of one KV head's sub-parts (0: nothing is cut).  An item has at most all tiles of its column, and less than split_weight()
@@ -172,7 +180,7 @@ inline int sub_weight(const Geo& tg) {
 // workgroups lead the key-major launch, one per slot, interleaved by KV head like the items and a multiple of 8 in all, so that item
 // r * Hkv + g behind them is still on KV head g's XCD.
 inline int sub_slots_max(const Geo& tg) {
-  if ((int64_t)tg.Hkv * tg.NQB >= kSubMinColumns) return 0;
+  if ((int64_t)tg.Hkv * tg.NQB >= sub_min_columns(tg)) return 0;
   const int64_t w = sub_weight(tg), col = (int64_t)tg.n_max * tg.G, part = (int64_t)split_weight(tg) + 32 * tg.G;
   if ((col < part ? col : part) <= 2 * w) return 0;
   int slots = (int)(2 * bwd_total_tiles(tg) / tg.Hkv / w) + 1;

@@ -252,8 +252,8 @@ __global__ __launch_bounds__(1024) void plan_bwd_order_kernel(const int32_t* __r
     cw.bm = bitmap + (int64_t)Hs * bm_off[s] + (hs0 * n + j) * cw.words;
     return cw;
   };
-  // A bin counts its items, and from bit 16 on their sub-parts: where items are cut there are fewer than kSubMinColumns columns, and so
-  // at most kSubMinColumns + 2048 items and, but for the rounding, 2 * kSubSlots sub-parts.
+  // A bin counts its items, and from bit 16 on their sub-parts: where items are cut there are fewer than 3 * kSubMinColumns columns, so
+  // at most 3072 + 2048 items and, but for the rounding, 4 * kSubSlots sub-parts.
   auto sub_parts = [&](int wt) { return wsub > 0 && wt > wsub ? (wt + wsub - 1) / wsub : 0; };
   auto count = [&](int wt) { return atomicAdd(&bins[min(wt, kBwdBins - 1)], 1 + (sub_parts(wt) << 16)); };
   // places an item and its sub-parts and returns where the item is

@@ -37,6 +37,7 @@ def check_backward_repeats(r, new_plan=False):
     ([64 * 520 - 3], 2, 1, 64, 0, (0.01, 0.01)),          # runs cross the chunks of 256 query blocks (512 at D = 128)
     ([64 * 520 - 3], 2, 1, 128, 0, (0.01, 0.01)),
     ([64 * 257 - 3], 2, 1, 64, 0, (0.02, 0.02)),          # one query block past a chunk
+    ([64 * 530 - 3], 2, 2, 64, 0, (0.02, 0.02)),          # 1060 columns: cut at head_dim 64 only, from half the weight on
 ])
 def test_columns_of_small_problems_walked_by_several_workgroups(lens, Hq, Hkv, D, mode, ratio):
     w = synth.small_ragged(seed=71, lens=lens, Hq=Hq, Hkv=Hkv, D=D, ratio=ratio)
