@@ -659,15 +659,17 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void a
 // concurrent columns of one KV head (same XCD) start at the same query block, advance at a similar
 // pace and so ask for the same Q/dO tiles at about the same time and meet them in that XCD's L2.
 // What bounds it: one wavefront per SIMD (it needs more than 256 registers), so every wait is idle time of the matrix cores, and
-// under matrix load the chip runs at 1.6 - 1.8 GHz of its 2.4.  Hence the software pipeline over half tiles (32 queries) below:
+// under matrix load the chip runs at 1.5 - 1.75 GHz of its 2.4.  Hence the software pipeline over half tiles (32 queries) below:
 // every matrix instruction carries the same share of vector work and LDS reads, fenced step by step, results are used two
 // stages after they were started, and the tile loads are issued two at a time between matrix instructions instead of 17 in a
 // row.  The scores are kept out of the accumulation registers (mfma32_first).  32768-token batch, 32/8 heads, D = 128:
-// 3.66 -> 3.24 ms (matrix cores busy 48 -> 56 % of the cycles), the 262144-token batch, whose gathers come through the fabric at
-// 6 TB/s: 36.7 -> 34.9 ms.
+// 3.66 -> 3.24 ms (matrix cores busy 48 -> 57 % of the cycles), the 262144-token batch, whose gathers come through the fabric at
+// 6 TB/s: 36.7 -> 34.9 ms.  The compiler spills 16 vector and 165 scalar registers for it (before: none and 127).  The loop over the
+// unmasked tiles has no reload of the former and two of the latter; the others are in what is done once per chunk and in a chunk's first
+// tile, and count for columns of few tiles.
 // D = 64 needs half the registers: there two wavefronts share a SIMD instead, a half tile is computed from start to end, and the
-// shorter tile list (8 bitmap words per chunk) lets four workgroups share a CU's LDS.  Matrix cores busy 39 -> 48 %, at a clock that
-// the chip lowers from 1.9 to 1.6 GHz for it; together with the forward kernel's second wavefront per SIMD a step of 65536 tokens,
+// shorter tile list (8 bitmap words per chunk) lets four workgroups share a CU's LDS.  Matrix cores busy 34 -> 48 %, at a clock that
+// the chip lowers from 1.86 to 1.62 GHz for it; together with the forward kernel's second wavefront per SIMD a step of 65536 tokens,
 // 14/2 heads, selection blocks of 256: 7.66 -> 6.81 ms.
 template <int D, bool OUT_F32>
 __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1))) void attn_bwd_dkv_kernel(AttnParams P) {

@@ -13,8 +13,8 @@
 // probabilities convert to the B operand of O^T += V^T P^T without any cross-lane movement; V^T is
 // read straight out of the row-major V strip with the transposing LDS read.
 // D = 128 needs more than 256 registers and runs one wavefront per SIMD.  D = 64 is held to 256, so that two share a SIMD and one
-// runs its exponentials (which outlast the matrix instructions there) under the other's matrix instructions: matrix cores busy
-// 28 -> 40 % of the cycles, 2.14 -> 1.67 ms on 65536 tokens, 14/2 heads, selection blocks of 256 (1.56 with the softmax's branch).
+// runs its exponentials (which outlast the matrix instructions there) under the other's matrix instructions: 2.14 -> 1.67 ms
+// on 65536 tokens, 14/2 heads, selection blocks of 256, and 1.56 with the softmax's branch (matrix cores busy 28 -> 44 % of the cycles).
 #include <type_traits>
 
 #include "sb_attn_common.h"
