@@ -60,16 +60,34 @@ constexpr int kTicketSlots = 64;    // one counter per head plane of a query-maj
 // the tail of the launch, handed out by ticket to whichever workgroup asks first.  The launch has twice as many tail
 // workgroups as tail items: a fast XCD gets through more of them, and those that find the tail empty exit at once.
 // Which workgroup computes an item never changes its result.
-// Returns the item's index in the list or -1; every thread of the workgroup must call it (it has a barrier).
-__device__ inline int claim_item(int pos, int n_items, int* counter) {
+// Returns the item's index in the list or -1; every thread of the workgroup must call it (it has a barrier).  `sh` is an LDS word that
+// only wavefronts other than the first write afterwards; a workgroup of one wavefront needs none.
+__device__ inline int claim_item(int pos, int n_items, int* counter, int* sh) {
   if (!counter) return pos < n_items ? pos : -1;
   const int groups = n_items >> 7, held = groups << 3;  // held-back items: indices 128 q + 120 .. 128 q + 127
   if (pos < n_items - held) return pos < 120 * groups ? (pos / 120 << 7) + pos % 120 : pos + held;
-  __shared__ int sh_claim;
-  if (threadIdx.x == 0) sh_claim = atomicAdd(counter, 1);
-  __syncthreads();
-  const int t = sh_claim;
+  int t = 0;
+  if (threadIdx.x == 0) {
+    t = atomicAdd(counter, 1);
+    if (sh) *sh = t;
+  }
+  t = __builtin_amdgcn_readfirstlane(t);
+  if (sh) {
+    __syncthreads();
+    if (threadIdx.x >= 64) t = __builtin_amdgcn_readfirstlane(*sh);
+  }
   return t < held ? ((t >> 3) << 7) + 120 + (t & 7) : -1;
+}
+__device__ inline int claim_item(int pos, int n_items, int* counter) {
+  __shared__ int sh_claim;
+  return claim_item(pos, n_items, counter, &sh_claim);
+}
+
+// Descriptor `pos` (wave-uniform) by scalar loads, so that everything that follows from it is scalar work.
+__device__ inline WorkItem uniform_item(const WorkItem* items, int pos) {
+  typedef int i32x8 __attribute__((ext_vector_type(8)));
+  const i32x8 x = ((const __attribute__((address_space(4))) i32x8*)(uintptr_t)items)[__builtin_amdgcn_readfirstlane(pos)];
+  return WorkItem{x[0], x[1], x[2], x[3], x[4], x[5], x[6], x[7]};
 }
 
 __device__ inline f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
@@ -329,6 +347,38 @@ struct RowLoader {
     if constexpr (LPS > 4) { issue2<4>(x); issue2<6>(x); }
   }
 };
+// The same with the resource as four scalar registers that the caller keeps, for the kernels whose wavefront has a SIMD to itself: those
+// issue one instruction every four cycles whatever it is, so a scalar instruction there costs as much as a vector one.  The immediate
+// offset moves both the global and the LDS address, so four loads in a row need one M0, and the lane offsets are pre-biased for it (row
+// 4a of the strip starts at least 1024 a bytes in, so they stay positive).  The resource's words must come from scalar instructions.
+template <int D>
+struct QuadLoader {
+  static constexpr int C = D / 8, RPI = 64 / C, LPS = 32 / RPI;  // 16-byte chunks per row, rows per load, loads per strip
+  unsigned voff[LPS];
+  __device__ inline void init(int H, int lane) {
+#pragma unroll
+    for (int a = 0; a < LPS; ++a) {
+      const int r = a * RPI + lane / C;
+      voff[a] = (unsigned)(r * H * D * 2 + 16 * ((lane % C) ^ chunk_swizzle<D>(r)) - 1024 * (a & 3));
+    }
+  }
+  // the first `bytes` bytes from `base` on exist, the rest arrives as zeros; both wave-uniform
+  __device__ static inline i32x4 resource(unsigned long long base, unsigned bytes) {
+    return i32x4{(int)(unsigned)base, (int)(unsigned)(base >> 32), (int)bytes, 0x20000};
+  }
+  template <int A>
+  __device__ inline void issue2(i32x4 rsrc, unsigned slot) const {  // loads A, A+1 (A even) of a strip
+    asm volatile("s_add_u32 m0, %2, %4\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %0, %3, 0 offen offset:%5 lds\n\tbuffer_load_dwordx4 %1, %3, 0 offen offset:%6 lds"
+                 : : "v"(voff[A]), "v"(voff[A + 1]), "s"(slot), "s"(rsrc), "n"(A / 4 * 4096), "n"(A % 4 * 1024), "n"(A % 4 * 1024 + 1024)
+                 : "memory", "m0", "scc");
+  }
+  __device__ inline void issue(i32x4 rsrc, unsigned slot) const {
+    issue2<0>(rsrc, slot);
+    issue2<2>(rsrc, slot);
+    if constexpr (LPS > 4) { issue2<4>(rsrc, slot); issue2<6>(rsrc, slot); }
+  }
+};
 // the first `bytes` of 64 consecutive floats from `src` (both wave-uniform) to LDS, the rest as zeros
 __device__ inline void load_floats(unsigned slot, unsigned long long src, unsigned bytes, int lane) {
   asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 s[84:85], %2\n\ts_mov_b32 s86, %3\n\ts_mov_b32 s87, 0x20000\n\t"
@@ -372,6 +422,37 @@ __device__ inline float max_across_halves(float x) {
 }
 
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// A wavefront stores 32 rows of one head that it holds as C tiles (lane%32: row, value(dt, v): column 32dt + c_row(v, lane/32)): the
+// rows go through LDS (`buf`, the wavefront's own, 32 rows), so that every store covers whole rows.  Straight from the registers a store
+// would be 8 bytes here and there, 16 of them to a row.
+template <int D, bool F32, typename V>
+__device__ inline void store_rows(char* buf, void* out, int64_t first, int64_t pitch, int rows, int lane, V value) {
+  constexpr int EB = F32 ? 4 : 2, C = D * EB / 16, RPI = 64 / C;  // bytes per element, 16-byte chunks per row, rows per store
+  const int l32 = lane & 31, hf = lane >> 5;
+#pragma unroll
+  for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+    for (int vg = 0; vg < 4; ++vg) {
+      const int byte = (32 * dt + 8 * vg + 4 * hf) * EB;
+      char* const at = buf + l32 * (D * EB) + 16 * ((byte >> 4) ^ (l32 & (C - 1))) + (byte & 15);
+      if constexpr (F32) {
+        *(f32x4*)at = f32x4{value(dt, 4 * vg), value(dt, 4 * vg + 1), value(dt, 4 * vg + 2), value(dt, 4 * vg + 3)};
+      } else {
+        bf16x4 y;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[e] = (bf16)value(dt, 4 * vg + e);
+        *(bf16x4*)at = y;
+      }
+    }
+  asm volatile("" ::: "memory");  // (LDS operations of a wavefront complete in order)
+#pragma unroll
+  for (int a = 0; a < 32 / RPI; ++a) {
+    const int r = a * RPI + lane / C, c = lane % C;
+    const f32x4 x = *(const f32x4*)(buf + r * (D * EB) + 16 * (c ^ (r & (C - 1))));
+    if (r < rows) *(f32x4*)((char*)out + (first + r * pitch) * EB + 16 * c) = x;
+  }
+}
 
 struct BusyTimer {
   long long t0;
