@@ -12,17 +12,19 @@
 // S^T = K Q^T puts a query in a C-matrix column, so the softmax statistics are per lane and the
 // probabilities convert to the B operand of O^T += V^T P^T without any cross-lane movement; V^T is
 // read straight out of the row-major V strip with the transposing LDS read.
-// D = 128 needs more than 256 registers and runs one wavefront per SIMD.  D = 64 is held to 256, so that two share a SIMD and one
-// runs its exponentials (which outlast the matrix instructions there) under the other's matrix instructions: 2.14 -> 1.67 ms
-// on 65536 tokens, 14/2 heads, selection blocks of 256, and 1.56 with the softmax's branch (matrix cores busy 28 -> 44 % of the cycles).
+// That is attn_fwd_kernel, for head_dim 64.  It is held to 256 registers, so that two wavefronts share a SIMD and one runs its
+// exponentials (which outlast the matrix instructions there) under the other's matrix instructions: 2.14 -> 1.67 ms on 65536 tokens,
+// 14/2 heads, selection blocks of 256, and 1.56 with the softmax's branch (matrix cores busy 28 -> 44 % of the cycles).
+// Head_dim 128 takes the registers of a whole SIMD and has a kernel of its own, attn_fwd_head_kernel.
 #include <type_traits>
 
 #include "sb_attn_common.h"
 
 namespace sb {
 
-template <int D, bool OUT_F32>
-__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1))) void attn_fwd_kernel(AttnParams P, int n_items, int heads) {
+template <bool OUT_F32>
+__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void attn_fwd_kernel(AttnParams P, int n_items, int heads) {
+  constexpr int D = 64;
   constexpr int NS = 4;          // strips in a wavefront's ring
   constexpr int SLOT = 32 * D;   // elements per strip
   constexpr int LPS = StripLoader<D>::LPS;
@@ -167,10 +169,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            if constexpr (D == 64) oacc[dt][b][v] *= alpha[b];
-            else oacc[dt][b][v] = scale_acc(oacc[dt][b][v], alpha[b]);
-          }
+          for (int v = 0; v < 16; ++v) oacc[dt][b][v] *= alpha[b];
     }
   };
   // online softmax on raw scores sc: p = exp2(scale*log2e * (s - m)) -> pb, running sums updated
@@ -203,17 +202,12 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
   };
   auto softmax = [&](const f32x16* sc) __attribute__((always_inline)) {
     const float mx[2] = {max_of(sc[0]), max_of(sc[1])};
-    if constexpr (D == 64) {
-      // Whether any lane's own maximum has grown that far is one comparison per lane, so everything else about the reference moves
-      // into a branch that a row takes in its first tiles: the vector work, not the matrix work, bounds this head dimension
-      // (1674 -> 1563 us on 65536 tokens, 14/2 heads, selection blocks of 256).  At D = 128 the branch gains nothing (1946 against
-      // 1941 us on the 32768-token batch, 7420 against 7458 on one 131072-token sequence): its waits are for the strips.
-      if (__builtin_amdgcn_ballot_w64(!((mx[0] - m[0]) * P.scale_log2e <= kLazy) | !((mx[1] - m[1]) * P.scale_log2e <= kLazy)) != 0) {
-        reference(mx);
-        rescale();
-      }
-    } else {
+    // Whether any lane's own maximum has grown that far is one comparison per lane, so everything else about the reference moves
+    // into a branch that a row takes in its first tiles: the vector work, not the matrix work, bounds this head dimension
+    // (1674 -> 1563 us on 65536 tokens, 14/2 heads, selection blocks of 256).
+    if (__builtin_amdgcn_ballot_w64(!((mx[0] - m[0]) * P.scale_log2e <= kLazy) | !((mx[1] - m[1]) * P.scale_log2e <= kLazy)) != 0) {
       reference(mx);
+      rescale();
     }
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
@@ -266,8 +260,8 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
     constexpr bool STEADY = decltype(steady_c)::value;
     constexpr int SV = (2 * PAR + 2) % NS, SK = (2 * PAR + 3) % NS;  // slots of strips 2t+2 (V_t) and 2t+3 (K_{t+2})
     // max3 in the softmax is inline asm, whose reads of the matrix instructions' results the compiler's hazard recogniser does not
-    // see (at D = 128 it copies the scores out of accumulation registers itself): 12 wait states after an 8-pass instruction
-    if constexpr (D == 64) asm volatile("s_nop 7\n\ts_nop 3" : "+v"(sa[PAR][0]), "+v"(sa[PAR][1]));
+    // see: 12 wait states after an 8-pass instruction
+    asm volatile("s_nop 7\n\ts_nop 3" : "+v"(sa[PAR][0]), "+v"(sa[PAR][1]));
     if (STEADY) wait_vmcnt<3 * LPS>(); else wait_strip(2 * t + 2);
     read_v(SV);
     scores(sa[PAR ^ 1]);
@@ -276,7 +270,6 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
     // exponentials overlap the score MFMAs; those of the other 16 may sink below it and overlap the
     // first half of the accumulation MFMAs.
     asm volatile("" : "+v"(pb[0][0]), "+v"(pb[1][0]));
-    if constexpr (D != 64) rescale();
     if (STEADY) {
       wait_vmcnt<2 * LPS>();
       read_k(SK);
@@ -320,7 +313,6 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
     for (int v = 0; v < 16; ++v)
       if (32 * wave + c_row(v, hf) > 32 * b + l32) sa[0][b][v] = -__builtin_inff();
   softmax(sa[0]);
-  if constexpr (D != 64) rescale();
   accumulate();
 
   // ---- merge the two key halves: wavefront w finalises query half w and hands the other half over
@@ -369,6 +361,371 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
             }
           }
         if (hf == 0) P.lse[(int64_t)h * P.T + tq[b]] = (mt * P.scale_log2e + __builtin_log2f(lt)) * 0.69314718055994531f;
+      }
+    }
+  }
+  timer.stop(P);
+}
+
+// ---------------------------------------------------------------------------------------------
+// The same for D = 128 and one query head, by one wavefront (NW = 1: it walks both 32-key strips of every tile, nothing is merged) or
+// two (as above; for problems of few items, see one_wavefront_per_item).
+// What bounds it: a wavefront has its SIMD to itself, so what it waits for is idle time of the matrix cores, and it issues one
+// instruction of any kind every four to five cycles (an exponential: nine), 6 beside each 32-cycle matrix instruction.  Hence a software
+// pipeline over half tiles u (32 keys x 32 queries) of two stages of 8 matrix instructions,
+//   O(u-1), S(u+1)
+// with the probabilities of u beside both; every matrix instruction is fenced with its share of the vector work, of the LDS reads and of
+// the tile loads (two at a time), whose addresses are scalar work; no branch but the one in check().  Beyond that the chip lowers its
+// clock under matrix load (a loop of these matrix instructions alone runs at 1.7 GHz of 2.4), so what saves instructions saves time
+// twice.  Per tile and SIMD, a third of the time is what the matrix instructions alone would take at 2.4 GHz.
+// The fixed part of an item (6 us: descriptor 0.7, indices 0.8, first strips and Q 2.0, output 2.7) counts half as much with one
+// wavefront per item as with two.  Against the kernel above at D = 128 (two wavefronts, a whole tile's softmax in a row) the forward of:
+// the 32768-token batch, 32/8 heads: 2.05 -> 1.67 ms (with NW = 2: 1.74), one 131072-token sequence, top 32: 7.30 -> 6.24 (6.51), the
+// 262144-token batch: 20.3 -> 18.0 (20.7), 65536 tokens whose selection is a sink and a window: 2.27 -> 1.75 (1.95).
+template <bool OUT_F32, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1))) void attn_fwd_head_kernel(AttnParams P, int n_items, int heads) {
+  constexpr int D = 128, ROW_B = D * 2, STRIP_B = 32 * ROW_B, NOP = D / 16, NV = 3;
+  constexpr float kLazy = 8.0f;
+  using Loader = QuadLoader<D>;
+  constexpr int LPS = Loader::LPS;
+  // per wavefront: K even, K odd, then V of strip t in slot 2 + t % 3.  Four wavefronts' rings fill a CU's LDS.
+  constexpr int RING_B = (2 + NV) * STRIP_B;
+  __shared__ __attribute__((aligned(1024))) char ring[NW][RING_B];
+  BusyTimer timer;
+  timer.start(P);
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+  // Workgroup id -> (position in the work list, query head of the group), see the kernel above
+  int pos = (int)(blockIdx.x / (8u * heads)) * 8 + (int)(blockIdx.x & 7u);
+  const int hh = (int)(blockIdx.x >> 3) % heads;
+  pos = claim_item(pos, n_items, P.ticket ? P.ticket + hh : nullptr, NW == 2 ? (int*)&ring[NW - 1][RING_B - 4] : nullptr);
+  if (pos < 0) return;
+  const WorkItem item = uniform_item(P.items, pos);
+  const int hs = item.hs, i = item.i, L = item.len, e0 = item.e0, ntiles = item.ntiles;
+  const int nstrips = NW == 2 ? ntiles : 2 * ntiles;  // strips of 32 keys that this wavefront walks
+  const int64_t seq0 = item.seq0;
+  const int h = P.mode == SB_SELECT_PER_QHEAD ? hs : hs * P.G + hh;
+  const int g = P.mode == SB_SELECT_PER_QHEAD ? hs / P.G : hs;
+
+  // the row's block indices: lane a holds entry jb0 + a (see the kernel above)
+  int jb0 = 0;
+  int jreg = lane < ntiles ? P.idx[e0 + lane] : 0;
+  auto refill = [&](int first) __attribute__((always_inline)) {
+    jb0 = first;
+    jreg = jb0 + lane < ntiles ? P.idx[e0 + jb0 + lane] : 0;
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), here and not at the join behind the caller's branch
+  };
+  // B operands of S^T = K Q^T: column = query 32b + lane%32, slots = d 16ks + 8hf + (0..7)
+  bf16x8 qf[2][NOP];
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    // (rows past the sequence's last repeat it and are not stored: a branch here would cost the loads' overlap)
+    const bf16* qp = P.q + ((seq0 + min(i * 64 + 32 * b + l32, L - 1)) * P.Hq + h) * D + 8 * hf;
+#pragma unroll
+    for (int ks = 0; ks < NOP; ++ks) qf[b][ks] = *(const bf16x8*)(qp + 16 * ks);
+  }
+  Loader loader;
+  loader.init(P.Hkv, lane);
+  const int pitch = P.Hkv * D * 2;
+  // this wavefront's first strip of block 0
+  const unsigned long long k0 = (unsigned long long)(P.k + ((seq0 + 32 * wave) * P.Hkv + g) * D);
+  const unsigned long long v0 = (unsigned long long)(P.v + ((seq0 + 32 * wave) * P.Hkv + g) * D);
+  const unsigned block_pitch = 64u * (unsigned)pitch;  // bytes from one key block to the next
+  const unsigned ring0 = lds_offset(&ring[wave][0]);
+  // Bytes of a strip that exist.  Only the row's last tile, the diagonal one, can end with the sequence; the missing rows arrive as zeros
+  // and are masked.  Strips past the last tile are requested like the others, with no byte in existence, so that the number of loads
+  // in flight is the same everywhere and the loop has no branch for it.
+  auto bytes_for = [&](int rows) { return rows > 0 ? (unsigned)(min(rows, 32) - 1) * pitch + D * 2 : 0u; };
+  const int last_rows = L - i * 64;
+  const unsigned full_bytes = 31u * pitch + D * 2, last_a = bytes_for(last_rows - (NW == 2 ? 32 * wave : 0)), last_b = bytes_for(last_rows - 32);
+  auto bytes_of = [&](int t) __attribute__((always_inline)) {
+    if (NW == 2) return t < nstrips - 1 ? full_bytes : t == nstrips - 1 ? last_a : 0u;
+    return t < nstrips - 2 ? full_bytes : t == nstrips - 2 ? last_a : t == nstrips - 1 ? last_b : 0u;
+  };
+  auto offset_of = [&](int t) __attribute__((always_inline)) {
+    const unsigned long long o = (unsigned long long)(unsigned)__builtin_amdgcn_readlane(jreg, (NW == 2 ? t : t >> 1) - jb0) * block_pitch;
+    return NW == 2 ? o : o + (t & 1) * 32u * (unsigned)pitch;
+  };
+  unsigned long long off = offset_of(0);  // of the newest strip requested
+  unsigned bytes = bytes_of(0);
+  loader.issue(Loader::resource(k0 + off, bytes), ring0);
+  loader.issue(Loader::resource(v0 + off, bytes), ring0 + 2 * STRIP_B);
+  // the query operands must have landed before the loop, which waits for strips by count; here the wait is for the first strips as well
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int ks = 0; ks < NOP; ++ks) asm volatile("" : "+a"(qf[b][ks]));
+  wait_vmcnt<0>();
+  off = offset_of(1);
+  bytes = bytes_of(1);
+  loader.issue(Loader::resource(k0 + off, bytes), ring0 + STRIP_B);
+  loader.issue(Loader::resource(v0 + off, bytes), ring0 + 3 * STRIP_B);
+
+  // LDS byte addresses of this lane's operand reads: K rows in the first slot, V^T in the slot of the current tile
+  unsigned row_a[NOP], tr_a[D / 32][2];
+#pragma unroll
+  for (int ks = 0; ks < NOP; ++ks) row_a[ks] = ring0 + l32 * ROW_B + 16 * ((2 * ks + hf) ^ chunk_swizzle<D>(l32));
+#pragma unroll
+  for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const int r = 8 * half + 4 * hf + ((lane & 15) >> 2), d = 32 * dt + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+      tr_a[dt][half] = ring0 + 2 * STRIP_B + r * ROW_B + 16 * ((d >> 3) ^ chunk_swizzle<D>(r)) + 2 * (d & 7);
+    }
+  auto ld_row = [&](int ks, unsigned off) __attribute__((always_inline)) {
+    return *(const bf16x8 __attribute__((address_space(3)))*)(row_a[ks] + off);
+  };
+  // A operand x = kk * 4 + dt of O^T += V^T P^T: row = d (32dt + lane%32), slots = keys 16kk + 8(e/4) + 4hf + e%4
+  auto ld_tr = [&](int x) __attribute__((always_inline)) {
+    const int kk = x / (D / 32), dt = x % (D / 32);
+    const unsigned o = kk * 16 * ROW_B;
+    bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((bf16x4 __attribute__((address_space(3)))*)(tr_a[dt][0] + o));
+    bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((bf16x4 __attribute__((address_space(3)))*)(tr_a[dt][1] + o));
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  };
+  bf16x8 ka[NOP], vt[NOP];
+  f32x16 sacc[2];
+  bf16x8 pb[2][2];
+  f32x16 oacc[D / 32][2];
+#pragma unroll
+  for (int dt = 0; dt < D / 32; ++dt) oacc[dt][0] = oacc[dt][1] = zero16();
+  // m: reference of the exponent, neg_m = -m * scale * log2 e.  Before a query's first tile neg_m is +inf, so that the first sum of
+  // probabilities fails the check below and m is set there.
+  float m[2] = {-__builtin_inff(), -__builtin_inff()}, l[2] = {0.f, 0.f}, neg_m[2] = {__builtin_inff(), __builtin_inff()};
+#pragma unroll
+  for (int k = 0; k < NOP; ++k) { ka[k] = ld_row(k, 0); vt[k] = zero_bf16x8(); }
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): K_0 has been read
+  off = offset_of(2);
+  bytes = bytes_of(2);
+  loader.issue(Loader::resource(k0 + off, bytes), ring0);
+
+  // P = exp2(S c - m c) of a half tile in steps s = 0 .. 14, one beside each matrix instruction: about one exponential a step, its
+  // argument a step before it and its conversion to bf16 a step after it, because an exponential's result is not ready for the next
+  // instruction.  The half tile's row sum, of the probabilities as rounded, i.e. of the weights that O applies, comes last and in four
+  // chains: a dot product waits for the one before it and for the matrix cores (one chain, a product a step: 834 ns a tile in a loop of
+  // these instructions alone, like this 740; without any sum 700).
+  float px[16], psum = 0.f;
+  bf16x2 py[8];
+  auto exp_step = [](int v) { return v < 9 ? v + 1 : v < 15 ? 10 + (v - 9) / 2 : 13; };
+  auto p_step = [&](int b, int s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      if (exp_step(v) == s) px[v] = fast_exp2(px[v]);
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+      if (exp_step(v) == s + 1) px[v] = __builtin_fmaf(sacc[b][v], P.scale_log2e, neg_m[b]);
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+      if (exp_step(2 * c + 1) + 1 == s) {
+        py[c][0] = (bf16)px[2 * c];
+        py[c][1] = (bf16)px[2 * c + 1];
+        pb[b][c >> 2][(2 * c) & 7] = py[c][0];
+        pb[b][c >> 2][(2 * c + 1) & 7] = py[c][1];
+      }
+    if (s == 14) {
+      float part[4];
+#pragma unroll
+      for (int c = 0; c < 8; ++c) part[c & 3] = sum2(py[c], c < 4 ? 0.f : part[c & 3]);
+      psum = (part[0] + part[1]) + (part[2] + part[3]);
+    }
+  };
+  // The reference follows the true maximum lazily: only when a lane's 16 probabilities add up to more than 2^12 (so one of them exceeds
+  // 2^8), which costs one comparison per half tile where the maximum of the scores would cost ten instructions.  The scores are still
+  // there: the reference moves, what has been summed with the old one is rescaled, and the probabilities are computed again.
+  auto check = [&](int b) __attribute__((always_inline)) {
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(psum <= 4096.f)) != 0, 0)) {
+      float mx = max3(sacc[b][0], sacc[b][1], sacc[b][2]);
+#pragma unroll
+      for (int v = 3; v < 15; v += 2) mx = max3(mx, sacc[b][v], sacc[b][v + 1]);
+      mx = max_across_halves(fmaxf(mx, sacc[b][15]));
+      const bool first = m[b] == -__builtin_inff();  // nothing accumulated yet for this query: nothing to rescale
+      const bool move = first | ((mx - m[b]) * P.scale_log2e > kLazy);
+      const float m_new = move ? fmaxf(m[b], mx) : m[b];
+      // a wavefront may have seen no unmasked key yet for a query: keep the exponent finite then
+      const float m_use = m_new == -__builtin_inff() ? 0.f : m_new;
+      const float alpha = first ? 1.0f : fast_exp2((m[b] - m_use) * P.scale_log2e);
+      neg_m[b] = -m_use * P.scale_log2e;
+      l[b] *= alpha;
+      m[b] = m_new;
+      if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+#pragma unroll
+        for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) oacc[dt][b][v] = scale_acc(oacc[dt][b][v], alpha);
+      }
+#pragma unroll
+      for (int v = 0; v < 15; ++v) p_step(b, v);
+      asm volatile("s_nop 1" ::: "memory");  // two wait states between a vector write and its use as an operand
+    }
+    l[b] += psum;
+  };
+
+#define SB_FENCE() __builtin_amdgcn_sched_barrier(0)
+  unsigned vs0 = ring0 + 2 * STRIP_B, vs1 = vs0 + STRIP_B, vs2 = vs1 + STRIP_B;  // LDS slots of V_t, V_{t+1}, V_{t+2}
+  // u = (strip t, query half B): stages O(u-1) and S(u+1) with the probabilities of u; PAR = t % 2.  DIAG: a strip of the diagonal tile,
+  // LAST: the row's last strip, nothing follows it.  With NW = 1 the last strip is the diagonal tile's keys 32 .. 63, which query half 0
+  // does not see: u = (last, 0) has no scores, no probabilities and no sum.
+  auto half_tile = [&](auto diag_c, auto last_c, auto par_c, auto b_c, int t) __attribute__((always_inline)) {
+    constexpr int B = decltype(b_c)::value, PAR = decltype(par_c)::value;
+    constexpr bool DIAG = decltype(diag_c)::value, LAST = decltype(last_c)::value;
+    constexpr bool SEEN = !(LAST && NW == 1 && B == 0);                       // u has visible keys
+    constexpr bool PREV = !(LAST && NW == 1 && B == 1);                       // u - 1 has
+    constexpr bool NEXT = LAST ? B == 0 : !(DIAG && NW == 1 && B == 1);       // u + 1 exists and has
+    const int key0 = NW == 2 ? 32 * wave : LAST ? 32 : 0;
+#pragma unroll
+    for (int k = 0; k < NOP; ++k) asm volatile("" : "+a"(qf[B ^ 1][k]));
+    // B = 0: V_{t+2} is requested, into the slot of V_{t-1}.  B = 1: K_{t+3}, into the slot of K_{t+1}, whose operands are in ka.
+    i32x4 rsrc;
+    unsigned slot = 0;
+    if constexpr (!LAST) {
+      if (B == 1) {
+        off = offset_of(t + 3);
+        bytes = bytes_of(t + 3);
+      }
+      rsrc = Loader::resource((B == 0 ? v0 : k0) + off, bytes);
+      slot = B == 0 ? vs2 : ring0 + (PAR ^ 1) * STRIP_B;
+    }
+    if (B == 0) {
+      // V_t has landed; K_{t+1}, V_{t+1} and K_{t+2} may still be on their way
+      wait_vmcnt<3 * LPS>();
+    }
+    SB_FENCE();
+#pragma unroll
+    for (int k = 0; k < NOP; ++k) {  // O(u-1); with B = 0 every operand register is refilled from V_t
+      if (PREV) mfma32_sum(oacc[k % (D / 32)][B ^ 1], vt[k], pb[B ^ 1][k / (D / 32)]);
+      if (B == 0) vt[k] = ld_tr(k);
+      if (B == 1 && !LAST) {
+        if (k == 2) __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): K_{t+1} is in ka
+        tr_a[k >> 1][k & 1] += vs1 - vs0;  // on to V of the next tile
+        if (k == NOP - 1) {
+          const unsigned vs = vs0;
+          vs0 = vs1; vs1 = vs2; vs2 = vs;
+        }
+      }
+      if (!PREV && k == 0) asm volatile("s_nop 7\n\ts_nop 7" : "+v"(sacc[B]));  // (no matrix instructions between S(u) and its first reader)
+      if (DIAG && SEEN && k == 1) {  // causal mask inside the diagonal tile
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          if (key0 + c_row(v, hf) > 32 * B + l32) sacc[B][v] = -__builtin_inff();
+      }
+      if (SEEN && k > 0) p_step(B, k - 1);
+      SB_FENCE();
+      if constexpr (!LAST) {
+        if (k == 3) loader.template issue2<0>(rsrc, slot);
+        if (k == 6) loader.template issue2<2>(rsrc, slot);
+      }
+      SB_FENCE();
+    }
+#pragma unroll
+    for (int k = 0; k < NOP; ++k) {  // S(u+1); with B = 0 every operand register is refilled from K_{t+1}
+      if (NEXT) {
+        if (k == 0) mfma32_first(sacc[B ^ 1], ka[k], qf[B ^ 1][k]);
+        else mfma32_more(sacc[B ^ 1], ka[k], qf[B ^ 1][k]);
+      }
+      if (B == 0 && !LAST) {
+        // V_t is in vt (its reads must not keep those of K_{t+1} waiting one by one)
+        if (k == 2) {
+          wait_vmcnt<2 * LPS + 4>();  // K_{t+1} has landed; V_{t+1}, K_{t+2} and half of V_{t+2} may still be on their way
+          __builtin_amdgcn_s_waitcnt(0xC07F);
+          ka[0] = ld_row(0, (PAR ^ 1) * STRIP_B);
+          ka[1] = ld_row(1, (PAR ^ 1) * STRIP_B);
+        }
+        if (k >= 2) ka[k] = ld_row(k, (PAR ^ 1) * STRIP_B);
+      }
+      if (SEEN) p_step(B, 7 + k);
+      SB_FENCE();
+      if constexpr (!LAST) {
+        if (k == 3) loader.template issue2<4>(rsrc, slot);
+        if (k == 6) loader.template issue2<6>(rsrc, slot);
+      }
+      SB_FENCE();
+    }
+    if (SEEN) check(B);
+    SB_FENCE();
+  };
+  using std::integral_constant;
+  using std::false_type;
+  using std::true_type;
+  using I0 = integral_constant<int, 0>;
+  using I1 = integral_constant<int, 1>;
+  {
+    // nothing precedes the first half tile: its O stage adds zeros
+#pragma unroll
+    for (int q = 0; q < 2; ++q) pb[1][q] = zero_bf16x8();
+#pragma unroll
+    for (int k = 0; k < NOP; ++k) {
+      if (k == 0) mfma32_first(sacc[0], ka[k], qf[0][k]);
+      else mfma32_more(sacc[0], ka[k], qf[0][k]);
+    }
+    int t = 0;
+    for (; t + 2 < nstrips; t += 2) {
+      if ((NW == 2 ? t + 4 : (t + 4) >> 1) - jb0 >= 64) refill(NW == 2 ? t : t >> 1);
+      half_tile(false_type(), false_type(), I0(), I0(), t);
+      half_tile(false_type(), false_type(), I0(), I1(), t);
+      half_tile(false_type(), false_type(), I1(), I0(), t + 1);
+      half_tile(false_type(), false_type(), I1(), I1(), t + 1);
+    }
+    if (NW == 1 || t + 2 == nstrips) {
+      using Diag = integral_constant<bool, NW == 1>;
+      half_tile(Diag(), false_type(), I0(), I0(), t);
+      half_tile(Diag(), false_type(), I0(), I1(), t);
+      ++t;
+    }
+    half_tile(true_type(), true_type(), I0(), I0(), t);
+    half_tile(true_type(), true_type(), I0(), I1(), t);
+#pragma unroll
+    for (int k = 0; k < NOP; ++k) mfma32_sum(oacc[k % (D / 32)][1], vt[k], pb[1][k / (D / 32)]);
+    // the compiler does not see these as matrix instructions: their results are read no sooner than this
+#pragma unroll
+    for (int dt = 0; dt < D / 32; ++dt) asm volatile("s_nop 7\n\ts_nop 7" : "+a"(oacc[dt][0]), "+a"(oacc[dt][1]));
+  }
+#undef SB_FENCE
+  wait_vmcnt<0>();  // the strips past the last tile
+  l[0] += __shfl_xor(l[0], 32, 64);
+  l[1] += __shfl_xor(l[1], 32, 64);
+  if constexpr (NW == 1) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const float inv = 1.0f / l[b];
+      const int64_t tq = seq0 + i * 64 + 32 * b;
+      const int rows = min(32, L - i * 64 - 32 * b);
+      store_rows<D, OUT_F32>(&ring[0][b * 2 * STRIP_B], P.o, (tq * P.Hq + h) * D, (int64_t)P.Hq * D, rows, lane,
+                             [&](int dt, int v) __attribute__((always_inline)) { return oacc[dt][b][v] * inv; });
+      if (hf == 0 && l32 < rows) P.lse[(int64_t)h * P.T + tq + l32] = (m[b] * P.scale_log2e + __builtin_log2f(l[b])) * 0.69314718055994531f;
+    }
+  } else {
+    // ---- merge the two key halves: wavefront w finalises query half w and hands the other half over
+    float* xbuf = (float*)&ring[wave][0];            // this wavefront's outgoing partial, [register][lane]
+    const float* ybuf = (const float*)&ring[wave ^ 1][0];  // the partner's
+    constexpr int NR = 16 * (D / 32);
+    static_assert((NR + 2) * 64 * sizeof(float) <= 3 * STRIP_B, "partial and output rows share the ring");
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      if (b != wave) {
+#pragma unroll
+        for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) xbuf[(16 * dt + v) * 64 + lane] = oacc[dt][b][v];
+        xbuf[NR * 64 + lane] = m[b];
+        xbuf[(NR + 1) * 64 + lane] = l[b];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      if (b == wave) {
+        const float m2 = ybuf[NR * 64 + lane], l2 = ybuf[(NR + 1) * 64 + lane];
+        const float mt = fmaxf(m[b], m2);  // finite for every existing query: its own key is never masked
+        const float w1 = fast_exp2((m[b] - mt) * P.scale_log2e), w2 = fast_exp2((m2 - mt) * P.scale_log2e);
+        const float lt = l[b] * w1 + l2 * w2;
+        const float inv = 1.0f / lt;
+        const float c1 = w1 * inv, c2 = w2 * inv;
+        const int64_t tq = seq0 + i * 64 + 32 * b;
+        const int rows = min(32, L - i * 64 - 32 * b);
+        store_rows<D, OUT_F32>(&ring[wave][3 * STRIP_B], P.o, (tq * P.Hq + h) * D, (int64_t)P.Hq * D, rows, lane, [&](int dt, int v) __attribute__((always_inline)) {
+          return oacc[dt][b][v] * c1 + ybuf[(16 * dt + v) * 64 + lane] * c2;
+        });
+        if (hf == 0 && l32 < rows) P.lse[(int64_t)h * P.T + tq + l32] = (mt * P.scale_log2e + __builtin_log2f(lt)) * 0.69314718055994531f;
       }
     }
   }
@@ -680,12 +1037,18 @@ extern "C" int sb_sparse_attn_fwd(const sb_problem* p, const void* q, const void
   } else {
     const int64_t n_wg = n_slots * heads;
     if (n_wg > 0x7fffffffll) { set_error("too many work items for one launch"); return SB_ERR_INVALID_ARG; }
-    dim3 grid((unsigned)n_wg), block(128);
-#define SB_FWD_LAUNCH(DD, FF) hipLaunchKernelGGL((attn_fwd_kernel<DD, FF>), grid, block, 0, st, P, (int)n_items, heads)
+    dim3 grid((unsigned)n_wg);
+#define SB_FWD_LAUNCH(FF) hipLaunchKernelGGL((attn_fwd_kernel<FF>), grid, dim3(128), 0, st, P, (int)n_items, heads)
     if (g.D == 128) {
-      if (P.out_f32) SB_FWD_LAUNCH(128, true); else SB_FWD_LAUNCH(128, false);
+#define SB_FWD_HEAD_LAUNCH(FF, NW) hipLaunchKernelGGL((attn_fwd_head_kernel<FF, NW>), grid, dim3(64 * NW), 0, st, P, (int)n_items, heads)
+      if (one_wavefront_per_item(g, (int64_t)g.Hq * g.NQB)) {
+        if (P.out_f32) SB_FWD_HEAD_LAUNCH(true, 1); else SB_FWD_HEAD_LAUNCH(false, 1);
+      } else {
+        if (P.out_f32) SB_FWD_HEAD_LAUNCH(true, 2); else SB_FWD_HEAD_LAUNCH(false, 2);
+      }
+#undef SB_FWD_HEAD_LAUNCH
     } else {
-      if (P.out_f32) SB_FWD_LAUNCH(64, true); else SB_FWD_LAUNCH(64, false);
+      if (P.out_f32) SB_FWD_LAUNCH(true); else SB_FWD_LAUNCH(false);
     }
 #undef SB_FWD_LAUNCH
   }

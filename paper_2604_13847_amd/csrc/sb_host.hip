@@ -86,7 +86,7 @@ int make_geo(const sb_problem* p, Geo* g) {
   g->softmax_scale = p->softmax_scale > 0.f ? p->softmax_scale : 1.0f / sqrtf((float)g->D);
   g->score_scale = p->score_scale > 0.f ? p->score_scale : g->softmax_scale;
   g->NQB = 0; g->n_max = 0; g->scores_unit = 0; g->nnz_unit = 0; g->bm_words_unit = 0; g->pairs_unit = 0;
-  g->NT = 0; g->nt_max = 0; g->nnzT_unit = 0; g->bmT_words_unit = 0;
+  g->NT = 0; g->nt_max = 0; g->nnzT_unit = 0; g->bmT_words_unit = 0; g->rowT_max = 0;
   if (g->S == 0 || g->T == 0) {
     if (g->S > 0 && p->cu_seqlens_host && p->cu_seqlens_host[g->S] != g->T) { set_error("cu_seqlens[S] != T"); return SB_ERR_INVALID_ARG; }
     if (g->S == 0 && g->T != 0) { set_error("T != 0 with S == 0"); return SB_ERR_INVALID_ARG; }
@@ -110,6 +110,8 @@ int make_geo(const sb_problem* p, Geo* g) {
       const int64_t nt = (L + 63) / 64;
       g->NT += nt;
       if (nt > g->nt_max) g->nt_max = (int)nt;
+      const int64_t row = k * g->r < nt ? k * g->r : nt;
+      if (row > g->rowT_max) g->rowT_max = (int)row;
       g->nnzT_unit += tile_entries_before(nt, k, g->r);
       g->bmT_words_unit += nt * ((nt + 31) / 32);
       // unmasked pairs: every past selected block is B x B except that the last query block may have

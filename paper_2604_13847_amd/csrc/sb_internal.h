@@ -56,6 +56,7 @@ struct Geo {
   int nt_max = 0;           // largest tile count of a sequence
   int64_t nnzT_unit = 0;    // tile-level selection entries per selection head
   int64_t bmT_words_unit = 0;  // sum_s nt_s * ceil(nt_s/32)
+  int rowT_max = 0;         // most tiles that a row keeps
 };
 // The same problem as the attention kernels see it: 64-row blocks, tile counts in the block fields.
 inline Geo tile_geo(const Geo& g) {
@@ -218,6 +219,19 @@ WsOffsets bwd_ws_offsets(const Geo& g);
 constexpr int64_t kTicketMinItems = 4096;  // shorter lists are dealt by position only
 inline bool use_tickets(int64_t n) { return n >= kTicketMinItems; }
 inline int64_t ticketed_grid(int64_t n, bool tickets) { return (n + (tickets ? (n >> 7) << 3 : 0) + 7) / 8 * 8; }
+// Is a query-major item of one query head (D = 128) one wavefront's work, or two's?  Of `items` with `avg` tiles on average and `most` at
+// most, w wavefronts each, the chip works on 1024 / w at a time; an item costs about 10 tile times of two wavefronts besides its tiles, and
+// the launch takes as long as its share of all items or as the longest item.  So one wavefront each where there are enough items, two
+// where the longest would stick out.  Forward, one / two wavefronts: 1230 items of 1 - 11 tiles 24 / 32 us, 1280 of them 27 / 33 us,
+// 1248 items of 1 - 78 tiles 127 / 114 us, 432 of 1 - 54 tiles 78 / 47 us, 592 of 1 - 11 tiles 20.1 / 20.4 us.
+inline bool one_wavefront_per_item(const Geo& tg, int64_t items) {
+  const int64_t tiles = (int64_t)tg.Hq * tg.nnz_unit, most = tg.rowT_max;
+  auto us = [&](int64_t w) {
+    const int64_t work = (10 * items + 2 * tiles / w) * w / 1024, longest = 10 + 2 * most / w;
+    return work > longest ? work : longest;
+  };
+  return us(1) <= us(2);
+}
 size_t scores_ws_bytes(const Geo& g);
 size_t coverage_ws_bytes(const Geo& g);
 
