@@ -41,7 +41,7 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(2))) void 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int pos = claim_item(blockIdx.x, P.n_items, P.ticket ? P.ticket + blockIdx.y : nullptr);
   if (pos < 0) return;
-  const WorkItem item = P.items[pos];
+  const WorkItem item = uniform_item(P.items, pos);
   const int hs = item.hs, i = item.i, L = item.len, e0 = item.e0, ntiles = item.ntiles;
   const int64_t seq0 = item.seq0;
   const int strip = wave & 1, kh = KS == 2 ? (wave >> 1) & 1 : 0;
