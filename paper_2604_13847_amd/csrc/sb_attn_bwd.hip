@@ -27,8 +27,9 @@ namespace sb {
 // K^T comes from the row-major K tile through the transposing LDS read.
 // The register budget (256) lets two wavefronts share a SIMD: one runs its exponentials while the
 // other runs matrix instructions.  Operands are fetched from LDS in sets of D/16, a set ahead of use.
-template <int D, bool OUT_F32, int KS, int MAXT>
+template <bool OUT_F32, int KS, int MAXT>
 __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(2))) void attn_bwd_dq_kernel(AttnParams P, int heads) {
+  constexpr int D = 64;
   constexpr int TILE_B = 64 * D * 2, ROW_B = D * 2, NOP = D / 16;
   constexpr int NMT = 2 / KS;  // 32-key halves of a tile this wavefront computes
   __shared__ __attribute__((aligned(1024))) bf16 tiles[2][2][64 * D];  // [buffer][K, V]
@@ -316,47 +317,48 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(2))) void 
 }
 
 // ---------------------------------------------------------------------------------------------
-// The same for one query head per item at D = 128 (per-query-head selection, or one query head per KV head): two wavefronts, split
-// by KEYS as in the forward kernel: wavefront w owns keys 32w .. 32w+31 of every tile and all 64 query rows, so an operand read
-// from LDS feeds two matrix instructions (with 32 rows per wavefront LDS reads take as long as the matrix instructions), and it
-// stages its own strips of K and V, two of each, without any barrier in the loop.  It needs the registers of a whole SIMD, so the
-// loop is a software pipeline over half tiles u (32 keys x 32 queries), stages of 8 matrix instructions:
+// The same for D = 128, one query head per workgroup, by one or two wavefronts as in the forward kernel (NW, StripWalk; see
+// one_wavefront_per_item): a wavefront owns all 64 query rows and walks 32-key strips, so that an operand read from LDS feeds two matrix
+// instructions (with 32 rows per wavefront LDS reads take as long as the matrix instructions); it stages its own strips of K and V, two
+// of each, without any barrier in the loop.  It needs the registers of a whole SIMD, so the loop is a software pipeline over half tiles u
+// (32 keys x 32 queries), stages of 8 matrix instructions:
 //   S(u), dP(u), dQ(u-1)
 // with P(u) beside dP(u) and dQ(u-1), and dS(u) beside dQ(u-1) and the next S; every matrix instruction is fenced with its share of
 // the vector work and LDS reads, and nothing waits for a result of the stage before.
-// Against the kernel above (four wavefronts, 32 rows each), the whole backward of: the 262144-token batch 62.2 -> 60.7 ms, 65536
-// tokens with 28/4 heads 13.9 -> 13.4 ms, with selection blocks of 256 10.50 -> 10.21 ms, one 131072-token sequence 19.3 -> 19.0 ms,
-// the 32768-token batch 5.94 -> 5.84 ms; 65536 tokens whose selection is a sink and a window 6.42 against 6.41 ms.  Results are bit
-// for bit the same.
 // The item's descriptor comes by scalar loads and no load is behind a branch (rows and strips that do not exist are loaded as copies of
-// the last row and as zeros), so that addresses and counts are scalar work and the loop is one block; the output goes out in whole
-// rows: 2.44 -> 2.28 ms on the 32768-token batch, 7.62 -> 7.35 on one 131072-token sequence, 2.66 -> 2.52 on the sink selection.
-template <bool OUT_F32>
-__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void attn_bwd_dq_head_kernel(AttnParams P) {
+// the last row and as zeros), so that addresses and counts are scalar work and the loop is one block; one wait for all of LDS stands
+// where nothing is due, instead of one before each use, and a strip's eight loads take 16 scalar instructions: 43 in the two-tile loop,
+// 119 before.  What bounds it now is the clock that the chip keeps under load (1.6 GHz, matrix cores busy 61 %) and, on long
+// sequences, the gathers.  With branches and half the item / without them / and one wavefront per item: the 32768-token batch, 32/8 heads
+// 2.44 / 2.23 / 2.14 ms, one 131072-token sequence, top 32: 7.62 / 7.24 / 6.49, the 262144-token batch 23.3 / 22.3 / 20.5, 65536 tokens
+// whose selection is a sink and a window 2.66 / 2.42 / 2.19.  Where the heads of a KV group share their selection, against one workgroup
+// of all of them that shares the tiles in LDS (32 rows per wavefront): the 32768-token batch 2.37 -> 2.09 ms, the 131072-token sequence
+// 6.45 -> 5.82, 65536 tokens with 28/4 heads 5.75 -> 4.54.
+template <bool OUT_F32, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1))) void attn_bwd_dq_head_kernel(AttnParams P, int heads) {
   constexpr int D = 128, ROW_B = D * 2, STRIP_B = 32 * ROW_B, NOP = D / 16;
-  using Loader = RowLoader<D>;
+  using Loader = QuadLoader<D>;
   constexpr int LPS = Loader::LPS;
   constexpr int KV = 6;  // Q, dQ and the dO operands below this one live in accumulation registers, the other dO operands do not fit there
-  __shared__ __attribute__((aligned(1024))) char ring[2][4 * STRIP_B];  // per wavefront: K even, K odd, V even, V odd tiles
+  __shared__ __attribute__((aligned(1024))) char ring[NW][4 * STRIP_B];  // per wavefront: K even, K odd, V even, V odd strips
   BusyTimer timer;
   timer.start(P);
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
-  const int pos = claim_item(blockIdx.x, P.n_items, P.ticket);
+  // workgroup id -> (position in the work list, query head of the group), see the forward kernel
+  int pos = (int)(blockIdx.x / (8u * heads)) * 8 + (int)(blockIdx.x & 7u);
+  const int hh = (int)(blockIdx.x >> 3) % heads;
+  pos = claim_item(pos, P.n_items, P.ticket ? P.ticket + hh : nullptr, NW == 2 ? (int*)&ring[NW - 1][4 * STRIP_B - 4] : nullptr);
   if (pos < 0) return;
   const WorkItem item = uniform_item(P.items, pos);
-  const int hs = item.hs, i = item.i, L = item.len, e0 = item.e0, ntiles = item.ntiles;
+  const int hs = item.hs, i = item.i, L = item.len, ntiles = item.ntiles;
   const int64_t seq0 = item.seq0;
-  const int h = hs, g = h / P.G;  // one query head per selection head
+  const int h = P.mode == SB_SELECT_PER_QHEAD ? hs : hs * P.G + hh;
+  const int g = P.mode == SB_SELECT_PER_QHEAD ? hs / P.G : hs;
 
-  // the row's block indices: lane a holds entry jb0 + a (see the forward kernel)
-  int jb0 = 0;
-  int jreg = lane < ntiles ? P.idx[e0 + lane] : 0;
-  auto refill = [&](int first) __attribute__((always_inline)) {
-    jb0 = first;
-    jreg = jb0 + lane < ntiles ? P.idx[e0 + jb0 + lane] : 0;
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), here and not at the join behind the caller's branch
-  };
+  StripWalk<D, NW> walk;
+  walk.init(item, P.idx, P.Hkv, wave, lane);
+  const int nstrips = walk.nstrips;
   // B operands: column = query 32b + lane%32, slots = d 16ks + 8hf + (0..7)
   // (rows past the sequence's last repeat it and are not stored: a branch here would cost the loads' overlap)
   bf16x8 qf[2][NOP], dof[2][NOP];
@@ -382,21 +384,14 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void a
   }
   Loader loader;
   loader.init(P.Hkv, lane);
-  const int pitch = P.Hkv * D * 2;
-  const char* const k0 = (const char*)(P.k + ((seq0 + 32 * wave) * P.Hkv + g) * D);  // this wavefront's strip of block 0
-  const char* const v0 = (const char*)(P.v + ((seq0 + 32 * wave) * P.Hkv + g) * D);
-  const unsigned block_pitch = 64u * (unsigned)pitch;  // bytes from one key block to the next
+  // this wavefront's first strip of block 0
+  const unsigned long long k0 = (unsigned long long)(P.k + ((seq0 + 32 * wave) * P.Hkv + g) * D);
+  const unsigned long long v0 = (unsigned long long)(P.v + ((seq0 + 32 * wave) * P.Hkv + g) * D);
   const unsigned ring0 = lds_offset(&ring[wave][0]);
-  const int Lw = L - 32 * wave;
-  // strip of tile t, rows past the end of the sequence as zeros (they are masked: only the diagonal tile can have such rows), and past the
-  // row's last tile nothing but zeros: those strips are requested like the others, so that the loop has no branch for them
-  auto strip_of = [&](bool is_v, int t) __attribute__((always_inline)) {
-    const int j = __builtin_amdgcn_readlane(jreg, t - jb0);
-    return Loader::strip(ring0 + ((is_v ? 2 : 0) + (t & 1)) * STRIP_B, (is_v ? v0 : k0) + (unsigned long long)(unsigned)j * block_pitch,
-                         t < ntiles ? Lw - j * 64 : 0, pitch);
-  };
-  loader.issue(strip_of(true, 0));
-  loader.issue(strip_of(false, 0));
+  unsigned long long off = walk.offset_of(0);  // of the newest strip requested
+  unsigned bytes = walk.bytes_of(0);
+  loader.issue(Loader::resource(v0 + off, bytes), ring0 + 2 * STRIP_B);
+  loader.issue(Loader::resource(k0 + off, bytes), ring0);
   // the rows' operands must have landed before the loop, which waits for strips by count; here the wait is for the first strips as well
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
@@ -418,10 +413,11 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void a
     }
     asm volatile("" : "+v"(lse2[b]), "+v"(dr[b]));
   }
-  asm volatile("" : "+v"(jreg));
   wait_vmcnt<0>();
-  loader.issue(strip_of(true, 1));
-  loader.issue(strip_of(false, 1));
+  off = walk.offset_of(1);
+  bytes = walk.bytes_of(1);
+  loader.issue(Loader::resource(v0 + off, bytes), ring0 + 3 * STRIP_B);
+  loader.issue(Loader::resource(k0 + off, bytes), ring0 + STRIP_B);
 
   // LDS byte addresses of this lane's operand reads in the wavefront's first slot
   unsigned row_a[NOP], tr_a[D / 32][2];
@@ -456,10 +452,10 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void a
 #pragma unroll
   for (int k = 0; k < NOP; ++k) { ka[k] = ld_row(k, 0); va[k] = ld_row(k, 2 * STRIP_B); }
 
-  // P = exp2(S c - lse2) of register v of query half b, in place; keys above the diagonal 0
-  auto prob = [&](auto diag_c, int b, int v) __attribute__((always_inline)) {
+  // P = exp2(S c - lse2) of register v of query half b, in place; in a strip of the diagonal tile (first key: key0) 0 above the diagonal
+  auto prob = [&](auto diag_c, int key0, int b, int v) __attribute__((always_inline)) {
     float pv = fast_exp2(__builtin_fmaf(sacc[b][v], P.scale_log2e, -lse2[b]));
-    if (decltype(diag_c)::value && 32 * wave + c_row(v, hf) > 32 * b + l32) pv = 0.f;
+    if (decltype(diag_c)::value && key0 + c_row(v, hf) > 32 * b + l32) pv = 0.f;
     sacc[b][v] = pv;
   };
   float ds_even;
@@ -471,93 +467,125 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void a
   };
   // Dr of a row that keeps only its own block comes from sum_j P_j dP_j / sum_j P_j, as in the kernel above
   if (ntiles == 1) {
-    __shared__ float drx[2][2][64];  // [wavefront][query half][sums, normalisers]
-    float num[2], den[2];
+    __shared__ float drx[NW][2][64];  // [wavefront][query half][sums, normalisers]
+    float num[2] = {0.f, 0.f}, den[2] = {0.f, 0.f};
+    if (NW == 1) wait_vmcnt<0>();
+#pragma unroll
+    for (int strip = 0; strip < 3 - NW; ++strip) {  // this wavefront's strips of the row's only tile
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        f32x16 s_ = zero16(), dp = zero16();
+#pragma unroll
+        for (int k = 0; k < NOP; ++k) s_ = mfma32(strip == 0 ? ka[k] : ld_row(k, STRIP_B), qf[b][k], s_);
+#pragma unroll
+        for (int k = 0; k < NOP; ++k) dp = mfma32(strip == 0 ? va[k] : ld_row(k, 3 * STRIP_B), dof[b][k], dp);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const bool masked = 32 * (wave + strip) + c_row(v, hf) > 32 * b + l32;
+          const float pv = masked ? 0.f : fast_exp2(__builtin_fmaf(s_[v], P.scale_log2e, -lse2[b]));
+          num[b] = __builtin_fmaf(pv, dp[v], num[b]);
+          den[b] += pv;
+        }
+      }
+    }
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-      f32x16 s_ = zero16(), dp = zero16();
-#pragma unroll
-      for (int k = 0; k < NOP; ++k) s_ = mfma32(ka[k], qf[b][k], s_);
-#pragma unroll
-      for (int k = 0; k < NOP; ++k) dp = mfma32(va[k], dof[b][k], dp);
-      num[b] = den[b] = 0.f;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const bool masked = 32 * wave + c_row(v, hf) > 32 * b + l32;
-        const float pv = masked ? 0.f : fast_exp2(__builtin_fmaf(s_[v], P.scale_log2e, -lse2[b]));
-        num[b] = __builtin_fmaf(pv, dp[v], num[b]);
-        den[b] += pv;
-      }
       num[b] += __shfl_xor(num[b], 32, 64);
       den[b] += __shfl_xor(den[b], 32, 64);
-      if (hf == 0) { drx[wave][b][l32] = num[b]; drx[wave][b][32 + l32] = den[b]; }
+      if (NW == 2 && hf == 0) { drx[wave][b][l32] = num[b]; drx[wave][b][32 + l32] = den[b]; }
     }
-    __syncthreads();
+    if constexpr (NW == 2) {
+      __syncthreads();
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      num[b] += drx[wave ^ 1][b][l32];
-      den[b] += drx[wave ^ 1][b][32 + l32];
-      if (den[b] > 0.f) dr[b] = num[b] / den[b];
+      for (int b = 0; b < 2; ++b) {
+        num[b] += drx[wave ^ 1][b][l32];
+        den[b] += drx[wave ^ 1][b][32 + l32];
+      }
     }
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+      if (den[b] > 0.f) dr[b] = num[b] / den[b];
   }
 
 #define SB_FENCE() __builtin_amdgcn_sched_barrier(0)
-  // half tile u = (tile t, query half B); PAR = t % 2, known at compile time but for the diagonal tile
-  auto half_tile = [&](auto diag_c, auto PAR, auto b_c, int t) __attribute__((always_inline)) {
+  // half tile u = (strip t, query half B); PAR = t % 2, known at compile time but for the last strip with NW = 2.  DIAG, LAST, and what the
+  // last strip's query half 0 does not see with NW = 1: as in the forward kernel.
+  auto half_tile = [&](auto diag_c, auto last_c, auto PAR, auto b_c, int t) __attribute__((always_inline)) {
     constexpr int B = decltype(b_c)::value;
-    constexpr bool LAST = decltype(diag_c)::value;  // the diagonal tile is the row's last: nothing follows it
+    constexpr bool LAST = decltype(last_c)::value;
+    constexpr bool SEEN = !(LAST && NW == 1 && B == 0);  // u has visible keys
+    constexpr bool PREV = !(LAST && NW == 1 && B == 1);  // u - 1 has
+    const int key0 = NW == 2 ? 32 * wave : LAST ? 32 : 0;
 #pragma unroll
     for (int k = 0; k < NOP; ++k) {
       asm volatile("" : "+a"(qf[B][k]));
       if (k < KV) asm volatile("" : "+a"(dof[B][k]));
       else asm volatile("" : "+v"(dof[B][k]));
     }
-    Strip nxt{};  // strips of tile t + 2 follow: V with B = 0, K with B = 1
-    if constexpr (!LAST) nxt = strip_of(B == 0, t + 2);
+    // strips t + 2 follow: V with B = 0, into the slot of V_t, whose operands are in va; K with B = 1, into the slot of K_t, likewise in kt
+    i32x4 rsrc;
+    unsigned slot = 0;
+    if constexpr (!LAST) {
+      if (B == 0) {
+        off = walk.offset_of(t + 2);
+        bytes = walk.bytes_of(t + 2);
+      }
+      rsrc = Loader::resource((B == 0 ? v0 : k0) + off, bytes);
+      slot = ring0 + ((B == 0 ? 2 : 0) + PAR) * STRIP_B;
+    }
+    SB_FENCE();
+    // One wait for all of LDS where nothing is due soon, instead of one before each use.  B = 0: K_t and V_t are in ka and va, and slot
+    // V_t is free.
+    if (B == 0) __builtin_amdgcn_s_waitcnt(0xC07F);
     SB_FENCE();
 #pragma unroll
     for (int k = 0; k < NOP; ++k) {
-      if (k == 0) mfma32_first(sacc[B], ka[k], qf[B][k]);
-      else mfma32_more(sacc[B], ka[k], qf[B][k]);
-      dscore(B ^ 1, 8 + k);  // (before the row's first half tile: zeros)
+      if (SEEN) {
+        if (k == 0) mfma32_first(sacc[B], ka[k], qf[B][k]);
+        else mfma32_more(sacc[B], ka[k], qf[B][k]);
+      }
+      if (PREV) dscore(B ^ 1, 8 + k);  // (before the row's first half tile: zeros)
       if (B == 1 && !LAST) {
-        // before the operands of tile t + 1 are fetched its strips must have landed (V_{t+2} may still be on its way)
-        if (k == 0) wait_vmcnt<LPS>();
-        ka[k] = ld_row(k, (PAR ^ 1) * STRIP_B);
-      }
-      SB_FENCE();
-      // the slot of V_t (its last reads belong to tile t - 1) or, with B = 1, of K_t (before the three reads just issued; LDS reads
-      // complete in order) may be refilled
-      if constexpr (!LAST) {
-        if (k == 2) {
-          asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(B == 1 ? 3 : 0) : "memory");
-          loader.template issue2<0>(nxt);
+        if (k == 1) {
+          __builtin_amdgcn_s_waitcnt(0xC07F);  // K_t is in kt, its slot is free
+          wait_vmcnt<LPS>();                   // strips t + 1 have landed (V_{t+2} may still be on its way)
+          ka[0] = ld_row(0, (PAR ^ 1) * STRIP_B);
         }
-        if (k == 5) loader.template issue2<2>(nxt);
+        if (k >= 1) ka[k] = ld_row(k, (PAR ^ 1) * STRIP_B);
       }
-      SB_FENCE();
-    }
-#pragma unroll
-    for (int k = 0; k < NOP; ++k) {
-      if (k == 0) mfma32_first(dpacc, va[k], dof[B][k]);
-      else if (k < KV) mfma32_more(dpacc, va[k], dof[B][k]);
-      else mfma32_more_v(dpacc, va[k], dof[B][k]);
-      if (B == 1 && !LAST) va[k] = ld_row(k, (2 + (PAR ^ 1)) * STRIP_B);
-      if (k > 1) prob(diag_c, B, k - 2);
       SB_FENCE();
       if constexpr (!LAST) {
-        if (k == 1) loader.template issue2<4>(nxt);
-        if (k == 5) loader.template issue2<6>(nxt);
+        if (k == 2) loader.template issue2<0>(rsrc, slot);
+        if (k == 5) loader.template issue2<2>(rsrc, slot);
       }
       SB_FENCE();
     }
 #pragma unroll
     for (int k = 0; k < NOP; ++k) {
-      mfma32_sum(dqacc[k % (D / 32)][B ^ 1], kt[k], dsb[B ^ 1][k / (D / 32)]);
+      if (SEEN) {
+        if (k == 0) mfma32_first(dpacc, va[k], dof[B][k]);
+        else if (k < KV) mfma32_more(dpacc, va[k], dof[B][k]);
+        else mfma32_more_v(dpacc, va[k], dof[B][k]);
+      }
+      if (B == 1 && !LAST) va[k] = ld_row(k, (2 + (PAR ^ 1)) * STRIP_B);
+      if (SEEN && k > 1) prob(diag_c, key0, B, k - 2);
+      SB_FENCE();
+      if constexpr (!LAST) {
+        if (k == 1) loader.template issue2<4>(rsrc, slot);
+        if (k == 5) loader.template issue2<6>(rsrc, slot);
+      }
+      SB_FENCE();
+    }
+    if (!PREV) asm volatile("s_nop 7\n\ts_nop 7" : "+v"(dpacc));  // (no matrix instructions between dP(u) and its first reader)
+#pragma unroll
+    for (int k = 0; k < NOP; ++k) {
+      if (PREV) mfma32_sum(dqacc[k % (D / 32)][B ^ 1], kt[k], dsb[B ^ 1][k / (D / 32)]);
       if (B == 0) kt[k] = ld_tr(k, PAR * STRIP_B);
-      if (k < 2) { prob(diag_c, B, 6 + 2 * k); prob(diag_c, B, 7 + 2 * k); }
-      else prob(diag_c, B, 8 + k);
-      if (k >= 4) { dscore(B, 2 * (k - 4)); dscore(B, 2 * (k - 4) + 1); }
+      if (SEEN) {
+        if (k < 2) { prob(diag_c, key0, B, 6 + 2 * k); prob(diag_c, key0, B, 7 + 2 * k); }
+        else prob(diag_c, key0, B, 8 + k);
+        if (k >= 4) { dscore(B, 2 * (k - 4)); dscore(B, 2 * (k - 4) + 1); }
+      }
       SB_FENCE();
     }
     // (the conversions stay where they are: the compiler would carry the floats over the loop's edge and convert them one by one)
@@ -575,20 +603,26 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void a
 #pragma unroll
     for (int q = 0; q < 2; ++q) dsb[1][q] = zero_bf16x8();
     int t = 0;
-    for (; t + 2 < ntiles; t += 2) {
-      if (t + 3 - jb0 >= 64) refill(t);
-      half_tile(false_type(), I0(), I0(), t);
-      half_tile(false_type(), I0(), I1(), t);
-      half_tile(false_type(), I1(), I0(), t + 1);
-      half_tile(false_type(), I1(), I1(), t + 1);
+    for (; t + 2 < nstrips; t += 2) {
+      walk.window(t, 3, lane);
+      half_tile(false_type(), false_type(), I0(), I0(), t);
+      half_tile(false_type(), false_type(), I0(), I1(), t);
+      half_tile(false_type(), false_type(), I1(), I0(), t + 1);
+      half_tile(false_type(), false_type(), I1(), I1(), t + 1);
     }
-    if (t + 2 == ntiles) {
-      half_tile(false_type(), I0(), I0(), t);
-      half_tile(false_type(), I0(), I1(), t);
+    if (NW == 1 || t + 2 == nstrips) {
+      using Diag = integral_constant<bool, NW == 1>;
+      half_tile(Diag(), false_type(), I0(), I0(), t);
+      half_tile(Diag(), false_type(), I0(), I1(), t);
       ++t;
     }
-    half_tile(true_type(), t & 1, I0(), t);
-    half_tile(true_type(), t & 1, I1(), t);
+    if constexpr (NW == 1) {
+      half_tile(true_type(), true_type(), I1(), I0(), t);
+      half_tile(true_type(), true_type(), I1(), I1(), t);
+    } else {
+      half_tile(true_type(), true_type(), t & 1, I0(), t);
+      half_tile(true_type(), true_type(), t & 1, I1(), t);
+    }
 #pragma unroll
     for (int v = 8; v < 16; ++v) dscore(1, v);
     asm volatile("s_nop 3" : "+v"(dsb[1][0]), "+v"(dsb[1][1]));  // two wait states between a vector write and its use as an operand
@@ -600,28 +634,32 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1))) void a
   }
 #undef SB_FENCE
   wait_vmcnt<0>();  // the strips past the last tile
-  // the two key halves are added: wavefront w finishes query half w and hands the other half over
+  // with two wavefronts the two key halves are added: wavefront w finishes query half w and hands the other half over
   float* xbuf = (float*)&ring[wave][0];
-  const float* ybuf = (const float*)&ring[wave ^ 1][0];
+  const float* ybuf = (const float*)&ring[NW == 2 ? wave ^ 1 : 0][0];
+  if constexpr (NW == 2) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+      if (b != wave) {
+#pragma unroll
+        for (int dt = 0; dt < D / 32; ++dt)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) xbuf[(16 * dt + v) * 64 + lane] = dqacc[dt][b][v];
+      }
+    __syncthreads();
+  }
 #pragma unroll
   for (int b = 0; b < 2; ++b)
-    if (b != wave) {
-#pragma unroll
-      for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) xbuf[(16 * dt + v) * 64 + lane] = dqacc[dt][b][v];
-    }
-  __syncthreads();
-#pragma unroll
-  for (int b = 0; b < 2; ++b)
-    if (b == wave) {
+    if (NW == 1 || b == wave) {
       if (qvalid[b] && hf == 0) {
         P.drow[(int64_t)h * P.T + tq[b]] = dr[b];
         P.lse2[(int64_t)h * P.T + tq[b]] = lse2[b];
       }
       const int64_t first = seq0 + i * 64 + 32 * b;
-      store_rows<D, OUT_F32>(&ring[wave][2 * STRIP_B], P.dq, (first * P.Hq + h) * D, (int64_t)P.Hq * D, min(32, L - i * 64 - 32 * b), lane,
-                             [&](int dt, int v) __attribute__((always_inline)) { return (dqacc[dt][b][v] + ybuf[(16 * dt + v) * 64 + lane]) * P.scale; });
+      store_rows<D, OUT_F32>(&ring[wave][(NW == 1 ? 2 * b : 2) * STRIP_B], P.dq, (first * P.Hq + h) * D, (int64_t)P.Hq * D, min(32, L - i * 64 - 32 * b), lane,
+                             [&](int dt, int v) __attribute__((always_inline)) {
+                               return (NW == 1 ? dqacc[dt][b][v] : dqacc[dt][b][v] + ybuf[(16 * dt + v) * 64 + lane]) * P.scale;
+                             });
     }
   timer.stop(P);
 }
@@ -1154,14 +1192,19 @@ static int launch_bwd(const Geo& g, const AttnParams& P, hipStream_t st) {
   // query-major dQ: one workgroup per (item, part of the item's query heads); 2 * KS wavefronts per head
   const int heads = g.mode == SB_SELECT_PER_QHEAD ? 1 : g.G;
   const int parts = (heads + 3) / 4, hpp = (heads + parts - 1) / parts;  // heads per workgroup: 1..4
-  dim3 grid((unsigned)ticketed_grid(P.n_items, P.ticket != nullptr), (unsigned)parts);
+  const int64_t n_slots = ticketed_grid(P.n_items, P.ticket != nullptr);
   KernelTimer kt(K_BWD_DQ, st);
-  if (hpp == 1) {  // figures at attn_bwd_dq_head_kernel, which is for D = 128: D = 64 is better served by two wavefronts per SIMD (see dK/dV)
-    if constexpr (D == 128) hipLaunchKernelGGL((attn_bwd_dq_head_kernel<F32>), grid, dim3(128), 0, st, P);
-    else hipLaunchKernelGGL((attn_bwd_dq_kernel<D, F32, 2, 256>), grid, dim3(256), 0, st, P, heads);
+  if constexpr (D == 128) {  // figures at attn_bwd_dq_head_kernel; D = 64 is better served by two wavefronts per SIMD (see dK/dV)
+    if (n_slots * heads > 0x7fffffffll) { set_error("too many work items for one launch"); return SB_ERR_INVALID_ARG; }
+    const dim3 grid((unsigned)(n_slots * heads));
+    if (one_wavefront_per_item(g, (int64_t)g.Hq * g.NQB, 24)) hipLaunchKernelGGL((attn_bwd_dq_head_kernel<F32, 1>), grid, dim3(64), 0, st, P, heads);
+    else hipLaunchKernelGGL((attn_bwd_dq_head_kernel<F32, 2>), grid, dim3(128), 0, st, P, heads);
+  } else {
+    const dim3 grid((unsigned)n_slots, (unsigned)parts);
+    if (hpp == 1) hipLaunchKernelGGL((attn_bwd_dq_kernel<F32, 2, 256>), grid, dim3(256), 0, st, P, heads);
+    else if (hpp == 2) hipLaunchKernelGGL((attn_bwd_dq_kernel<F32, 2, 512>), grid, dim3(512), 0, st, P, heads);
+    else hipLaunchKernelGGL((attn_bwd_dq_kernel<F32, 1, 512>), grid, dim3(128 * hpp), 0, st, P, heads);
   }
-  else if (hpp == 2) hipLaunchKernelGGL((attn_bwd_dq_kernel<D, F32, 2, 512>), grid, dim3(512), 0, st, P, heads);
-  else hipLaunchKernelGGL((attn_bwd_dq_kernel<D, F32, 1, 512>), grid, dim3(128 * hpp), 0, st, P, heads);
   SB_LAUNCH_CHECK("attn_bwd_dq_kernel");
   return SB_OK;
 }

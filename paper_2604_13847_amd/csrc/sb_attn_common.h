@@ -379,6 +379,52 @@ struct QuadLoader {
     if constexpr (LPS > 4) { issue2<4>(rsrc, slot); issue2<6>(rsrc, slot); }
   }
 };
+// The 32-key strips that a wavefront of a query-major item walks: with two wavefronts per item (NW = 2) wavefront w takes strip w of every
+// tile the row keeps, with one it takes both, one after the other.
+template <int D, int NW>
+struct StripWalk {
+  const int32_t* idx;  // the row's block indices
+  int ntiles, nstrips;
+  // Lane a holds index jb0 + a; refilled every ~64 tiles, which waits for all loads in flight.
+  int jb0, jreg;
+  unsigned block_pitch, half_pitch;     // bytes from one key block to the next, from one strip to the next
+  // Bytes of a strip that exist.  Only the row's last tile, the diagonal one, can end with the sequence; the missing rows arrive as zeros
+  // and are masked.  Strips past the last tile are requested like the others, with no byte in existence, so that the number of loads
+  // in flight is the same everywhere and a loop has no branch for it.
+  unsigned full_bytes, last_a, last_b;  // of any other strip, of the last tile's first (or this wavefront's) strip, of its second
+  __device__ inline void init(const WorkItem& item, const int32_t* all_idx, int Hkv, int wave, int lane) {
+    idx = all_idx + item.e0;
+    ntiles = item.ntiles;
+    nstrips = NW == 2 ? ntiles : 2 * ntiles;
+    jb0 = 0;
+    jreg = lane < ntiles ? idx[lane] : 0;
+    const unsigned pitch = (unsigned)Hkv * D * 2;
+    block_pitch = 64u * pitch;
+    half_pitch = 32u * pitch;
+    auto bytes = [&](int rows) { return rows > 0 ? (unsigned)(min(rows, 32) - 1) * pitch + D * 2 : 0u; };
+    const int rows = item.len - item.i * 64;
+    full_bytes = 31u * pitch + D * 2;
+    last_a = bytes(rows - (NW == 2 ? 32 * wave : 0));
+    last_b = bytes(rows - 32);
+  }
+  // strips t, t + 1, ... t + ahead are about to be asked for
+  __device__ inline void window(int t, int ahead, int lane) {
+    const int tile = NW == 2 ? t : t >> 1, end = NW == 2 ? t + ahead : (t + ahead) >> 1;
+    if (end - jb0 < 64) return;
+    jb0 = tile;
+    jreg = jb0 + lane < ntiles ? idx[jb0 + lane] : 0;
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), here and not at the join behind this branch, where it would drain the loads in flight every time
+  }
+  __device__ inline unsigned bytes_of(int t) const {
+    if (NW == 2) return t < nstrips - 1 ? full_bytes : t == nstrips - 1 ? last_a : 0u;
+    return t < nstrips - 2 ? full_bytes : t == nstrips - 2 ? last_a : t == nstrips - 1 ? last_b : 0u;
+  }
+  // from the wavefront's strip of the sequence's first block
+  __device__ inline unsigned long long offset_of(int t) const {
+    const unsigned long long o = (unsigned long long)(unsigned)__builtin_amdgcn_readlane(jreg, (NW == 2 ? t : t >> 1) - jb0) * block_pitch;
+    return NW == 2 ? o : o + (t & 1) * half_pitch;
+  }
+};
 // the first `bytes` of 64 consecutive floats from `src` (both wave-uniform) to LDS, the rest as zeros
 __device__ inline void load_floats(unsigned slot, unsigned long long src, unsigned bytes, int lane) {
   asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 s[84:85], %2\n\ts_mov_b32 s86, %3\n\ts_mov_b32 s87, 0x20000\n\t"

@@ -401,20 +401,14 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1))) vo
   pos = claim_item(pos, n_items, P.ticket ? P.ticket + hh : nullptr, NW == 2 ? (int*)&ring[NW - 1][RING_B - 4] : nullptr);
   if (pos < 0) return;
   const WorkItem item = uniform_item(P.items, pos);
-  const int hs = item.hs, i = item.i, L = item.len, e0 = item.e0, ntiles = item.ntiles;
-  const int nstrips = NW == 2 ? ntiles : 2 * ntiles;  // strips of 32 keys that this wavefront walks
+  const int hs = item.hs, i = item.i, L = item.len;
   const int64_t seq0 = item.seq0;
   const int h = P.mode == SB_SELECT_PER_QHEAD ? hs : hs * P.G + hh;
   const int g = P.mode == SB_SELECT_PER_QHEAD ? hs / P.G : hs;
 
-  // the row's block indices: lane a holds entry jb0 + a (see the kernel above)
-  int jb0 = 0;
-  int jreg = lane < ntiles ? P.idx[e0 + lane] : 0;
-  auto refill = [&](int first) __attribute__((always_inline)) {
-    jb0 = first;
-    jreg = jb0 + lane < ntiles ? P.idx[e0 + jb0 + lane] : 0;
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), here and not at the join behind the caller's branch
-  };
+  StripWalk<D, NW> walk;
+  walk.init(item, P.idx, P.Hkv, wave, lane);
+  const int nstrips = walk.nstrips;
   // B operands of S^T = K Q^T: column = query 32b + lane%32, slots = d 16ks + 8hf + (0..7)
   bf16x8 qf[2][NOP];
 #pragma unroll
@@ -426,28 +420,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1))) vo
   }
   Loader loader;
   loader.init(P.Hkv, lane);
-  const int pitch = P.Hkv * D * 2;
   // this wavefront's first strip of block 0
   const unsigned long long k0 = (unsigned long long)(P.k + ((seq0 + 32 * wave) * P.Hkv + g) * D);
   const unsigned long long v0 = (unsigned long long)(P.v + ((seq0 + 32 * wave) * P.Hkv + g) * D);
-  const unsigned block_pitch = 64u * (unsigned)pitch;  // bytes from one key block to the next
   const unsigned ring0 = lds_offset(&ring[wave][0]);
-  // Bytes of a strip that exist.  Only the row's last tile, the diagonal one, can end with the sequence; the missing rows arrive as zeros
-  // and are masked.  Strips past the last tile are requested like the others, with no byte in existence, so that the number of loads
-  // in flight is the same everywhere and the loop has no branch for it.
-  auto bytes_for = [&](int rows) { return rows > 0 ? (unsigned)(min(rows, 32) - 1) * pitch + D * 2 : 0u; };
-  const int last_rows = L - i * 64;
-  const unsigned full_bytes = 31u * pitch + D * 2, last_a = bytes_for(last_rows - (NW == 2 ? 32 * wave : 0)), last_b = bytes_for(last_rows - 32);
-  auto bytes_of = [&](int t) __attribute__((always_inline)) {
-    if (NW == 2) return t < nstrips - 1 ? full_bytes : t == nstrips - 1 ? last_a : 0u;
-    return t < nstrips - 2 ? full_bytes : t == nstrips - 2 ? last_a : t == nstrips - 1 ? last_b : 0u;
-  };
-  auto offset_of = [&](int t) __attribute__((always_inline)) {
-    const unsigned long long o = (unsigned long long)(unsigned)__builtin_amdgcn_readlane(jreg, (NW == 2 ? t : t >> 1) - jb0) * block_pitch;
-    return NW == 2 ? o : o + (t & 1) * 32u * (unsigned)pitch;
-  };
-  unsigned long long off = offset_of(0);  // of the newest strip requested
-  unsigned bytes = bytes_of(0);
+  unsigned long long off = walk.offset_of(0);  // of the newest strip requested
+  unsigned bytes = walk.bytes_of(0);
   loader.issue(Loader::resource(k0 + off, bytes), ring0);
   loader.issue(Loader::resource(v0 + off, bytes), ring0 + 2 * STRIP_B);
   // the query operands must have landed before the loop, which waits for strips by count; here the wait is for the first strips as well
@@ -456,8 +434,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1))) vo
 #pragma unroll
     for (int ks = 0; ks < NOP; ++ks) asm volatile("" : "+a"(qf[b][ks]));
   wait_vmcnt<0>();
-  off = offset_of(1);
-  bytes = bytes_of(1);
+  off = walk.offset_of(1);
+  bytes = walk.bytes_of(1);
   loader.issue(Loader::resource(k0 + off, bytes), ring0 + STRIP_B);
   loader.issue(Loader::resource(v0 + off, bytes), ring0 + 3 * STRIP_B);
 
@@ -495,8 +473,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1))) vo
 #pragma unroll
   for (int k = 0; k < NOP; ++k) { ka[k] = ld_row(k, 0); vt[k] = zero_bf16x8(); }
   __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): K_0 has been read
-  off = offset_of(2);
-  bytes = bytes_of(2);
+  off = walk.offset_of(2);
+  bytes = walk.bytes_of(2);
   loader.issue(Loader::resource(k0 + off, bytes), ring0);
 
   // P = exp2(S c - m c) of a half tile in steps s = 0 .. 14, one beside each matrix instruction: about one exponential a step, its
@@ -579,8 +557,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1))) vo
     unsigned slot = 0;
     if constexpr (!LAST) {
       if (B == 1) {
-        off = offset_of(t + 3);
-        bytes = bytes_of(t + 3);
+        off = walk.offset_of(t + 3);
+        bytes = walk.bytes_of(t + 3);
       }
       rsrc = Loader::resource((B == 0 ? v0 : k0) + off, bytes);
       slot = B == 0 ? vs2 : ring0 + (PAR ^ 1) * STRIP_B;
@@ -659,7 +637,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1))) vo
     }
     int t = 0;
     for (; t + 2 < nstrips; t += 2) {
-      if ((NW == 2 ? t + 4 : (t + 4) >> 1) - jb0 >= 64) refill(NW == 2 ? t : t >> 1);
+      walk.window(t, 4, lane);
       half_tile(false_type(), false_type(), I0(), I0(), t);
       half_tile(false_type(), false_type(), I0(), I1(), t);
       half_tile(false_type(), false_type(), I1(), I0(), t + 1);
@@ -1042,7 +1020,7 @@ extern "C" int sb_sparse_attn_fwd(const sb_problem* p, const void* q, const void
 #define SB_FWD_LAUNCH(FF) hipLaunchKernelGGL((attn_fwd_kernel<FF>), grid, dim3(128), 0, st, P, (int)n_items, heads)
     if (g.D == 128) {
 #define SB_FWD_HEAD_LAUNCH(FF, NW) hipLaunchKernelGGL((attn_fwd_head_kernel<FF, NW>), grid, dim3(64 * NW), 0, st, P, (int)n_items, heads)
-      if (one_wavefront_per_item(g, (int64_t)g.Hq * g.NQB)) {
+      if (one_wavefront_per_item(g, (int64_t)g.Hq * g.NQB, 16)) {
         if (P.out_f32) SB_FWD_HEAD_LAUNCH(true, 1); else SB_FWD_HEAD_LAUNCH(false, 1);
       } else {
         if (P.out_f32) SB_FWD_HEAD_LAUNCH(true, 2); else SB_FWD_HEAD_LAUNCH(false, 2);
