@@ -715,10 +715,10 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
   timer.start(P);
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
-  const int64_t col = item.col;  // g * NQB + global block index
+  // item.col: g * NQB + global block index
   const int wlo = item.wrange & 0xffff, whi = item.wrange >> 16;  // bitmap words of the column this item covers
-  const int g = (int)(col / P.NQB);
-  const int qbj = (int)(col - (int64_t)g * P.NQB);
+  const int g = (int)((unsigned)item.col / (unsigned)P.NQB);
+  const int qbj = item.col - g * (int)P.NQB;
   const int s = P.qb_seq[qbj];
   const int j = qbj - P.qb_off[s];
   const int n = P.qb_off[s + 1] - P.qb_off[s];
@@ -776,28 +776,37 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
   // A half tile is 32 query rows: wavefront 0 loads its Q rows, wavefront 1 its dO rows, and each 32 of the rows' statistics
   // (wavefront 0 the LSE, wavefront 1 Dr).  Rows past the end of the sequence arrive as zeros: their P is 1 and their dS 0,
   // and both meet zero rows of dO and Q.
-  using Loader = RowLoader<D>;
+  using Loader = QuadLoader<D>;
   Loader loader;
   loader.init(P.Hq, lane);
   constexpr int kLoadsPerHalf = Loader::LPS + 1;  // asynchronous loads one wavefront issues per half tile
-  const int pitch = P.Hq * D * 2;
-  const char* const src0 = (const char*)((wave == 0 ? P.q : P.d_o) + seq0 * P.Hq * D);
-  const float* const stat0 = (wave == 0 ? P.lse2 : P.drow) + seq0;
+  const unsigned pitch = (unsigned)P.Hq * D * 2;
+  const unsigned long long src0 = (unsigned long long)((wave == 0 ? P.q : P.d_o) + (seq0 * P.Hq + (int64_t)g * P.G) * D);
+  const unsigned long long stat0 = (unsigned long long)((wave == 0 ? P.lse2 : P.drow) + (int64_t)g * P.G * P.T + seq0);
   const unsigned dst0 = lds_offset(tiles[0][wave]), sdst0 = lds_offset(rowstat[0][wave]);
-  // where rows 32 half .. +31 of query block i, head h come from, and where they go
-  struct Half { Strip rows; unsigned long long stat; unsigned stat_bytes, stat_slot; };
-  auto half_of = [&](int buf, int half, int i, int h) __attribute__((always_inline)) {
-    const int r0 = i * 64 + half * 32;
-    Half x;
-    x.rows = Loader::strip(dst0 + buf * BUF_B + half * 32 * ROW_B, src0 + ((int64_t)r0 * P.Hq + h) * (D * 2), L - r0, pitch);
-    x.stat = uniform((unsigned long long)(stat0 + (int64_t)h * P.T + r0));
-    x.stat_bytes = uniform((unsigned)max(L - r0, 0) * 4u);
-    x.stat_slot = sdst0 + (2 * buf + half) * 512;
+  const int lane4 = 4 * lane;
+  // Only the sequence's last query block, n - 1, can lack rows: bytes that exist of rows 32 half .. +31 and of their statistics.
+  const int last_rows = L - (n - 1) * 64;
+  const unsigned full_bytes = 31u * pitch + D * 2;
+  const unsigned last_bytes[2] = {(unsigned)(min(last_rows, 32) - 1) * pitch + D * 2, last_rows > 32 ? (unsigned)(last_rows - 33) * pitch + D * 2 : 0u};
+  const unsigned last_stat[2] = {4u * min(last_rows, 32), 4u * max(last_rows - 32, 0)};
+  // where query block i, head sel of the group come from (wave-uniform), and of a half tile: where from and where to
+  struct Tile { unsigned long long rows, stat; bool last; };
+  auto tile_of = [&](int i, int sel) __attribute__((always_inline)) {
+    Tile x;
+    x.rows = src0 + (unsigned long long)(unsigned)i * (64u * pitch) + (unsigned)sel * (unsigned)(D * 2);
+    x.stat = stat0 + (unsigned long long)(unsigned)sel * (4u * (unsigned)P.T) + (unsigned)i * 256u;
+    x.last = i == n - 1;
     return x;
   };
+  struct Half { i32x4 rows, stat; unsigned slot, stat_slot; };
+  auto half_of = [&](int buf, int half, Tile x) __attribute__((always_inline)) {
+    return Half{Loader::resource(x.rows + half * (32u * pitch), x.last ? last_bytes[half] : full_bytes),
+                Loader::resource(x.stat + half * 128u, x.last ? last_stat[half] : 128u), dst0 + buf * BUF_B + half * 32 * ROW_B, sdst0 + (2 * buf + half) * 512};
+  };
   auto issue_half = [&](Half x) __attribute__((always_inline)) {
-    load_floats(x.stat_slot, x.stat, x.stat_bytes, lane);
-    loader.issue(x.rows);
+    load_floats(x.stat_slot, x.stat, lane4);
+    loader.issue(x.rows, x.slot);
   };
 
   f32x16 sacc[2], dpacc[2];  // [half]: scores, then (in place) probabilities; dP
@@ -892,11 +901,8 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
         if constexpr (D == 64) asm volatile("" : "+v"(kf[ks]), "+v"(vf[ks]));
         else asm volatile("" : "+a"(kf[ks]), "+a"(vf[ks]));
       }
-      auto entry = [&](int t, int& i, int& h) __attribute__((always_inline)) {
-        const int e = __builtin_amdgcn_readfirstlane((int)list[-t]);
-        i = 32 * w0 + (e >> 3);
-        h = g * P.G + sel0 + (e & 7);
-      };
+      auto tile_from = [&](int e) __attribute__((always_inline)) { return tile_of(32 * w0 + (e >> 3), sel0 + (e & 7)); };
+      auto entry = [&](int t) __attribute__((always_inline)) { return tile_from(__builtin_amdgcn_readfirstlane((int)list[-t])); };
       using H0 = std::integral_constant<int, 0>;
       using H1 = std::integral_constant<int, 1>;
       const int nn = ntl - nd;  // tiles without a mask
@@ -904,20 +910,19 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
         // ---- D = 64: the kernel fits 256 registers, two wavefronts share a SIMD and hide each other's latencies, so a half tile
         // is computed from start to end.  Half tile u: its loads have landed for everyone and u - 1 has been read by everyone, so
         // u - 1's buffer takes the loads of u + 3.
-        int i0, h0, i1, h1;
-        entry(0, i0, h0);
-        issue_half(half_of(0, 0, i0, h0));
-        issue_half(half_of(0, 1, i0, h0));
-        entry(min(1, ntl - 1), i1, h1);
-        issue_half(half_of(1, 0, i1, h1));
+        Tile newest = entry(0);  // the newest tile that loads have been issued for
+        issue_half(half_of(0, 0, newest));
+        issue_half(half_of(0, 1, newest));
+        newest = entry(min(1, ntl - 1));
+        issue_half(half_of(1, 0, newest));
         auto half_tile = [&](auto diag_c, auto half_c, int buf, int t) __attribute__((always_inline)) {
           constexpr bool DIAG = decltype(diag_c)::value;
           constexpr int HALF = decltype(half_c)::value;
           const unsigned CO = buf * BUF_B + HALF * 32 * ROW_B, SO = (2 * buf + HALF) * 512;
           asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(2 * kLoadsPerHalf) : "memory");
           __builtin_amdgcn_s_barrier();
-          if (HALF == 1) entry(min(t + 2, ntl - 1), i1, h1);
-          issue_half(half_of(HALF == 0 ? 1 - buf : buf, 1 - HALF, i1, h1));  // (past the last tile: that tile once more, never read)
+          if (HALF == 1) newest = entry(min(t + 2, ntl - 1));
+          issue_half(half_of(HALF == 0 ? 1 - buf : buf, 1 - HALF, newest));  // (past the last tile: that tile once more, never read)
           bf16x8 rows[NOP], tr[NOP];
           f32x4 sl[4], sd[4];
 #pragma unroll
@@ -967,15 +972,11 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
         // share of vector work beside it and nothing waits for a result of the stage before.  The operands of a stage are
         // fetched from LDS while the previous one computes.  Half tile u-1 has been read when stage dK(u-1) begins: after a
         // barrier its buffer takes the loads of half tile u+3, two at a time.
-        int i1, h1;  // the newest tile that loads have been issued for
-        {
-          int i0, h0;
-          entry(0, i0, h0);
-          issue_half(half_of(0, 0, i0, h0));
-          issue_half(half_of(0, 1, i0, h0));
-        }
-        entry(min(1, ntl - 1), i1, h1);
-        Half nxt = half_of(1, 0, i1, h1);
+        Tile newest = entry(0);  // the newest tile that loads have been issued for
+        issue_half(half_of(0, 0, newest));
+        issue_half(half_of(0, 1, newest));
+        newest = entry(min(1, ntl - 1));
+        Half nxt = half_of(1, 0, newest);
         issue_half(nxt);
         wait_vmcnt<2 * kLoadsPerHalf>();
         __builtin_amdgcn_s_barrier();
@@ -1009,7 +1010,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
               for (int e = 0; e < EPS; ++e) dscore(PREV, EPS * k + e, PSO);
             SB_FENCE();
           }
-          if constexpr (!FIRST && !LAST && LPS > 4) loader.template issue2<LPS - 4>(nxt.rows);
+          if constexpr (!FIRST && !LAST && LPS > 4) loader.template issue2<LPS - 4>(nxt.rows, nxt.slot);
           if (!LAST) { st_l[0] = ld_stat(SO, 0); st_l[1] = ld_stat(SO, 1); }
           SB_FENCE();
 #pragma unroll
@@ -1025,7 +1026,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
             }
             SB_FENCE();
           }
-          if constexpr (!FIRST && !LAST) loader.template issue2<LPS - 2>(nxt.rows);
+          if constexpr (!FIRST && !LAST) loader.template issue2<LPS - 2>(nxt.rows, nxt.slot);
           SB_FENCE();
 #pragma unroll
           for (int k = 0; k < NOP; ++k) {
@@ -1037,22 +1038,19 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
 #pragma unroll
               for (int e = 0; e < EPS; ++e) prob(diag_c, HALF, EPS * k + e, SO);
             if (!LAST && k == NOP / 2) {  // scalar work for the loads below, while matrix instructions run
-              if (HALF == 1) {
-                const int e = __builtin_amdgcn_readfirstlane(e2);
-                i1 = 32 * w0 + (e >> 3);
-                h1 = g * P.G + sel0 + (e & 7);
-              }
-              nxt = half_of(HALF == 0 ? 1 - buf : buf, PREV, i1, h1);
+              if (HALF == 1) newest = tile_from(__builtin_amdgcn_readfirstlane(e2));
+              nxt = half_of(HALF == 0 ? 1 - buf : buf, PREV, newest);
             }
             SB_FENCE();
           }
           if (!LAST) {
             // half tile u - 1 has been read by this wavefront and its part of u + 1 has landed
-            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(kLoadsPerHalf) : "memory");
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+            wait_vmcnt<kLoadsPerHalf>();
             __builtin_amdgcn_s_barrier();
             st_d[0] = ld_stat(SO + 256, 0);
             st_d[1] = ld_stat(SO + 256, 1);
-            load_floats(nxt.stat_slot, nxt.stat, nxt.stat_bytes, lane);
+            load_floats(nxt.stat_slot, nxt.stat, lane4);
             SB_FENCE();
           }
 #pragma unroll
@@ -1065,8 +1063,8 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
             }
             SB_FENCE();
             if constexpr (!LAST) {
-              if (k == 0) loader.template issue2<0>(nxt.rows);
-              if constexpr (LPS > 4) { if (k == NOP / 2) loader.template issue2<2>(nxt.rows); }
+              if (k == 0) loader.template issue2<0>(nxt.rows, nxt.slot);
+              if constexpr (LPS > 4) { if (k == NOP / 2) loader.template issue2<2>(nxt.rows, nxt.slot); }
               SB_FENCE();
             }
           }

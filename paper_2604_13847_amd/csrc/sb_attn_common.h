@@ -425,6 +425,10 @@ struct StripWalk {
     return NW == 2 ? o : o + (t & 1) * half_pitch;
   }
 };
+// 64 consecutive floats to LDS, those that the resource (see QuadLoader) does not cover as zeros
+__device__ inline void load_floats(unsigned slot, i32x4 rsrc, int lane4) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dword %0, %2, 0 offen lds" : : "v"(lane4), "s"(slot), "s"(rsrc) : "memory", "m0");
+}
 // the first `bytes` of 64 consecutive floats from `src` (both wave-uniform) to LDS, the rest as zeros
 __device__ inline void load_floats(unsigned slot, unsigned long long src, unsigned bytes, int lane) {
   asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 s[84:85], %2\n\ts_mov_b32 s86, %3\n\ts_mov_b32 s87, 0x20000\n\t"
