@@ -241,116 +241,17 @@ struct TileLoader {
     }
   }
 };
-// One wavefront copies a strip of 32 rows of one head of a [T][H][D] tensor into an LDS slot of its
-// own, with the same swizzled layout as above.  `strip` points at the first row's head slice (it is
-// wave-uniform), `valid` is the number of rows of the strip that exist (<= 0 when the whole strip
-// lies past the end of the sequence): missing rows repeat the sequence's last row, and the consumer
-// masks them.
-// Full strips (the common case) are issued four loads at a time: the instruction's immediate
-// offset moves both the global and the LDS address, so one M0 value serves four consecutive KiB of
-// the slot and the per-lane global offsets are pre-biased by the same amount.  A wavefront issues
-// one instruction per four clocks at best, so every instruction saved here is time the wavefront
-// can spend issuing MFMAs.
-template <int D>
-struct StripLoader {
-  static constexpr int C = D / 8;        // 16-byte chunks per row
-  static constexpr int RPI = 64 / C;     // rows covered by one wavefront-wide load
-  static constexpr int LPS = 32 / RPI;   // loads per strip
-  static_assert(LPS % 4 == 0, "loads are issued in groups of four");
-  unsigned voff[LPS];                    // lane offset of load a, minus 1024 * (a % 4)
-  int rl, pc;                            // row within a load's group of RPI rows, 16-byte chunk of this lane
-  int pitch;                             // bytes between consecutive rows
-  __device__ inline void init(int H, int lane) {
-    rl = lane / C;
-    pc = lane % C;
-    pitch = H * D * 2;
-#pragma unroll
-    for (int a = 0; a < LPS; ++a) {
-      const int r = a * RPI + rl;
-      // r * pitch >= 1024 * a * H, so the bias never makes the offset negative
-      voff[a] = (unsigned)(r * pitch + 16 * (pc ^ chunk_swizzle<D>(r)) - 1024 * (a & 3));
-    }
-  }
-  // all 32 rows exist; `strip` must be wave-uniform
-  __device__ inline void issue_full(unsigned slot, const char* strip) const {
-    const unsigned long long tv = (unsigned long long)strip;
-    // (readfirstlane returns int: go through unsigned so that the low half is not sign-extended)
-    const unsigned t_hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(tv >> 32));
-    const unsigned t_lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(tv & 0xffffffffull));
-    const unsigned long long ts = ((unsigned long long)t_hi << 32) | (unsigned long long)t_lo;
-    // The base is copied by a scalar instruction first: a scalar register written by a vector
-    // instruction (readfirstlane) must not be read by a vector-memory instruction within 5 wait
-    // states, while scalar reads of it are interlocked.  M0 needs one wait state (s_nop 0) before
-    // the load that uses it.
-#pragma unroll
-    for (int a = 0; a < LPS; a += 4) {
-      unsigned long long base;
-      asm volatile("s_mov_b64 %0, %6\n\ts_mov_b32 m0, %5\n\ts_nop 0\n\t"
-                   "global_load_lds_dwordx4 %1, %0\n\t"
-                   "global_load_lds_dwordx4 %2, %0 offset:1024\n\t"
-                   "global_load_lds_dwordx4 %3, %0 offset:2048\n\t"
-                   "global_load_lds_dwordx4 %4, %0 offset:3072"
-                   : "=&s"(base) : "v"(voff[a]), "v"(voff[a + 1]), "v"(voff[a + 2]), "v"(voff[a + 3]), "s"(slot + a * 1024), "s"(ts) : "memory", "m0");
-    }
-  }
-  __device__ inline void issue(unsigned slot, const char* strip, int valid) const {
-    if (valid >= 32) {
-      issue_full(slot, strip);
-    } else {
-#pragma unroll
-      for (int a = 0; a < LPS; ++a) {  // ragged strip (rare): the lane offsets are recomputed instead of being kept in registers
-        const int r = a * RPI + rl;
-        dma16(strip + (int64_t)min(r, valid - 1) * pitch + 16 * (pc ^ chunk_swizzle<D>(r)), slot + a * 1024);
-      }
-    }
-  }
-};
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
-// One wavefront copies a strip of 32 rows of one head of a [T][H][D] tensor into LDS (layout as above) with buffer loads: the
-// buffer resource covers the rows that exist, and rows past it arrive as zeros without a branch or a per-lane clamp.
-// The resource is put together by scalar instructions inside the block: a scalar register written by a vector instruction
-// (readfirstlane) must not be read by a vector-memory instruction within 5 wait states, while scalar reads of it are
-// interlocked.  M0 needs one wait state before the load that uses it.
-__device__ inline unsigned uniform(unsigned x) { return (unsigned)__builtin_amdgcn_readfirstlane((int)x); }
-__device__ inline unsigned long long uniform(unsigned long long x) {
-  return ((unsigned long long)uniform((unsigned)(x >> 32)) << 32) | (unsigned long long)uniform((unsigned)(x & 0xffffffffull));
-}
-struct Strip { unsigned long long base; unsigned bytes, slot; };  // first row's head slice, bytes that exist from there, LDS address
-template <int D>
-struct RowLoader {
-  static constexpr int C = D / 8, RPI = 64 / C, LPS = 32 / RPI;  // 16-byte chunks per row, rows per load, loads per strip
-  unsigned voff[LPS];
-  __device__ inline void init(int H, int lane) {
-#pragma unroll
-    for (int a = 0; a < LPS; ++a) {
-      const int r = a * RPI + lane / C;
-      voff[a] = (unsigned)(r * H * D * 2 + 16 * ((lane % C) ^ chunk_swizzle<D>(r)));
-    }
-  }
-  // `first`: the first row's head slice (wave-uniform); `valid` rows exist (<= 0: none); `pitch`: bytes from row to row
-  __device__ static inline Strip strip(unsigned slot, const char* first, int valid, int pitch) {
-    return Strip{uniform((unsigned long long)first), uniform(valid > 0 ? (unsigned)((min(valid, 32) - 1) * pitch + D * 2) : 0u), slot};
-  }
-  template <int A>
-  __device__ inline void issue2(Strip x) const {  // loads A, A+1 of the strip
-    asm volatile("s_add_u32 m0, %2, %3\n\ts_mov_b64 s[84:85], %5\n\ts_mov_b32 s86, %6\n\ts_mov_b32 s87, 0x20000\n\t"
-                 "buffer_load_dwordx4 %0, s[84:87], 0 offen lds\n\ts_add_u32 m0, %2, %4\n\ts_nop 0\n\t"
-                 "buffer_load_dwordx4 %1, s[84:87], 0 offen lds"
-                 : : "v"(voff[A]), "v"(voff[A + 1]), "s"(x.slot), "n"(A * 1024), "n"(A * 1024 + 1024), "s"(x.base), "s"(x.bytes)
-                 : "memory", "m0", "scc", "s84", "s85", "s86", "s87");
-  }
-  __device__ inline void issue(Strip x) const {
-    issue2<0>(x);
-    issue2<2>(x);
-    if constexpr (LPS > 4) { issue2<4>(x); issue2<6>(x); }
-  }
-};
-// The same with the resource as four scalar registers that the caller keeps, for the kernels whose wavefront has a SIMD to itself: those
-// issue one instruction every four cycles whatever it is, so a scalar instruction there costs as much as a vector one.  The immediate
-// offset moves both the global and the LDS address, so four loads in a row need one M0, and the lane offsets are pre-biased for it (row
-// 4a of the strip starts at least 1024 a bytes in, so they stay positive).  The resource's words must come from scalar instructions.
+// One wavefront copies a strip of 32 rows of one head of a [T][H][D] tensor into LDS (layout as above) with buffer loads: the buffer
+// resource covers the rows that exist, and rows past it arrive as zeros without a branch or a per-lane clamp.  The resource is four
+// scalar registers that the caller keeps: a wavefront that has its SIMD to itself issues one instruction every four cycles whatever it
+// is, so a scalar instruction there costs as much as a vector one.  The immediate offset moves both the global and the LDS address, so
+// four loads in a row need one M0, and the lane offsets are pre-biased for it (row 4a of the strip starts at least 1024 a bytes in, so
+// they stay positive).  The resource's words must come from scalar instructions: a scalar register written by a vector instruction
+// (readfirstlane, readlane) must not be read by a vector-memory instruction within 5 wait states, and the compiler does not look into
+// the block for that (tests/test_hazards.py looks at what it made).  M0 needs one wait state before the load that uses it.
 template <int D>
 struct QuadLoader {
   static constexpr int C = D / 8, RPI = 64 / C, LPS = 32 / RPI;  // 16-byte chunks per row, rows per load, loads per strip
@@ -428,13 +329,6 @@ struct StripWalk {
 // 64 consecutive floats to LDS, those that the resource (see QuadLoader) does not cover as zeros
 __device__ inline void load_floats(unsigned slot, i32x4 rsrc, int lane4) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tbuffer_load_dword %0, %2, 0 offen lds" : : "v"(lane4), "s"(slot), "s"(rsrc) : "memory", "m0");
-}
-// the first `bytes` of 64 consecutive floats from `src` (both wave-uniform) to LDS, the rest as zeros
-__device__ inline void load_floats(unsigned slot, unsigned long long src, unsigned bytes, int lane) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 s[84:85], %2\n\ts_mov_b32 s86, %3\n\ts_mov_b32 s87, 0x20000\n\t"
-               "buffer_load_dword %0, s[84:87], 0 offen lds"
-               : : "v"(4 * lane), "s"(slot), "s"(src), "s"(bytes)
-               : "memory", "m0", "s84", "s85", "s86", "s87");
 }
 // x * f for an accumulator element that lives in an accumulation register.  Written as one opaque
 // block so that the copies to and from the arithmetic registers stay inside the (rarely taken)

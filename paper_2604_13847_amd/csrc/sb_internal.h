@@ -219,19 +219,24 @@ WsOffsets bwd_ws_offsets(const Geo& g);
 constexpr int64_t kTicketMinItems = 4096;  // shorter lists are dealt by position only
 inline bool use_tickets(int64_t n) { return n >= kTicketMinItems; }
 inline int64_t ticketed_grid(int64_t n, bool tickets) { return (n + (tickets ? (n >> 7) << 3 : 0) + 7) / 8 * 8; }
-// Is a query-major item of one query head (D = 128) one wavefront's work, or two's?  Of `items` with at most `most` tiles, w wavefronts
-// each, the chip works on 1024 / w at a time; an item costs about `fixed` tile times of two wavefronts besides its tiles (where the chip
-// is not full and its clock is high: forward 16, dQ 24), and the launch takes as long as its share of all items, as the longest item, or,
-// where there are more items than fit, as two short ones.  So one wavefront each where there are enough items, two where the longest would
-// stick out.  One / two wavefronts, forward and dQ: 1230 items of 1 - 11 tiles 24 / 32 and 31 / 41 us, 1280 of them 27 / 33 and 35 / 44,
-// 1248 items of 1 - 78 tiles 127 / 114 and 162 / 152, 432 of 1 - 54 tiles 78 / 47 and 92 / 59, 592 of 1 - 11 tiles 20.0 / 20.4 and
-// 24.2 / 26.5 us.
+// Is a query-major item of one query head one wavefront's work, or two's?  Of `items` with at most `most` tiles, w wavefronts each, the
+// chip works on 1024 / w at a time (head_dim 64: twice as many); an item costs about `fixed` tile times of two wavefronts besides its
+// tiles (where the chip is not full and its clock is high: forward 16, dQ and head_dim 64 24), and the launch takes as long as its share
+// of all items, as the longest item, or, where there are more items than fit, as two short ones.  So one wavefront each where there are
+// enough items, two where the longest would stick out.  One / two wavefronts at head_dim 128, forward and dQ: 1230 items of 1 - 11 tiles
+// 24 / 32 and 31 / 41 us, 1280 of them 27 / 33 and 35 / 44, 1248 items of 1 - 78 tiles 127 / 114 and 162 / 152, 432 of 1 - 54 tiles
+// 78 / 47 and 92 / 59, 592 of 1 - 11 tiles 20.0 / 20.4 and 24.2 / 26.5 us.
+// At head_dim 64 the SIMD's other wavefront works through three quarters of the fixed part, and an item alone on its wavefront costs 3 %
+// in the caches (65536 tokens, 14/2 heads, blocks of 256: 1482 / 1436 us; 1190 items of 1 - 11 tiles: 16.2 / 18.6 us).
 inline bool one_wavefront_per_item(const Geo& tg, int64_t items, int fixed) {
-  const int64_t tiles = (int64_t)tg.Hq * tg.nnz_unit, most = tg.rowT_max;
-  auto time = [&](int64_t w) {  // of the launch, in tile times of two wavefronts
-    int64_t t = (fixed * items * w + 2 * tiles) / 1024;
-    if (fixed + 2 * most / w > t) t = fixed + 2 * most / w;
-    if (items * w > 1024 && 2 * fixed + 2 > t) t = 2 * fixed + 2;
+  const bool d64 = tg.D == 64;
+  const int64_t tiles = (int64_t)tg.Hq * tg.nnz_unit, most = tg.rowT_max, slots = d64 ? 2048 : 1024;
+  auto time = [&](int64_t w) {  // of the launch, in 1/32 of the time that two wavefronts take for a tile
+    int64_t t = 32 * ((d64 ? fixed / 4 : fixed) * items * w + 2 * tiles) / slots;
+    if (d64 && w == 1) t += t / 32;
+    const int64_t longest = 32 * (fixed + 2 * most / w), two = 32 * (2 * fixed + 2);
+    if (longest > t) t = longest;
+    if (items * w > slots && two > t) t = two;
     return t;
   };
   return time(1) <= time(2);
