@@ -14,52 +14,45 @@
 namespace sb {
 
 // ---------------------------------------------------------------------------------------------
-// Query-major dQ kernel.  Same work items as the forward.  A workgroup takes one item (sequence,
-// selection head, query block) and HPW query heads that share its selection (one in per-query-head
-// mode); the K and V tiles of the selected blocks are double-buffered in LDS as whole tiles by
-// asynchronous loads and shared by all wavefronts of the workgroup.  A wavefront owns 32 query rows
-// of one head and, with the key split KS = 2, one 32-key half of every tile (the two partial dQ of a
-// row are added through LDS at the end); Q, dO, LSE and Dr of its rows stay in registers.  Every (token,
-// query head) row belongs to exactly one workgroup of this kernel, so its prologue is also where Dr is
-// computed (from the dO registers and one read of O) and left, with LSE * log2 e, for the key-major kernel.
-// Transposed products put a query in a C-matrix column: S^T = K Q^T, dP^T = V dO^T, so LSE and Dr are
-// per-lane scalars and dS^T converts to the B operand of dQ^T += K^T dS^T without cross-lane movement;
-// K^T comes from the row-major K tile through the transposing LDS read.
-// The register budget (256) lets two wavefronts share a SIMD: one runs its exponentials while the
-// other runs matrix instructions.  Operands are fetched from LDS in sets of D/16, a set ahead of use.
-template <bool OUT_F32, int KS, int MAXT>
-__global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(2))) void attn_bwd_dq_kernel(AttnParams P, int heads) {
+// Query-major dQ kernel for few items at D = 64.  Same work items as the forward, one query head per workgroup of four wavefronts: the K and
+// V tiles of the selected blocks are double-buffered in LDS as whole tiles by asynchronous loads and shared by the workgroup; a wavefront
+// owns 32 query rows and one 32-key half of every tile (the two partial dQ of a row are added through LDS at the end); Q, dO, LSE and
+// Dr of its rows stay in registers.  Every (token, query head) row belongs to exactly one workgroup of this kernel, so its prologue is also
+// where Dr is computed (from the dO registers and one read of O) and left, with LSE * log2 e, for the key-major kernel.
+// Transposed products put a query in a C-matrix column: S^T = K Q^T, dP^T = V dO^T, so LSE and Dr are per-lane scalars and dS^T converts to
+// the B operand of dQ^T += K^T dS^T without cross-lane movement; K^T comes from the row-major K tile through the transposing LDS read.
+// Four wavefronts get through the longest item sooner than the kernel below, which wins where the chip is full: 336 items of 1 - 42 tiles
+// 30.6 against 32.8 us, 1504 of 1 - 16 tiles 47 against 49, but 6144 of 1 - 16 tiles 152 against 131.
+template <bool OUT_F32>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void attn_bwd_dq_kernel(AttnParams P) {
   constexpr int D = 64;
   constexpr int TILE_B = 64 * D * 2, ROW_B = D * 2, NOP = D / 16;
-  constexpr int NMT = 2 / KS;  // 32-key halves of a tile this wavefront computes
   __shared__ __attribute__((aligned(1024))) bf16 tiles[2][2][64 * D];  // [buffer][K, V]
   constexpr int kJ = 256;
   __shared__ int jbuf[kJ];
-  static_assert(KS == 1 || sizeof(tiles) >= (MAXT / 128) * 16 * (D / 32) * 64 * sizeof(float), "partial dQ must fit in the tile buffers");
+  static_assert(sizeof(tiles) >= 2 * 16 * (D / 32) * 64 * sizeof(float), "partial dQ must fit in the tile buffers");
   BusyTimer timer;
   timer.start(P);
-  const int tid = threadIdx.x, nthr = blockDim.x;
+  const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
-  const int pos = claim_item(blockIdx.x, P.n_items, P.ticket ? P.ticket + blockIdx.y : nullptr);
+  const int pos = (int)blockIdx.x < P.n_items ? (int)blockIdx.x : -1;  // (so few items are dealt by position, see claim_item)
   if (pos < 0) return;
   const WorkItem item = uniform_item(P.items, pos);
   const int hs = item.hs, i = item.i, L = item.len, e0 = item.e0, ntiles = item.ntiles;
   const int64_t seq0 = item.seq0;
-  const int strip = wave & 1, kh = KS == 2 ? (wave >> 1) & 1 : 0;
-  const int hh = blockIdx.y * (nthr / (128 * KS)) + wave / (2 * KS);  // query head of the group this wavefront works for
-  const bool head_ok = hh < heads;
-  const int h = P.mode == SB_SELECT_PER_QHEAD ? hs : hs * P.G + (head_ok ? hh : 0);
+  const int strip = wave & 1, kh = wave >> 1;
+  const int h = P.mode == SB_SELECT_PER_QHEAD ? hs : hs * P.G + (int)blockIdx.y;
   const int g = h / P.G;
   const int qloc = strip * 32 + l32;
-  const bool qvalid = head_ok && i * 64 + qloc < L;
+  const bool qvalid = i * 64 + qloc < L;
   const int64_t tq = seq0 + i * 64 + qloc;
 
   auto stage_indices = [&](int t0) {
     __syncthreads();
-    for (int a = tid; a < kJ; a += nthr) jbuf[a] = t0 + a < ntiles ? P.idx[e0 + t0 + a] : 0;
+    for (int a = tid; a < kJ; a += 256) jbuf[a] = t0 + a < ntiles ? P.idx[e0 + t0 + a] : 0;
     __syncthreads();
   };
-  TileLoader<D, 4> loader;  // every workgroup of this kernel has at least four wavefronts: they share the tile loads
+  TileLoader<D, 4> loader;
   loader.init(P.Hkv, wave, lane);
   auto issue = [&](int t) {
     const int j = __builtin_amdgcn_readfirstlane(jbuf[t % kJ]);
@@ -142,38 +135,32 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(2))) void 
   // where one key dominates the row.  For these items Dr is taken from the identity rowsum(dO * O) = sum_j P_j dP_j
   // instead, in fp32 from the one tile the row has, normalised by sum_j P_j (P carries the rounding of the stored LSE).
   if (ntiles == 1) {
-    __shared__ float drx[MAXT / 64][64];
+    __shared__ float drx[4][64];
     wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
     float num = 0.f, den = 0.f;
+    f32x16 sacc = zero16(), dpacc = zero16();
 #pragma unroll
-    for (int mt = 0; mt < NMT; ++mt) {
-      const unsigned ro = mt * 32 * ROW_B;
-      f32x16 sacc = zero16(), dpacc = zero16();
+    for (int ks = 0; ks < NOP; ++ks) op[ks] = ld_row(ks, 0);
 #pragma unroll
-      for (int ks = 0; ks < NOP; ++ks) op[ks] = ld_row(ks, ro);
+    for (int ks = 0; ks < NOP; ++ks) sacc = mfma32(op[ks], qf[ks], sacc);
 #pragma unroll
-      for (int ks = 0; ks < NOP; ++ks) sacc = mfma32(op[ks], qf[ks], sacc);
+    for (int ks = 0; ks < NOP; ++ks) op[ks] = ld_row(ks, TILE_B);
 #pragma unroll
-      for (int ks = 0; ks < NOP; ++ks) op[ks] = ld_row(ks, ro + TILE_B);
+    for (int ks = 0; ks < NOP; ++ks) dpacc = mfma32(op[ks], dof[ks], dpacc);
 #pragma unroll
-      for (int ks = 0; ks < NOP; ++ks) dpacc = mfma32(op[ks], dof[ks], dpacc);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const bool masked = 32 * (mt + kh) + c_row(v, hf) > qloc;  // the tile is the diagonal block
-        const float pv = masked ? 0.f : fast_exp2(__builtin_fmaf(sacc[v], P.scale_log2e, -lse2));
-        num = __builtin_fmaf(pv, dpacc[v], num);
-        den += pv;
-      }
+    for (int v = 0; v < 16; ++v) {
+      const bool masked = 32 * kh + c_row(v, hf) > qloc;  // the tile is the diagonal block
+      const float pv = masked ? 0.f : fast_exp2(__builtin_fmaf(sacc[v], P.scale_log2e, -lse2));
+      num = __builtin_fmaf(pv, dpacc[v], num);
+      den += pv;
     }
     num += __shfl_xor(num, 32, 64);
     den += __shfl_xor(den, 32, 64);
-    if (KS == 2) {  // the other key half of the row is with wavefront wave ^ 2
-      if (hf == 0) { drx[wave][l32] = num; drx[wave][32 + l32] = den; }
-      __syncthreads();
-      num += drx[wave ^ 2][l32];
-      den += drx[wave ^ 2][32 + l32];
-    }
+    if (hf == 0) { drx[wave][l32] = num; drx[wave][32 + l32] = den; }
+    __syncthreads();  // the other key half of the row is with wavefront wave ^ 2
+    num += drx[wave ^ 2][l32];
+    den += drx[wave ^ 2][32 + l32];
     if (den > 0.f) dr = num / den;
   }
   if (qvalid && kh == 0 && hf == 0) {
@@ -189,77 +176,63 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(2))) void 
   // body, so that the other tiles carry no mask selects.
   auto tile = [&](auto diag_c, auto buf_c, int t) __attribute__((always_inline)) {
     constexpr bool diag = decltype(diag_c)::value;
-    // BUF = 0 / 1: the tile's buffer is an immediate offset of every LDS read; BUF = -1: the operand addresses are
-    // moved to the other buffer after every tile
-    constexpr int BUF = decltype(buf_c)::value;
-    constexpr unsigned BO = BUF > 0 ? 2 * TILE_B : 0;
+    constexpr unsigned BO = decltype(buf_c)::value * 2 * TILE_B;  // the tile's buffer is an immediate offset of every LDS read
     const bool more = t + 1 < ntiles;
     if (more && (t + 1) % kJ == 0) stage_indices(t + 1);
     wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();  // tile t has landed for everyone; everyone is done with tile t-1
     if (more) issue(t + 1);
-    if (BUF < 0 && t > 0) {
-      const int dl = (t & 1) ? 2 * TILE_B : -2 * TILE_B;
 #pragma unroll
-      for (int ks = 0; ks < NOP; ++ks) row_a[ks] += dl;
+    for (int ks = 0; ks < NOP; ++ks) op[ks] = ld_row(ks, BO);  // K rows
+    __builtin_amdgcn_sched_barrier(0);
+    f32x16 sacc = zero16(), dpacc = zero16();
 #pragma unroll
-      for (int dt = 0; dt < D / 32; ++dt) { tr_a[dt][0] += dl; tr_a[dt][1] += dl; }
+    for (int ks = 0; ks < NOP; ++ks) {  // S^T = K Q^T, refilling every operand register with the V row operand
+      sacc = mfma32(op[ks], qf[ks], sacc);
+      op[ks] = ld_row(ks, BO + TILE_B);
     }
 #pragma unroll
-    for (int mt = 0; mt < NMT; ++mt) {  // keys 32(mt + kh) .. +31 of the tile
-      const unsigned ro = BO + mt * 32 * ROW_B;
-#pragma unroll
-      for (int ks = 0; ks < NOP; ++ks) op[ks] = ld_row(ks, ro);  // K rows
-      __builtin_amdgcn_sched_barrier(0);
-      f32x16 sacc = zero16(), dpacc = zero16();
-#pragma unroll
-      for (int ks = 0; ks < NOP; ++ks) {  // S^T = K Q^T, refilling every operand register with the V row operand
-        sacc = mfma32(op[ks], qf[ks], sacc);
-        op[ks] = ld_row(ks, ro + TILE_B);
-      }
-#pragma unroll
-      for (int i_ = 0; i_ < NOP; ++i_) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int ks = 0; ks < NOP; ++ks) {  // dP^T = V dO^T, refilling with the K^T operands of the dQ step
-        dpacc = mfma32(op[ks], dof[ks], dpacc);
-        op[ks] = ld_tr(2 * mt + ks / (D / 32), ks % (D / 32), BO);
-      }
-#pragma unroll
-      for (int i_ = 0; i_ < NOP; ++i_) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      if (diag) {  // causal mask inside the diagonal block (also removes keys past the end of the sequence)
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          if (32 * (mt + kh) + c_row(v, hf) > qloc) sacc[v] = -__builtin_inff();
-      }
-      bf16x8 dsb[2];
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const float pv = fast_exp2(__builtin_fmaf(sacc[v], P.scale_log2e, -lse2));
-        dsb[v >> 3][v & 7] = (bf16)(pv * (dpacc[v] - dr));
-      }
-#pragma unroll
-      for (int q = 0; q < 2; ++q)
-#pragma unroll
-        for (int dt = 0; dt < D / 32; ++dt) dqacc[dt] = mfma32(op[q * (D / 32) + dt], dsb[q], dqacc[dt]);
-      // the matrix instructions of the first 16 keys run under the pointwise work of the other 16
-      __builtin_amdgcn_sched_group_barrier(0x002, 40, 0);
-#pragma unroll
-      for (int i_ = 0; i_ < D / 32; ++i_) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, 40 / (D / 32), 0);
-      }
-      __builtin_amdgcn_sched_group_barrier(0x008, D / 32, 0);
+    for (int i_ = 0; i_ < NOP; ++i_) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
     }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < NOP; ++ks) {  // dP^T = V dO^T, refilling with the K^T operands of the dQ step
+      dpacc = mfma32(op[ks], dof[ks], dpacc);
+      op[ks] = ld_tr(ks / (D / 32), ks % (D / 32), BO);
+    }
+#pragma unroll
+    for (int i_ = 0; i_ < NOP; ++i_) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (diag) {  // causal mask inside the diagonal block (also removes keys past the end of the sequence)
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        if (32 * kh + c_row(v, hf) > qloc) sacc[v] = -__builtin_inff();
+    }
+    bf16x8 dsb[2];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const float pv = fast_exp2(__builtin_fmaf(sacc[v], P.scale_log2e, -lse2));
+      dsb[v >> 3][v & 7] = (bf16)(pv * (dpacc[v] - dr));
+    }
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int dt = 0; dt < D / 32; ++dt) dqacc[dt] = mfma32(op[q * (D / 32) + dt], dsb[q], dqacc[dt]);
+    // the matrix instructions of the first 16 keys run under the pointwise work of the other 16
+    __builtin_amdgcn_sched_group_barrier(0x002, 40, 0);
+#pragma unroll
+    for (int i_ = 0; i_ < D / 32; ++i_) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, 40 / (D / 32), 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, D / 32, 0);
   };
-  if (KS == 2) {  // two tiles per iteration, so that the buffer of a tile is known at compile time
+  {  // two tiles per iteration, so that the buffer of a tile is known at compile time
     using B0 = std::integral_constant<int, 0>;
     using B1 = std::integral_constant<int, 1>;
     int t = 0;
@@ -273,13 +246,9 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(2))) void 
     } else {
       tile(std::true_type(), B0(), t);
     }
-  } else {  // a wavefront that computes both key halves has twice the tile body: the copies would not fit the register budget
-    using BR = std::integral_constant<int, -1>;
-    for (int t = 0; t + 1 < ntiles; ++t) tile(std::false_type(), BR(), t);
-    tile(std::true_type(), BR(), ntiles - 1);
   }
-  if (KS == 2) {  // add the two key halves of every row: the kh = 1 wavefront hands its partial over
-    float* xbuf = (float*)&tiles[0][0][0] + (size_t)(wave >> 2) * 2 * (16 * (D / 32) * 64) + (size_t)strip * (16 * (D / 32) * 64);
+  {  // add the two key halves of every row: the kh = 1 wavefront hands its partial over
+    float* xbuf = (float*)&tiles[0][0][0] + (size_t)strip * (16 * (D / 32) * 64);
     __syncthreads();  // everyone is done with the tile buffers
     if (kh == 1) {
 #pragma unroll
@@ -317,11 +286,10 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(2))) void 
 }
 
 // ---------------------------------------------------------------------------------------------
-// The same for D = 128, one query head per workgroup, by one or two wavefronts as in the forward kernel (NW, StripWalk; see
-// one_wavefront_per_item): a wavefront owns all 64 query rows and walks 32-key strips, so that an operand read from LDS feeds two matrix
+// The same by one or two wavefronts as in the forward kernel (NW, StripWalk; see one_wavefront_per_item): a wavefront owns all 64 query rows and walks 32-key strips, so that an operand read from LDS feeds two matrix
 // instructions (with 32 rows per wavefront LDS reads take as long as the matrix instructions); it stages its own strips of K and V, two
-// of each, without any barrier in the loop.  It needs the registers of a whole SIMD, so the loop is a software pipeline over half tiles u
-// (32 keys x 32 queries), stages of 8 matrix instructions:
+// of each, without any barrier in the loop.  At D = 128 it needs the registers of a whole SIMD, so the loop is a software pipeline over
+// half tiles u (32 keys x 32 queries), stages of D/16 matrix instructions:
 //   S(u), dP(u), dQ(u-1)
 // with P(u) beside dP(u) and dQ(u-1), and dS(u) beside dQ(u-1) and the next S; every matrix instruction is fenced with its share of
 // the vector work and LDS reads, and nothing waits for a result of the stage before.
@@ -333,13 +301,15 @@ __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(2))) void 
 // 2.44 / 2.23 / 2.14 ms, one 131072-token sequence, top 32: 7.62 / 7.24 / 6.49, the 262144-token batch 23.3 / 22.3 / 20.5, 65536 tokens
 // whose selection is a sink and a window 2.66 / 2.42 / 2.19.  Where the heads of a KV group share their selection, against one workgroup
 // of all of them that shares the tiles in LDS (32 rows per wavefront): the 32768-token batch 2.37 -> 2.09 ms, the 131072-token sequence
-// 6.45 -> 5.82, 65536 tokens with 28/4 heads 5.75 -> 4.54.
-template <bool OUT_F32, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1))) void attn_bwd_dq_head_kernel(AttnParams P, int heads) {
-  constexpr int D = 128, ROW_B = D * 2, STRIP_B = 32 * ROW_B, NOP = D / 16;
+// 6.45 -> 5.82, 65536 tokens with 28/4 heads 5.75 -> 4.54.  At D = 64 two wavefronts share a SIMD (four or five registers spilled before the
+// loop); against the kernel above on 65536 tokens, 14/2 heads, blocks of 256: 1.98 -> 1.77 ms, per KV group 2.45 -> 1.75.
+template <int D, bool OUT_F32, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1))) void attn_bwd_dq_head_kernel(AttnParams P, int heads) {
+  constexpr int ROW_B = D * 2, STRIP_B = 32 * ROW_B, NOP = D / 16;
   using Loader = QuadLoader<D>;
   constexpr int LPS = Loader::LPS;
-  constexpr int KV = 6;  // Q, dQ and the dO operands below this one live in accumulation registers, the other dO operands do not fit there
+  constexpr int KV = D == 64 ? NOP : 6;  // Q, dQ and the dO operands below this one live in accumulation registers, the other dO operands do not fit there
+  constexpr int PER = 8 / NOP;           // registers of the vector work per matrix instruction
   __shared__ __attribute__((aligned(1024))) char ring[NW][4 * STRIP_B];  // per wavefront: K even, K odd, V even, V odd strips
   BusyTimer timer;
   timer.start(P);
@@ -544,7 +514,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1))) vo
         if (k == 0) mfma32_first(sacc[B], ka[k], qf[B][k]);
         else mfma32_more(sacc[B], ka[k], qf[B][k]);
       }
-      if (PREV) dscore(B ^ 1, 8 + k);  // (before the row's first half tile: zeros)
+      if (PREV) {  // (before the row's first half tile: zeros)
+#pragma unroll
+        for (int a = 0; a < PER; ++a) dscore(B ^ 1, 8 + PER * k + a);
+      }
       if (B == 1 && !LAST) {
         if (k == 1) {
           __builtin_amdgcn_s_waitcnt(0xC07F);  // K_t is in kt, its slot is free
@@ -556,7 +529,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1))) vo
       SB_FENCE();
       if constexpr (!LAST) {
         if (k == 2) loader.template issue2<0>(rsrc, slot);
-        if (k == 5) loader.template issue2<2>(rsrc, slot);
+        if constexpr (D == 128) { if (k == 5) loader.template issue2<2>(rsrc, slot); }
       }
       SB_FENCE();
     }
@@ -568,11 +541,18 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1))) vo
         else mfma32_more_v(dpacc, va[k], dof[B][k]);
       }
       if (B == 1 && !LAST) va[k] = ld_row(k, (2 + (PAR ^ 1)) * STRIP_B);
-      if (SEEN && k > 1) prob(diag_c, key0, B, k - 2);
+      if (SEEN && k >= NOP / 4) {  // 0 .. 5
+#pragma unroll
+        for (int a = 0; a < PER; ++a) prob(diag_c, key0, B, PER * (k - NOP / 4) + a);
+      }
       SB_FENCE();
       if constexpr (!LAST) {
-        if (k == 1) loader.template issue2<4>(rsrc, slot);
-        if (k == 5) loader.template issue2<6>(rsrc, slot);
+        if constexpr (D == 128) {
+          if (k == 1) loader.template issue2<4>(rsrc, slot);
+          if (k == 5) loader.template issue2<6>(rsrc, slot);
+        } else {
+          if (k == 1) loader.template issue2<2>(rsrc, slot);
+        }
       }
       SB_FENCE();
     }
@@ -582,9 +562,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1))) vo
       if (PREV) mfma32_sum(dqacc[k % (D / 32)][B ^ 1], kt[k], dsb[B ^ 1][k / (D / 32)]);
       if (B == 0) kt[k] = ld_tr(k, PAR * STRIP_B);
       if (SEEN) {
-        if (k < 2) { prob(diag_c, key0, B, 6 + 2 * k); prob(diag_c, key0, B, 7 + 2 * k); }
-        else prob(diag_c, key0, B, 8 + k);
-        if (k >= 4) { dscore(B, 2 * (k - 4)); dscore(B, 2 * (k - 4) + 1); }
+        constexpr int P128[9] = {6, 8, 10, 11, 12, 13, 14, 15, 16}, P64[5] = {6, 9, 12, 14, 16};
+#pragma unroll
+        for (int v = D == 64 ? P64[k % 4] : P128[k]; v < (D == 64 ? P64[k % 4 + 1] : P128[k + 1]); ++v) prob(diag_c, key0, B, v);
+        if (k >= NOP / 2) {  // (two matrix instructions after the last of dP at the least)
+#pragma unroll
+          for (int v = 0; v < 2 * PER; ++v) dscore(B, 2 * PER * (k - NOP / 2) + v);
+        }
       }
       SB_FENCE();
     }
@@ -1185,23 +1169,22 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_reduce_kernel(AttnParams P, 
   }
 }
 
+constexpr int64_t kDqFewItems = 2048;  // (items, query heads) below which D = 64 takes attn_bwd_dq_kernel: fewer than kTicketMinItems
+static_assert(kDqFewItems <= kTicketMinItems, "attn_bwd_dq_kernel deals its items by position");
+
 template <int D, bool F32>
 static int launch_bwd(const Geo& g, const AttnParams& P, hipStream_t st) {
-  // query-major dQ: one workgroup per (item, part of the item's query heads); 2 * KS wavefronts per head
+  // query-major dQ: one workgroup per (item, query head)
   const int heads = g.mode == SB_SELECT_PER_QHEAD ? 1 : g.G;
-  const int parts = (heads + 3) / 4, hpp = (heads + parts - 1) / parts;  // heads per workgroup: 1..4
-  const int64_t n_slots = ticketed_grid(P.n_items, P.ticket != nullptr);
+  const int64_t n_slots = ticketed_grid(P.n_items, P.ticket != nullptr), items = (int64_t)g.Hq * g.NQB;
   KernelTimer kt(K_BWD_DQ, st);
-  if constexpr (D == 128) {  // figures at attn_bwd_dq_head_kernel; D = 64 is better served by two wavefronts per SIMD (see dK/dV)
+  if (D == 64 && items < kDqFewItems) {
+    hipLaunchKernelGGL((attn_bwd_dq_kernel<F32>), dim3((unsigned)n_slots, (unsigned)heads), dim3(256), 0, st, P);
+  } else {
     if (n_slots * heads > 0x7fffffffll) { set_error("too many work items for one launch"); return SB_ERR_INVALID_ARG; }
     const dim3 grid((unsigned)(n_slots * heads));
-    if (one_wavefront_per_item(g, (int64_t)g.Hq * g.NQB, 24)) hipLaunchKernelGGL((attn_bwd_dq_head_kernel<F32, 1>), grid, dim3(64), 0, st, P, heads);
-    else hipLaunchKernelGGL((attn_bwd_dq_head_kernel<F32, 2>), grid, dim3(128), 0, st, P, heads);
-  } else {
-    const dim3 grid((unsigned)n_slots, (unsigned)parts);
-    if (hpp == 1) hipLaunchKernelGGL((attn_bwd_dq_kernel<F32, 2, 256>), grid, dim3(256), 0, st, P, heads);
-    else if (hpp == 2) hipLaunchKernelGGL((attn_bwd_dq_kernel<F32, 2, 512>), grid, dim3(512), 0, st, P, heads);
-    else hipLaunchKernelGGL((attn_bwd_dq_kernel<F32, 1, 512>), grid, dim3(128 * hpp), 0, st, P, heads);
+    if (one_wavefront_per_item(g, items, 24)) hipLaunchKernelGGL((attn_bwd_dq_head_kernel<D, F32, 1>), grid, dim3(64), 0, st, P, heads);
+    else hipLaunchKernelGGL((attn_bwd_dq_head_kernel<D, F32, 2>), grid, dim3(128), 0, st, P, heads);
   }
   SB_LAUNCH_CHECK("attn_bwd_dq_kernel");
   return SB_OK;

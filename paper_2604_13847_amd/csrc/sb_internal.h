@@ -226,14 +226,15 @@ inline int64_t ticketed_grid(int64_t n, bool tickets) { return (n + (tickets ? (
 // enough items, two where the longest would stick out.  One / two wavefronts at head_dim 128, forward and dQ: 1230 items of 1 - 11 tiles
 // 24 / 32 and 31 / 41 us, 1280 of them 27 / 33 and 35 / 44, 1248 items of 1 - 78 tiles 127 / 114 and 162 / 152, 432 of 1 - 54 tiles
 // 78 / 47 and 92 / 59, 592 of 1 - 11 tiles 20.0 / 20.4 and 24.2 / 26.5 us.
-// At head_dim 64 the SIMD's other wavefront works through three quarters of the fixed part, and an item alone on its wavefront costs 3 %
-// in the caches (65536 tokens, 14/2 heads, blocks of 256: 1482 / 1436 us; 1190 items of 1 - 11 tiles: 16.2 / 18.6 us).
+// At head_dim 64 the SIMD's other wavefront works through three quarters of the fixed part, and twice the items at a time miss the caches
+// more often, taken as 6 % (65536 tokens, 14/2 heads, blocks of 256: forward 1482 / 1436 us, dQ 1812 / 1767; 24551 tokens, 32/8 heads, rows
+// of up to 256 tiles: dQ 1156 / 1066; but 6144 items of 1 - 16 tiles: dQ 131 / 143, 1190 of 1 - 11 tiles: forward 16.2 / 18.6 us).
 inline bool one_wavefront_per_item(const Geo& tg, int64_t items, int fixed) {
   const bool d64 = tg.D == 64;
   const int64_t tiles = (int64_t)tg.Hq * tg.nnz_unit, most = tg.rowT_max, slots = d64 ? 2048 : 1024;
   auto time = [&](int64_t w) {  // of the launch, in 1/32 of the time that two wavefronts take for a tile
     int64_t t = 32 * ((d64 ? fixed / 4 : fixed) * items * w + 2 * tiles) / slots;
-    if (d64 && w == 1) t += t / 32;
+    if (d64 && w == 1) t += t / 16;
     const int64_t longest = 32 * (fixed + 2 * most / w), two = 32 * (2 * fixed + 2);
     if (longest > t) t = longest;
     if (items * w > slots && two > t) t = two;

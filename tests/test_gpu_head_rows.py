@@ -1,4 +1,4 @@
-"""The head_dim 128 query-major kernels at the edges of their pipelines: rows of one to a few tiles, the window of 64 block indices, ragged
+"""The query-major kernels at the edges of their pipelines: rows of one to a few tiles, the window of 64 block indices, ragged
 last blocks, items of one and of two wavefronts, the ticketed tail of a launch, and scores that outgrow the softmax's reference.  Every
 element against the float64 checker, with the tolerances of helpers.py."""
 import numpy as np
@@ -27,17 +27,18 @@ def check(w, mode, bwd=True):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("mode,Hq,Hkv", [(0, 2, 1), (0, 24, 4), (1, 4, 2), (1, 40, 20)])
-def test_row_lengths_and_ragged_blocks(mode, Hq, Hkv, dtype):
-    """Few items (two wavefronts each) and many (one each): rows of 1 .. 9 tiles, sequences that end anywhere in a block."""
-    w = synth.Workload("edges", EDGES, Hq, Hkv, 128, keep_ratio=[1.0] * len(EDGES), dtype=dtype, seed=300 + Hq)
+@pytest.mark.parametrize("mode,Hq,Hkv,D", [(0, 2, 1, 128), (0, 24, 4, 128), (1, 4, 2, 128), (1, 40, 20, 128), (0, 2, 1, 64), (0, 48, 4, 64), (1, 6, 2, 64), (1, 48, 12, 64)])
+def test_row_lengths_and_ragged_blocks(mode, Hq, Hkv, D, dtype):
+    """Few items (two wavefronts each, four for dQ at head_dim 64) and many (one each): rows of 1 .. 9 tiles, sequences that end anywhere in
+    a block."""
+    w = synth.Workload("edges", EDGES, Hq, Hkv, D, keep_ratio=[1.0] * len(EDGES), dtype=dtype, seed=300 + Hq)
     check(w, mode)
 
 
-@pytest.mark.parametrize("Hq,Hkv", [(2, 1), (24, 8)])
-def test_rows_longer_than_the_index_window(Hq, Hkv):
-    w = synth.Workload("window", (64 * 70 - 5,), Hq, Hkv, 128, topk=[67], seed=320 + Hq)
-    check(w, 0, bwd=Hq == 2)
+@pytest.mark.parametrize("Hq,Hkv,D", [(2, 1, 128), (24, 8, 128), (32, 8, 64)])
+def test_rows_longer_than_the_index_window(Hq, Hkv, D):
+    w = synth.Workload("window", (64 * 70 - 5,), Hq, Hkv, D, topk=[67], seed=320 + Hq)
+    check(w, 0, bwd=Hq != 24)
 
 
 @pytest.mark.parametrize("lens,topk", [((64 * 300, 64 * 250 + 5), (3, 4)), ((64 * 80,) + (64 * 4,) * 120, (75,) + (2,) * 120)])
@@ -48,16 +49,16 @@ def test_ticketed_launches(lens, topk):
     assert r.pb.layout.sel_rows >= 4096
 
 
-@pytest.mark.parametrize("Hq,Hkv", [(2, 1), (24, 8)])
+@pytest.mark.parametrize("Hq,Hkv,D", [(2, 1, 128), (24, 8, 128), (24, 8, 64)])
 @pytest.mark.parametrize("jump", [5.0, 13.0, 150.0])
-def test_scores_that_outgrow_the_reference(Hq, Hkv, jump):
+def test_scores_that_outgrow_the_reference(Hq, Hkv, D, jump):
     """Scores that grow from block to block by `jump` powers of two and fall again: probabilities against the old reference are large or
     infinite, so the reference moves and what has been summed is rescaled; a row sees rises inside and across its tiles."""
     lens = (64 * 9 + 17, 64 * 14, 40)
-    w = synth.Workload("jump", lens, Hq, Hkv, 128, topk=[12, 14, 1], seed=340 + Hq)
+    w = synth.Workload("jump", lens, Hq, Hkv, D, topk=[12, 14, 1], seed=340 + Hq)
     t = w.tensors()
-    u = np.full(128, 128 ** -0.5, dtype=np.float32)
-    level = np.array([0, 1, 2, 3, 1, 0.5, 3, 0], dtype=np.float32) * jump / (8.0 * 128 ** -0.5 * 1.4427)
+    u = np.full(D, D ** -0.5, dtype=np.float32)
+    level = np.array([0, 1, 2, 3, 1, 0.5, 3, 0], dtype=np.float32) * jump / (8.0 * D ** -0.5 * 1.4427)
     for s, L in enumerate(lens):
         at = int(w.cu[s])
         steps = level[(np.arange(L) // 48) % len(level)]  # 48: rises also inside a 64-key tile and inside a 32-key strip
@@ -65,5 +66,5 @@ def test_scores_that_outgrow_the_reference(Hq, Hkv, jump):
     t["q"] += 8.0 * u
     t = {n: synth.round_to_bf16(x) for n, x in t.items()}
     w.tensors = lambda: t
-    w.seed = 1000 + w.seed + int(jump)  # (the arrays of a workload are kept by its seed)
+    w.seed = 1000 + w.seed + int(jump) + D  # (the arrays of a workload are kept by its seed)
     check(w, 0, bwd=False)
