@@ -297,7 +297,16 @@ __global__ __launch_bounds__(256) void coverage_partial_kernel(const float* __re
   if (k >= 2) {
     for (int gidx = 0; gidx < groups; ++gidx) {
       const float* col = pacc + (int64_t)gidx * slab + sc_off[s] + (k - 2);
-      for (int i = i0; i < i1; ++i) sum += col[(int64_t)i * n];
+      // eight rows in flight: one after the other, the latencies of up to 128 loads are all that a small problem waits for
+      int i = i0;
+      for (; i + 8 <= i1; i += 8) {
+        float x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = col[(int64_t)(i + u) * n];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) sum += x[u];
+      }
+      for (; i < i1; ++i) sum += col[(int64_t)i * n];
     }
   }
   part[(int64_t)blockIdx.y * NQB + qb] = sum;
@@ -312,7 +321,16 @@ __global__ __launch_bounds__(256) void coverage_reduce_kernel(const float* __res
   const int n = qb_off[s + 1] - qb_off[s];
   const int k = (int)(qb - qb_off[s]) + 1;
   double sum = (double)Hs * k;  // the k rows i < k are fully covered
-  for (int y = k / kCovSlab; y * kCovSlab < n; ++y) sum += (double)part[(int64_t)y * NQB + qb];
+  const int slabs = (n + kCovSlab - 1) / kCovSlab;
+  int y = k / kCovSlab;
+  for (; y + 8 <= slabs; y += 8) {
+    float x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = part[(int64_t)(y + u) * NQB + qb];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) sum += (double)x[u];
+  }
+  for (; y < slabs; ++y) sum += (double)part[(int64_t)y * NQB + qb];
   cov[qb] = (float)(sum / ((double)Hs * n));
 }
 
