@@ -60,24 +60,28 @@ __global__ __launch_bounds__(256) void pool_kernel(const void* __restrict__ Q, c
 }
 
 // Score tiles on the fp32 matrix cores (the selection is taken on fp32 scores, so the operands stay
-// fp32).  One workgroup per (64 query blocks of one sequence, chunk of up to kScChunk * 64 key
+// fp32).  One workgroup per (64 query blocks of one sequence, chunk of up to 2^kScChunkLog * 64 key
 // blocks, selection head): the pooled query tile is staged in LDS once, the pooled key tiles one
 // after the other; each of the four wavefronts keeps 16 query rows in registers and computes the
 // four 16 x 16 tiles of its rows in every 64 x 64 score tile.  Tiles right of the diagonal are
 // -infinity without being computed, and the last chunk of a row tile also fills every column to
 // its right with -infinity, so that the whole n x n matrix is defined.  Splitting the columns over
 // workgroups keeps the longest workgroup short however long the sequence is.
-constexpr int kScChunk = 4;
+// A key tile takes a workgroup 2 us, so where four to a workgroup make fewer workgroups than the chip runs at once, each gets one
+// (18889 tokens, 32/8 heads: 27 -> 21 us, 26565 tokens in several sequences, 16/2 heads: 22 -> 17); otherwise four, which share the staged query tile.
+constexpr int kScChunkLog = 2;
+constexpr int64_t kScFewWgs = 512;
 
-// workgroups of a sequence with nt row tiles: sum over it < nt of (it / kScChunk + 1)
-__host__ __device__ inline int64_t score_items(int64_t nt) {
-  const int64_t q = nt / kScChunk, r = nt % kScChunk;
-  return kScChunk * q * (q + 1) / 2 + r * (q + 1);
+// workgroups of a sequence with nt row tiles, 2^lg key tiles each: sum over it < nt of (it / 2^lg + 1)
+__host__ __device__ inline int64_t score_items(int64_t nt, int lg) {
+  const int64_t q = nt >> lg, r = nt & ((1 << lg) - 1);
+  return ((q * (q + 1) / 2) << lg) + r * (q + 1);
 }
 
-template <int D>
+template <int D, int lg>
 __global__ __launch_bounds__(256) void score_kernel(const float* __restrict__ qbar, const float* __restrict__ kbar, GeomArgs ga, int Hq,
                                                     int Hkv, int Hs, int G, int mode, float scale, float* __restrict__ scores) {
+  constexpr int chunk = 1 << lg;
   constexpr int LD = D + 4;  // padded row length (floats) of the LDS tiles
   __shared__ float qs[64 * LD];
   __shared__ float ks[64 * LD];
@@ -85,13 +89,13 @@ __global__ __launch_bounds__(256) void score_kernel(const float* __restrict__ qb
   // (sequence, row tile, column chunk) of this workgroup
   const BatchGeom bg(ga);
   int64_t x = blockIdx.x;
-  const int s = bg.locate(x, [](int n) { return score_items((n + 63) >> 6); });
+  const int s = bg.locate(x, [](int n) { return score_items((n + 63) >> 6, lg); });
   if (s >= ga.S) return;
-  // row tile `it` starts at item score_items(it), with it / kScChunk + 1 chunks: about sqrt(2 kScChunk x), then corrected
-  int it = (int)sqrtf(2.f * kScChunk * (float)x);
-  while (it > 0 && score_items(it) > x) --it;
-  while (score_items(it + 1) <= x) ++it;
-  const int jc = (int)(x - score_items(it));
+  // row tile `it` starts at item score_items(it), with it / chunk + 1 chunks: about sqrt(2 chunk x), then corrected
+  int it = (int)sqrtf(2.f * chunk * (float)x);
+  while (it > 0 && score_items(it, lg) > x) --it;
+  while (score_items(it + 1, lg) <= x) ++it;
+  const int jc = (int)(x - score_items(it, lg));
   const int hs = blockIdx.y;
   const SeqGeom sg = bg.get(s);
   const int n = sg.n;
@@ -131,9 +135,9 @@ __global__ __launch_bounds__(256) void score_kernel(const float* __restrict__ qb
     }
   };
   auto computed = [&](int jt) { return jt * 64 < n && jt <= it; };  // key tiles that are multiplied (a prefix of the chunk)
-  if (computed(jc * kScChunk)) fetch(jc * kScChunk);
-  for (int c = 0; c < kScChunk; ++c) {
-    const int jt = jc * kScChunk + c, j0 = jt * 64;
+  if (computed(jc * chunk)) fetch(jc * chunk);
+  for (int c = 0; c < chunk; ++c) {
+    const int jt = jc * chunk + c, j0 = jt * 64;
     if (j0 >= n) break;
     if (jt > it) {  // entirely in the future of these rows
       for (int u = tid; u < rows * 64; u += 256) {
@@ -152,7 +156,7 @@ __global__ __launch_bounds__(256) void score_kernel(const float* __restrict__ qb
       const int u = tid + 256 * x, r = u / (D / 4), cc = (u % (D / 4)) * 4;
       *(float4*)(ks + r * LD + cc) = pf[x];
     }
-    if (c + 1 < kScChunk && computed(jt + 1)) fetch(jt + 1);
+    if (c + 1 < chunk && computed(jt + 1)) fetch(jt + 1);
     __syncthreads();
 #pragma unroll
     for (int c4 = 0; c4 < 4; ++c4) {
@@ -173,8 +177,8 @@ __global__ __launch_bounds__(256) void score_kernel(const float* __restrict__ qb
       }
     }
   }
-  if (jc == it / kScChunk) {  // last chunk of this row tile: every column to its right is in the future
-    const int jstart = (jc + 1) * kScChunk * 64;
+  if (jc == it >> lg) {  // last chunk of this row tile: every column to its right is in the future
+    const int jstart = (jc + 1) * chunk * 64;
     for (int r = 0; r < rows; ++r)
       for (int j = jstart + tid; j < n; j += 256) out[(int64_t)(i0 + r) * n + j] = ninf;
   }
@@ -222,19 +226,29 @@ extern "C" int sb_block_scores(const sb_problem* p, const void* q, const void* k
   const GeomArgs ga = make_geom_args(g, p, make_tables(g, p, ws));
   float *qbar = nullptr, *kbar = nullptr;
   if ((rc = launch_pool(g, ga, q, k, kbar_out, ws, st, &qbar, &kbar)) != SB_OK) return rc;
-  int64_t items = 0;  // (sequence, row tile, column chunk) triples
-  for (int s = 0; s < g.S; ++s) {
-    const int64_t L = (int64_t)p->cu_seqlens_host[s + 1] - p->cu_seqlens_host[s];
-    const int64_t n = (L + g.B - 1) / g.B;
-    items += score_items((n + 63) / 64);
-  }
+  auto count = [&](int lg) {  // (sequence, row tile, column chunk) triples
+    int64_t items = 0;
+    for (int s = 0; s < g.S; ++s) {
+      const int64_t L = (int64_t)p->cu_seqlens_host[s + 1] - p->cu_seqlens_host[s];
+      const int64_t n = (L + g.B - 1) / g.B;
+      items += score_items((n + 63) / 64, lg);
+    }
+    return items;
+  };
+  int lg = kScChunkLog;
+  int64_t items = count(lg);
+  if (items * g.Hs < kScFewWgs) items = count(lg = 0);
   if (items > 0x7fffffffll) { set_error("too many score tiles for one launch"); return SB_ERR_INVALID_ARG; }
   dim3 gs((unsigned)items, (unsigned)g.Hs);
   KernelTimer kt(K_SCORE, st);
-  if (g.D == 128)
-    hipLaunchKernelGGL(score_kernel<128>, gs, dim3(256), 0, st, qbar, kbar, ga, g.Hq, g.Hkv, g.Hs, g.G, g.mode, g.score_scale, scores_out);
-  else
-    hipLaunchKernelGGL(score_kernel<64>, gs, dim3(256), 0, st, qbar, kbar, ga, g.Hq, g.Hkv, g.Hs, g.G, g.mode, g.score_scale, scores_out);
+#define SB_SCORE_LAUNCH(DD, LG) \
+  hipLaunchKernelGGL((score_kernel<DD, LG>), gs, dim3(256), 0, st, qbar, kbar, ga, g.Hq, g.Hkv, g.Hs, g.G, g.mode, g.score_scale, scores_out)
+  if (g.D == 128) {
+    if (lg == 0) SB_SCORE_LAUNCH(128, 0); else SB_SCORE_LAUNCH(128, kScChunkLog);
+  } else {
+    if (lg == 0) SB_SCORE_LAUNCH(64, 0); else SB_SCORE_LAUNCH(64, kScChunkLog);
+  }
+#undef SB_SCORE_LAUNCH
   SB_LAUNCH_CHECK("score_kernel");
   return SB_OK;
 }
