@@ -153,19 +153,54 @@ __global__ __launch_bounds__(256) void coverage_rows_kernel(const float* __restr
 // The same rows for sequences of at most kCovRegMax blocks, sorted in registers: one wavefront per (row, selection
 // head), 64 E = N keys (N the row length rounded up to a power of two, at least 64), E per lane.  Key number lane * E + r
 // of the bitonic network lives in register r of the lane, so the compare-exchanges at distances below E stay inside a lane
-// (two instructions per pair, no memory) and only those at distances E and above cross lanes (one permute each); a
-// wavefront alone needs no barrier.  A block of the network that sorts ascending is handled by negating its lanes' keys,
+// (two instructions per pair, no memory) and only those at distances E and above cross lanes (cross_stage); a wavefront alone needs no
+// barrier.  Keys are integers of the scores' order.  A block of the network that sorts ascending is handled by inverting its lanes' keys,
 // so that every compare-exchange puts the larger key first.  The four wavefronts of a workgroup take the heads of the
 // group in turn, keep their sums in registers and add them in wavefront order at the end: fixed summation order again.
-// Scores must be numbers (a NaN is dropped by the max/min of a compare-exchange); sb_block_scores writes none for finite
-// inputs.
+// Scores must be numbers (a NaN counts as -infinity); sb_block_scores writes none for finite inputs.
 constexpr int kCovRegMax = 2048;
+
+// Scores as integers of the same order (and back): integer comparisons take a partner lane's key as an operand (DPP) as it is, float
+// ones would first quiet a NaN in it.
+__device__ __forceinline__ int ordered(int bits) { return bits ^ ((bits >> 31) & 0x7fffffff); }
+template <int CTRL>
+__device__ __forceinline__ int dpp(int x) {
+  return __builtin_amdgcn_mov_dpp(x, CTRL, 0xf, 0xf, true);
+}
+// One stage of the network across lanes: lane l against lane l ^ d, lanes with (l & d) == 0 keep the larger key.  No LDS: at distances 1, 2
+// and 8 the partner's key is an operand of the comparison, at 4 one move away; at 16 and 32 two registers swap halves, so that each
+// then holds one side of every pair, are compared with each other and swap back.
+template <int E, int D_>
+__device__ __forceinline__ void cross_stage(int (&x)[E], int lane) {
+  if constexpr (D_ >= 16 && E > 1) {
+#pragma unroll
+    for (int r = 0; r < E; r += 2) {
+      const auto s = D_ == 32 ? __builtin_amdgcn_permlane32_swap(x[r], x[r + 1], false, false) : __builtin_amdgcn_permlane16_swap(x[r], x[r + 1], false, false);
+      const int hi = max((int)s[0], (int)s[1]), lo = min((int)s[0], (int)s[1]);
+      const auto u = D_ == 32 ? __builtin_amdgcn_permlane32_swap(hi, lo, false, false) : __builtin_amdgcn_permlane16_swap(hi, lo, false, false);
+      x[r] = (int)u[0];
+      x[r + 1] = (int)u[1];
+    }
+  } else {
+    const bool first = (lane & D_) == 0;
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+      int hi, lo;
+      if constexpr (D_ == 1) { hi = max(dpp<0xB1>(x[r]), x[r]); lo = min(dpp<0xB1>(x[r]), x[r]); }
+      else if constexpr (D_ == 2) { hi = max(dpp<0x4E>(x[r]), x[r]); lo = min(dpp<0x4E>(x[r]), x[r]); }
+      else if constexpr (D_ == 4) { const int m = dpp<0x141>(x[r]); hi = max(dpp<0x1B>(m), x[r]); lo = min(dpp<0x1B>(m), x[r]); }
+      else if constexpr (D_ == 8) { hi = max(dpp<0x128>(x[r]), x[r]); lo = min(dpp<0x128>(x[r]), x[r]); }
+      else { const int m = __builtin_amdgcn_ds_bpermute((lane ^ D_) << 2, x[r]); hi = max(m, x[r]); lo = min(m, x[r]); }
+      x[r] = first ? hi : lo;
+    }
+  }
+}
 
 template <int E>
 __device__ __forceinline__ void coverage_row_regs(const float* __restrict__ row, int i, int lane, float (&acc)[E]) {
-  float x[E];
+  int x[E];
 #pragma unroll
-  for (int r = 0; r < E; ++r) x[r] = r * 64 + lane < i ? row[r * 64 + lane] : -INFINITY;  // any initial placement will do
+  for (int r = 0; r < E; ++r) x[r] = ordered(__float_as_int(fmaxf(r * 64 + lane < i ? row[r * 64 + lane] : -INFINITY, -INFINITY)));  // any placement will do
   // phases k2 = 2 .. E/2: inside a lane, directions known at compile time (bit k2 of r)
 #pragma unroll
   for (int k2 = 2; k2 < E; k2 <<= 1) {
@@ -174,7 +209,7 @@ __device__ __forceinline__ void coverage_row_regs(const float* __restrict__ row,
 #pragma unroll
       for (int r = 0; r < E; ++r) {
         if ((r & j2) == 0) {
-          const float hi = fmaxf(x[r], x[r | j2]), lo = fminf(x[r], x[r | j2]);
+          const int hi = max(x[r], x[r | j2]), lo = min(x[r], x[r | j2]);
           const bool desc = (r & k2) == 0;
           x[r] = desc ? hi : lo;
           x[r | j2] = desc ? lo : hi;
@@ -183,38 +218,28 @@ __device__ __forceinline__ void coverage_row_regs(const float* __restrict__ row,
       __builtin_amdgcn_sched_barrier(0);  // (left alone, the scheduler interleaves the stages and triples the register count)
     }
   }
-  // phases k2 = E .. 64 E: the direction is bit k2 / E of the lane; ascending lanes work on negated keys
-  bool negated = false;
+  // phases k2 = E .. 64 E: the direction is bit k2 / E of the lane; ascending lanes work on inverted keys
+  bool inverted = false;
 #pragma unroll 1
   for (int t = (E > 1 ? 0 : 1); t <= 6; ++t) {
     const bool want = ((lane >> t) & 1) != 0 && t < 6;  // (the last phase, k2 = N, is descending everywhere)
-    const uint32_t flip = want != negated ? 0x80000000u : 0u;
-    negated = want;
+    const int flip = want != inverted ? -1 : 0;
+    inverted = want;
 #pragma unroll
-    for (int r = 0; r < E; ++r) x[r] = __uint_as_float(__float_as_uint(x[r]) ^ flip);
-    for (int d = (1 << t) >> 1; d > 0; d >>= 1) {  // distances d * E: lane l against lane l ^ d
-      const int partner = (lane ^ d) << 2;
-      const bool first = (lane & d) == 0;
-      constexpr int C = E < 8 ? E : 8;  // registers exchanged at a time (keeps the values in flight few)
-#pragma unroll
-      for (int r0 = 0; r0 < E; r0 += C) {
-        float y[C];
-#pragma unroll
-        for (int r = 0; r < C; ++r) y[r] = __int_as_float(__builtin_amdgcn_ds_bpermute(partner, __float_as_int(x[r0 + r])));
-#pragma unroll
-        for (int r = 0; r < C; ++r) {
-          const float hi = fmaxf(x[r0 + r], y[r]), lo = fminf(x[r0 + r], y[r]);
-          x[r0 + r] = first ? hi : lo;
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
+    for (int r = 0; r < E; ++r) x[r] ^= flip;
+    // distances d * E, d = 2^(t-1) .. 1
+    if (t >= 6) { cross_stage<E, 32>(x, lane); __builtin_amdgcn_sched_barrier(0); }
+    if (t >= 5) { cross_stage<E, 16>(x, lane); __builtin_amdgcn_sched_barrier(0); }
+    if (t >= 4) { cross_stage<E, 8>(x, lane); __builtin_amdgcn_sched_barrier(0); }
+    if (t >= 3) { cross_stage<E, 4>(x, lane); __builtin_amdgcn_sched_barrier(0); }
+    if (t >= 2) { cross_stage<E, 2>(x, lane); __builtin_amdgcn_sched_barrier(0); }
+    if (t >= 1) { cross_stage<E, 1>(x, lane); __builtin_amdgcn_sched_barrier(0); }
 #pragma unroll
     for (int j2 = E >> 1; j2 > 0; j2 >>= 1) {
 #pragma unroll
       for (int r = 0; r < E; ++r) {
         if ((r & j2) == 0) {
-          const float hi = fmaxf(x[r], x[r | j2]), lo = fminf(x[r], x[r | j2]);
+          const int hi = max(x[r], x[r | j2]), lo = min(x[r], x[r | j2]);
           x[r] = hi;
           x[r | j2] = lo;
         }
@@ -223,12 +248,12 @@ __device__ __forceinline__ void coverage_row_regs(const float* __restrict__ row,
     }
   }
   // shares in sorted order (key 0 is the row maximum), their running sum, the coverage of every prefix
-  const float mx = __shfl(x[0], 0, 64);
-  float run = 0.f;
+  const float mx = __int_as_float(ordered(__shfl(x[0], 0, 64)));
+  float run = 0.f, e[E];
 #pragma unroll
   for (int r = 0; r < E; ++r) {
-    x[r] = lane * E + r < i ? __expf(x[r] - mx) : 0.f;
-    run += x[r];
+    e[r] = lane * E + r < i ? __expf(__int_as_float(ordered(x[r])) - mx) : 0.f;
+    run += e[r];
   }
   float incl = run;
 #pragma unroll
@@ -241,7 +266,7 @@ __device__ __forceinline__ void coverage_row_regs(const float* __restrict__ row,
 #pragma unroll
   for (int r = 0; r < E; ++r) {
     const int p = lane * E + r;
-    run += x[r];
+    run += e[r];
     if (p < i) acc[r] += p == i - 1 ? 1.0f : run * inv;
   }
 }
@@ -261,7 +286,7 @@ __device__ __forceinline__ void coverage_rows_regs_body(const float* __restrict_
     out[p] = ((part[p] + part[kCovRegMax + p]) + part[2 * kCovRegMax + p]) + part[3 * kCovRegMax + p];
 }
 
-__global__ __launch_bounds__(256) void coverage_rows_regs_kernel(const float* __restrict__ scores, const int32_t* __restrict__ qb_off,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void coverage_rows_regs_kernel(const float* __restrict__ scores, const int32_t* __restrict__ qb_off,
                                                                  const int64_t* __restrict__ sc_off, const int32_t* __restrict__ qb_seq,
                                                                  int Hs, int64_t slab, float* __restrict__ pacc) {
   __shared__ float part[4 * kCovRegMax];
