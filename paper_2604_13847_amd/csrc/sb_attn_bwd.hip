@@ -664,9 +664,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64
 // stages after they were started, and the tile loads are issued two at a time between matrix instructions instead of 17 in a
 // row.  The scores are kept out of the accumulation registers (mfma32_first).  32768-token batch, 32/8 heads, D = 128:
 // 3.66 -> 3.24 ms (matrix cores busy 48 -> 57 % of the cycles), the 262144-token batch, whose gathers come through the fabric at
-// 6 TB/s: 36.7 -> 34.9 ms.  The compiler spills 16 vector and 165 scalar registers for it (before: none and 127).  The loop over the
-// unmasked tiles has no reload of the former and two of the latter; the others are in what is done once per chunk and in a chunk's first
-// tile, and count for columns of few tiles.
+// 6 TB/s: 36.7 -> 34.9 ms.  A scalar instruction takes as long to issue as a vector one here: with a half tile's two resources put
+// together once from the tile's addresses, instead of before every pair of loads (50 scalar instructions a tile, before: 110), 3.25 ->
+// 3.06 and 35.8 -> 34.3 ms.  The compiler spills 16 vector and 176 scalar registers.  The loop over the unmasked tiles has no reload of
+// the former and eight a tile of the latter; the others are in what is done once per chunk and in a chunk's first tile, and count for
+// columns of few tiles.  One wait per half stage for its LDS operands, instead of one before each matrix instruction: the same time.
 // D = 64 needs half the registers: there two wavefronts share a SIMD instead, a half tile is computed from start to end, and the
 // shorter tile list (8 bitmap words per chunk) lets four workgroups share a CU's LDS.  Matrix cores busy 34 -> 48 %, at a clock that
 // the chip lowers from 1.86 to 1.62 GHz for it; together with the forward kernel's second wavefront per SIMD a step of 65536 tokens,
