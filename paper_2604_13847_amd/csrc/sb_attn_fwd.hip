@@ -113,9 +113,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64
   f32x16 oacc[D / 32][2];
 #pragma unroll
   for (int dt = 0; dt < D / 32; ++dt) oacc[dt][0] = oacc[dt][1] = zero16();
-  // m: reference of the exponent, neg_m = -m * scale * log2 e.  Before a query's first tile neg_m is +inf, so that the first sum of
-  // probabilities fails the check below and m is set there.
-  float m[2] = {-__builtin_inff(), -__builtin_inff()}, l[2] = {0.f, 0.f}, neg_m[2] = {__builtin_inff(), __builtin_inff()};
+  // m: reference of the exponent, neg_m = -m * scale * log2 e.  As long as a query has seen no score above -inf, m is -inf and neg_m the
+  // largest number: a score of -inf then has probability 0, and the first finite one an infinite one, which fails the check below and
+  // sets m there.
+  constexpr float kNone = __FLT_MAX__;
+  float m[2] = {-__builtin_inff(), -__builtin_inff()}, l[2] = {0.f, 0.f}, neg_m[2] = {kNone, kNone};
 #pragma unroll
   for (int k = 0; k < NOP; ++k) { ka[k] = ld_row(k, 0); vt[k] = zero_bf16x8(); }
   __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): K_0 has been read
@@ -165,10 +167,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64
       const bool first = m[b] == -__builtin_inff();  // nothing accumulated yet for this query: nothing to rescale
       const bool move = first | ((mx - m[b]) * P.scale_log2e > kLazy);
       const float m_new = move ? fmaxf(m[b], mx) : m[b];
-      // a wavefront may have seen no unmasked key yet for a query: keep the exponent finite then
-      const float m_use = m_new == -__builtin_inff() ? 0.f : m_new;
-      const float alpha = first ? 1.0f : fast_exp2((m[b] - m_use) * P.scale_log2e);
-      neg_m[b] = -m_use * P.scale_log2e;
+      const float alpha = first ? 1.0f : fast_exp2((m[b] - m_new) * P.scale_log2e);
+      neg_m[b] = m_new == -__builtin_inff() ? kNone : -m_new * P.scale_log2e;
       l[b] *= alpha;
       m[b] = m_new;
       if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
@@ -327,7 +327,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64
       const int rows = min(32, L - i * 64 - 32 * b);
       store_rows<D, OUT_F32>(&ring[0][b * 2 * STRIP_B], P.o, (tq * P.Hq + h) * D, (int64_t)P.Hq * D, rows, lane,
                              [&](int dt, int v) __attribute__((always_inline)) { return oacc[dt][b][v] * inv; });
-      if (hf == 0 && l32 < rows) P.lse[(int64_t)h * P.T + tq + l32] = (m[b] * P.scale_log2e + __builtin_log2f(l[b])) * 0.69314718055994531f;
+      // (a row without any score above -inf has no softmax: NaN, as the merge below makes of it)
+      const float lse = l[b] > 0.f ? (m[b] * P.scale_log2e + __builtin_log2f(l[b])) * 0.69314718055994531f : __builtin_nanf("");
+      if (hf == 0 && l32 < rows) P.lse[(int64_t)h * P.T + tq + l32] = lse;
     }
   } else {
     // ---- merge the two key halves: wavefront w finalises query half w and hands the other half over

@@ -7,6 +7,7 @@ import torch
 
 from helpers import Run, check_close, check_lse, to_host_f32
 from oracle import oracle as orc
+from paper_2604_13847_amd import binding as sb
 from paper_2604_13847_amd import synth
 
 pytestmark = pytest.mark.gpu
@@ -68,3 +69,46 @@ def test_scores_that_outgrow_the_reference(Hq, Hkv, D, jump):
     w.tensors = lambda: t
     w.seed = 1000 + w.seed + int(jump) + D  # (the arrays of a workload are kept by its seed)
     check(w, 0, bwd=False)
+
+
+# Ten-, nine- and one-block sequences: few heads, two wavefronts per item; many, one (tests/test_launch_variants.py holds them to it).
+# Four query heads per KV head: an element of dK and dV adds the roundings of every head's rows, sqrt(heads) times one head's, which with
+# sixteen reaches 1.1 of the elementwise bound whatever the forward does.
+SHORT = (64 * 9 + 17, 64 * 9, 40)
+ONE_WAVEFRONT = [(0, 64, 16, 128), (0, 128, 32, 64)]
+TWO_WAVEFRONTS = [(0, 4, 2, 128), (0, 4, 2, 64)]
+
+
+@pytest.mark.parametrize("masked", [32, 64])
+@pytest.mark.parametrize("mode,Hq,Hkv,D", ONE_WAVEFRONT + TWO_WAVEFRONTS + [(1, 8, 2, 128)])
+def test_first_keys_that_score_minus_infinity(mode, Hq, Hkv, D, masked):
+    """Channel 0 masks the first keys of every sequence: 16384 in the queries from the second block on times -1e35 in these keys is
+    beyond float32, 0 in all others.  So the first strip or the first tile of those rows adds nothing, and the softmax's reference comes
+    from a later one.  The channel's own gradients are sums of such numbers and are left out."""
+    w = synth.Workload("masked", SHORT, Hq, Hkv, D, topk=[10, 9, 1], seed=350 + Hq + masked)
+    t = w.tensors()
+    for s, L in enumerate(SHORT):
+        at = int(w.cu[s])
+        t["q"][at:at + L, :, 0] = np.where(np.arange(L) < 64, 0.0, 16384.0)[:, None]
+        t["k"][at:at + L, :, 0] = np.where(np.arange(L) < masked, -1e35, 0.0)[:, None]
+    t = {n: synth.round_to_bf16(x) for n, x in t.items()}
+    w.tensors = lambda: t
+    w.seed += 2000 + D  # (the arrays of a workload are kept by its seed)
+    r = Run(w, mode)
+    q, k, v, do = r.oracle_inputs()
+    O, LSE = orc.attn_fwd(r.opb, q, k, v, r.rowptr_h, r.idx_h, r.scale)
+    stats = [check_close("O", to_host_f32(r.o), O), check_lse(r.lse.cpu().numpy(), LSE)]
+    for name, got, ref in zip(("dQ", "dK", "dV"), (r.dq, r.dk, r.dv), orc.attn_bwd(r.opb, q, k, v, do, r.rowptr_h, r.idx_h, r.scale)):
+        first = 0 if name == "dV" else 1
+        stats.append(check_close(name, to_host_f32(got)[..., first:], ref[..., first:]))
+    # the channel on in all queries: rows whose keys are all masked have no softmax, the others are what they were
+    q = r.q.clone()
+    q[:, :, 0] = 16384.0
+    o, lse = sb.sb_sparse_attn_fwd(r.pb, q, r.k, r.v, r.rowptr, r.idx, r.plan)
+    empty, same = np.zeros(w.T, dtype=bool), np.zeros(w.T, dtype=bool)
+    for s, L in enumerate(SHORT):
+        empty[w.cu[s]:w.cu[s] + min(L, masked)] = True
+        same[w.cu[s] + min(L, 64):w.cu[s + 1]] = True
+    assert bool(torch.isnan(o[empty]).all()) and not bool(torch.isfinite(lse[:, empty]).any())
+    assert torch.equal(o[same], r.o[same]) and torch.equal(lse[:, same], r.lse[:, same])
+    print(w, stats, flush=True)

@@ -1,0 +1,54 @@
+"""Which form of a kernel a problem takes is decided by its sizes.  The tests on the GPU that mean one form by their shapes are held to
+it here, in a process whose HIP launch calls only write down what would be launched (CPU only; no buffer is read)."""
+import json
+import os
+import re
+import subprocess
+import sys
+
+import pytest
+
+import test_gpu_head_rows as rows
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+CALLS = """
+import ctypes as C, json, sys
+shim = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)
+shim.recorded_kernel.restype = C.c_char_p
+import numpy as np
+from paper_2604_13847_amd import binding as sb
+lens, topk, mode, Hq, Hkv, D = json.loads(sys.argv[2])
+pb = sb.Problem(np.concatenate([[0], np.cumsum(lens)]), topk, Hq, Hkv, D, select_mode=mode)
+pb.c.cu_seqlens_dev = pb.c.topk_dev = 4096
+b, lib, p = C.c_void_p(4096), sb.lib(), pb.ref()
+sb._check(lib.sb_sparse_attn_fwd(p, b, b, b, b, b, b, b, b, b, None))
+sb._check(lib.sb_sparse_attn_bwd(p, b, b, b, b, b, b, b, b, b, b, b, b, b, None))
+for i in range(shim.recorded_launches(np.zeros((256, 6), dtype=np.uint32).ctypes.data_as(C.c_void_p))):
+    print("kernel", shim.recorded_kernel(i).decode())
+"""
+
+
+@pytest.fixture(scope="module")
+def query_major(tmp_path_factory):
+    """(lens, topk, mode, Hq, Hkv, D) -> wavefronts per item of the forward and of dQ (4: the kernel for few items) and whether items
+    are handed out by ticket."""
+    shim = str(tmp_path_factory.mktemp("launch") / "record_launches.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", shim, os.path.join(ROOT, "tests", "launch", "record_launches.c")], check=True)
+
+    def of(*problem):
+        r = subprocess.run([sys.executable, "-c", CALLS, shim, json.dumps(problem)], cwd=ROOT, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        assert r.returncode == 0, r.stdout[-3000:]
+        names = [l.split()[1] for l in r.stdout.splitlines() if l.startswith("kernel ")]
+        fwd = [m[1] for n in names if (m := re.search(r"attn_fwd_head_kernelILi\d+ELb[01]ELi(\d)E", n))]
+        dq = [m[1] for n in names if (m := re.search(r"attn_bwd_dq_head_kernelILi\d+ELb[01]ELi(\d)E", n))] + ["4" for n in names if "attn_bwd_dq_kernel" in n]
+        assert len(fwd) == len(dq) == 1, names
+        return int(fwd[0]), int(dq[0]), any("fill" in n for n in names)
+
+    return of
+
+
+@pytest.mark.parametrize("shape", rows.ONE_WAVEFRONT + rows.TWO_WAVEFRONTS)
+def test_short_sequences(query_major, shape):
+    fwd, dq, _ = query_major(rows.SHORT, [10, 9, 1], *shape)
+    assert (fwd, dq) == ((1, 1) if shape in rows.ONE_WAVEFRONT else (2, 2 if shape[3] == 128 else 4))
