@@ -541,6 +541,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64
         else mfma32_more_v(dpacc, va[k], dof[B][k]);
       }
       if (B == 1 && !LAST) va[k] = ld_row(k, (2 + (PAR ^ 1)) * STRIP_B);
+      // (two matrix instructions after the last of S before its first reader, see mfma32_first: of the two at D = 64 the compiler would put
+      // the reader ahead of the second)
+      if (D == 64 && k == NOP / 4) SB_FENCE();
       if (SEEN && k >= NOP / 4) {  // 0 .. 5
 #pragma unroll
         for (int a = 0; a < PER; ++a) prob(diag_c, key0, B, PER * (k - NOP / 4) + a);

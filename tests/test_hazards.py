@@ -1,6 +1,11 @@
-"""The attention kernels issue buffer loads from inline assembly, where the compiler does not look for hazards: a scalar register written by a
-vector instruction (v_readlane, v_readfirstlane) must not be read by a vector-memory instruction within five wait states.  The
-assembly that the compiler makes of the present sources is scanned for it."""
+"""The attention kernels issue matrix instructions and loads from inline assembly, where the compiler does not look for hazards.  The
+assembly that it makes of the present sources is scanned, along every branch, for the three distances that the sources keep by hand:
+
+  a scalar register written by a vector instruction (v_readlane, v_readfirstlane)   5 wait states before a load or store reads it
+  a vector register written by a vector instruction                                2 before a matrix instruction reads it
+  the result of a matrix instruction                                              12 before anything but the sum it is part of touches it
+
+An instruction is one wait state, s_nop N is N + 1, and a matrix instruction of these kernels (8 passes) holds the next one back by 8."""
 import os
 import re
 import subprocess
@@ -9,40 +14,129 @@ import pytest
 
 from paper_2604_13847_amd import build
 
-WAIT_STATES = 5
-LOAD = re.compile(r"buffer_load_dword\S* v\d+, s\[(\d+):(\d+)\], 0 offen")
-WRITE = re.compile(r"v_read(?:lane|firstlane)_b32 s(\d+),")
+SCALAR, OPERAND, RESULT = 5, 2, 12
+PASSES = 8
+MFMA = "v_mfma_f32_32x32x16_bf16"
+REGISTERS = re.compile(r"(?<![\w.])([avs])(?:(\d+)|\[(\d+):(\d+)\])(?!\w)")
 
 
-def hazards(lines):
-    seen, loads, bad = [], 0, []
-    for line in (l.strip() for l in lines):
-        if not line or line[0] in ";.":
+def registers(operands):
+    return {m[1] + str(i) for x in operands for m in REGISTERS.finditer(x) for i in range(int(m[2] or m[3]), int(m[2] or m[4]) + 1)}
+
+
+class Instruction:
+    def __init__(self, text):
+        self.text = text
+        self.op, _, rest = text.partition(" ")
+        x = self.operands = [o.strip() for o in re.split(r",(?![^\[]*\])", rest)] if rest else []
+        self.matrix = self.op.startswith("v_mfma")
+        self.memory = bool(re.match(r"(buffer|global|flat|scratch|ds)_", self.op))
+        self.vector = self.op.startswith("v_") and not self.matrix
+        written = 2 if "_swap_" in self.op else 0 if re.search(r"_(store|write)", self.op) and self.memory or rest.endswith(" lds") else 1
+        self.writes = registers(x[:written])
+        self.touches = registers(x)
+        self.states = int(x[0]) + 1 if self.op == "s_nop" else 1
+        assert not self.matrix or self.op == MFMA, text  # PASSES and RESULT are this one's
+
+
+def kernels(lines):
+    """(name, instructions, {label: index}) of every function."""
+    name, code, labels = None, [], {}
+    for line in (l.split(";")[0].strip() for l in lines):
+        m = re.match(r"([\w.$]+):$", line)
+        if m and m[1].startswith("_Z"):
+            if code:
+                yield name, code, labels
+            name, code, labels = m[1], [], {}
+        elif m:
+            labels[m[1]] = len(code)
+        elif line and line[0] != "." and name:
+            code.append(Instruction(line.replace("\t", " ")))
+    if code:
+        yield name, code, labels
+
+
+def hazards(code, labels):
+    """[(what, wait states, instruction, the one that is too close)]"""
+    def after(i):
+        x = code[i]
+        if x.op == "s_endpgm":
+            return []
+        target = [labels[x.operands[0]]] if x.op.startswith(("s_branch", "s_cbranch")) else []
+        return target + ([i + 1] if x.op != "s_branch" and i + 1 < len(code) else [])
+
+    found = []
+    for i, x in enumerate(code):
+        if x.matrix:
+            what, need, watch = "result", RESULT, x.writes
+        elif x.vector:
+            scalars = {r for r in x.writes if r[0] == "s"}
+            what, need, watch = ("scalar", SCALAR, scalars) if scalars else ("operand", OPERAND, x.writes)
+        else:
             continue
-        m = LOAD.match(line)
-        if m:
-            loads += 1
-            states = 0
-            for before in reversed(seen[-WAIT_STATES:]):
-                w = WRITE.match(before)
-                if w and int(m[1]) <= int(w[1]) <= int(m[2]) and states < WAIT_STATES:
-                    bad.append((before, line, states))
-                nop = re.match(r"s_nop (\d+)", before)
-                states += int(nop[1]) + 1 if nop else 1
-        seen.append(line)
-    return loads, bad
+        # (index, states since x was issued, when the last matrix instruction was, registers of x not written again since)
+        todo, seen = [(j, 1, 0 if x.matrix else -PASSES, frozenset(watch)) for j in after(i)], set()
+        while todo:
+            j, at, matrix_at, left = state = todo.pop()
+            if state in seen or not left:
+                continue
+            seen.add(state)
+            y = code[j]
+            if y.matrix:
+                at = matrix_at = max(at, matrix_at + PASSES)
+            if at - 1 >= need:
+                continue
+            if what == "scalar":
+                close = y.memory and y.touches & left
+            elif what == "operand":
+                close = y.matrix and registers(y.operands[1:]) & left
+            elif y.matrix:  # the next product of the same sum needs no wait
+                close = registers(y.operands[1:3]) & left or (registers(y.operands[3:]) & left and y.operands[3] != x.operands[0])
+            else:
+                close = (y.vector or y.memory) and y.touches & left
+            if close:
+                found.append((what, at - 1, x.text, y.text))
+            else:
+                todo += [(n, at + y.states, matrix_at, left - y.writes) for n in after(j)]
+    return found
+
+
+def scan(*text):
+    (_, code, labels), = kernels(["_Zkernel:", *text, "s_endpgm"])
+    return [h[0] for h in hazards(code, labels)]
 
 
 def test_the_scan_sees_a_hazard():
     load = "buffer_load_dwordx4 v1, s[20:23], 0 offen offset:0 lds"
-    assert hazards(["v_readlane_b32 s22, v1, 3", "s_nop 2", load])[1]
-    assert not hazards(["v_readlane_b32 s22, v1, 3", "s_nop 4", load])[1]
-    assert not hazards(["v_readlane_b32 s24, v1, 3", load])[1]
+    assert scan("v_readlane_b32 s22, v1, 3", "s_nop 2", load) == ["scalar"]
+    assert not scan("v_readlane_b32 s22, v1, 3", "s_nop 4", load)
+    assert not scan("v_readlane_b32 s24, v1, 3", load)
+    assert scan("v_readfirstlane_b32 s3, v1", "global_load_lds_dwordx4 v1, s[2:3] offset:1024") == ["scalar"]
+    # at the end of a loop, with the load at its head, and in front of a branch to the load
+    assert scan(".LBB0_1:", load, "v_readlane_b32 s22, v1, 3", "s_cbranch_scc1 .LBB0_1") == ["scalar"]
+    assert scan("v_readlane_b32 s22, v1, 3", "s_branch .LBB0_2", "s_nop 9", ".LBB0_2:", load) == ["scalar"]
+
+
+def test_the_scan_sees_the_matrix_instructions():
+    product = MFMA + " v[16:31], v[0:3], a[0:3], v[16:31]"
+    other = MFMA + " a[16:31], v[4:7], v[8:11], a[16:31]"
+    read = "v_exp_f32_e32 v40, v20"
+    assert scan(product, read) == ["result"] and scan(product, "s_nop 10", read) == ["result"] and not scan(product, "s_nop 11", read)
+    assert scan(product, other, read) == ["result"] and not scan(product, other, other, read)  # 8 and 16 states
+    assert not scan(product, product) and scan(product, MFMA + " a[16:31], v[28:31], v[8:11], a[16:31]") == ["result"]
+    assert scan("v_cvt_pk_bf16_f32 v9, v40, v41", "s_nop 0", other) == ["operand"]
+    assert not scan("v_cvt_pk_bf16_f32 v9, v40, v41", "s_nop 1", other)
 
 
 @pytest.mark.parametrize("source", ["sb_attn_fwd.hip", "sb_attn_bwd.hip"])
 def test_no_vector_write_right_before_a_load_that_reads_it(source, tmp_path):
+    """... and no operand or result of a matrix instruction too close to it."""
     out = str(tmp_path / "a.s")
     subprocess.run(["hipcc", *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, source), "-o", out], check=True, capture_output=True)
-    loads, bad = hazards(open(out).read().splitlines())
-    assert loads > 100 and not bad, bad[:3]
+    loads = products = 0
+    for name, code, labels in kernels(open(out).read().splitlines()):
+        loads += sum(bool(re.match(r"(buffer_load\S* .* lds$|global_load_lds)", x.text)) for x in code)
+        products += sum(x.matrix for x in code)
+        bad = hazards(code, labels)
+        assert not bad, (name, bad[:3])
+    assert loads > 100 and products > 500
