@@ -18,9 +18,9 @@
 // go with the same vector work, which bounds it; two wavefronts share a SIMD.
 // The fixed part of an item (6 us at D = 128: descriptor 0.7, indices 0.8, first strips and Q 2.0, output 2.7) counts half as much with
 // one wavefront per item as with two.  Against a whole tile's softmax in a row on two wavefronts the forward of: the 32768-token batch,
-// 32/8 heads: 2.05 -> 1.67 ms (with NW = 2: 1.74), one 131072-token sequence, top 32: 7.30 -> 6.24 (6.51), the 262144-token batch 20.3 ->
-// 16.9 (20.7), 65536 tokens whose selection is a sink and a window 2.27 -> 1.75 (1.95); D = 64, 65536 tokens, 14/2 heads, blocks of 256:
-// 1.59 -> 1.44 ms.
+// 32/8 heads: 2.02 -> 1.69 ms (with NW = 2: 1.74), one 131072-token sequence, top 32: 7.32 -> 6.2 (6.60), the 262144-token batch 20.9 ->
+// 17.2 (18.5), 65536 tokens whose selection is a sink and a window 2.28 -> 1.79 (1.95); D = 64, 65536 tokens, 14/2 heads, blocks of 256:
+// 1.59 -> 1.44 ms (there NW = 2).
 #include <type_traits>
 
 #include "sb_attn_common.h"
@@ -30,7 +30,7 @@ namespace sb {
 template <int D, bool OUT_F32, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1))) void attn_fwd_head_kernel(AttnParams P, int n_items, int heads) {
   constexpr int ROW_B = D * 2, STRIP_B = 32 * ROW_B, NOP = D / 16, NV = 3;
-  constexpr float kLazy = 8.0f;
+  constexpr float kLazy = 4.0f;
   using Loader = QuadLoader<D>;
   constexpr int LPS = Loader::LPS;
   // per wavefront: K even, K odd, then V of strip t in slot 2 + t % 3.  Four wavefronts' rings fill a CU's LDS.
@@ -155,31 +155,62 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64
       psum = (part[0] + part[1]) + (part[2] + part[3]);
     }
   };
-  // The reference follows the true maximum lazily: only when a lane's 16 probabilities add up to more than 2^12 (so one of them exceeds
-  // 2^8), which costs one comparison per half tile where the maximum of the scores would cost ten instructions.  The scores are still
-  // there: the reference moves, what has been summed with the old one is rescaled, and the probabilities are computed again.
+  // The reference follows the true maximum lazily: only when a lane's 16 probabilities add up to more than 16 * 2^kLazy (so one of them
+  // exceeds 2^kLazy, and one above 2^8 always does it), which costs one comparison per half tile where the maximum of the scores would
+  // cost ten instructions.  The scores are still there: the reference moves, what has been summed with the old one is rescaled, and the
+  // probabilities are computed again.
+  // The score that becomes the reference has probability 1, which bf16 holds exactly.  Two wavefronts have a reference each, so that two
+  // strips of a row have such a score where one wavefront has one: it adds what rounding took from the strip after the one that moved the
+  // reference (`limit` is negative then, so that the branch is taken), 8 matrix instructions per query half and move: 0.7 us of an item,
+  // 0.5 - 2 % of a launch.  Without it float32 outputs of rows of 1 to 27 tiles were 4 to 6 % further off than two wavefronts' (2-norm), with
+  // it they are 4 to 7 % less.  (Scores of standard deviation 3 and 2^8 for kLazy: 4 % further off with two wavefronts, 9 to 21 % with one.)
+  constexpr float kMost = 16.0f * 16.0f;  // 16 * 2^kLazy
+  float limit[2] = {kMost, kMost};
   auto check = [&](int b) __attribute__((always_inline)) {
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(psum <= 4096.f)) != 0, 0)) {
-      float mx = max3(sacc[b][0], sacc[b][1], sacc[b][2]);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(psum <= limit[b])) != 0, 0)) {
+      int add_rest = __builtin_amdgcn_readfirstlane(limit[b] < 0.f);
+      asm volatile("" : "+s"(add_rest));  // (from here on the old limit is not needed: else the loop would copy it from register to register)
+      limit[b] = kMost;
+      if (NW == 2 || __builtin_amdgcn_ballot_w64(!(psum <= kMost)) != 0) {
+        float mx = max3(sacc[b][0], sacc[b][1], sacc[b][2]);
 #pragma unroll
-      for (int v = 3; v < 15; v += 2) mx = max3(mx, sacc[b][v], sacc[b][v + 1]);
-      mx = max_across_halves(fmaxf(mx, sacc[b][15]));
-      const bool first = m[b] == -__builtin_inff();  // nothing accumulated yet for this query: nothing to rescale
-      const bool move = first | ((mx - m[b]) * P.scale_log2e > kLazy);
-      const float m_new = move ? fmaxf(m[b], mx) : m[b];
-      const float alpha = first ? 1.0f : fast_exp2((m[b] - m_new) * P.scale_log2e);
-      neg_m[b] = m_new == -__builtin_inff() ? kNone : -m_new * P.scale_log2e;
-      l[b] *= alpha;
-      m[b] = m_new;
-      if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+        for (int v = 3; v < 15; v += 2) mx = max3(mx, sacc[b][v], sacc[b][v + 1]);
+        mx = max_across_halves(fmaxf(mx, sacc[b][15]));
+        const bool first = m[b] == -__builtin_inff();  // nothing accumulated yet for this query: nothing to rescale
+        const bool move = first | ((mx - m[b]) * P.scale_log2e > kLazy);
+        const float m_new = move ? fmaxf(m[b], mx) : m[b];
+        const float alpha = first ? 1.0f : fast_exp2((m[b] - m_new) * P.scale_log2e);
+        neg_m[b] = m_new == -__builtin_inff() ? kNone : -m_new * P.scale_log2e;
+        l[b] *= alpha;
+        m[b] = m_new;
+        if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
 #pragma unroll
-        for (int dt = 0; dt < D / 32; ++dt)
+          for (int dt = 0; dt < D / 32; ++dt)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) oacc[dt][b][v] = scale_acc(oacc[dt][b][v], alpha);
+            for (int v = 0; v < 16; ++v) oacc[dt][b][v] = scale_acc(oacc[dt][b][v], alpha);
+        }
+#pragma unroll
+        for (int v = 0; v < 15; ++v) p_step(b, v);
+        if (NW == 1) limit[b] = -1.0f;
       }
+      if (NW == 1 && add_rest) {
+        bf16x8 rest[2];
+        float part[2] = {0.f, 0.f};
 #pragma unroll
-      for (int v = 0; v < 15; ++v) p_step(b, v);
-      asm volatile("s_nop 1" ::: "memory");  // two wait states between a vector write and its use as an operand
+        for (int c = 0; c < 8; ++c) {
+          bf16x2 y;
+          y[0] = (bf16)(px[2 * c] - (float)py[c][0]);
+          y[1] = (bf16)(px[2 * c + 1] - (float)py[c][1]);
+          rest[c >> 2][(2 * c) & 7] = y[0];
+          rest[c >> 2][(2 * c + 1) & 7] = y[1];
+          part[c & 1] = sum2(y, part[c & 1]);
+        }
+        psum += part[0] + part[1];
+        asm volatile("s_nop 1" : "+v"(rest[0]), "+v"(rest[1]));  // two wait states between a vector write and its use as an operand
+#pragma unroll
+        for (int k = 0; k < NOP; ++k) mfma32_sum(oacc[k % (D / 32)][b], vt[k], rest[k / (D / 32)]);
+      }
+      asm volatile("s_nop 1" ::: "memory");  // likewise
     }
     l[b] += psum;
   };

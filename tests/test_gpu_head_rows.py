@@ -112,3 +112,41 @@ def test_first_keys_that_score_minus_infinity(mode, Hq, Hkv, D, masked):
     assert bool(torch.isnan(o[empty]).all()) and not bool(torch.isfinite(lse[:, empty]).any())
     assert torch.equal(o[same], r.o[same]) and torch.equal(lse[:, same], r.lse[:, same])
     print(w, stats, flush=True)
+
+
+ROUNDED = (64,) * 8 + (128,) * 4 + (512,)
+
+
+@pytest.mark.parametrize("mode,Hq,Hkv,D", ONE_WAVEFRONT)
+def test_one_wavefront_rounds_no_more_than_two(mode, Hq, Hkv, D):
+    """Float32 outputs, whose error is that of the probabilities' rounding to bf16: no larger than with a reference of its own for the even
+    and for the odd 32-key strips of a row, whose largest scores of the first strip are then exact, as two wavefronts have it."""
+    w = synth.Workload("rounded", ROUNDED, Hq, Hkv, D, keep_ratio=[1.0] * len(ROUNDED), dtype="f32", seed=360 + Hq)
+    r = Run(w, mode, do_bwd=False)
+    q, k, v, _ = r.oracle_inputs()
+    O, _ = orc.attn_fwd(r.opb, q, k, v, r.rowptr_h, r.idx_h, r.scale)
+    heads = range(0, Hq, Hq // 8)
+    for lo, hi in ((0, 512), (512, 1024), (1024, 1536)):  # rows of one tile, of up to two, of up to eight
+        two = here = 0.0
+        for s in range(len(ROUNDED)):
+            at = slice(int(w.cu[s]), int(w.cu[s + 1]))
+            if not lo <= at.start < hi:
+                continue
+            n = np.arange(at.stop - at.start)
+            for h in heads:
+                g = h * Hkv // Hq
+                x = q[at, h].astype(np.float64) @ k[at, g].astype(np.float64).T * r.scale
+                x[n[:, None] < n] = -np.inf
+                num, den = 0.0, 0.0
+                top = x.max(axis=1)
+                for odd in (0, 1):
+                    mine = n // 32 % 2 == odd
+                    m = x[:, mine][:, :32].max(axis=1)
+                    seen = np.isfinite(m)
+                    p = np.exp(np.where(seen[:, None], x[:, mine] - np.where(seen, m, 0.0)[:, None], -np.inf))
+                    p = synth.round_to_bf16(p.astype(np.float32)).astype(np.float64) * np.exp(np.where(seen, m, 0.0) - top)[:, None]
+                    num, den = num + p @ v[at, g][mine].astype(np.float64), den + p.sum(axis=1)
+                two += ((num / den[:, None] - O[at, h]) ** 2).sum()
+                here += ((to_host_f32(r.o[at, h]) - O[at, h]) ** 2).sum()
+        print(w, (lo, hi), "two references", two ** 0.5, "here", here ** 0.5, flush=True)
+        assert here <= two

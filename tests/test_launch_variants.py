@@ -52,3 +52,9 @@ def query_major(tmp_path_factory):
 def test_short_sequences(query_major, shape):
     fwd, dq, _ = query_major(rows.SHORT, [10, 9, 1], *shape)
     assert (fwd, dq) == ((1, 1) if shape in rows.ONE_WAVEFRONT else (2, 2 if shape[3] == 128 else 4))
+
+
+@pytest.mark.parametrize("shape", rows.ONE_WAVEFRONT)
+def test_rounding(query_major, shape):
+    budgets = [(L + 63) // 64 for L in rows.ROUNDED]
+    assert query_major(rows.ROUNDED, budgets, *shape)[0] == 1
