@@ -44,18 +44,34 @@ def test_rows_longer_than_the_index_window(Hq, Hkv, D):
 
 @pytest.mark.parametrize("lens,topk", [((64 * 300, 64 * 250 + 5), (3, 4)), ((64 * 80,) + (64 * 4,) * 120, (75,) + (2,) * 120)])
 def test_ticketed_launches(lens, topk):
-    """More than 4096 items: all short (one wavefront each), and one long sequence among short ones (two each)."""
+    """More than 4096 items of one wavefront each: all of them short, and those of one long sequence among short ones."""
     w = synth.Workload("tickets", lens, 8, 2, 128, topk=topk, seed=330 + len(lens))
     r = check(w, 0, bwd=len(lens) == 2)
     assert r.pb.layout.sel_rows >= 4096
 
 
-@pytest.mark.parametrize("Hq,Hkv,D", [(2, 1, 128), (24, 8, 128), (24, 8, 64)])
+# one sequence of 140 blocks at full budget and 1920 short ones: two wavefronts per item, tests/test_launch_variants.py holds it to them
+LONG_AND_SHORT = ((64 * 140 - 3,) + (1, 40, 64) * 640, (140,) + (1,) * 1920)
+
+
+@pytest.mark.parametrize("D", [128, 64])
+def test_ticketed_launches_of_two_wavefronts(D):
+    """The ticket of an item passes from one wavefront to the other through LDS that strips are loaded into afterwards."""
+    w = synth.Workload("tickets", LONG_AND_SHORT[0], 2, 1, D, topk=LONG_AND_SHORT[1], seed=335)
+    r = check(w, 0)
+    assert r.pb.layout.sel_rows >= 4096
+
+
+JUMP = (64 * 9 + 17, 64 * 14, 40)
+JUMP_SHAPES = {1: [(64, 16, 128), (192, 48, 64)], 2: [(2, 1, 128), (24, 8, 128), (24, 8, 64)]}  # wavefronts per item of the forward
+
+
+@pytest.mark.parametrize("Hq,Hkv,D", JUMP_SHAPES[2] + JUMP_SHAPES[1])
 @pytest.mark.parametrize("jump", [5.0, 13.0, 150.0])
 def test_scores_that_outgrow_the_reference(Hq, Hkv, D, jump):
     """Scores that grow from block to block by `jump` powers of two and fall again: probabilities against the old reference are large or
     infinite, so the reference moves and what has been summed is rescaled; a row sees rises inside and across its tiles."""
-    lens = (64 * 9 + 17, 64 * 14, 40)
+    lens = JUMP
     w = synth.Workload("jump", lens, Hq, Hkv, D, topk=[12, 14, 1], seed=340 + Hq)
     t = w.tensors()
     u = np.full(D, D ** -0.5, dtype=np.float32)

@@ -58,3 +58,18 @@ def test_short_sequences(query_major, shape):
 def test_rounding(query_major, shape):
     budgets = [(L + 63) // 64 for L in rows.ROUNDED]
     assert query_major(rows.ROUNDED, budgets, *shape)[0] == 1
+
+
+@pytest.mark.parametrize("wavefronts,shape", [(n, s) for n, shapes in rows.JUMP_SHAPES.items() for s in shapes])
+def test_moving_reference(query_major, wavefronts, shape):
+    assert query_major(rows.JUMP, [12, 14, 1], 0, *shape)[0] == wavefronts
+
+
+@pytest.mark.parametrize("D", [128, 64])
+def test_tickets_of_two_wavefronts(query_major, D):
+    assert query_major(*rows.LONG_AND_SHORT, 0, 2, 1, D) == (2, 2, True)
+
+
+@pytest.mark.parametrize("lens,topk", [((64 * 300, 64 * 250 + 5), (3, 4)), ((64 * 80,) + (64 * 4,) * 120, (75,) + (2,) * 120)])
+def test_tickets_of_one_wavefront(query_major, lens, topk):
+    assert query_major(lens, topk, 0, 8, 2, 128) == (1, 1, True)
