@@ -52,7 +52,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
     for (int a = tid; a < kJ; a += 256) jbuf[a] = t0 + a < ntiles ? P.idx[e0 + t0 + a] : 0;
     __syncthreads();
   };
-  TileLoader<D, 4> loader;
+  TileLoader<D> loader;
   loader.init(P.Hkv, wave, lane);
   auto issue = [&](int t) {
     const int j = __builtin_amdgcn_readfirstlane(jbuf[t % kJ]);
@@ -1252,7 +1252,6 @@ extern "C" int sb_sparse_attn_bwd(const sb_problem* p, const void* q, const void
   float* drow = (float*)(wb + wo.drow);
   float* lse2 = (float*)(wb + wo.lse2);
   P.o = (void*)o; P.lse = (float*)lse; P.drow = drow; P.lse2 = lse2; P.dq = dq; P.dk = dk; P.dv = dv;
-  P.rowptr = gb.r == 1 ? sel_rowptr : (const int32_t*)(pb + po.t_rowptr);
   P.idx = gb.r == 1 ? sel_idx : (const int32_t*)(pb + po.t_idx);
   P.items = (const WorkItem*)(pb + po.items);
   P.bitmap = (const uint32_t*)(pb + po.bitmap);
@@ -1283,21 +1282,19 @@ extern "C" int sb_sparse_attn_bwd(const sb_problem* p, const void* q, const void
   if (n_items > 0x3fffffffll) { set_error("too many work items for one launch"); return SB_ERR_INVALID_ARG; }
   P.n_items = (int)n_items;
   P.ticket = nullptr;
-  AttnParams Pq = P, Pk = P;
+  AttnParams Pq = P;
   if (use_tickets(n_items) && heads <= kTicketSlots) {
     Pq.ticket = (int*)(wb + wo.ticket);
     if ((rc = fill_zero(Pq.ticket, sizeof(int32_t) * kTicketSlots, st)) != SB_OK) return rc;
   }
-  Pq.work = (const int32_t*)(pb + po.work_fwd);
-  Pk.work = nullptr;  // the key-major kernel reads bwd_items
   if (g.D == 128) {
     rc = f32 ? launch_bwd<128, true>(g, Pq, st) : launch_bwd<128, false>(g, Pq, st);
     if (rc != SB_OK) return rc;
-    rc = f32 ? launch_dkv<128, true>(g, Pk, st) : launch_dkv<128, false>(g, Pk, st);
+    rc = f32 ? launch_dkv<128, true>(g, P, st) : launch_dkv<128, false>(g, P, st);
   } else {
     rc = f32 ? launch_bwd<64, true>(g, Pq, st) : launch_bwd<64, false>(g, Pq, st);
     if (rc != SB_OK) return rc;
-    rc = f32 ? launch_dkv<64, true>(g, Pk, st) : launch_dkv<64, false>(g, Pk, st);
+    rc = f32 ? launch_dkv<64, true>(g, P, st) : launch_dkv<64, false>(g, P, st);
   }
   return rc;
 }

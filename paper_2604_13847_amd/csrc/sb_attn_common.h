@@ -19,7 +19,7 @@ struct AttnParams {
   float* drow;        // [Hq][T] rowsum(dO * O): written by the dQ kernel, read by the dK/dV kernel
   float* lse2;        // [Hq][T] lse * log2(e), likewise
   void* dq; void* dk; void* dv;
-  const int32_t* rowptr; const int32_t* idx; const int32_t* work;
+  const int32_t* idx;  // the selected tiles
   const WorkItem* items;  // descriptors of the query-major items, in work order
   const uint32_t* bitmap;
   const ColItem* bwd_items;    // key-major items (whole columns or parts of heavy ones), see ColItem
@@ -170,19 +170,18 @@ __device__ inline void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
-// Per-lane byte offsets (from the tile's first row, head h) of the loads a loader wavefront issues
-// for a tile: wavefront w takes the LPT consecutive KiB (LPT * w + a) of the tile, a = 0 .. LPT-1, i.e.
-// tile rows (LPT * w + a) * RPI .. +RPI-1.  The offsets depend only on the lane and on the tensor's row
-// pitch, so they are computed once per kernel.
-template <int D, int NW = 2>  // NW: wavefronts (0 .. NW-1 of the workgroup) that share the loads of a tile
+// Per-lane byte offsets (from the tile's first row, head h) of the loads a loader wavefront issues for a tile: the first four wavefronts
+// of the workgroup share them, and wavefront w takes the LPT consecutive KiB (LPT * w + a) of the tile, a = 0 .. LPT-1, i.e. tile rows
+// (LPT * w + a) * RPI .. +RPI-1.  The offsets depend only on the lane and on the tensor's row pitch, so they are computed once per kernel.
+template <int D>
 struct TileLoader {
-  static constexpr int C = D / 8;      // 16-byte chunks per row
-  static constexpr int RPI = 64 / C;   // rows covered by one wavefront-wide load
-  static constexpr int LPT = (D / 8) / NW;  // loads per loader wavefront per tile
-  static_assert(LPT >= 1 && LPT * NW * RPI == 64, "the loader wavefronts must cover the 64 rows exactly");
-  // Consecutive loads of a wavefront land 1 KiB apart in LDS, so up to four of them share one M0 value: the
-  // instruction's immediate offset moves both the global and the LDS address, and voff is pre-biased for it.
-  static constexpr int GRP = LPT % 4 == 0 ? 4 : (LPT % 2 == 0 ? 2 : 1);
+  static constexpr int NW = 4;
+  static constexpr int C = D / 8;           // 16-byte chunks per row
+  static constexpr int RPI = 64 / C;        // rows covered by one wavefront-wide load
+  // Loads per loader wavefront and tile.  They land 1 KiB apart in LDS, so one M0 value serves all of them: the instruction's immediate
+  // offset moves both the global and the LDS address, and voff is pre-biased for it.
+  static constexpr int LPT = (D / 8) / NW;
+  static_assert((LPT == 2 || LPT == 4) && LPT * NW * RPI == 64, "the loader wavefronts must cover the 64 rows exactly");
   unsigned voff[LPT];
   int rl, pc;  // row within a load's group of RPI rows, 16-byte chunk of this lane
   int wave;
@@ -193,7 +192,7 @@ struct TileLoader {
 #pragma unroll
     for (int a = 0; a < LPT; ++a) {
       const int r = (LPT * (wave & (NW - 1)) + a) * RPI + rl;
-      voff[a] = (unsigned)(r * H * D * 2 + 16 * (pc ^ chunk_swizzle<D>(r))) - 1024u * (a % GRP);
+      voff[a] = (unsigned)(r * H * D * 2 + 16 * (pc ^ chunk_swizzle<D>(r))) - 1024u * a;
     }
   }
   // Issue the copy of rows row0 .. row0+63 (head h) of `src` into `slot`.  Rows >= valid repeat the
@@ -214,24 +213,18 @@ struct TileLoader {
       // (readfirstlane) must not be read by a vector-memory instruction within 5 wait states, while scalar reads of
       // it are interlocked.  M0 needs one wait state (s_nop 0) before the load that uses it.
       unsigned long long sbase;
-#pragma unroll
-      for (int a = 0; a < LPT; a += GRP) {
-        if (GRP == 4)
-          asm volatile("s_mov_b64 %0, %6\n\ts_mov_b32 m0, %5\n\ts_nop 0\n\t"
-                       "global_load_lds_dwordx4 %1, %0\n\t"
-                       "global_load_lds_dwordx4 %2, %0 offset:1024\n\t"
-                       "global_load_lds_dwordx4 %3, %0 offset:2048\n\t"
-                       "global_load_lds_dwordx4 %4, %0 offset:3072"
-                       : "=&s"(sbase) : "v"(voff[a]), "v"(voff[a + 1]), "v"(voff[a + 2]), "v"(voff[a + 3]), "s"(base + a * 1024), "s"(ts) : "memory", "m0");
-        else if (GRP == 2)
-          asm volatile("s_mov_b64 %0, %4\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\t"
-                       "global_load_lds_dwordx4 %1, %0\n\t"
-                       "global_load_lds_dwordx4 %2, %0 offset:1024"
-                       : "=&s"(sbase) : "v"(voff[a]), "v"(voff[a + 1]), "s"(base + a * 1024), "s"(ts) : "memory", "m0");
-        else
-          asm volatile("s_mov_b64 %0, %3\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %0"
-                       : "=&s"(sbase) : "v"(voff[a]), "s"(base + a * 1024), "s"(ts) : "memory", "m0");
-      }
+      if constexpr (LPT == 4)
+        asm volatile("s_mov_b64 %0, %6\n\ts_mov_b32 m0, %5\n\ts_nop 0\n\t"
+                     "global_load_lds_dwordx4 %1, %0\n\t"
+                     "global_load_lds_dwordx4 %2, %0 offset:1024\n\t"
+                     "global_load_lds_dwordx4 %3, %0 offset:2048\n\t"
+                     "global_load_lds_dwordx4 %4, %0 offset:3072"
+                     : "=&s"(sbase) : "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(base), "s"(ts) : "memory", "m0");
+      else
+        asm volatile("s_mov_b64 %0, %4\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\t"
+                     "global_load_lds_dwordx4 %1, %0\n\t"
+                     "global_load_lds_dwordx4 %2, %0 offset:1024"
+                     : "=&s"(sbase) : "v"(voff[0]), "v"(voff[1]), "s"(base), "s"(ts) : "memory", "m0");
     } else {
 #pragma unroll
       for (int a = 0; a < LPT; ++a) {  // ragged tile (rare): the lane offsets are recomputed instead of being kept in registers

@@ -441,7 +441,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void a
     for (int a = tid; a < kJ; a += nthr) jbuf[a] = t0 + a < ntiles ? P.idx[e0 + t0 + a] : 0;
     __syncthreads();
   };
-  TileLoader<D, 4> loader;  // a workgroup has six or eight wavefronts: the first four share the tile loads
+  TileLoader<D> loader;  // a workgroup has six or eight wavefronts
   loader.init(P.Hkv, wave, lane);
   auto issue = [&](int t) {
     const int j = __builtin_amdgcn_readfirstlane(jbuf[t % kJ]);
@@ -683,8 +683,7 @@ extern "C" int sb_sparse_attn_fwd(const sb_problem* p, const void* q, const void
     P.q = (const bf16*)q; P.k = (const bf16*)k; P.v = (const bf16*)v;
   }
   P.o = o; P.lse = lse;
-  P.rowptr = gb.r == 1 ? sel_rowptr : (const int32_t*)(pb + po.t_rowptr);
-  P.idx = gb.r == 1 ? sel_idx : (const int32_t*)(pb + po.t_idx); P.work = (const int32_t*)(pb + po.work_fwd);
+  P.idx = gb.r == 1 ? sel_idx : (const int32_t*)(pb + po.t_idx);
   P.items = (const WorkItem*)(pb + po.items);
   P.cu = t.cu; P.qb_off = t.qb_off; P.qb_seq = t.qb_seq; P.bm_off = t.bm_off;
   P.NQB = g.NQB; P.T = g.T; P.Hq = g.Hq; P.Hkv = g.Hkv; P.G = g.G; P.Hs = g.Hs; P.mode = g.mode;
