@@ -194,18 +194,26 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64
         if (NW == 1) limit[b] = -1.0f;
       }
       if (NW == 1 && add_rest) {
+        // P = its upper 16 bits + the rest: both above 0, so that an infinite value in V stays infinite (0 * inf, or a rest below 0, would
+        // make NaN of it).  The rest has 2^-23 P added, for a P that has no other.
         bf16x8 rest[2];
-        float part[2] = {0.f, 0.f};
+        float part[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
-          bf16x2 y;
-          y[0] = (bf16)(px[2 * c] - (float)py[c][0]);
-          y[1] = (bf16)(px[2 * c + 1] - (float)py[c][1]);
-          rest[c >> 2][(2 * c) & 7] = y[0];
-          rest[c >> 2][(2 * c + 1) & 7] = y[1];
-          part[c & 1] = sum2(y, part[c & 1]);
+          const unsigned x0 = __float_as_uint(px[2 * c]), x1 = __float_as_uint(px[2 * c + 1]);
+          const bf16x2 upper = __builtin_bit_cast(bf16x2, __builtin_amdgcn_perm(x1, x0, 0x07060302));
+          bf16x2 lower;
+          lower[0] = (bf16)__builtin_fmaf(px[2 * c], 1.0f + 0x1p-23f, -__uint_as_float(x0 & 0xffff0000u));
+          lower[1] = (bf16)__builtin_fmaf(px[2 * c + 1], 1.0f + 0x1p-23f, -__uint_as_float(x1 & 0xffff0000u));
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            pb[b][c >> 2][(2 * c + e) & 7] = upper[e];
+            rest[c >> 2][(2 * c + e) & 7] = lower[e];
+          }
+          part[c & 1] = sum2(upper, part[c & 1]);
+          part[2 + (c & 1)] = sum2(lower, part[2 + (c & 1)]);
         }
-        psum += part[0] + part[1];
+        psum = (part[0] + part[1]) + (part[2] + part[3]);
         asm volatile("s_nop 1" : "+v"(rest[0]), "+v"(rest[1]));  // two wait states between a vector write and its use as an operand
 #pragma unroll
         for (int k = 0; k < NOP; ++k) mfma32_sum(oacc[k % (D / 32)][b], vt[k], rest[k / (D / 32)]);

@@ -223,12 +223,14 @@ inline int64_t ticketed_grid(int64_t n, bool tickets) { return (n + (tickets ? (
 // chip works on 1024 / w at a time (head_dim 64: twice as many); an item costs about `fixed` tile times of two wavefronts besides its
 // tiles (where the chip is not full and its clock is high: forward 16, dQ and head_dim 64 24), and the launch takes as long as its share
 // of all items, as the longest item, or, where there are more items than fit, as two short ones.  So one wavefront each where there are
-// enough items, two where the longest would stick out.  One / two wavefronts at head_dim 128, forward and dQ: 1230 items of 1 - 11 tiles
-// 24 / 32 and 31 / 41 us, 1280 of them 27 / 33 and 35 / 44, 1248 items of 1 - 78 tiles 127 / 114 and 162 / 152, 432 of 1 - 54 tiles
-// 78 / 47 and 92 / 59, 592 of 1 - 11 tiles 20.0 / 20.4 and 24.2 / 26.5 us.
-// At head_dim 64 the SIMD's other wavefront works through three quarters of the fixed part, and twice the items at a time miss the caches
-// more often, taken as 6 % (65536 tokens, 14/2 heads, blocks of 256: forward 1482 / 1436 us, dQ 1812 / 1767; 24551 tokens, 32/8 heads, rows
-// of up to 256 tiles: dQ 1156 / 1066; but 6144 items of 1 - 16 tiles: dQ 131 / 143, 1190 of 1 - 11 tiles: forward 16.2 / 18.6 us).
+// enough items, two where the longest would stick out.  One / two wavefronts at head_dim 128: forward, 1280 items of 1 - 11 tiles
+// 45.6 / 46.6 us, 1056 of 1 - 8 tiles 26 / 34, 592 of 1 - 11 tiles 25.4 / 26.8, 1248 of 1 - 78 tiles 126 / 113, 432 of 1 - 54 tiles 78 / 47;
+// dQ, 1230 items of 1 - 11 tiles 31 / 41, 592 of them 24.2 / 26.5, 1248 items of 1 - 78 tiles 162 / 152, 432 of 1 - 54 tiles 92 / 59.
+// At head_dim 64 the SIMD's other wavefront works through three quarters of the fixed part.  The sixteenth added to one wavefront's time
+// there is a tie-break: where the two terms are about equal, two wavefronts, which gather for half as many items at a time, were the
+// faster ones in what was measured, for reasons not shown (65536 tokens, 14/2 heads, blocks of 256: forward 1482 / 1436 us, dQ 1812 / 1767; 24551
+// tokens, 32/8 heads, rows of up to 256 tiles: dQ 1156 / 1066, 24576 tokens: forward 2424 / 2227); where one wavefront wins it does so by more
+// (6144 items of 1 - 16 tiles: forward 121 / 131, dQ 131 / 143).
 inline bool one_wavefront_per_item(const Geo& tg, int64_t items, int fixed) {
   const bool d64 = tg.D == 64;
   const int64_t tiles = (int64_t)tg.Hq * tg.nnz_unit, most = tg.rowT_max, slots = d64 ? 2048 : 1024;

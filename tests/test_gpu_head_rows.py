@@ -130,6 +130,24 @@ def test_first_keys_that_score_minus_infinity(mode, Hq, Hkv, D, masked):
     print(w, stats, flush=True)
 
 
+@pytest.mark.parametrize("mode,Hq,Hkv,D", ONE_WAVEFRONT + TWO_WAVEFRONTS)
+def test_an_infinite_value_stays_infinite(mode, Hq, Hkv, D):
+    """One infinite element of V per sequence, in the first or the second 32-key strip: that column of O is infinite in every later block,
+    everything else is what it is without it."""
+    w = synth.Workload("infinite", SHORT, Hq, Hkv, D, topk=[10, 9, 1], seed=370 + Hq)
+    r = Run(w, mode, do_bwd=False)
+    for key, sign in ((3, 1.0), (40, -1.0)):
+        v, want = r.v.clone(), r.o.clone()
+        later = np.zeros(w.T, dtype=bool)
+        for s, L in enumerate(SHORT[:2]):
+            at = int(w.cu[s])
+            v[at + key, :, 5] = sign * float("inf")
+            want[at + 64:at + L, :, 5] = sign * float("inf")
+            later[at + 64:at + L] = True
+        o, lse = sb.sb_sparse_attn_fwd(r.pb, r.q, r.k, v, r.rowptr, r.idx, r.plan)
+        assert torch.equal(o[later], want[later]) and torch.equal(lse, r.lse)
+
+
 ROUNDED = (64,) * 8 + (128,) * 4 + (512,)
 
 
