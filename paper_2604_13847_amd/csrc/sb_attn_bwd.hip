@@ -301,7 +301,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
 // 2.44 / 2.23 / 2.14 ms, one 131072-token sequence, top 32: 7.62 / 7.24 / 6.49, the 262144-token batch 23.3 / 22.3 / 20.5, 65536 tokens
 // whose selection is a sink and a window 2.66 / 2.42 / 2.19.  Where the heads of a KV group share their selection, against one workgroup
 // of all of them that shares the tiles in LDS (32 rows per wavefront): the 32768-token batch 2.37 -> 2.09 ms, the 131072-token sequence
-// 6.45 -> 5.82, 65536 tokens with 28/4 heads 5.75 -> 4.54.  At D = 64 two wavefronts share a SIMD (four or five registers spilled before the
+// 6.45 -> 5.82, 65536 tokens with 28/4 heads 5.75 -> 4.54.  At D = 64 two wavefronts share a SIMD (one to five registers spilled before the
 // loop); against the kernel above on 65536 tokens, 14/2 heads, blocks of 256: 1.98 -> 1.77 ms, per KV group 2.45 -> 1.75.
 template <int D, bool OUT_F32, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1))) void attn_bwd_dq_head_kernel(AttnParams P, int heads) {

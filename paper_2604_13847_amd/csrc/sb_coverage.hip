@@ -158,6 +158,8 @@ __global__ __launch_bounds__(256) void coverage_rows_kernel(const float* __restr
 // so that every compare-exchange puts the larger key first.  The four wavefronts of a workgroup take the heads of the
 // group in turn, keep their sums in registers and add them in wavefront order at the end: fixed summation order again.
 // Scores must be numbers (a NaN counts as -infinity); sb_block_scores writes none for finite inputs.
+// All row lengths share one kernel, so E = 32 sets the registers of all: four wavefronts per SIMD are asked for, which leaves 128, and the
+// compiler spills 16 vector and 130 scalar registers (131072 tokens, 32/8 heads: 384 us, without the request 400).
 constexpr int kCovRegMax = 2048;
 
 // Scores as integers of the same order (and back): integer comparisons take a partner lane's key as an operand (DPP) as it is, float
