@@ -50,14 +50,14 @@ def test_ticketed_launches(lens, topk):
     assert r.pb.layout.sel_rows >= 4096
 
 
-# one sequence of 140 blocks at full budget and 1920 short ones: two wavefronts per item, tests/test_launch_variants.py holds it to them
-LONG_AND_SHORT = ((64 * 140 - 3,) + (1, 40, 64) * 640, (140,) + (1,) * 1920)
+# one sequence of 104 blocks at full budget and 4002 short ones: two wavefronts per item, tests/test_launch_variants.py holds it to them
+LONG_AND_SHORT = ((64 * 104 - 3,) + (1, 40, 64) * 1334, (104,) + (1,) * 4002)
 
 
 @pytest.mark.parametrize("D", [128, 64])
 def test_ticketed_launches_of_two_wavefronts(D):
     """The ticket of an item passes from one wavefront to the other through LDS that strips are loaded into afterwards."""
-    w = synth.Workload("tickets", LONG_AND_SHORT[0], 2, 1, D, topk=LONG_AND_SHORT[1], seed=335)
+    w = synth.Workload("tickets", LONG_AND_SHORT[0], 1, 1, D, topk=LONG_AND_SHORT[1], seed=335)
     r = check(w, 0)
     assert r.pb.layout.sel_rows >= 4096
 

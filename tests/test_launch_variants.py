@@ -67,7 +67,7 @@ def test_moving_reference(query_major, wavefronts, shape):
 
 @pytest.mark.parametrize("D", [128, 64])
 def test_tickets_of_two_wavefronts(query_major, D):
-    assert query_major(*rows.LONG_AND_SHORT, 0, 2, 1, D) == (2, 2, True)
+    assert query_major(*rows.LONG_AND_SHORT, 0, 1, 1, D) == (2, 2, True)
 
 
 @pytest.mark.parametrize("lens,topk", [((64 * 300, 64 * 250 + 5), (3, 4)), ((64 * 80,) + (64 * 4,) * 120, (75,) + (2,) * 120)])
