@@ -35,7 +35,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
   timer.start(P);
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
-  const int pos = (int)blockIdx.x < P.n_items ? (int)blockIdx.x : -1;  // (so few items are dealt by position, see claim_item)
+  const int pos = (int)blockIdx.x < P.n_items ? (int)blockIdx.x : -1;  // (so few items are dealt by position)
   if (pos < 0) return;
   const WorkItem item = uniform_item(P.items, pos);
   const int hs = item.hs, i = item.i, L = item.len, e0 = item.e0, ntiles = item.ntiles;
@@ -303,24 +303,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
 // of all of them that shares the tiles in LDS (32 rows per wavefront): the 32768-token batch 2.37 -> 2.09 ms, the 131072-token sequence
 // 6.45 -> 5.82, 65536 tokens with 28/4 heads 5.75 -> 4.54.  At D = 64 two wavefronts share a SIMD (one to five registers spilled before the
 // loop); against the kernel above on 65536 tokens, 14/2 heads, blocks of 256: 1.98 -> 1.77 ms, per KV group 2.45 -> 1.75.
+template <int D> constexpr int kDqRing = 4 * 32 * D * 2;  // a wavefront's K even, K odd, V even, V odd strips
+
 template <int D, bool OUT_F32, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1))) void attn_bwd_dq_head_kernel(AttnParams P, int heads) {
+__device__ __attribute__((always_inline)) inline void dq_head_item(const AttnParams& P, const WorkItem& item, int hh, char (&ring)[NW][kDqRing<D>]) {
   constexpr int ROW_B = D * 2, STRIP_B = 32 * ROW_B, NOP = D / 16;
   using Loader = QuadLoader<D>;
   constexpr int LPS = Loader::LPS;
   constexpr int KV = D == 64 ? NOP : 6;  // Q, dQ and the dO operands below this one live in accumulation registers, the other dO operands do not fit there
   constexpr int PER = 8 / NOP;           // registers of the vector work per matrix instruction
-  __shared__ __attribute__((aligned(1024))) char ring[NW][4 * STRIP_B];  // per wavefront: K even, K odd, V even, V odd strips
-  BusyTimer timer;
-  timer.start(P);
-  const int tid = threadIdx.x;
+  const int tid = item_tid<D>();
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
-  // workgroup id -> (position in the work list, query head of the group), see the forward kernel
-  int pos = (int)(blockIdx.x / (8u * heads)) * 8 + (int)(blockIdx.x & 7u);
-  const int hh = (int)(blockIdx.x >> 3) % heads;
-  pos = claim_item(pos, P.n_items, P.ticket ? P.ticket + hh : nullptr, NW == 2 ? (int*)&ring[NW - 1][4 * STRIP_B - 4] : nullptr);
-  if (pos < 0) return;
-  const WorkItem item = uniform_item(P.items, pos);
   const int hs = item.hs, i = item.i, L = item.len, ntiles = item.ntiles;
   const int64_t seq0 = item.seq0;
   const int h = P.mode == SB_SELECT_PER_QHEAD ? hs : hs * P.G + hh;
@@ -648,6 +641,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64
                                return (NW == 1 ? dqacc[dt][b][v] : dqacc[dt][b][v] + ybuf[(16 * dt + v) * 64 + lane]) * P.scale;
                              });
     }
+}
+
+template <int D, bool OUT_F32, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1))) void attn_bwd_dq_head_kernel(AttnParams P, int heads) {
+  __shared__ __attribute__((aligned(1024))) char ring[NW][kDqRing<D>];
+  BusyTimer timer;
+  timer.start(P);
+  for_items<D, NW>(P, heads, (int*)&ring[NW - 1][kDqRing<D> - 4],
+                [&](const AttnParams& p, const WorkItem& item, int hh) __attribute__((always_inline)) { dq_head_item<D, OUT_F32, NW>(p, item, hh, ring); });
   timer.stop(P);
 }
 
@@ -688,7 +690,18 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
   __shared__ uint16_t tl_s[kCW * 32 * 8];  // the chunk's tiles in processing order
   __shared__ int ntl_s;
   // workgroups 0 .. sub_slots-1: the sub-parts; then one per item, for those that are walked as a whole
-  const int at = (int)blockIdx.x - P.sub_slots;
+  int at = (int)blockIdx.x - P.sub_slots;
+  if (P.ticket) {  // the list's second half by ticket (only where there are no sub-parts)
+    const int n_items = P.counters[3] * P.Hkv, lead = key_lead(n_items);
+    if (at >= n_items + (int)key_extra(n_items)) return;
+    if (at >= lead) {
+      __shared__ int sh_claim;
+      if (threadIdx.x == 0) sh_claim = draw_item(at & 7, lead, n_items, P.ticket);
+      __syncthreads();
+      at = __builtin_amdgcn_readfirstlane(sh_claim);
+      if (at < 0) return;
+    }
+  }
   const ColItem item = at < 0 ? P.sub_items[blockIdx.x].item : P.bwd_items[at];
   if (item.col < 0) return;  // the lists are padded to their largest possible length
   int nsub = 1, run0 = 0, run1 = item.weight;  // workgroups that walk the item; this one's run of its tiles in walk order
@@ -1181,14 +1194,15 @@ template <int D, bool F32>
 static int launch_bwd(const Geo& g, const AttnParams& P, hipStream_t st) {
   // query-major dQ: one workgroup per (item, query head)
   const int heads = g.mode == SB_SELECT_PER_QHEAD ? 1 : g.G;
-  const int64_t n_slots = ticketed_grid(P.n_items, P.ticket != nullptr), items = (int64_t)g.Hq * g.NQB;
+  const int64_t items = (int64_t)g.Hq * g.NQB;
   KernelTimer kt(K_BWD_DQ, st);
   if (D == 64 && items < kDqFewItems) {
-    hipLaunchKernelGGL((attn_bwd_dq_kernel<F32>), dim3((unsigned)n_slots, (unsigned)heads), dim3(256), 0, st, P);
+    hipLaunchKernelGGL((attn_bwd_dq_kernel<F32>), dim3((unsigned)((P.n_items + 7) / 8 * 8), (unsigned)heads), dim3(256), 0, st, P);
   } else {
-    if (n_slots * heads > 0x7fffffffll) { set_error("too many work items for one launch"); return SB_ERR_INVALID_ARG; }
-    const dim3 grid((unsigned)(n_slots * heads));
-    if (one_wavefront_per_item(g, items, 24)) hipLaunchKernelGGL((attn_bwd_dq_head_kernel<D, F32, 1>), grid, dim3(64), 0, st, P, heads);
+    if (head_ids(P.n_items, heads) > 0x7fffffffll) { set_error("too many work items for one launch"); return SB_ERR_INVALID_ARG; }
+    const bool one = one_wavefront_per_item(g, items, 24);
+    const dim3 grid((unsigned)head_grid(P, heads, D, one ? 1 : 2));
+    if (one) hipLaunchKernelGGL((attn_bwd_dq_head_kernel<D, F32, 1>), grid, dim3(64), 0, st, P, heads);
     else hipLaunchKernelGGL((attn_bwd_dq_head_kernel<D, F32, 2>), grid, dim3(128), 0, st, P, heads);
   }
   SB_LAUNCH_CHECK("attn_bwd_dq_kernel");
@@ -1200,7 +1214,7 @@ static int launch_dkv(const Geo& g, const AttnParams& P, hipStream_t st) {
   const int64_t extra = split_extra_max(g);
   const int64_t n_items = (int64_t)g.Hkv * (g.NQB + extra);
   if (P.sub_slots + n_items > 0x7fffffffll) { set_error("too many key-major items for one launch"); return SB_ERR_INVALID_ARG; }
-  dim3 grid((unsigned)(P.sub_slots + n_items)), block(128);
+  dim3 grid((unsigned)(P.sub_slots + n_items + (P.ticket ? key_extra(n_items) : 0))), block(128);
   KernelTimer kt(K_BWD_DKV, st);
   hipLaunchKernelGGL((attn_bwd_dkv_kernel<D, F32>), grid, block, 0, st, P);
   SB_LAUNCH_CHECK("attn_bwd_dkv_kernel");
@@ -1274,18 +1288,17 @@ extern "C" int sb_sparse_attn_bwd(const sb_problem* p, const void* q, const void
     if ((rc = fill_zero(wb + wo.cu_busy, sizeof(uint64_t) * SB_CU_SLOTS, st)) != SB_OK) return rc;
     P.cu_busy = (unsigned long long*)(wb + wo.cu_busy);
   }
-  // The query-major launch hands one item in sixteen out by ticket (see claim_item).  The key-major launch does not: its
-  // items are few and very unequal, and a heavy one that is held back for the tail lengthens the launch (measured: +23 %
-  // on the 32768-token batch, -1 % on the 262144-token one).
   const int heads = g.mode == SB_SELECT_PER_QHEAD ? 1 : g.G;
   const int64_t n_items = (int64_t)g.Hs * g.NQB;
   if (n_items > 0x3fffffffll) { set_error("too many work items for one launch"); return SB_ERR_INVALID_ARG; }
   P.n_items = (int)n_items;
   P.ticket = nullptr;
   AttnParams Pq = P;
-  if (use_tickets(n_items) && heads <= kTicketSlots) {
+  if (use_head_tickets(n_items, heads)) {
     Pq.ticket = (int*)(wb + wo.ticket);
-    if ((rc = fill_zero(Pq.ticket, sizeof(int32_t) * kTicketSlots, st)) != SB_OK) return rc;
+    // (the sub-parts of small problems are dealt by position)
+    if (P.sub_slots == 0 && use_key_tickets((int64_t)g.Hkv * (g.NQB + split_extra_max(g)))) P.ticket = Pq.ticket + kTicketInts;
+    if ((rc = fill_zero(Pq.ticket, sizeof(int32_t) * kTicketInts * 2, st)) != SB_OK) return rc;
   }
   if (g.D == 128) {
     rc = f32 ? launch_bwd<128, true>(g, Pq, st) : launch_bwd<128, false>(g, Pq, st);

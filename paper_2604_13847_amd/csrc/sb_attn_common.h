@@ -37,8 +37,8 @@ struct AttnParams {
   float scale, scale_log2e;
   int out_f32;
   unsigned long long* cu_busy;  // null when instrumentation is off
-  // Work distribution (see claim_item)
-  int* ticket;        // [kTicketSlots] counters, zero at launch; null: every item is taken by position
+  // Work distribution (see draw_item)
+  int* ticket;        // 8 counters, zero at launch (the group kernel: 8 per head plane); null: every item is taken by position
   int n_items;        // query-major items
 };
 // float -> bf16 copies of one launch
@@ -49,38 +49,40 @@ struct Conversions {
 };
 int convert_f32_to_bf16(const Conversions& c, hipStream_t st);
 
-constexpr int kTicketSlots = 64;    // one counter per head plane of a query-major launch
-
-// Which item does the workgroup at position `pos` of a launch work on?
-// Workgroup ids are dealt to the 8 XCDs in turn, so every XCD gets the same number of workgroups whatever its pace, and
-// the XCDs do differ by several percent (the L2 hit rate depends on which heads an XCD serves, and the dies themselves
-// differ): a launch that ties every item to a position ends when the slowest XCD is through its share.  So one item in
-// sixteen (the last 8 of every 128 in list order, a cross-section of the whole list) is held back: the other items are
-// tied to the leading positions, in list order and on the XCD they would have had anyway, and the held-back ones form
-// the tail of the launch, handed out by ticket to whichever workgroup asks first.  The launch has twice as many tail
-// workgroups as tail items: a fast XCD gets through more of them, and those that find the tail empty exit at once.
+// Which item does a workgroup work on?
+// Workgroup ids are dealt to the 8 XCDs in turn, so every XCD gets the same number of workgroups whatever its pace, and the XCDs do
+// differ by several percent (the L2 hit rate depends on which heads an XCD serves, and the dies themselves differ): a launch that ties
+// every item to a position ends when the slowest XCD is through its share.  So only the list's first part, the heavier items, is tied to positions
+// (*_lead).  Of the rest every eighth item is an XCD's, as if it were dealt by position, but handed out in list order by that XCD's
+// own counter, and an XCD that is through its items takes the next one of the XCD that has most left.  An item so stays on the XCD whose
+// L2 holds its head unless it is one of the launch's last, and those are the lightest.  (One counter for all, which gives that up, for one
+// item in sixteen, against this: one 131072-token sequence, top 32: forward 6.20 -> 5.75 ms, dQ 6.39 -> 6.18.  dK/dV without any, against
+// this: that sequence 10.4 -> 10.15 ms, 65536 tokens with 28/4 heads 7.3 -> 6.9, with a sink 3.47 -> 3.28, the 262144-token batch 34.2 -> 33.3.)
 // Which workgroup computes an item never changes its result.
-// Returns the item's index in the list or -1; every thread of the workgroup must call it (it has a barrier).  `sh` is an LDS word that
-// only wavefronts other than the first write afterwards; a workgroup of one wavefront needs none.
-__device__ inline int claim_item(int pos, int n_items, int* counter, int* sh) {
-  if (!counter) return pos < n_items ? pos : -1;
-  const int groups = n_items >> 7, held = groups << 3;  // held-back items: indices 128 q + 120 .. 128 q + 127
-  if (pos < n_items - held) return pos < 120 * groups ? (pos / 120 << 7) + pos % 120 : pos + held;
-  int t = 0;
-  if (threadIdx.x == 0) {
-    t = atomicAdd(counter, 1);
-    if (sh) *sh = t;
+// draw_item: an index from `lead` on, or -1 if all have been drawn; by one thread.
+__device__ inline int draw_item(int xcd, int lead, int n, int* counters) {
+  for (int tries = 0; tries < 9; ++tries) {
+    const int item = lead + 8 * atomicAdd(&counters[kTicketPitch * xcd], 1) + xcd;
+    if (item < n) return item;
+    int left[8], most = 0;
+#pragma unroll
+    for (int x = 0; x < 8; ++x) left[x] = (n - lead - x + 7) / 8 - __hip_atomic_load(&counters[kTicketPitch * x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int x = 0; x < 8; ++x)
+      if (left[x] > most) { most = left[x]; xcd = x; }
+    if (most == 0) break;
   }
-  t = __builtin_amdgcn_readfirstlane(t);
-  if (sh) {
-    __syncthreads();
-    if (threadIdx.x >= 64) t = __builtin_amdgcn_readfirstlane(*sh);
-  }
-  return t < held ? ((t >> 3) << 7) + 120 + (t & 7) : -1;
+  return -1;
 }
-__device__ inline int claim_item(int pos, int n_items, int* counter) {
+// The item of the workgroup at position `pos`, or -1; every thread of the workgroup must call it (it has a barrier).
+__device__ inline int claim_item(int pos, int n_items, int* counters) {
+  if (!counters) return pos < n_items ? pos : -1;
+  const int lead = query_lead(n_items);
+  if (pos < lead) return pos;
   __shared__ int sh_claim;
-  return claim_item(pos, n_items, counter, &sh_claim);
+  if (threadIdx.x == 0) sh_claim = draw_item(pos & 7, lead, n_items, counters);
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(sh_claim);
 }
 
 // Descriptor `pos` (wave-uniform) by scalar loads, so that everything that follows from it is scalar work.
@@ -88,6 +90,88 @@ __device__ inline WorkItem uniform_item(const WorkItem* items, int pos) {
   typedef int i32x8 __attribute__((ext_vector_type(8)));
   const i32x8 x = ((const __attribute__((address_space(4))) i32x8*)(uintptr_t)items)[__builtin_amdgcn_readfirstlane(pos)];
   return WorkItem{x[0], x[1], x[2], x[3], x[4], x[5], x[6], x[7]};
+}
+
+// The items of a query-major launch of one query head each: id -> (position in the work list, query head of the group).  In per-KV-group
+// mode the `heads` query heads of an item have ids that are 8 apart, so they run on the same XCD (workgroup ids are dealt to the XCDs in
+// turn) and share its L2.
+inline __host__ __device__ int64_t head_ids(int64_t n_items, int heads) { return (n_items + 7) / 8 * 8 * heads; }
+inline bool use_head_tickets(int64_t n_items, int heads) { return use_tickets(n_items) && head_ids(n_items, heads) < (1ll << 30); }
+inline int64_t head_grid(const AttnParams& P, int heads, int D, int nw) {
+  const int64_t ids = head_ids(P.n_items, heads);
+  if (!P.ticket) return ids;
+  return D == 128 ? 1024 / nw : ticketed_grid(ids, true);
+}
+// The items of one workgroup.  A launch without tickets: workgroup w takes item w.  With tickets at D = 128, where a wavefront fills its
+// SIMD: as many workgroups as the chip runs at a time, which draw one item after the other.  At D = 64 workgroups take one item each, the
+// last ones by ticket: there the next workgroup's start overlaps the end of the last (drawing all: forward of 65536 tokens, 14/2 heads,
+// blocks of 256 1.40 -> 1.44 ms).  At D = 128 the draw takes the place of a workgroup's start, against a quarter of the items by ticket, one a
+// workgroup: the forward of 65536 tokens whose selection is a sink and a window 1.76 -> 1.66 ms, dQ 2.13 -> 2.06, of 131072 items of one or
+// four tiles 650 -> 613 us and 1.19 -> 1.15 ms.  (The draw ahead of an item's output: 2 % faster on rows of 32 tiles, 4 % slower on short ones.)
+// `sh` is an LDS word for launches of two wavefronts per item, which only wavefronts other than the first write otherwise.
+template <int D, int NW>
+struct ItemQueue {
+  static constexpr bool kLoop = D == 128;
+  WorkItem item;
+  int hh;  // query head of the group
+  int id, ids, lead, heads;
+  __device__ inline int pos_of(int id) const { return id / (8 * heads) * 8 + (id & 7); }
+  __device__ inline void draw(const AttnParams& P, int* sh) {
+    int t = 0;
+    if (threadIdx.x == 0) {
+      do t = draw_item(blockIdx.x & 7, lead, ids, P.ticket);
+      while (t >= 0 && pos_of(t) >= P.n_items);  // (the last ids may have no item)
+      if (NW == 2) *sh = t;
+    }
+    id = __builtin_amdgcn_readfirstlane(t);
+    if (NW == 2) {
+      __syncthreads();
+      if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) != 0) id = __builtin_amdgcn_readfirstlane(*sh);
+    }
+  }
+  __device__ inline void descriptor(const AttnParams& P) {
+    if (id < 0) return;
+    item = uniform_item(P.items, pos_of(id));
+    hh = (id >> 3) % heads;
+  }
+  __device__ inline void first(const AttnParams& P, int heads_, int* sh) {
+    heads = heads_;
+    ids = (int)head_ids(P.n_items, heads);
+    lead = !P.ticket ? ids : kLoop ? (int)gridDim.x : query_lead(ids);
+    id = (int)blockIdx.x;
+    if (id >= lead) draw(P, sh);
+    else if (pos_of(id) >= P.n_items) id = -1;
+    descriptor(P);
+  }
+  __device__ inline void next(const AttnParams& P, int* sh) {
+    id = -1;
+    if (!P.ticket) return;
+    if (NW == 2) __syncthreads();  // the item's LDS is free
+    draw(P, sh);
+    descriptor(P);
+  }
+};
+// What does not depend on the item would otherwise be worked out and kept in registers from before the loop, ahead of what the item needs.
+template <int D>
+__device__ inline int item_tid() {
+  int x = (int)threadIdx.x;
+  if (ItemQueue<D, 1>::kLoop) asm volatile("" : "+v"(x));
+  return x;
+}
+__device__ inline AttnParams reloaded_params() {  // the kernel's first argument, by scalar loads
+  const __attribute__((address_space(4))) AttnParams* p = (const __attribute__((address_space(4))) AttnParams*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const AttnParams*)p;
+}
+template <int D, int NW, typename F>
+__device__ __attribute__((always_inline)) inline void for_items(const AttnParams& P, int heads, int* sh, F work) {
+  ItemQueue<D, NW> queue;
+  queue.first(P, heads, sh);
+  if constexpr (ItemQueue<D, NW>::kLoop) {
+    for (; queue.id >= 0; queue.next(P, sh)) work(reloaded_params(), queue.item, queue.hh);
+  } else {
+    if (queue.id >= 0) work(P, queue.item, queue.hh);
+  }
 }
 
 __device__ inline f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {

@@ -27,26 +27,17 @@
 
 namespace sb {
 
+constexpr int kFwdV = 3;  // V strips in a wavefront's ring: K even, K odd, then V of strip t in slot 2 + t % kFwdV.  Four rings fill a CU's LDS.
+template <int D> constexpr int kFwdRing = (2 + kFwdV) * 32 * D * 2;
+
 template <int D, bool OUT_F32, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1))) void attn_fwd_head_kernel(AttnParams P, int n_items, int heads) {
-  constexpr int ROW_B = D * 2, STRIP_B = 32 * ROW_B, NOP = D / 16, NV = 3;
+__device__ __attribute__((always_inline)) inline void fwd_head_item(const AttnParams& P, const WorkItem& item, int hh, char (&ring)[NW][kFwdRing<D>]) {
+  constexpr int ROW_B = D * 2, STRIP_B = 32 * ROW_B, NOP = D / 16;
   constexpr float kLazy = 4.0f;
   using Loader = QuadLoader<D>;
   constexpr int LPS = Loader::LPS;
-  // per wavefront: K even, K odd, then V of strip t in slot 2 + t % 3.  Four wavefronts' rings fill a CU's LDS.
-  constexpr int RING_B = (2 + NV) * STRIP_B;
-  __shared__ __attribute__((aligned(1024))) char ring[NW][RING_B];
-  BusyTimer timer;
-  timer.start(P);
-  const int tid = threadIdx.x;
+  const int tid = item_tid<D>();
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
-  // Workgroup id -> (position in the work list, query head of the group).  In per-KV-group mode the `heads` query heads of an item take
-  // ids that are 8 apart, so they run on the same XCD (ids are dealt round-robin to the 8 XCDs) and share its L2 for the strips.
-  int pos = (int)(blockIdx.x / (8u * heads)) * 8 + (int)(blockIdx.x & 7u);
-  const int hh = (int)(blockIdx.x >> 3) % heads;
-  pos = claim_item(pos, n_items, P.ticket ? P.ticket + hh : nullptr, NW == 2 ? (int*)&ring[NW - 1][RING_B - 4] : nullptr);
-  if (pos < 0) return;
-  const WorkItem item = uniform_item(P.items, pos);
   const int hs = item.hs, i = item.i, L = item.len;
   const int64_t seq0 = item.seq0;
   const int h = P.mode == SB_SELECT_PER_QHEAD ? hs : hs * P.G + hh;
@@ -406,6 +397,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64
       }
     }
   }
+}
+
+template <int D, bool OUT_F32, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1))) void attn_fwd_head_kernel(AttnParams P, int heads) {
+  __shared__ __attribute__((aligned(1024))) char ring[NW][kFwdRing<D>];
+  BusyTimer timer;
+  timer.start(P);
+  for_items<D, NW>(P, heads, (int*)&ring[NW - 1][kFwdRing<D> - 4],
+                [&](const AttnParams& p, const WorkItem& item, int hh) __attribute__((always_inline)) { fwd_head_item<D, OUT_F32, NW>(p, item, hh, ring); });
   timer.stop(P);
 }
 
@@ -430,7 +430,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void a
   timer.start(P);
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
-  const int pos = claim_item(blockIdx.x, P.n_items, P.ticket ? P.ticket + blockIdx.y : nullptr);
+  const int pos = claim_item(blockIdx.x, P.n_items, P.ticket ? P.ticket + kTicketInts * blockIdx.y : nullptr);
   if (pos < 0) return;
   const WorkItem item = P.items[pos];  // (scalar loads make the compiler keep more in registers than there are: 1.70 -> 1.74 ms on the 32768-token batch)
   const int hs = item.hs, i = item.i, L = item.len, e0 = item.e0, ntiles = item.ntiles;
@@ -649,9 +649,10 @@ int convert_f32_to_bf16(const Conversions& c, hipStream_t st) {
 }
 
 template <int D>
-static void launch_fwd_head(const Geo& g, const AttnParams& P, dim3 grid, hipStream_t st, int n_items, int heads) {
+static void launch_fwd_head(const Geo& g, const AttnParams& P, hipStream_t st, int heads) {
   const bool one = one_wavefront_per_item(g, (int64_t)g.Hq * g.NQB, D == 64 ? 24 : 16);
-#define SB_FWD_LAUNCH(FF, NW) hipLaunchKernelGGL((attn_fwd_head_kernel<D, FF, NW>), grid, dim3(64 * NW), 0, st, P, n_items, heads)
+  const dim3 grid((unsigned)head_grid(P, heads, D, one ? 1 : 2));
+#define SB_FWD_LAUNCH(FF, NW) hipLaunchKernelGGL((attn_fwd_head_kernel<D, FF, NW>), grid, dim3(64 * NW), 0, st, P, heads)
   if (one) {
     if (P.out_f32) SB_FWD_LAUNCH(true, 1); else SB_FWD_LAUNCH(false, 1);
   } else {
@@ -706,27 +707,25 @@ extern "C" int sb_sparse_attn_fwd(const sb_problem* p, const void* q, const void
   const int64_t n_items = (int64_t)g.Hs * g.NQB;
   if (n_items > 0x3fffffffll) { set_error("too many work items for one launch"); return SB_ERR_INVALID_ARG; }
   const int parts = (heads + 3) / 4, hpp = (heads + parts - 1) / parts;  // the group kernel takes `hpp` heads per workgroup
-  const bool tickets = use_tickets(n_items) && heads <= kTicketSlots;
   P.n_items = (int)n_items; P.ticket = nullptr;
+  const bool group = g.D == 128 && hpp >= 3 && parts * hpp == heads;
+  const bool tickets = group ? use_tickets(n_items) && parts <= kTicketPlanes : use_head_tickets(n_items, heads);
   KernelTimer kt(K_FWD, st);
   if (tickets) {
     P.ticket = (int*)(wb + wo.ticket);
-    if ((rc = fill_zero(P.ticket, sizeof(int32_t) * kTicketSlots, st)) != SB_OK) return rc;
+    if ((rc = fill_zero(P.ticket, sizeof(int32_t) * kTicketInts * (group ? parts : 1), st)) != SB_OK) return rc;
   }
-  const int64_t n_slots = ticketed_grid(n_items, tickets);  // workgroups per head plane
   // Heads that share K/V tiles in LDS gather a third of what the per-head kernel does: faster on long sequences (131072 tokens, top 32:
   // 4.58 against 4.69 ms, 262144 tokens 15.8 against 16.0; the 32768-token batch 1.78 against 1.76), but not with a head slot left idle,
   // and not at D = 64 (65536 tokens, 14/2 heads, blocks of 256: 1.49 against 1.37).
-  if (g.D == 128 && hpp >= 3 && parts * hpp == heads) {
-    dim3 grid((unsigned)n_slots, (unsigned)parts), block(128 * hpp);
+  if (group) {
+    dim3 grid((unsigned)ticketed_grid(n_items, tickets), (unsigned)parts), block(128 * hpp);
     if (P.out_f32) hipLaunchKernelGGL((attn_fwd_group_kernel<true>), grid, block, 0, st, P, heads);
     else hipLaunchKernelGGL((attn_fwd_group_kernel<false>), grid, block, 0, st, P, heads);
   } else {
-    const int64_t n_wg = n_slots * heads;
-    if (n_wg > 0x7fffffffll) { set_error("too many work items for one launch"); return SB_ERR_INVALID_ARG; }
-    dim3 grid((unsigned)n_wg);
-    if (g.D == 128) launch_fwd_head<128>(g, P, grid, st, (int)n_items, heads);
-    else launch_fwd_head<64>(g, P, grid, st, (int)n_items, heads);
+    if (head_ids(n_items, heads) > 0x7fffffffll) { set_error("too many work items for one launch"); return SB_ERR_INVALID_ARG; }
+    if (g.D == 128) launch_fwd_head<128>(g, P, st, heads);
+    else launch_fwd_head<64>(g, P, st, heads);
   }
   SB_LAUNCH_CHECK("attn_fwd_kernel");
   return SB_OK;

@@ -201,7 +201,7 @@ static WsOffsets ws_offsets(const Geo& g, bool bwd) {
   w.doc = o; o = align_up(o + (bwd ? qbytes : 0));
   w.drow = o; o = align_up(o + (bwd ? sizeof(float) * (size_t)g.T * g.Hq : 0));
   w.lse2 = o; o = align_up(o + (bwd ? sizeof(float) * (size_t)g.T * g.Hq : 0));
-  w.ticket = o; o = align_up(o + sizeof(int32_t) * 64);
+  w.ticket = o; o = align_up(o + sizeof(int32_t) * kTicketInts * kTicketPlanes);
   const Geo tg = tile_geo(g);  // idempotent
   w.partials = o; o = align_up(o + (bwd ? sizeof(float) * (2 * (size_t)split_extra_max(tg) + (size_t)tg.Hkv * (size_t)sub_slots_max(tg)) * 2 * 64 * g.D : 0));
   w.bytes = o;

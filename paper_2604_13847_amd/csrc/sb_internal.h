@@ -119,7 +119,7 @@ struct PlanOffsets {
   size_t colcost;    // int32 [Hkv*NQB]  tiles in each key-major column (summed over the group's heads)
   size_t zeros_end;  // end of colcost
   size_t bwd_items;  // ColItem [Hkv*(NQB+E)]  key-major items: entry r*Hkv + g is the r-th heaviest item of KV head g (col = -1: none)
-  size_t counters;   // int32 [4]  {partial slots in use, split columns, sub-part slots in use}, zeroed by every plan call
+  size_t counters;   // int32 [4]  {partial slots in use, split columns, sub-part slots in use, most key-major items of a KV head}, zeroed by every plan call
   size_t split_cols; // int32 [3*E]  (column, first partial slot, parts) of every split column
   size_t sub_base;   // int32 [Hkv*(NQB+E)]  first sub-part slot of every key-major item (see sub_weight), -1: none
   size_t sub_items;  // SubItem [Hkv*sub_slots_max]  the sub-parts: entry r*Hkv + g, those of KV head g's heaviest items first (col = -1: none)
@@ -208,17 +208,27 @@ struct WsOffsets {
   size_t qc, kc, vc, oc, doc;  // bf16 copies when dtype == SB_F32 (0 size otherwise)
   size_t drow;       // float [Hq][T]
   size_t lse2;       // float [Hq][T]
-  size_t ticket;     // int32 [64] work tickets of the query-major attention kernels (kTicketSlots)
+  size_t ticket;     // int32 [kTicketPlanes][kTicketInts] work tickets of the attention kernels
   size_t partials;   // float [2*E + sub-parts][dK, dV][64][D]  partial sums of the parts of split key-major columns, then of the sub-parts
   size_t bytes;
 };
 WsOffsets fwd_ws_offsets(const Geo& g);
 WsOffsets bwd_ws_offsets(const Geo& g);
-// Workgroups to launch for a list of n items when one item in sixteen is handed out by ticket at the end of the launch
-// (see claim_item in sb_attn_common.h): two tail workgroups per held-back item, the total a multiple of 8.
+// Launches whose list is handed out by ticket (see draw_item and ItemQueue in sb_attn_common.h): its first *_lead items are tied to workgroups,
+// and there are more workgroups than items, for XCDs that draw more than their share.  Where the lines lie: what is drawn must be
+// enough to even out what the XCDs' paces differ by (up to 10 %).  Key-major items are columns, few and heavy: half of them; an
+// eighth or a quarter of the list by ticket is 4 and 1 % slower (65536 tokens, 28/4 heads: 7.26 and 7.08 ms against 6.97), three quarters and
+// all of it equal or slower.  Query-major launches that do not draw item after item: a quarter, where a draw (1 us, or 5 for a
+// workgroup that finds nothing left) is to a workgroup's 20 us and more.
 constexpr int64_t kTicketMinItems = 4096;  // shorter lists are dealt by position only
+constexpr int kTicketPlanes = 16;          // of 8 counters, which are cache lines apart (in one line 8 XCDs' draws waited for each other: 15 us each)
+constexpr int kTicketPitch = 64, kTicketInts = 8 * kTicketPitch;
 inline bool use_tickets(int64_t n) { return n >= kTicketMinItems; }
-inline int64_t ticketed_grid(int64_t n, bool tickets) { return (n + (tickets ? (n >> 7) << 3 : 0) + 7) / 8 * 8; }
+inline __host__ __device__ int query_lead(int n) { return n / 32 * 24; }
+inline int64_t ticketed_grid(int64_t n, bool tickets) { return (n + (tickets ? n / 64 : 0) + 7) / 8 * 8; }
+inline __host__ __device__ int key_lead(int n) { return n / 16 * 8; }
+inline __host__ __device__ int64_t key_extra(int64_t n) { return n / 8; }
+inline bool use_key_tickets(int64_t n) { return use_tickets(n) && n + key_extra(n) < (1ll << 24); }  // (a launch has fewer than 2^32 threads)
 // Is a query-major item of one query head one wavefront's work, or two's?  Of `items` with at most `most` tiles, w wavefronts each, the
 // chip works on 1024 / w at a time (head_dim 64: twice as many); an item costs about `fixed` tile times of two wavefronts besides its
 // tiles (where the chip is not full and its clock is high: forward 16, dQ and head_dim 64 24), and the launch takes as long as its share

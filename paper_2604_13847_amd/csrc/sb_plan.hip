@@ -299,6 +299,7 @@ __global__ __launch_bounds__(1024) void plan_bwd_order_kernel(const int32_t* __r
   for (int w = 0; w < (tid >> 6); ++w) run += sh[w];
 #pragma unroll
   for (int a = 0; a < per; ++a) { bins[kBwdBins - 1 - (tid * per + a)] = run; run += v[a]; }
+  if (tid == 1023) atomicMax(&counters[3], wsub > 0 ? run & 0xffff : run);
   __syncthreads();
   for (int64_t c = tid; c < NQB; c += 1024) {
     const int32_t col = (int32_t)(g * NQB + c);

@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("case", ["small", "ticketed"])
 def test_captured_step_replays_bitwise(case):
     """"ticketed": more than 4096 query-major items, so the forward and dQ launches hand the tail of their work list out
-    through a ticket counter that a fill kernel clears in every step; this step also scores and selects in one kernel."""
+    through ticket counters that a fill kernel clears in every step; this step also scores and selects in one kernel."""
     if case == "small":
         w = synth.small_ragged(seed=2, lens=(700, 64, 1, 2100, 333), Hq=8, Hkv=2, D=128, ratio=(0.2, 0.6))
     else:
