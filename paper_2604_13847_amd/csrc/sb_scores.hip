@@ -61,14 +61,17 @@ __global__ __launch_bounds__(256) void pool_kernel(const void* __restrict__ Q, c
 
 // Score tiles on the fp32 matrix cores (the selection is taken on fp32 scores, so the operands stay
 // fp32).  One workgroup per (64 query blocks of one sequence, chunk of up to 2^kScChunkLog * 64 key
-// blocks, selection head): the pooled query tile is staged in LDS once, the pooled key tiles one
-// after the other; each of the four wavefronts keeps 16 query rows in registers and computes the
-// four 16 x 16 tiles of its rows in every 64 x 64 score tile.  Tiles right of the diagonal are
+// blocks, selection head): each of the four wavefronts keeps 16 query rows in registers, straight from memory; the pooled key
+// tiles are staged in LDS one after the other, and a wavefront computes the four 16 x 16 tiles of its rows in every 64 x 64 score
+// tile, transposed, so that a lane holds four columns of a row and stores 16 bytes at once.  Tiles right of the diagonal are
 // -infinity without being computed, and the last chunk of a row tile also fills every column to
 // its right with -infinity, so that the whole n x n matrix is defined.  Splitting the columns over
 // workgroups keeps the longest workgroup short however long the sequence is.
+// What bounds it: the matrix takes 0.11 ms to write and 0.11 ms of the fp32 matrix cores (131072 tokens, 32 heads: 537 MB), and a
+// workgroup waits between two barriers per tile, so it needs others beside it: with the query tile in LDS too two of them fitted a CU,
+// without it four, at 128 registers: 0.306 -> 0.229 ms.
 // A key tile takes a workgroup 2 us, so where four to a workgroup make fewer workgroups than the chip runs at once, each gets one
-// (18889 tokens, 32/8 heads: 27 -> 21 us, 26565 tokens in several sequences, 16/2 heads: 22 -> 17); otherwise four, which share the staged query tile.
+// (18889 tokens, 32/8 heads: 27 -> 21 us, 26565 tokens in several sequences, 16/2 heads: 22 -> 17); otherwise four, which share the query rows.
 constexpr int kScChunkLog = 2;
 constexpr int64_t kScFewWgs = 512;
 
@@ -79,11 +82,11 @@ __host__ __device__ inline int64_t score_items(int64_t nt, int lg) {
 }
 
 template <int D, int lg>
-__global__ __launch_bounds__(256) void score_kernel(const float* __restrict__ qbar, const float* __restrict__ kbar, GeomArgs ga, int Hq,
-                                                    int Hkv, int Hs, int G, int mode, float scale, float* __restrict__ scores) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void score_kernel(
+    const float* __restrict__ qbar, const float* __restrict__ kbar, GeomArgs ga, int Hq, int Hkv, int Hs, int G, int mode, float scale,
+    float* __restrict__ scores) {
   constexpr int chunk = 1 << lg;
-  constexpr int LD = D + 4;  // padded row length (floats) of the LDS tiles
-  __shared__ float qs[64 * LD];
+  constexpr int LD = D + 4;  // padded row length (floats) of the LDS tile
   __shared__ float ks[64 * LD];
   const int tid = threadIdx.x;
   // (sequence, row tile, column chunk) of this workgroup
@@ -106,21 +109,26 @@ __global__ __launch_bounds__(256) void score_kernel(const float* __restrict__ qb
   const int heads = mode == SB_SELECT_PER_QHEAD ? 1 : G;
   const int h0 = mode == SB_SELECT_PER_QHEAD ? hs : hs * G;
   const int g = h0 / G;
-  // stage the pooled query tile (summed over the group's heads in per-KV-group mode)
-  for (int u = tid; u < 64 * (D / 4); u += 256) {
-    const int r = u / (D / 4), c = (u % (D / 4)) * 4;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (r < rows)
-      for (int hh = 0; hh < heads; ++hh) {
-        const float4 v = *(const float4*)(qbar + ((qb0 + i0 + r) * Hq + h0 + hh) * D + c);
-        acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
-      }
-    *(float4*)(qs + r * LD + c) = acc;
-  }
   const int wave = tid >> 6, lane = tid & 63, l16 = lane & 15, kq = lane >> 4;
   const float ninf = -__builtin_inff();
-  float a[D / 4];  // this lane's quarter of query row 16 * wave + l16 (filled once the tile is staged)
-  bool have_a = false;
+  // This lane's quarter of query row 16 * wave + l16, summed over the group's heads in per-KV-group mode.  Rows past the end repeat the
+  // last one; their results are dropped.
+  float a[D / 4];
+#pragma unroll
+  for (int t = 0; t < D / 4; ++t) a[t] = 0.f;
+  for (int hh = 0; hh < heads; ++hh) add_quarter<D>(a, qbar + ((qb0 + min(i0 + 16 * wave + l16, n - 1)) * Hq + h0 + hh) * D, kq);
+  // columns j .. j+3 of row i; where the row ends in between, those that exist
+  auto store4 = [&](int i, int j, f32x4s x) __attribute__((always_inline)) {
+    typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // (a row starts at any multiple of four bytes)
+    float* o = out + (int64_t)i * n + j;
+    if (j + 4 <= n) {
+      *(f32x4u*)o = x;
+    } else {
+#pragma unroll
+      for (int v = 0; v < 3; ++v)
+        if (j + v < n) o[v] = x[v];
+    }
+  };
   // A key tile is fetched into registers one tile ahead (its loads are in flight while the tile before it is being
   // multiplied) and written to LDS between the two barriers.
   constexpr int PF = 64 * (D / 4) / 256;  // float4 per thread and key tile
@@ -140,17 +148,10 @@ __global__ __launch_bounds__(256) void score_kernel(const float* __restrict__ qb
     const int jt = jc * chunk + c, j0 = jt * 64;
     if (j0 >= n) break;
     if (jt > it) {  // entirely in the future of these rows
-      for (int u = tid; u < rows * 64; u += 256) {
-        const int r = u >> 6, j = j0 + (u & 63);
-        if (j < n) out[(int64_t)(i0 + r) * n + j] = ninf;
-      }
+      for (int u = tid; u < rows * 16; u += 256) store4(i0 + (u >> 4), j0 + 4 * (u & 15), f32x4s{ninf, ninf, ninf, ninf});
       continue;
     }
-    __syncthreads();  // the previous key tile has been consumed (and, the first time, the query tile is staged)
-    if (!have_a) {
-      load_quarter<D>(a, qs + (16 * wave + l16) * LD, kq);
-      have_a = true;
-    }
+    __syncthreads();  // the previous key tile has been consumed
 #pragma unroll
     for (int x = 0; x < PF; ++x) {
       const int u = tid + 256 * x, r = u / (D / 4), cc = (u % (D / 4)) * 4;
@@ -160,27 +161,23 @@ __global__ __launch_bounds__(256) void score_kernel(const float* __restrict__ qb
     __syncthreads();
 #pragma unroll
     for (int c4 = 0; c4 < 4; ++c4) {
-      const int j = j0 + 16 * c4 + l16;
+      const int i = i0 + 16 * wave + l16, j = j0 + 16 * c4 + 4 * kq;  // this lane's row, first of its four columns
       const bool future = j0 + 16 * c4 > i0 + 16 * wave + 15;  // the whole 16 x 16 tile lies right of the diagonal
       f32x4s acc = {0.f, 0.f, 0.f, 0.f};
       if (!future) {
         float b[D / 4];
         load_quarter<D>(b, ks + (16 * c4 + l16) * LD, kq);
-        acc = score_tile16<D>(a, b);
+        acc = score_tile16<D>(b, a);  // (transposed: the lane gets four columns of a row, not four rows of a column)
       }
-      if (j < n) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int i = i0 + 16 * wave + 4 * kq + v;
-          if (i < n) out[(int64_t)i * n + j] = j < i ? scale * acc[v] : ninf;
-        }
-      }
+      for (int v = 0; v < 4; ++v) acc[v] = j + v < i ? scale * acc[v] : ninf;
+      if (i < n) store4(i, j, acc);
     }
   }
   if (jc == it >> lg) {  // last chunk of this row tile: every column to its right is in the future
     const int jstart = (jc + 1) * chunk * 64;
-    for (int r = 0; r < rows; ++r)
-      for (int j = jstart + tid; j < n; j += 256) out[(int64_t)(i0 + r) * n + j] = ninf;
+    for (int r = wave; r < rows; r += 4)
+      for (int j = jstart + 4 * lane; j < n; j += 256) store4(i0 + r, j, f32x4s{ninf, ninf, ninf, ninf});
   }
 }
 
