@@ -77,25 +77,46 @@ __device__ inline int64_t sel_rows_before(int i, int k) {
 // the scale of the scores), then a ranking of the few keys in the bin that holds the threshold.
 // Otherwise, or when the threshold lies outside those bins or its bin holds more than 64 keys: a radix
 // select over all 32 bits, 8 bits per pass.
+// The keys are walked several at a time, all LDS reads of a step in flight, and in the two walks that look for few of them 64 keys
+// without one cost two instructions (kept and candidate keys are rare where the budget is small): 131072 tokens, 32 heads, top 32:
+// 0.199 -> 0.180 ms, with the largest key taken along where the keys are made.
 constexpr int kDistShift = 17;
 
-__device__ inline void select_row(const uint32_t* keys, int* hist, int lane, int m, int need, int i, int32_t* __restrict__ out) {
+// f(j, key, j < m) for this lane's keys j = lane, lane + 64, ...; every lane takes part in every call
+template <typename F>
+__device__ __forceinline__ void walk_keys(const uint32_t* keys, int lane, int m, F f) {
+  constexpr int U = 4;
+  int j0 = 0;
+  for (; j0 + 64 * U <= m; j0 += 64 * U) {
+    uint32_t k[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) k[u] = keys[j0 + 64 * u + lane];
+#pragma unroll
+    for (int u = 0; u < U; ++u) f(j0 + 64 * u + lane, k[u], true);
+  }
+  for (; j0 < m; j0 += 64) {
+    const bool valid = j0 + lane < m;
+    f(j0 + lane, valid ? keys[j0 + lane] : 0u, valid);
+  }
+}
+
+// `largest`: the largest of this lane's keys lane, lane + 64, ...
+__device__ inline void select_row(const uint32_t* keys, int* hist, int lane, int m, int need, int i, int32_t* __restrict__ out, uint32_t largest) {
   const unsigned long long lt = (1ull << lane) - 1ull;
   uint32_t thr = 0;
   int remaining = 0;
   bool found_thr = false;
   if (need * 4 <= m) {
-    uint32_t kmax = 0;
-    for (int j = lane; j < m; j += 64) kmax = max(kmax, keys[j]);
+    uint32_t kmax = largest;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, off, 64));
 #pragma unroll
     for (int a = 0; a < 4; ++a) hist[lane + 64 * a] = 0;
     wave_lds_fence();
-    for (int j = lane; j < m; j += 64) {
-      const uint32_t d = (kmax - keys[j]) >> kDistShift;
-      if (d < 255u) atomicAdd(&hist[d], 1);
-    }
+    walk_keys(keys, lane, m, [&](int, uint32_t kk, bool valid) {
+      const uint32_t d = (kmax - kk) >> kDistShift;
+      if (valid && d < 255u) atomicAdd(&hist[d], 1);
+    });
     wave_lds_fence();
     // lane L owns bins 4L .. 4L+3 (ascending distance = descending key; bin 255 is never counted)
     int v[4], sum = 0;
@@ -124,14 +145,13 @@ __device__ inline void select_row(const uint32_t* keys, int* hist, int lane, int
         wave_lds_fence();
         uint32_t* cand = (uint32_t*)hist;
         int pos = 0;
-        for (int j0 = 0; j0 < m; j0 += 64) {
-          const int j = j0 + lane;
-          const uint32_t kk = j < m ? keys[j] : 0u;
-          const bool is_c = j < m && ((kmax - kk) >> kDistShift) == (uint32_t)bin;
+        walk_keys(keys, lane, m, [&](int, uint32_t kk, bool valid) {
+          const bool is_c = valid && ((kmax - kk) >> kDistShift) == (uint32_t)bin;
           const unsigned long long bc = __builtin_amdgcn_ballot_w64(is_c);
+          if (bc == 0) return;
           if (is_c) cand[pos + __builtin_popcountll(bc & lt)] = kk;
           pos += __builtin_popcountll(bc);
-        }
+        });
         wave_lds_fence();
         const bool valid = lane < cnt;
         const uint32_t mine = valid ? cand[lane] : 0u;
@@ -157,10 +177,9 @@ __device__ inline void select_row(const uint32_t* keys, int* hist, int lane, int
 #pragma unroll
       for (int a = 0; a < 4; ++a) hist[lane + 64 * a] = 0;
       wave_lds_fence();
-      for (int j = lane; j < m; j += 64) {
-        const uint32_t kk = keys[j];
-        if ((kk & mask) == prefix) atomicAdd(&hist[(kk >> shift) & 255u], 1);
-      }
+      walk_keys(keys, lane, m, [&](int, uint32_t kk, bool valid) {
+        if (valid && (kk & mask) == prefix) atomicAdd(&hist[(kk >> shift) & 255u], 1);
+      });
       wave_lds_fence();
       // lane L owns bins 255-4L .. 252-4L (descending); `above` = matching keys in higher bins
       int v[4], sum = 0;
@@ -191,10 +210,8 @@ __device__ inline void select_row(const uint32_t* keys, int* hist, int lane, int
   }
   // keys > thr are all kept; of the keys == thr the `remaining` lowest indices are kept; output in index order
   int eq_seen = 0, pos = 0;
-  for (int j0 = 0; j0 < m; j0 += 64) {
-    const int j = j0 + lane;
-    const bool valid = j < m;
-    const uint32_t kk = valid ? keys[j] : 0u;
+  walk_keys(keys, lane, m, [&](int j, uint32_t kk, bool valid) {
+    if (__builtin_amdgcn_ballot_w64(valid && kk >= thr) == 0) return;
     const bool is_eq = valid && kk == thr;
     const unsigned long long beq = __builtin_amdgcn_ballot_w64(is_eq);
     const int eq_rank = eq_seen + __builtin_popcountll(beq & lt);
@@ -203,7 +220,7 @@ __device__ inline void select_row(const uint32_t* keys, int* hist, int lane, int
     if (keep) out[pos + __builtin_popcountll(bk & lt)] = j;
     pos += __builtin_popcountll(bk);
     eq_seen += __builtin_popcountll(beq);
-  }
+  });
   if (lane == 0) out[need] = i;
 }
 

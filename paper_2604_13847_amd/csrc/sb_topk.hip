@@ -43,16 +43,21 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ sco
     return;
   }
   const float* row = scores + (int64_t)Hs * sg.sc_off + ((int64_t)hs * n + i) * n;
+  uint32_t largest = 0;
   for (int j0 = lane; j0 < m; j0 += 64 * 8) {  // eight independent loads in flight per lane: the row comes from HBM
     float x[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) x[u] = j0 + 64 * u < m ? row[j0 + 64 * u] : 0.f;
 #pragma unroll
     for (int u = 0; u < 8; ++u)
-      if (j0 + 64 * u < m) keys[j0 + 64 * u] = order_key(x[u]);
+      if (j0 + 64 * u < m) {
+        const uint32_t key = order_key(x[u]);
+        largest = max(largest, key);
+        keys[j0 + 64 * u] = key;
+      }
   }
   wave_lds_fence();
-  select_row(keys, hist, lane, m, need, i, out);
+  select_row(keys, hist, lane, m, need, i, out, largest);
 }
 
 // Scores and selection in one kernel: the scores of a row never leave the compute unit.  One
@@ -128,7 +133,9 @@ __global__ __launch_bounds__(64 * kFusedWaves) void score_select_kernel(
       } else if (need == 0) {
         if (lane == 0) out[0] = i;
       } else {
-        select_row(keys + (size_t)wave * stride, hist + 256 * wave, lane, m, need, i, out);
+        uint32_t largest = 0;
+        walk_keys(keys + (size_t)wave * stride, lane, m, [&](int, uint32_t key, bool) { largest = max(largest, key); });
+        select_row(keys + (size_t)wave * stride, hist + 256 * wave, lane, m, need, i, out, largest);
       }
     }
     __syncthreads();  // the keys are overwritten by the next segment
