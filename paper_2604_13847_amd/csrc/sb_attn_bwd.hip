@@ -305,14 +305,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void a
 // loop); against the kernel above on 65536 tokens, 14/2 heads, blocks of 256: 1.98 -> 1.77 ms, per KV group 2.45 -> 1.75.
 template <int D> constexpr int kDqRing = 4 * 32 * D * 2;  // a wavefront's K even, K odd, V even, V odd strips
 
-template <int D, bool OUT_F32, int NW>
+template <int D, bool OUT_F32, int NW, bool LOOP>
 __device__ __attribute__((always_inline)) inline void dq_head_item(const AttnParams& P, const WorkItem& item, int hh, char (&ring)[NW][kDqRing<D>]) {
   constexpr int ROW_B = D * 2, STRIP_B = 32 * ROW_B, NOP = D / 16;
   using Loader = QuadLoader<D>;
   constexpr int LPS = Loader::LPS;
   constexpr int KV = D == 64 ? NOP : 6;  // Q, dQ and the dO operands below this one live in accumulation registers, the other dO operands do not fit there
   constexpr int PER = 8 / NOP;           // registers of the vector work per matrix instruction
-  const int tid = item_tid<D>();
+  const int tid = item_tid<LOOP>();
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int hs = item.hs, i = item.i, L = item.len, ntiles = item.ntiles;
   const int64_t seq0 = item.seq0;
@@ -643,13 +643,13 @@ __device__ __attribute__((always_inline)) inline void dq_head_item(const AttnPar
     }
 }
 
-template <int D, bool OUT_F32, int NW>
+template <int D, bool OUT_F32, int NW, bool LOOP>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1))) void attn_bwd_dq_head_kernel(AttnParams P, int heads) {
   __shared__ __attribute__((aligned(1024))) char ring[NW][kDqRing<D>];
   BusyTimer timer;
   timer.start(P);
-  for_items<D, NW>(P, heads, (int*)&ring[NW - 1][kDqRing<D> - 4],
-                [&](const AttnParams& p, const WorkItem& item, int hh) __attribute__((always_inline)) { dq_head_item<D, OUT_F32, NW>(p, item, hh, ring); });
+  for_items<D, NW, LOOP>(P, heads, (int*)&ring[NW - 1][kDqRing<D> - 4],
+                [&](const AttnParams& p, const WorkItem& item, int hh) __attribute__((always_inline)) { dq_head_item<D, OUT_F32, NW, LOOP>(p, item, hh, ring); });
   timer.stop(P);
 }
 
@@ -1202,8 +1202,17 @@ static int launch_bwd(const Geo& g, const AttnParams& P, hipStream_t st) {
     if (head_ids(P.n_items, heads) > 0x7fffffffll) { set_error("too many work items for one launch"); return SB_ERR_INVALID_ARG; }
     const bool one = one_wavefront_per_item(g, items, 24);
     const dim3 grid((unsigned)head_grid(P, heads, D, one ? 1 : 2));
-    if (one) hipLaunchKernelGGL((attn_bwd_dq_head_kernel<D, F32, 1>), grid, dim3(64), 0, st, P, heads);
-    else hipLaunchKernelGGL((attn_bwd_dq_head_kernel<D, F32, 2>), grid, dim3(128), 0, st, P, heads);
+    auto launch = [&](auto nw, auto loop) {
+      constexpr int NW = decltype(nw)::value;
+      hipLaunchKernelGGL((attn_bwd_dq_head_kernel<D, F32, NW, decltype(loop)::value>), grid, dim3(64 * NW), 0, st, P, heads);
+    };
+    auto with_loop = [&](auto nw) {
+      if constexpr (D == 128) {
+        if (head_loop(P, D)) return launch(nw, std::true_type());
+      }
+      launch(nw, std::false_type());
+    };
+    if (one) with_loop(std::integral_constant<int, 1>()); else with_loop(std::integral_constant<int, 2>());
   }
   SB_LAUNCH_CHECK("attn_bwd_dq_kernel");
   return SB_OK;

@@ -97,10 +97,11 @@ __device__ inline WorkItem uniform_item(const WorkItem* items, int pos) {
 // turn) and share its L2.
 inline __host__ __device__ int64_t head_ids(int64_t n_items, int heads) { return (n_items + 7) / 8 * 8 * heads; }
 inline bool use_head_tickets(int64_t n_items, int heads) { return use_tickets(n_items) && head_ids(n_items, heads) < (1ll << 30); }
+inline bool head_loop(const AttnParams& P, int D) { return P.ticket && D == 128; }
 inline int64_t head_grid(const AttnParams& P, int heads, int D, int nw) {
   const int64_t ids = head_ids(P.n_items, heads);
   if (!P.ticket) return ids;
-  return D == 128 ? 1024 / nw : ticketed_grid(ids, true);
+  return head_loop(P, D) ? 1024 / nw : ticketed_grid(ids, true);
 }
 // The items of one workgroup.  A launch without tickets: workgroup w takes item w.  With tickets at D = 128, where a wavefront fills its
 // SIMD: as many workgroups as the chip runs at a time, which draw one item after the other.  At D = 64 workgroups take one item each, the
@@ -108,10 +109,12 @@ inline int64_t head_grid(const AttnParams& P, int heads, int D, int nw) {
 // blocks of 256 1.40 -> 1.44 ms).  At D = 128 the draw takes the place of a workgroup's start, against a quarter of the items by ticket, one a
 // workgroup: the forward of 65536 tokens whose selection is a sink and a window 1.76 -> 1.66 ms, dQ 2.13 -> 2.06, of 131072 items of one or
 // four tiles 650 -> 613 us and 1.19 -> 1.15 ms.  (The draw ahead of an item's output: 2 % faster on rows of 32 tiles, 4 % slower on short ones.)
+// LOOP: the launch draws item after item.  A kernel of its own, because the loop costs a launch without tickets up to 1.4 us (2039 tokens,
+// 16/2 heads: forward 22.0 -> 20.7 us).
 // `sh` is an LDS word for launches of two wavefronts per item, which only wavefronts other than the first write otherwise.
-template <int D, int NW>
+template <int D, int NW, bool LOOP>
 struct ItemQueue {
-  static constexpr bool kLoop = D == 128;
+  static constexpr bool kDraw = LOOP || D != 128;  // a launch at D = 128 that does not loop has no tickets
   WorkItem item;
   int hh;  // query head of the group
   int id, ids, lead, heads;
@@ -137,25 +140,23 @@ struct ItemQueue {
   __device__ inline void first(const AttnParams& P, int heads_, int* sh) {
     heads = heads_;
     ids = (int)head_ids(P.n_items, heads);
-    lead = !P.ticket ? ids : kLoop ? (int)gridDim.x : query_lead(ids);
+    lead = LOOP ? (int)gridDim.x : kDraw && P.ticket ? query_lead(ids) : ids;
     id = (int)blockIdx.x;
-    if (id >= lead) draw(P, sh);
+    if (kDraw && id >= lead) draw(P, sh);
     else if (pos_of(id) >= P.n_items) id = -1;
     descriptor(P);
   }
   __device__ inline void next(const AttnParams& P, int* sh) {
-    id = -1;
-    if (!P.ticket) return;
     if (NW == 2) __syncthreads();  // the item's LDS is free
     draw(P, sh);
     descriptor(P);
   }
 };
 // What does not depend on the item would otherwise be worked out and kept in registers from before the loop, ahead of what the item needs.
-template <int D>
+template <bool LOOP>
 __device__ inline int item_tid() {
   int x = (int)threadIdx.x;
-  if (ItemQueue<D, 1>::kLoop) asm volatile("" : "+v"(x));
+  if (LOOP) asm volatile("" : "+v"(x));
   return x;
 }
 __device__ inline AttnParams reloaded_params() {  // the kernel's first argument, by scalar loads
@@ -163,11 +164,11 @@ __device__ inline AttnParams reloaded_params() {  // the kernel's first argument
   asm volatile("" : "+s"(p));
   return *(const AttnParams*)p;
 }
-template <int D, int NW, typename F>
+template <int D, int NW, bool LOOP, typename F>
 __device__ __attribute__((always_inline)) inline void for_items(const AttnParams& P, int heads, int* sh, F work) {
-  ItemQueue<D, NW> queue;
+  ItemQueue<D, NW, LOOP> queue;
   queue.first(P, heads, sh);
-  if constexpr (ItemQueue<D, NW>::kLoop) {
+  if constexpr (LOOP) {
     for (; queue.id >= 0; queue.next(P, sh)) work(reloaded_params(), queue.item, queue.hh);
   } else {
     if (queue.id >= 0) work(P, queue.item, queue.hh);

@@ -30,13 +30,13 @@ namespace sb {
 constexpr int kFwdV = 3;  // V strips in a wavefront's ring: K even, K odd, then V of strip t in slot 2 + t % kFwdV.  Four rings fill a CU's LDS.
 template <int D> constexpr int kFwdRing = (2 + kFwdV) * 32 * D * 2;
 
-template <int D, bool OUT_F32, int NW>
+template <int D, bool OUT_F32, int NW, bool LOOP>
 __device__ __attribute__((always_inline)) inline void fwd_head_item(const AttnParams& P, const WorkItem& item, int hh, char (&ring)[NW][kFwdRing<D>]) {
   constexpr int ROW_B = D * 2, STRIP_B = 32 * ROW_B, NOP = D / 16;
   constexpr float kLazy = 4.0f;
   using Loader = QuadLoader<D>;
   constexpr int LPS = Loader::LPS;
-  const int tid = item_tid<D>();
+  const int tid = item_tid<LOOP>();
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
   const int hs = item.hs, i = item.i, L = item.len;
   const int64_t seq0 = item.seq0;
@@ -399,13 +399,13 @@ __device__ __attribute__((always_inline)) inline void fwd_head_item(const AttnPa
   }
 }
 
-template <int D, bool OUT_F32, int NW>
+template <int D, bool OUT_F32, int NW, bool LOOP>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1))) void attn_fwd_head_kernel(AttnParams P, int heads) {
   __shared__ __attribute__((aligned(1024))) char ring[NW][kFwdRing<D>];
   BusyTimer timer;
   timer.start(P);
-  for_items<D, NW>(P, heads, (int*)&ring[NW - 1][kFwdRing<D> - 4],
-                [&](const AttnParams& p, const WorkItem& item, int hh) __attribute__((always_inline)) { fwd_head_item<D, OUT_F32, NW>(p, item, hh, ring); });
+  for_items<D, NW, LOOP>(P, heads, (int*)&ring[NW - 1][kFwdRing<D> - 4],
+                [&](const AttnParams& p, const WorkItem& item, int hh) __attribute__((always_inline)) { fwd_head_item<D, OUT_F32, NW, LOOP>(p, item, hh, ring); });
   timer.stop(P);
 }
 
@@ -652,13 +652,20 @@ template <int D>
 static void launch_fwd_head(const Geo& g, const AttnParams& P, hipStream_t st, int heads) {
   const bool one = one_wavefront_per_item(g, (int64_t)g.Hq * g.NQB, D == 64 ? 24 : 16);
   const dim3 grid((unsigned)head_grid(P, heads, D, one ? 1 : 2));
-#define SB_FWD_LAUNCH(FF, NW) hipLaunchKernelGGL((attn_fwd_head_kernel<D, FF, NW>), grid, dim3(64 * NW), 0, st, P, heads)
-  if (one) {
-    if (P.out_f32) SB_FWD_LAUNCH(true, 1); else SB_FWD_LAUNCH(false, 1);
-  } else {
-    if (P.out_f32) SB_FWD_LAUNCH(true, 2); else SB_FWD_LAUNCH(false, 2);
-  }
-#undef SB_FWD_LAUNCH
+  auto launch = [&](auto f32, auto nw, auto loop) {
+    constexpr int NW = decltype(nw)::value;
+    hipLaunchKernelGGL((attn_fwd_head_kernel<D, decltype(f32)::value, NW, decltype(loop)::value>), grid, dim3(64 * NW), 0, st, P, heads);
+  };
+  auto with_loop = [&](auto f32, auto nw) {
+    if constexpr (D == 128) {
+      if (head_loop(P, D)) return launch(f32, nw, std::true_type());
+    }
+    launch(f32, nw, std::false_type());
+  };
+  auto with_nw = [&](auto f32) {
+    if (one) with_loop(f32, std::integral_constant<int, 1>()); else with_loop(f32, std::integral_constant<int, 2>());
+  };
+  if (P.out_f32) with_nw(std::true_type()); else with_nw(std::false_type());
 }
 
 }  // namespace sb
