@@ -9,8 +9,7 @@
 // its min(k-1, i) largest shares (pref_i[i] = 1).  C_s(k) is the mean over the sequence's rows.
 // All kernels are deterministic (fixed summation order, no atomics):
 //   coverage_rows_regs_kernel   rows of at most 2048 candidates: one wavefront per (row, selection head) sorts the row in
-//                           registers (bitonic network, cross-lane permutes only at distances of a lane's share and
-//                           above), then softmax and prefix sums; summed over the heads of a group into
+//                           registers (long rows by a histogram first, short ones by a bitonic network), then softmax and prefix sums; summed over the heads of a group into
 //                           Pacc[s][i][m-1] = sum_hs pref_{hs,i}[m], m = 1..i
 //   coverage_rows_kernel    longer rows: one workgroup per query block and group of selection heads, for every head in
 //                           turn softmax + bitonic sort + prefix sum in LDS, into the same Pacc
@@ -20,6 +19,7 @@
 
 #include <mutex>
 
+#include "sb_geom.h"
 #include "sb_internal.h"
 
 namespace sb {
@@ -158,8 +158,8 @@ __global__ __launch_bounds__(256) void coverage_rows_kernel(const float* __restr
 // so that every compare-exchange puts the larger key first.  The four wavefronts of a workgroup take the heads of the
 // group in turn, keep their sums in registers and add them in wavefront order at the end: fixed summation order again.
 // Scores must be numbers (a NaN counts as -infinity); sb_block_scores writes none for finite inputs.
-// All row lengths share one kernel, so E = 32 sets the registers of all: four wavefronts per SIMD are asked for, which leaves 128, and the
-// compiler spills 16 vector and 130 scalar registers (131072 tokens, 32/8 heads: 384 us, without the request 400).
+// All row lengths share one kernel, so E = 32 sets the registers of all: 168 for three wavefronts per SIMD, nothing spilled (four would
+// leave 128 and 54 of them spilled).
 constexpr int kCovRegMax = 2048;
 
 // Scores as integers of the same order (and back): integer comparisons take a partner lane's key as an operand (DPP) as it is, float
@@ -198,11 +198,132 @@ __device__ __forceinline__ void cross_stage(int (&x)[E], int lane) {
   }
 }
 
+// Rows of 512 keys and more: most of the sorting is done by a histogram.  The keys fall, by value, into 64 E bins between the row's smallest
+// and largest; a key's place is where its bin begins plus how many came before it in the bin, an LDS atomic each; what is left out of order,
+// inside bins, an odd-even transposition network puts right in as many stages as the fullest bin has keys.  A bin with kCovBin keys or more
+// (ties, outliers) or a row whose values are not finite: false, and the network below does it all.
+// In which order a bin's keys are counted decides nothing: the result is the sorted row.  `lds`: cov_lds<E> words, the wavefront's own; a
+// lane's E words are four words further from the next lane's than they would have to be, or all lanes would read from the same banks.
+// What bounds both: instruction issue.  For 2048 keys the network takes 4000 vector instructions, this 1200 and 100 LDS operations: 131072
+// tokens, 32 heads: 0.370 -> 0.241 ms; 65536 tokens 0.110 -> 0.083 (both with the launch saved below).
+constexpr int kCovBin = 32;
+// (comparisons of all keys' places with the row's length would be kept, 64 scalar registers of them, from one phase to the next)
+__device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+s"(x));
+  return x;
+}
+// keys lane, lane + 64, ... of a row of i (any placement will do for what is then sorted), -infinity past its end and for a NaN
 template <int E>
-__device__ __forceinline__ void coverage_row_regs(const float* __restrict__ row, int i, int lane, float (&acc)[E]) {
-  int x[E];
+__device__ __forceinline__ void load_keys(const float* __restrict__ row, int i, int lane, int (&x)[E]) {
+  asm volatile("" : "+s"(row));
+  i = opaque(i);
+  // a buffer that ends with the row: no branch and no address of its own for any of the loads
+  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)row, 0, 4 * i, 0x20000);
 #pragma unroll
-  for (int r = 0; r < E; ++r) x[r] = ordered(__float_as_int(fmaxf(r * 64 + lane < i ? row[r * 64 + lane] : -INFINITY, -INFINITY)));  // any placement will do
+  for (int r = 0; r < E; ++r) {
+    const float f = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, 4 * lane, 256 * r, 0));
+    x[r] = __float_as_int(fmaxf(lane < i - 64 * r ? f : -INFINITY, -INFINITY));
+  }
+}
+template <int E> constexpr int cov_lds = 64 * (E + 4);
+// The keys are read from memory again where they are needed again: with them, their places and the sums of the heads in registers all the
+// while, a hundred were spilled.
+template <int E>
+__device__ __forceinline__ bool bucket_sort(const float* __restrict__ row, int (&x)[E], int i, int lane, int* lds) {
+  load_keys<E>(row, i, lane, x);
+  asm volatile("" : "+v"(lane));  // (what follows from the lane is not kept over the loop of rows)
+  float hi = -INFINITY, lo = INFINITY;  // of the finite keys
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const float f = __int_as_float(x[r]);
+    hi = fmaxf(hi, f);
+    lo = f > -INFINITY ? fminf(lo, f) : lo;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) { hi = fmaxf(hi, __shfl_xor(hi, off, 64)); lo = fminf(lo, __shfl_xor(lo, off, 64)); }
+  constexpr float last = 64 * E - 1;
+  const float scale = last / (hi - lo);
+  if (!__builtin_amdgcn_readfirstlane(hi < INFINITY && scale > 0.f && scale < 1e30f)) return false;  // (also a row without a finite key, and one of equal keys)
+  typedef int i32x4s __attribute__((ext_vector_type(4)));
+  i32x4s* const own = (i32x4s*)(lds + lane * (E + 4));
+#pragma unroll
+  for (int r = 0; r < E / 4; ++r) own[r] = i32x4s{0, 0, 0, 0};
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  int at[E], most = 0;  // word of the key's bin | keys before it << 16, then its place's word
+  int m = opaque(i);
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const unsigned bin = (unsigned)fminf((hi - __int_as_float(x[r])) * scale, last);  // (no smaller for a smaller key)
+    const bool key = lane < m - 64 * r;
+    int word = bin + bin / E * 4;
+    asm volatile("" : "+v"(word));  // (or a branch round it)
+    at[r] = key ? word : lane * (E + 4) + E;  // past the row's end: a word between two lanes' that is no bin
+    const int before = atomicAdd(&lds[at[r]], 1);
+    most = max(most, key ? before : 0);
+    at[r] |= before << 16;
+    if (r % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) most = max(most, __shfl_xor(most, off, 64));
+  most = __builtin_amdgcn_readfirstlane(most);
+  if (most + 1 >= kCovBin) return false;
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  int sum = 0;
+#pragma unroll
+  for (int r = 0; r < E / 4; ++r) { const i32x4s c = own[r]; sum += c[0] + c[1] + c[2] + c[3]; if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0); }
+  int run = sum;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int up = __shfl_up(run, off, 64);
+    if (lane >= off) run += up;
+  }
+  run -= sum;
+  asm volatile("" ::: "memory");  // (read again instead of kept)
+#pragma unroll
+  for (int r = 0; r < E / 4; ++r) {
+    const i32x4s c = own[r];
+    own[r] = i32x4s{run, run + c[0], run + c[0] + c[1], run + c[0] + c[1] + c[2]};
+    run += c[0] + c[1] + c[2] + c[3];
+    if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  m = opaque(m);
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const unsigned counted = ((volatile int*)lds)[at[r] & 0xffff] + (at[r] >> 16), place = lane < m - 64 * r ? counted : r * 64 + lane;
+    at[r] = place + place / E * 4;
+    if (r % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  load_keys<E>(row, m, lane, x);
+#pragma unroll
+  for (int r = 0; r < E; ++r)
+    lds[at[r]] = ordered(x[r]);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+  for (int r = 0; r < E / 4; ++r) {
+    const i32x4s c = own[r];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[4 * r + e] = c[e];
+    if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+  }
+  auto put = [](int& a, int& b) { const int big = max(a, b), small = min(a, b); a = big; b = small; };
+#pragma unroll 1
+  for (int stage = 0; stage <= most; stage += 2) {
+#pragma unroll
+    for (int r = 0; r < E; r += 2) put(x[r], x[r + 1]);
+    __builtin_amdgcn_sched_barrier(0);
+    const int next = __shfl_down(x[0], 1, 64), before = __shfl_up(x[E - 1], 1, 64);
+#pragma unroll
+    for (int r = 1; r + 1 < E; r += 2) put(x[r], x[r + 1]);
+    x[E - 1] = lane < 63 ? max(x[E - 1], next) : x[E - 1];
+    x[0] = lane > 0 ? min(x[0], before) : x[0];
+  }
+  return true;
+}
+
+template <int E>
+__device__ __forceinline__ void bitonic_sort(int (&x)[E], int lane) {
   // phases k2 = 2 .. E/2: inside a lane, directions known at compile time (bit k2 of r)
 #pragma unroll
   for (int k2 = 2; k2 < E; k2 <<= 1) {
@@ -249,6 +370,21 @@ __device__ __forceinline__ void coverage_row_regs(const float* __restrict__ row,
       __builtin_amdgcn_sched_barrier(0);
     }
   }
+}
+
+template <int E>
+__device__ __forceinline__ void coverage_row_regs(const float* __restrict__ row, int i, int lane, int* lds, float (&acc)[E]) {
+  int x[E];
+  i = opaque(i);
+  bool sorted = false;
+  if constexpr (E >= 8) sorted = bucket_sort<E>(row, x, i, lane, lds);
+  if (!sorted) {
+    load_keys<E>(row, i, lane, x);
+#pragma unroll
+    for (int r = 0; r < E; ++r) x[r] = ordered(x[r]);
+    bitonic_sort<E>(x, lane);
+  }
+  i = opaque(i);
   // shares in sorted order (key 0 is the row maximum), their running sum, the coverage of every prefix
   const float mx = __int_as_float(ordered(__shfl(x[0], 0, 64)));
   float run = 0.f, e[E];
@@ -265,6 +401,7 @@ __device__ __forceinline__ void coverage_row_regs(const float* __restrict__ row,
   }
   const float inv = 1.0f / __shfl(incl, 63, 64);
   run = incl - run;  // the shares of the lanes before this one
+  i = opaque(i);
 #pragma unroll
   for (int r = 0; r < E; ++r) {
     const int p = lane * E + r;
@@ -273,34 +410,42 @@ __device__ __forceinline__ void coverage_row_regs(const float* __restrict__ row,
   }
 }
 
+constexpr int kCovLds = cov_lds<32>;  // words of a wavefront
 template <int E>
-__device__ __forceinline__ void coverage_rows_regs_body(const float* __restrict__ scores_s, int n, int i, int hs0, int hs1, float* part,
+__device__ __forceinline__ void coverage_rows_regs_body(const float* __restrict__ scores_s, int n, int i, int hs0, int hs1, int* lds,
                                                float* __restrict__ out) {
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   float acc[E];
 #pragma unroll
   for (int r = 0; r < E; ++r) acc[r] = 0.f;
-  for (int hs = hs0 + wave; hs < hs1; hs += 4) coverage_row_regs<E>(scores_s + ((int64_t)hs * n + i) * n, i, lane, acc);
+  for (int hs = hs0 + wave; hs < hs1; hs += 4) coverage_row_regs<E>(scores_s + ((int64_t)hs * n + i) * n, i, lane, lds + wave * kCovLds, acc);
+  float* const part = (float*)lds;
 #pragma unroll
-  for (int r = 0; r < E; ++r) part[wave * kCovRegMax + lane * E + r] = acc[r];
+  for (int r = 0; r < E; ++r) part[wave * kCovLds + lane * E + r] = acc[r];
   __syncthreads();
   for (int p = tid; p < i; p += 256)
-    out[p] = ((part[p] + part[kCovRegMax + p]) + part[2 * kCovRegMax + p]) + part[3 * kCovRegMax + p];
+    out[p] = ((part[p] + part[kCovLds + p]) + part[2 * kCovLds + p]) + part[3 * kCovLds + p];
 }
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void coverage_rows_regs_kernel(const float* __restrict__ scores, const int32_t* __restrict__ qb_off,
-                                                                 const int64_t* __restrict__ sc_off, const int32_t* __restrict__ qb_seq,
-                                                                 int Hs, int64_t slab, float* __restrict__ pacc) {
-  __shared__ float part[4 * kCovRegMax];
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void coverage_rows_regs_kernel(
+    const float* __restrict__ scores, GeomArgs ga, int Hs, int64_t slab, int32_t* qb_off, int64_t* sc_off, int32_t* qb_seq,
+    float* __restrict__ pacc) {
+  __shared__ __attribute__((aligned(16))) int part[4 * kCovLds];
   const int qb = blockIdx.x;
-  const int s = qb_seq[qb];
-  const int i = qb - qb_off[s];
-  const int n = qb_off[s + 1] - qb_off[s];
+  const BatchGeom bg(ga);
+  const int s = bg.seq_of(qb);
+  const SeqGeom sg = bg.get(s);
+  const int i = qb - sg.qb0, n = sg.n;
+  // Up to kLaneSeqs sequences nobody has filled the tables that the next kernels read: a launch of 4 - 5 us saved.
+  if (ga.S <= kLaneSeqs && blockIdx.y == 0 && threadIdx.x == 0) {
+    qb_seq[qb] = s;
+    if (i == 0) { qb_off[s] = sg.qb0; qb_off[s + 1] = sg.qb0 + n; sc_off[s] = sg.sc_off; }
+  }
   if (i == 0 || i > kCovRegMax) return;  // no candidates; longer rows are left to coverage_rows_kernel
   const int hpg = (Hs + (int)gridDim.y - 1) / (int)gridDim.y;  // selection heads per group
   const int hs0 = blockIdx.y * hpg, hs1 = min(Hs, hs0 + hpg);
-  const float* scores_s = scores + (int64_t)Hs * sc_off[s];
-  float* out = pacc + (int64_t)blockIdx.y * slab + sc_off[s] + (int64_t)i * n;
+  const float* scores_s = scores + (int64_t)Hs * sg.sc_off;
+  float* out = pacc + (int64_t)blockIdx.y * slab + sg.sc_off + (int64_t)i * n;
   if (i <= 64) coverage_rows_regs_body<1>(scores_s, n, i, hs0, hs1, part, out);
   else if (i <= 128) coverage_rows_regs_body<2>(scores_s, n, i, hs0, hs1, part, out);
   else if (i <= 256) coverage_rows_regs_body<4>(scores_s, n, i, hs0, hs1, part, out);
@@ -425,8 +570,8 @@ int sb_score_coverage(const sb_problem* p, const float* scores, float* coverage_
   if (g.S == 0 || g.T == 0 || g.NQB == 0) return SB_OK;
   if (!scores || !coverage_out || !ws) { set_error("null scores, coverage_out or ws"); return SB_ERR_INVALID_ARG; }
   hipStream_t st = (hipStream_t)stream;
-  rc = launch_geom(g, p, ws, st);
-  if (rc != SB_OK) return rc;
+  if ((rc = check_device_arrays(p)) != SB_OK) return rc;
+  if (g.S > kLaneSeqs && (rc = launch_geom(g, p, ws, st)) != SB_OK) return rc;
   Tables t = make_tables(g, p, ws);
   float* pacc = (float*)((char*)ws + align_up(table_offsets(g).bytes));
   int N = 1;
@@ -448,8 +593,8 @@ int sb_score_coverage(const sb_problem* p, const float* scores, float* coverage_
   KernelTimer kt(K_COVERAGE, st);
   const int groups = coverage_groups(g);
   const int64_t slab = (int64_t)coverage_slab(g);
-  hipLaunchKernelGGL(coverage_rows_regs_kernel, dim3((unsigned)g.NQB, (unsigned)groups), dim3(256), 0, st, scores, t.qb_off, t.sc_off,
-                     t.qb_seq, g.Hs, slab, pacc);
+  hipLaunchKernelGGL(coverage_rows_regs_kernel, dim3((unsigned)g.NQB, (unsigned)groups), dim3(256), 0, st, scores,
+                     make_geom_args(g, p, t), g.Hs, slab, (int32_t*)t.qb_off, (int64_t*)t.sc_off, (int32_t*)t.qb_seq, pacc);
   SB_LAUNCH_CHECK("coverage_rows_regs_kernel");
   if (g.n_max > kCovRegMax + 1) {  // rows with more than kCovRegMax candidates
     hipLaunchKernelGGL(coverage_rows_kernel, dim3((unsigned)g.NQB, (unsigned)groups), dim3(256), smem, st, scores, t.qb_off, t.sc_off,
