@@ -82,7 +82,8 @@ __device__ inline int64_t sel_rows_before(int i, int k) {
 // 0.199 -> 0.180 ms, with the largest key taken along where the keys are made.
 constexpr int kDistShift = 17;
 
-// f(j, key, j < m) for this lane's keys j = lane, lane + 64, ...; every lane takes part in every call
+// f(j, key, j < m) for this lane's keys j = lane, lane + 64, ...; every lane takes part in every call.  Reads up to 255 words past the
+// keys: a histogram of 256 lies behind every row's keys, or behind those of the rows after it.
 template <typename F>
 __device__ __forceinline__ void walk_keys(const uint32_t* keys, int lane, int m, F f) {
   constexpr int U = 4;
@@ -94,9 +95,14 @@ __device__ __forceinline__ void walk_keys(const uint32_t* keys, int lane, int m,
 #pragma unroll
     for (int u = 0; u < U; ++u) f(j0 + 64 * u + lane, k[u], true);
   }
-  for (; j0 < m; j0 += 64) {
-    const bool valid = j0 + lane < m;
-    f(j0 + lane, valid ? keys[j0 + lane] : 0u, valid);
+  if (j0 >= m) return;
+  uint32_t k[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) k[u] = keys[j0 + 64 * u + lane];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const bool valid = j0 + 64 * u + lane < m;
+    if (j0 + 64 * u < m) f(j0 + 64 * u + lane, valid ? k[u] : 0u, valid);
   }
 }
 
@@ -106,7 +112,8 @@ __device__ inline void select_row(const uint32_t* keys, int* hist, int lane, int
   uint32_t thr = 0;
   int remaining = 0;
   bool found_thr = false;
-  if (need * 4 <= m) {
+  const bool few = need * 4 <= m;
+  if (few) {
     uint32_t kmax = largest;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, off, 64));
@@ -211,7 +218,7 @@ __device__ inline void select_row(const uint32_t* keys, int* hist, int lane, int
   // keys > thr are all kept; of the keys == thr the `remaining` lowest indices are kept; output in index order
   int eq_seen = 0, pos = 0;
   walk_keys(keys, lane, m, [&](int j, uint32_t kk, bool valid) {
-    if (__builtin_amdgcn_ballot_w64(valid && kk >= thr) == 0) return;
+    if (few && __builtin_amdgcn_ballot_w64(valid && kk >= thr) == 0) return;
     const bool is_eq = valid && kk == thr;
     const unsigned long long beq = __builtin_amdgcn_ballot_w64(is_eq);
     const int eq_rank = eq_seen + __builtin_popcountll(beq & lt);
