@@ -64,15 +64,16 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ sco
 // workgroup of 16 wavefronts owns R consecutive query blocks of the packed batch and one selection
 // head.  For each sequence that these blocks touch, every wavefront computes 16 x 16 score tiles
 // (the rows' pooled queries in registers, pooled keys straight from memory: they are small and stay
-// in L2) and leaves the order keys of the past blocks in LDS, row by row; after a barrier wavefront
+// in L2), the tiles of all these sequences dealt to the wavefronts in turn, and leaves the order keys of the past blocks in LDS, row by row;
+// after one barrier wavefront
 // w selects for row w exactly as topk_kernel does.  R (16, or fewer for very long sequences) is what
-// fits in LDS: R rows of `stride` keys plus one histogram per wavefront.
+// fits in LDS: R rows of `stride` keys plus one histogram per wavefront.  SCORES: the matrix is written as well, as score_kernel writes it.
 constexpr int kFusedWaves = 16;
 
-template <int D>
+template <int D, bool SCORES>
 __global__ __launch_bounds__(64 * kFusedWaves) void score_select_kernel(
     const float* __restrict__ qbar, const float* __restrict__ kbar, GeomArgs ga, int64_t NQB, int Hq, int Hkv, int Hs, int G, int mode,
-    float scale, int64_t nnz_unit, int R, int stride, int32_t* __restrict__ rowptr, int32_t* __restrict__ idx) {
+    float scale, int64_t nnz_unit, int R, int stride, float* __restrict__ scores, int32_t* __restrict__ rowptr, int32_t* __restrict__ idx) {
   extern __shared__ uint32_t smem[];
   uint32_t* keys = smem;                            // [R][stride]
   int* hist = (int*)(smem + (size_t)R * stride);    // [kFusedWaves][256]
@@ -89,57 +90,71 @@ __global__ __launch_bounds__(64 * kFusedWaves) void score_select_kernel(
   const int g = h0 / G;
   // rows late in a sequence have the most past blocks: hand out the last groups of blocks first
   const int64_t b0 = (ngroups - 1 - gy) * R, b1 = min(NQB, b0 + R);
+  int dealt = 0;  // 16 x 16 tiles so far: the wavefronts take them in turn, whichever sequence they are of
   for (int64_t ba = b0; ba < b1;) {
     const SeqGeom sg = bg.get(bg.seq_of((int)ba));
     const int64_t qb0 = sg.qb0;
     const int n = sg.n;
     const int ia = (int)(ba - qb0), ib = (int)min((int64_t)n, ia + (b1 - ba));  // rows [ia, ib) of sequence s
-    const int nrows = ib - ia;
+    const int nrows = ib - ia, r0 = (int)(ba - b0);
     const int k = sg.k;
     // a row needs its scores only if it keeps some but not all of its past blocks: 2 <= k <= i
-    if (k >= 2 && ib - 1 >= k) {
-      float a[D / 4];
+    const bool choose = k >= 2 && ib - 1 >= k;
+    if (SCORES || choose) {
+      const int ntiles = (ib - 1 + 15) / 16;  // block j is in the past of some row of the segment iff j < ib - 1
+      int ct = (wave - dealt) & (kFusedWaves - 1);
+      dealt += ntiles;
+      if (ct < ntiles) {
+        float a[D / 4];
 #pragma unroll
-      for (int t = 0; t < D / 4; ++t) a[t] = 0.f;
-      const int ra = min(ia + l16, ib - 1);  // rows past the segment repeat its last row; their results are dropped
-      for (int hh = 0; hh < heads; ++hh) add_quarter<D>(a, qbar + ((qb0 + ra) * Hq + h0 + hh) * D, kq);
-      const int ncol = ib - 1;  // block j is in the past of some row of the segment iff j < ib - 1
-      for (int ct = wave; ct * 16 < ncol; ct += kFusedWaves) {
-        const int j = ct * 16 + l16;
-        float b[D / 4];
-        load_quarter<D>(b, kbar + ((qb0 + min(j, n - 1)) * Hkv + g) * D, kq);
-        const f32x4s acc = score_tile16<D>(a, b);
+        for (int t = 0; t < D / 4; ++t) a[t] = 0.f;
+        const int ra = min(ia + l16, ib - 1);  // rows past the segment repeat its last row; their results are dropped
+        for (int hh = 0; hh < heads; ++hh) add_quarter<D>(a, qbar + ((qb0 + ra) * Hq + h0 + hh) * D, kq);
+        for (; ct < ntiles; ct += kFusedWaves) {
+          const int j = ct * 16 + l16;
+          float b[D / 4];
+          load_quarter<D>(b, kbar + ((qb0 + min(j, n - 1)) * Hkv + g) * D, kq);
+          const f32x4s acc = score_tile16<D>(a, b);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int r = 4 * kq + v;
-          if (r < nrows && j < ia + r) keys[(size_t)r * stride + j] = order_key(scale * acc[v]);
+          for (int v = 0; v < 4; ++v) {
+            const int r = 4 * kq + v;
+            if (r < nrows && j < ia + r) {
+              if (choose) keys[(size_t)(r0 + r) * stride + j] = order_key(scale * acc[v]);
+              if (SCORES) scores[(int64_t)Hs * sg.sc_off + ((int64_t)hs * n + ia + r) * n + j] = scale * acc[v];
+            }
+          }
         }
       }
     }
-    __syncthreads();
-    if (wave < nrows) {
-      const int i = ia + wave;
-      const int c = min(k, i + 1);
-      const int64_t row_id = (int64_t)hs * NQB + ba + wave;
-      const int64_t start = (int64_t)hs * nnz_unit + sg.row_base + sel_rows_before(i, k);
-      if (lane == 0) {
-        rowptr[row_id] = (int32_t)start;
-        if (row_id == (int64_t)Hs * NQB - 1) rowptr[(int64_t)Hs * NQB] = (int32_t)(start + c);
-      }
-      int32_t* out = idx + start;
-      const int need = c - 1, m = i;
-      if (need == m) {
-        for (int j = lane; j <= i; j += 64) out[j] = j;
-      } else if (need == 0) {
-        if (lane == 0) out[0] = i;
-      } else {
-        uint32_t largest = 0;
-        walk_keys(keys + (size_t)wave * stride, lane, m, [&](int, uint32_t key, bool) { largest = max(largest, key); });
-        select_row(keys + (size_t)wave * stride, hist + 256 * wave, lane, m, need, i, out, largest);
-      }
-    }
-    __syncthreads();  // the keys are overwritten by the next segment
     ba += nrows;
+  }
+  __syncthreads();
+  if (b0 + wave >= b1) return;
+  // wavefront w: row b0 + w
+  const int qb = (int)b0 + wave;
+  const SeqGeom sg = bg.get(bg.seq_of(qb));
+  const int n = sg.n, i = qb - sg.qb0, k = sg.k;
+  const int c = min(k, i + 1);
+  const int64_t row_id = (int64_t)hs * NQB + qb;
+  const int64_t start = (int64_t)hs * nnz_unit + sg.row_base + sel_rows_before(i, k);
+  if (lane == 0) {
+    rowptr[row_id] = (int32_t)start;
+    if (row_id == (int64_t)Hs * NQB - 1) rowptr[(int64_t)Hs * NQB] = (int32_t)(start + c);
+  }
+  if (SCORES) {  // the blocks that are not in the row's past
+    float* row = scores + (int64_t)Hs * sg.sc_off + ((int64_t)hs * n + i) * n;
+    for (int j = i + lane; j < n; j += 64) row[j] = -__builtin_inff();
+  }
+  int32_t* out = idx + start;
+  const int need = c - 1, m = i;
+  if (need == m) {
+    for (int j = lane; j <= i; j += 64) out[j] = j;
+  } else if (need == 0) {
+    if (lane == 0) out[0] = i;
+  } else {
+    uint32_t largest = 0;
+    walk_keys(keys + (size_t)wave * stride, lane, m, [&](int, uint32_t key, bool) { largest = max(largest, key); });
+    select_row(keys + (size_t)wave * stride, hist + 256 * wave, lane, m, need, i, out, largest);
   }
 }
 
@@ -199,8 +214,13 @@ extern "C" int sb_select_topk(const sb_problem* p, const float* scores, int32_t*
   return select_launch(g, make_geom_args(g, p, make_tables(g, p, ws)), scores, sel_rowptr_out, sel_idx_out, st);
 }
 
-// launches the kernel that scores and selects; qbar/kbar are the pooled arrays
-static int score_select_launch(const Geo& g, const GeomArgs& ga, const float* qbar, const float* kbar, int32_t* sel_rowptr_out,
+// LDS layout of the kernel that scores and selects.  A row of keys is padded to a stride of 4 mod 16 words, so that the four query rows a
+// store instruction touches fall into different banks.
+static int fused_stride(const Geo& g) { return (g.n_max + 63) / 64 * 64 + 4; }
+static size_t fused_lds(const Geo& g, int R) { return sizeof(uint32_t) * ((size_t)R * fused_stride(g) + 256 * (size_t)kFusedWaves); }
+
+// launches the kernel that scores and selects; qbar/kbar are the pooled arrays, `scores` may be null
+static int score_select_launch(const Geo& g, const GeomArgs& ga, const float* qbar, const float* kbar, float* scores, int32_t* sel_rowptr_out,
                                int32_t* sel_idx_out, hipStream_t st) {
   static std::mutex mu;
   static int lds_of_device[kMaxDevices] = {};  // LDS a workgroup may use, once the kernels' limit has been raised to it
@@ -213,19 +233,17 @@ static int score_select_launch(const Geo& g, const GeomArgs& ga, const float* qb
     if (!lds_of_device[dev]) {
       int per_block = 0;
       SB_CHECK_HIP(hipDeviceGetAttribute(&per_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-      SB_CHECK_HIP(hipFuncSetAttribute((const void*)score_select_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, per_block));
-      SB_CHECK_HIP(hipFuncSetAttribute((const void*)score_select_kernel<64>, hipFuncAttributeMaxDynamicSharedMemorySize, per_block));
+      const void* kernels[4] = {(const void*)score_select_kernel<128, false>, (const void*)score_select_kernel<64, false>,
+                                (const void*)score_select_kernel<128, true>, (const void*)score_select_kernel<64, true>};
+      for (const void* k : kernels) SB_CHECK_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, per_block));
       lds_of_device[dev] = per_block;
     }
     cap = lds_of_device[dev];
   }
-  // a row of keys is padded to a stride of 4 mod 16 words, so that the four query rows a store instruction touches
-  // fall into different banks
-  const int stride = (g.n_max + 63) / 64 * 64 + 4;
-  const size_t hist_words = 256 * (size_t)kFusedWaves;
+  const int stride = fused_stride(g);
   int R = kFusedWaves;
-  while (R > 1 && sizeof(uint32_t) * ((size_t)R * stride + hist_words) > (size_t)cap) R >>= 1;
-  const size_t smem = sizeof(uint32_t) * ((size_t)R * stride + hist_words);
+  while (R > 1 && fused_lds(g, R) > (size_t)cap) R >>= 1;
+  const size_t smem = fused_lds(g, R);
   if (smem > (size_t)cap) {
     set_error("a sequence of %d blocks does not fit the fused selection (%zu bytes of LDS, %d available): pass scores_out", g.n_max,
               smem, cap);
@@ -233,16 +251,26 @@ static int score_select_launch(const Geo& g, const GeomArgs& ga, const float* qb
   }
   const int64_t groups = (g.NQB + R - 1) / R;
   if (groups * g.Hs > 0x7fffffffll) { set_error("too many rows for one launch of the fused selection: pass scores_out"); return SB_ERR_UNSUPPORTED; }
-  dim3 grid((unsigned)(groups * g.Hs));
   KernelTimer kt(K_SCORE_SELECT, st);
-  if (g.D == 128)
-    hipLaunchKernelGGL(score_select_kernel<128>, grid, dim3(64 * kFusedWaves), smem, st, qbar, kbar, ga, g.NQB, g.Hq, g.Hkv, g.Hs, g.G,
-                       g.mode, g.score_scale, g.nnz_unit, R, stride, sel_rowptr_out, sel_idx_out);
-  else
-    hipLaunchKernelGGL(score_select_kernel<64>, grid, dim3(64 * kFusedWaves), smem, st, qbar, kbar, ga, g.NQB, g.Hq, g.Hkv, g.Hs, g.G,
-                       g.mode, g.score_scale, g.nnz_unit, R, stride, sel_rowptr_out, sel_idx_out);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(groups * g.Hs)), dim3(64 * kFusedWaves), smem, st, qbar, kbar, ga, g.NQB, g.Hq, g.Hkv, g.Hs, g.G,
+                       g.mode, g.score_scale, g.nnz_unit, R, stride, scores, sel_rowptr_out, sel_idx_out);
+  };
+  if (g.D == 128) launch(scores ? score_select_kernel<128, true> : score_select_kernel<128, false>);
+  else launch(scores ? score_select_kernel<64, true> : score_select_kernel<64, false>);
   SB_LAUNCH_CHECK("score_select_kernel");
   return SB_OK;
+}
+
+// Where the caller wants the score matrix too, one kernel or two?  One saves a launch and reads no scores, but gathers the pooled keys
+// for 16 rows at a time where score_kernel takes 64: up to one round of its workgroups.  Two kernels / one, with the pooling: 1000 tokens,
+// one head 15.1 / 12.9 us, 8192 tokens, 32/8 heads (256 workgroups) 34.1 / 24.8, four sequences of 2048 tokens 30.0 / 24.5.  At 512
+// workgroups the two are level (the two kernels of then took 55 us, of which score_kernel has since lost a fifth, one takes 52).  With the
+// sequences of a workgroup's rows one after the other, a barrier each, 2039 tokens in short sequences took 19.9 us in place of 12.6; their
+// tiles dealt to all wavefronts: 10.5.
+constexpr int64_t kFusedWgs = 256;
+static bool score_and_select_at_once(const Geo& g) {
+  return (g.NQB + kFusedWaves - 1) / kFusedWaves * g.Hs <= kFusedWgs && fused_lds(g, kFusedWaves) <= 64 * 1024;
 }
 
 extern "C" int sb_score_select(const sb_problem* p, const void* q, const void* k, float* kbar_out, float* scores_out,
@@ -259,7 +287,7 @@ extern "C" int sb_score_select(const sb_problem* p, const void* q, const void* k
   if (!q || !k || !ws) { set_error("null q, k or ws"); return SB_ERR_INVALID_ARG; }
   if ((rc = check_device_arrays(p)) != SB_OK) return rc;
   const GeomArgs ga = make_geom_args(g, p, make_tables(g, p, ws));
-  if (scores_out) {  // the caller wants the score matrix: write it, then select from it
+  if (scores_out && !score_and_select_at_once(g)) {  // write the score matrix, then select from it
     rc = sb_block_scores(p, q, k, kbar_out, scores_out, ws, stream);  // leaves the geometry tables, where they are needed, at the start of ws
     if (rc != SB_OK) return rc;
     return select_launch(g, ga, scores_out, sel_rowptr_out, sel_idx_out, st);
@@ -267,7 +295,7 @@ extern "C" int sb_score_select(const sb_problem* p, const void* q, const void* k
   if ((rc = need_tables(g, p, ws, st)) != SB_OK) return rc;
   float *qbar = nullptr, *kbar = nullptr;
   if ((rc = launch_pool(g, ga, q, k, kbar_out, ws, st, &qbar, &kbar)) != SB_OK) return rc;
-  return score_select_launch(g, ga, qbar, kbar, sel_rowptr_out, sel_idx_out, st);
+  return score_select_launch(g, ga, qbar, kbar, scores_out, sel_rowptr_out, sel_idx_out, st);
 }
 
 // ---------------------------------------------------------------------------------------------

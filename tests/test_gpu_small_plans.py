@@ -1,0 +1,96 @@
+"""Forms that small problems take: scores and selection by one kernel that writes the matrix too, plans of two launches, and the walk of
+key-major columns of few tiles; and the histogram sort of the coverage curves.  Sizes lie at the edges of each rule."""
+import numpy as np
+import pytest
+import torch
+
+from helpers import DEV, Run
+from oracle import dst_oracle as dst
+from oracle import oracle as orc
+from paper_2604_13847_amd import binding as sb
+from paper_2604_13847_amd import synth
+from test_gpu_parity import check_attention, check_plan
+
+pytestmark = pytest.mark.gpu
+
+
+# (groups of 16 blocks) x (selection heads) up to 256 take one kernel; 65 sequences read tables instead of lanes
+@pytest.mark.parametrize("lens,Hq,Hkv,D,mode", [
+    ((64 * 511 + 1,), 8, 8, 128, 0), ((64 * 512 + 1,), 8, 8, 128, 0), ((1,), 1, 1, 64, 0), ((64, 1, 0, 65) * 9, 6, 2, 64, 1),
+    ((1, 63, 700) * 22, 4, 2, 128, 1), ((64 * 16, 64 * 15 + 1, 64 * 17 - 1), 4, 4, 64, 0), ((100,) * 40, 16, 2, 128, 0)])
+def test_scores_and_selection_at_once(lens, Hq, Hkv, D, mode):
+    """The same bits as sb_block_scores and sb_select_topk, -infinity included."""
+    w = synth.small_ragged(seed=500 + Hq, lens=lens, Hq=Hq, Hkv=Hkv, D=D, ratio=(0.1, 0.9))
+    r = Run(w, mode, do_bwd=False)
+    n, nnz = r.pb.layout.scores_elems, int(r.rowptr_h[-1])
+    del_me = torch.full_like(r.scores, float("nan"))
+    del del_me  # (the allocator hands the same memory out again)
+    scores, rowptr, idx = sb.sb_score_select(r.pb, r.q, r.k)
+    torch.cuda.synchronize()
+    assert torch.equal(scores[:n].view(torch.int32), r.scores[:n].view(torch.int32))
+    assert torch.equal(rowptr, r.rowptr) and torch.equal(idx[:nnz], r.idx[:nnz])
+
+
+# two launches up to 512 blocks, 64 sequences and 64 bitmap words of a column; a sink fills columns and cuts them, so that sub-parts and
+# unused entries of both lists occur
+@pytest.mark.parametrize("lens,Hq,Hkv,mode", [
+    ((64 * 511 + 1,), 4, 2, 0), ((64 * 512 + 1,), 4, 2, 0), ((64 * 512,), 8, 2, 0), ((64 * 256,), 8, 1, 0), ((64 * 257,), 8, 1, 0),
+    ((0, 1, 0, 130, 0) * 13, 4, 2, 1), ((2039,), 16, 2, 0), ((1,), 1, 1, 1)])
+def test_plans_of_two_launches(lens, Hq, Hkv, mode):
+    w = synth.small_ragged(seed=520 + Hq, lens=lens, Hq=Hq, Hkv=Hkv, D=64, ratio=(0.05, 0.2))
+    r = Run(w, mode)
+    check_plan(r)
+    if w.T <= 4096:
+        print(w, check_attention(r), flush=True)
+
+
+def test_plan_in_a_buffer_that_held_another():
+    """Nothing that an earlier plan, or anything else, left in the buffer shows: unused entries are written in every call."""
+    w = synth.small_ragged(seed=530, lens=(64 * 37 - 9, 200), Hq=8, Hkv=2, D=128, ratio=(0.6, 0.9))
+    r = Run(w, 0)
+    for fill in (0, 0x7f, 0xff):
+        plan = torch.full_like(r.plan, fill)
+        sb.sb_plan_worklist(r.pb, r.rowptr, r.idx, plan=plan)
+        grads = sb.sb_sparse_attn_bwd(r.pb, r.q, r.k, r.v, r.o, r.lse, r.do, r.rowptr, r.idx, plan)
+        torch.cuda.synchronize()
+        r.plan = plan
+        check_plan(r)
+        for a, b in zip(grads, (r.dq, r.dk, r.dv)):
+            assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,mode", [(1, 1, 0), (3, 1, 0), (2, 1, 1), (9, 1, 0)])
+def test_columns_of_few_tiles(Hq, Hkv, mode, D):
+    """One to some twenty tiles a column, odd and even, with one to nine of them on the diagonal, none of them or all of them."""
+    lens = [64 * n - 17 * (n % 3) for n in range(1, 8)] + [1, 33]
+    w = synth.Workload("few", lens, Hq, Hkv, D, topk=[1, 2, 2, 3, 3, 7, 2, 1, 1], seed=540 + Hq)
+    print(check_attention(Run(w, mode)), flush=True)
+
+
+KINDS = {
+    "normal": lambda rng, s: rng.normal(size=s),
+    "wide": lambda rng, s: rng.normal(size=s) * 40.0,
+    "equal": lambda rng, s: np.full(s, 1.5),
+    "few values": lambda rng, s: rng.integers(0, 40, size=s) * 0.25,          # bins of 32 keys and more
+    "thirty to a value": lambda rng, s: np.argsort(rng.random(s), axis=-1) // 30 * 0.01,  # just below
+    "outlier": lambda rng, s: rng.normal(size=s) + 1e4 * (rng.random(s) < 1.0 / s[-1]),
+    "masked": lambda rng, s: np.where(rng.random(s) < 0.01, -np.inf, rng.normal(size=s)),
+    "half masked": lambda rng, s: np.where(rng.random(s) < 0.5, -np.inf, rng.normal(size=s)),
+    "tiny": lambda rng, s: rng.normal(size=s) * 1e-30,
+}
+
+
+@pytest.mark.parametrize("kind", sorted(KINDS))
+@pytest.mark.parametrize("n", [300, 2049])
+def test_coverage_sorted_by_a_histogram(kind, n):
+    """Rows of 257 to 2048 keys: spread, tied, with outliers that leave all others in one bin, and with -infinity among them.  The curves
+    against the float64 checker (2e-6, as in tests/test_gpu_dst.py: shares are at most 1 and a curve is a mean of row sums)."""
+    Hs = 2
+    sc = KINDS[kind](np.random.default_rng(n), (Hs, n, n)).astype(np.float32)
+    sc[:, :, 0] = np.where(np.isneginf(sc[:, :, 0]), 0.0, sc[:, :, 0])  # (a row without any finite score has no softmax)
+    pb = sb.Problem(np.array([0, n * 64 - 5]), [8], Hs, Hs, 64, 64, device=DEV)
+    po = orc.Problem(np.array([0, n * 64 - 5]), Hs, Hs, 64, 64, 0)
+    got = sb.sb_score_coverage(pb, torch.from_numpy(sc.ravel()).to(DEV)).cpu().numpy()[:n]
+    ref = dst.coverage_curves(po.nblk, po.Hs, sc.ravel(), po.score_off)
+    assert np.abs(got - ref).max() <= 2e-6
