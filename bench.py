@@ -233,7 +233,7 @@ def run(workload, mode_name, seed, steps, warmup, selection="topk", cu_busy=True
         del ws_cov
         res["score_coverage_ms"] = round(kc["coverage"][0] / 3, 4)
         res["fused_score_select"] = {"kernel_ms": round(kt["score_select"][0] / 5, 4),
-                                     "two_kernel_ms": round(k_step["score"] + k_step["topk"], 4),
+                                     "two_kernel_ms": round(k_step["score"] + k_step["topk"], 4) if k_step["topk"] else None,  # (small: one kernel)
                                      "identical_selection": bool(torch.equal(rp2, rowptr) and torch.equal(ix2[:nnz], idx[:nnz]))}
 
     # cold caches (outside the timed region): five more steps, each after 1 GiB of unrelated writes has gone through the

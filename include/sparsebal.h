@@ -134,7 +134,8 @@ int sb_select_topk_static(const sb_problem *p, const float *scores, int32_t *sel
  * sb_block_scores and sb_select_topk; ws: dev, scores_ws_bytes.  sel_rowptr_out and sel_idx_out are
  * bit-identical to calling the two separately, whichever form is used:
  *   scores_out != NULL  the score matrix is written as by sb_block_scores (it stays available for the
- *                       budget controller below) and the selection is taken from it;
+ *                       budget controller below) and the selection is taken from it (small problems: one kernel
+ *                       writes it and selects);
  *   scores_out == NULL  one kernel computes each row's scores on chip and selects there: the score
  *                       matrix (scores_elems floats) is neither allocated nor written nor read back.
  *                       A sequence so long that a single row of keys does not fit the compute unit's
@@ -284,7 +285,7 @@ int sb_sab_batches(const sb_perf_table *perf, const int32_t *lengths, const doub
 #define SB_INSTR_KERNEL_EVENTS 2
 #define SB_NUM_KERNELS 10 /* pool, score, topk, plan, fwd, bwd_prep, bwd_dq, bwd_dkv, coverage, score_select; bwd_prep is the
                              conversion of float32 inputs in the backward call (nothing for bf16 inputs); score_select is the
-                             single kernel of sb_score_select without scores_out */
+                             single kernel of sb_score_select, without scores_out or in small problems */
 int sb_set_instrumentation(int flag);
 int sb_read_cu_busy(const void *ws, uint64_t *busy_out_host, void *stream);
 int sb_read_kernel_times(double *total_ms_host, int64_t *launches_host);
