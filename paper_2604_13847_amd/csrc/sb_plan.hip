@@ -11,6 +11,7 @@
 // Key-major transpose.  Bit i of word (s,hs,j,i/32) says query block i kept key block j; the bitmap
 // is a pure function of the selection, so the backward pass walks a column's query blocks in a
 // fixed order and accumulates deterministically.
+#include "sb_geom.h"
 #include "sb_internal.h"
 
 namespace sb {
@@ -29,7 +30,32 @@ struct PlanArgs {
   int32_t* colcost;
   int64_t row_x;                           // grid columns of the query-major part (Hs workgroups each)
   int64_t words;                           // (sequence, 32 query tiles) pairs
+  // a plan of two launches (see plan_in_two) works the tables out itself and leaves them, and the counters cleared, for those after it
+  const int32_t* topk;
+  int32_t *w_qb_off, *w_row_base, *w_kclamp, *w_qb_seq, *w_counters;
+  int64_t *w_sc_off, *w_bm_off;
 };
+
+// Plans of few tiles are all launches: geometry and fills, lists, order, 3 - 5 us each.  Up to kLaneSeqs sequences every workgroup of the
+// second can work the tables out for itself, and up to kTwoMaxTiles tiles one workgroup per KV head counts its columns from the bitmap, so
+// that nothing has to be cleared for the counting: 4.2 us less for the first launch, 1.3 more for the last (2039 tokens, 16/2 heads), a
+// step of 1024 tokens on one head 58.6 -> 56.2 us.  Larger plans keep the three: there the counting would be serial work of a few workgroups.
+constexpr int64_t kTwoMaxTiles = 512;
+constexpr int64_t kTwoMaxWords = 64;  // bitmap words of a column, over the selection heads of its KV head: eight lanes read them
+inline bool plan_in_two(const Geo& tg) {
+  const int64_t heads = tg.mode == SB_SELECT_PER_QHEAD ? tg.G : 1;
+  return tg.S <= kLaneSeqs && tg.NQB <= kTwoMaxTiles && heads * ((tg.n_max + 31) / 32) <= kTwoMaxWords;
+}
+// the sequence of tile qb: the last one that starts at or before it
+__device__ inline int seq_of_tile(const PlanArgs& A, int qb) {
+  if (A.qb_seq) return A.qb_seq[qb];
+  int lo = 0, hi = A.S - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (A.qb_off[mid] <= qb) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
 
 // order of the selection heads inside one query block: KV head fastest
 __device__ inline int head_rank(const PlanArgs& A, int hs) { return A.mode == SB_SELECT_PER_QHEAD ? (hs % A.G) * A.Hkv + hs / A.G : hs; }
@@ -38,7 +64,7 @@ __device__ inline int head_rank(const PlanArgs& A, int hs) { return A.mode == SB
 __device__ inline void plan_row(const PlanArgs& A, int64_t row) {
   const int hs = (int)(row / A.NQB);
   const int qb = (int)(row - (int64_t)hs * A.NQB);
-  const int s = A.qb_seq[qb];
+  const int s = seq_of_tile(A, qb);
   const int i = qb - A.qb_off[s];
   const int ks = A.kclamp[s];
   const int c = min(ks, i + 1);
@@ -168,15 +194,61 @@ __device__ inline void plan_transpose(const PlanArgs& A, int64_t word, int hs) {
     for (int j = tid; j < nj; j += 256) {
       const uint32_t x = wcol[j];
       bm[(int64_t)(j0 + j) * w + wi] = x;
-      if (x) atomicAdd(&cost[j0 + j], weight * __popc(x));
+      if (A.qb_seq && x) atomicAdd(&cost[j0 + j], weight * __popc(x));
     }
     __syncthreads();
   }
 }
 
+// The tables of a plan of two launches (tiles are blocks there), in LDS; one workgroup also writes them out.
+struct LdsTables { int32_t qb_off[kLaneSeqs + 1], kclamp[kLaneSeqs]; int64_t bm_off[kLaneSeqs + 1]; };
+__device__ inline void tables_in_lds(PlanArgs& A, LdsTables& t) {
+  const int lane = threadIdx.x & 63;
+  const bool writes = blockIdx.x == 0 && blockIdx.y == 0;
+  if (threadIdx.x < 64) {
+    int n = 0, k = 0;
+    if (lane < A.S) {
+      n = (A.cu[lane + 1] - A.cu[lane] + 63) / 64;
+      k = max(min(A.topk[lane], n), min(n, 1));
+    }
+    int qb = n, row = k * n - k * (k - 1) / 2;
+    int64_t bm = (int64_t)n * ((n + 31) >> 5), sc = (int64_t)n * n;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int q = __shfl_up(qb, off, 64), r = __shfl_up(row, off, 64);
+      const int64_t b = __shfl_up(bm, off, 64), c = __shfl_up(sc, off, 64);
+      if (lane >= off) { qb += q; row += r; bm += b; sc += c; }
+    }
+    if (lane == 0) { t.qb_off[0] = 0; t.bm_off[0] = 0; }
+    t.qb_off[lane + 1] = qb;
+    t.bm_off[lane + 1] = bm;
+    t.kclamp[lane] = k;
+    if (writes) {
+      if (lane == 0) { A.w_qb_off[0] = 0; A.w_bm_off[0] = 0; A.w_sc_off[0] = 0; A.w_row_base[0] = 0; }
+      if (lane < A.S) {
+        A.w_qb_off[lane + 1] = qb; A.w_bm_off[lane + 1] = bm; A.w_sc_off[lane + 1] = sc; A.w_row_base[lane + 1] = row;
+        A.w_kclamp[lane] = k;
+      }
+      if (lane < 4) A.w_counters[lane] = 0;
+    }
+  }
+  __syncthreads();
+  A.qb_off = A.b_qb_off = t.qb_off;
+  A.kclamp = A.b_kclamp = t.kclamp;
+  A.bm_off = t.bm_off;
+  A.qb_seq = nullptr;
+  if (writes)
+    for (int qb = threadIdx.x; qb < A.NQB; qb += 256) A.w_qb_seq[qb] = seq_of_tile(A, qb);
+}
+
 // The query-major lists and the transpose, side by side: neither needs the other.  The selection heads are the grid's second
 // dimension, so that half a million one-token sequences on 32 heads stay below the 2^32 threads of one dimension.
+template <bool SELF>
 __global__ __launch_bounds__(256) void plan_lists_kernel(PlanArgs A) {
+  if constexpr (SELF) {
+    __shared__ LdsTables tables;
+    tables_in_lds(A, tables);
+  }
   if ((int64_t)blockIdx.x < A.row_x) {
     const int64_t wg = (int64_t)blockIdx.x * A.Hs + blockIdx.y;
     if (A.r == 1) {
@@ -228,18 +300,21 @@ struct ColumnWalk {
   }
 };
 
-__global__ __launch_bounds__(1024) void plan_bwd_order_kernel(const int32_t* __restrict__ colcost, const uint32_t* __restrict__ bitmap,
+// SELF: the second of two launches; it counts the columns' tiles and fills the lists' unused entries.
+template <bool SELF>
+__global__ __launch_bounds__(1024) void plan_bwd_order_kernel(int32_t* __restrict__ colcost, const uint32_t* __restrict__ bitmap,
                                                               const int32_t* __restrict__ qb_off, const int32_t* __restrict__ qb_seq,
                                                               const int64_t* __restrict__ bm_off, int64_t NQB, int Hkv, int Hs, int G,
-                                                              int mode, int wmax, int wsub, int slots, ColItem* __restrict__ items,
+                                                              int mode, int wmax, int wsub, int slots, int extra, ColItem* __restrict__ items,
                                                               int32_t* __restrict__ counters, int32_t* __restrict__ split_cols,
                                                               int32_t* __restrict__ sub_base, SubItem* __restrict__ sub_items,
                                                               int32_t* __restrict__ part_item) {
   __shared__ int bins[kBwdBins];
-  __shared__ int sh[16];
+  __shared__ int sh[16], listed;
   const int tid = threadIdx.x;
   const int64_t g = blockIdx.x;
-  const int32_t* cost = colcost + g * NQB;
+  __shared__ int32_t counted[SELF ? kTwoMaxTiles : 1];
+  const int32_t* cost = SELF ? counted : colcost + g * NQB;
   auto walk_of = [&](int64_t c) {
     ColumnWalk cw;
     const int s = qb_seq[c], j = (int)(c - qb_off[s]), n = qb_off[s + 1] - qb_off[s];
@@ -263,7 +338,11 @@ __global__ __launch_bounds__(1024) void plan_bwd_order_kernel(const int32_t* __r
     items[at] = it;
     if (wsub > 0) {
       int base = n > 0 ? before >> 16 : -1;
-      if (base + n > slots) base = -1;  // more entries on this KV head than the budgets give it: the item is walked as a whole
+      if (base + n > slots) {  // more entries on this KV head than the budgets give it: the item is walked as a whole
+        if (SELF)
+          for (int u = base; u < slots; ++u) sub_items[(int64_t)u * Hkv + g].item.col = -1;
+        base = -1;
+      }
       sub_base[at] = base;
       if (base >= 0) {
         atomicAdd(&counters[2], n);
@@ -273,6 +352,19 @@ __global__ __launch_bounds__(1024) void plan_bwd_order_kernel(const int32_t* __r
     return at;
   };
   for (int b = tid; b < kBwdBins; b += 1024) bins[b] = 0;
+  if constexpr (SELF) {
+    for (int64_t c = tid >> 3; c < (NQB + 127) / 128 * 128; c += 128) {  // eight lanes a column
+      int t = 0;
+      if (c < NQB) {
+        const ColumnWalk cw = walk_of(c);
+        for (int x = tid & 7; x < cw.nsel * cw.words; x += 8) t += __popc(cw.bm[x / cw.words * cw.head_stride + x % cw.words]);
+        t *= cw.hpe;
+      }
+#pragma unroll
+      for (int off = 4; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+      if (c < NQB && (tid & 7) == 0) { counted[c] = t; colcost[g * NQB + c] = t; }
+    }
+  }
   __syncthreads();
   for (int64_t c = tid; c < NQB; c += 1024) {
     if (cost[c] <= wmax) {
@@ -299,8 +391,16 @@ __global__ __launch_bounds__(1024) void plan_bwd_order_kernel(const int32_t* __r
   for (int w = 0; w < (tid >> 6); ++w) run += sh[w];
 #pragma unroll
   for (int a = 0; a < per; ++a) { bins[kBwdBins - 1 - (tid * per + a)] = run; run += v[a]; }
-  if (tid == 1023) atomicMax(&counters[3], wsub > 0 ? run & 0xffff : run);
+  if (tid == 1023) {
+    atomicMax(&counters[3], wsub > 0 ? run & 0xffff : run);
+    listed = run;
+  }
   __syncthreads();
+  if constexpr (SELF) {
+    const int placed = wsub > 0 ? listed & 0xffff : listed, cut = wsub > 0 ? listed >> 16 : 0;
+    for (int64_t r = placed + tid; r < NQB + extra; r += 1024) items[r * Hkv + g].col = -1;
+    for (int64_t r = cut + tid; r < slots; r += 1024) sub_items[r * Hkv + g].item.col = -1;
+  }
   for (int64_t c = tid; c < NQB; c += 1024) {
     const int32_t col = (int32_t)(g * NQB + c);
     const ColumnWalk cw = walk_of(c);
@@ -343,13 +443,17 @@ extern "C" int sb_plan_worklist(const sb_problem* p, const int32_t* sel_rowptr, 
   int32_t* counters = (int32_t*)(base + po.counters);
   uint32_t* bitmap = (uint32_t*)(base + po.bitmap);
   KernelTimer kt(K_PLAN, st);
-  // Three launches: tables and fills, lists and transpose, order of the key-major items (each costs 4 - 5 us whatever it does; as
-  // seven to nine launches the plan took 20 us of a 1024-token step and 43 us of a 32768-token one, now 14 and 38 us).
+  // Three launches: tables and fills (unless plan_in_two), lists and transpose, order of the key-major items (each costs 4 - 5 us whatever
+  // it does; as seven to nine launches the plan took 20 us of a 1024-token step and 43 us of a 32768-token one, as three 14 and 38 us).
   // The item lists are padded to their largest possible length; unused entries say "no item".
   const size_t n_items = (size_t)g.Hkv * ((size_t)g.NQB + (size_t)split_extra_max(g));
-  rc = launch_geom_and_fills(g, base + po.tables, gb.r > 1 ? &gb : nullptr, base + po.blk_tables, p, base + po.counters, po.zeros_end - po.counters,
-                             base + po.sub_items, po.bwd_items - po.sub_items + sizeof(ColItem) * n_items, st);
-  if (rc != SB_OK) return rc;
+  if ((rc = check_device_arrays(p)) != SB_OK) return rc;
+  const bool two = gb.r == 1 && plan_in_two(g);
+  if (!two) {
+    rc = launch_geom_and_fills(g, base + po.tables, gb.r > 1 ? &gb : nullptr, base + po.blk_tables, p, base + po.counters, po.zeros_end - po.counters,
+                               base + po.sub_items, po.bwd_items - po.sub_items + sizeof(ColItem) * n_items, st);
+    if (rc != SB_OK) return rc;
+  }
   PlanArgs A{};
   A.rowptr = sel_rowptr; A.idx = sel_idx;
   A.cu = t.cu; A.qb_off = t.qb_off; A.kclamp = t.kclamp; A.qb_seq = t.qb_seq; A.bm_off = t.bm_off;
@@ -366,11 +470,20 @@ extern "C" int sb_plan_worklist(const sb_problem* p, const int32_t* sel_rowptr, 
     const int64_t L = (int64_t)p->cu_seqlens_host[s + 1] - p->cu_seqlens_host[s];
     A.words += ((L + g.B - 1) / g.B + 31) / 32;
   }
-  hipLaunchKernelGGL(plan_lists_kernel, dim3((unsigned)(A.row_x + A.words), (unsigned)g.Hs), dim3(256), 0, st, A);
+  if (two) {
+    const TableOffsets to = table_offsets(g);
+    char* tb = base + po.tables;
+    A.topk = p->topk_dev;
+    A.w_qb_off = (int32_t*)(tb + to.qb_off); A.w_row_base = (int32_t*)(tb + to.row_base); A.w_kclamp = (int32_t*)(tb + to.kclamp);
+    A.w_qb_seq = (int32_t*)(tb + to.qb_seq); A.w_sc_off = (int64_t*)(tb + to.sc_off); A.w_bm_off = (int64_t*)(tb + to.bm_off);
+    A.w_counters = counters;
+  }
+  hipLaunchKernelGGL(two ? plan_lists_kernel<true> : plan_lists_kernel<false>, dim3((unsigned)(A.row_x + A.words), (unsigned)g.Hs), dim3(256), 0, st, A);
   SB_LAUNCH_CHECK("plan_lists_kernel");
-  hipLaunchKernelGGL(plan_bwd_order_kernel, dim3((unsigned)g.Hkv), dim3(1024), 0, st, colcost, bitmap, t.qb_off, t.qb_seq, t.bm_off,
-                     g.NQB, g.Hkv, g.Hs, g.G, g.mode, split_weight(g), sub_slots_max(g) > 0 ? sub_weight(g) : 0, sub_slots_max(g), bwd_items, counters,
-                     (int32_t*)(base + po.split_cols), (int32_t*)(base + po.sub_base), (SubItem*)(base + po.sub_items), (int32_t*)(base + po.part_item));
+  hipLaunchKernelGGL(two ? plan_bwd_order_kernel<true> : plan_bwd_order_kernel<false>, dim3((unsigned)g.Hkv), dim3(1024), 0, st, colcost, bitmap,
+                     t.qb_off, t.qb_seq, t.bm_off, g.NQB, g.Hkv, g.Hs, g.G, g.mode, split_weight(g), sub_slots_max(g) > 0 ? sub_weight(g) : 0,
+                     sub_slots_max(g), split_extra_max(g), bwd_items, counters, (int32_t*)(base + po.split_cols), (int32_t*)(base + po.sub_base),
+                     (SubItem*)(base + po.sub_items), (int32_t*)(base + po.part_item));
   SB_LAUNCH_CHECK("plan_bwd kernels");
   return SB_OK;
 }
