@@ -282,18 +282,29 @@ struct ColumnWalk {
   const uint32_t* bm;  // first bitmap word of the column's first selection head
   int64_t head_stride; // words between the same column of consecutive selection heads
   int nsel, hpe, words, wj;
-  __device__ inline int word_weight(int w) const {
-    int t = 0;
-    for (int sel = 0; sel < nsel; ++sel) t += __popc(bm[sel * head_stride + w]);
-    return t * hpe;
-  }
   // calls emit(lo, hi, weight) for every part, last query blocks first; returns the number of parts
   template <typename F>
   __device__ inline int parts(int wmax, F emit) const {
+    // the loads of four words' selection heads in flight together: one word after the other, a column of 32 words waited 32 times
+    // (the order of 65536 tokens in blocks of 256, 14/2 heads: 55 -> 36 us, with a sink, 32/8 heads: 43 -> 26).
     int acc = 0, hi = words, np = 0;
-    for (int w = words - 1; w >= wj; --w) {
-      acc += word_weight(w);
-      if (acc >= wmax && w > wj) { emit(w, hi, acc); hi = w; acc = 0; ++np; }
+    for (int w0 = words - 1; w0 >= wj; w0 -= 4) {
+      int t[4] = {0, 0, 0, 0};
+#pragma unroll 4
+      for (int sel = 0; sel < nsel; ++sel) {
+        uint32_t x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = bm[sel * head_stride + max(w0 - u, wj)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) t[u] += __popc(x[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int w = w0 - u;
+        if (w < wj) break;
+        acc += t[u] * hpe;
+        if (acc >= wmax && w > wj) { emit(w, hi, acc); hi = w; acc = 0; ++np; }
+      }
     }
     emit(wj, hi, acc);
     return np + 1;
