@@ -671,9 +671,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64
 // 3.66 -> 3.24 ms (matrix cores busy 48 -> 57 % of the cycles), the 262144-token batch, whose gathers come through the fabric at
 // 6 TB/s: 36.7 -> 34.9 ms.  A scalar instruction takes as long to issue as a vector one here: with a half tile's two resources put
 // together once from the tile's addresses, instead of before every pair of loads (50 scalar instructions a tile, before: 110), 3.25 ->
-// 3.06 and 35.8 -> 34.3 ms.  The compiler spills 16 vector and 176 scalar registers.  The loop over the unmasked tiles has no reload of
-// the former and eight a tile of the latter; the others are in what is done once per chunk and in a chunk's first tile, and count for
-// columns of few tiles.  One wait per half stage for its LDS operands, instead of one before each matrix instruction: the same time.
+// 3.06 and 35.8 -> 34.3 ms.  A tile that is not one of a pair of unmasked ones takes the masked form, its mask
+// moved out of the way where there is nothing to mask: with a form for each the code was a quarter longer and 16 vector and 176 scalar
+// registers were spilled around the loop, now 39 scalar ones (2039 tokens in short sequences 31.9 -> 30.9 us, long columns the same).
+// One wait per half stage for its LDS operands, instead of one before each matrix instruction: the same time.
 // D = 64 needs half the registers: there two wavefronts share a SIMD instead, a half tile is computed from start to end, and the
 // shorter tile list (8 bitmap words per chunk) lets four workgroups share a CU's LDS.  Matrix cores busy 34 -> 48 %, at a clock that
 // the chip lowers from 1.86 to 1.62 GHz for it; together with the forward kernel's second wavefront per SIMD a step of 65536 tokens,
@@ -818,9 +819,9 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
   auto ld_stat = [&](unsigned so, int vg) __attribute__((always_inline)) { return lds_f4(stat_a + so + 32 * vg); };
   // P = exp2(S c - lse2) of register v of a half tile (query row 32 half + 8(v/4) + 4hf + v%4), in place, and to bf16 in pairs;
   // once the last row of a group of four has been used, the statistics two groups on are fetched in its place
-  auto prob = [&](auto diag_c, int half, int v, unsigned so) __attribute__((always_inline)) {
+  auto prob = [&](auto diag_c, int key, int half, int v, unsigned so) __attribute__((always_inline)) {
     float pv = fast_exp2(__builtin_fmaf(sacc[half][v], P.scale_log2e, -st_l[(v >> 2) & 1][v & 3]));
-    if (decltype(diag_c)::value && kloc > 32 * half + c_row(v, hf)) pv = 0.f;  // causal mask inside the diagonal tile
+    if (decltype(diag_c)::value && key > 32 * half + c_row(v, hf)) pv = 0.f;  // causal mask inside the diagonal tile
     sacc[half][v] = pv;
     if (v & 1) {
       pa[half][v >> 3][(v & 7) - 1] = (bf16)sacc[half][v - 1];
@@ -994,6 +995,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
           const unsigned PO = (HALF ? buf : 1 - buf) * BUF_B + PREV * 32 * ROW_B;             // u - 1
           const unsigned NO = (HALF ? 1 - buf : buf) * BUF_B + PREV * 32 * ROW_B;             // u + 1
           const unsigned SO = (2 * buf + HALF) * 512, PSO = (HALF ? 2 * buf : 2 * (1 - buf) + 1) * 512;
+          const int key = t < nn ? -1 : kloc;  // (no row lies before it: nothing is masked)
           int e2 = 0;
           constexpr int EPS = 8 / NOP;  // rows (accumulator registers) of the pointwise work per matrix instruction
           // Every step is fenced: one matrix instruction, the refill of its operand, its share of the vector work.
@@ -1038,7 +1040,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
             }
             if (!LAST)
 #pragma unroll
-              for (int e = 0; e < EPS; ++e) prob(diag_c, HALF, EPS * k + e, SO);
+              for (int e = 0; e < EPS; ++e) prob(diag_c, key, HALF, EPS * k + e, SO);
             if (!LAST && k == NOP / 2) {  // scalar work for the loads below, while matrix instructions run
               if (HALF == 1) newest = tile_from(__builtin_amdgcn_readfirstlane(e2));
               nxt = half_of(HALF == 0 ? 1 - buf : buf, PREV, newest);
@@ -1061,7 +1063,7 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
             if (!LAST) {
               op[k] = ld_row(k, NO);  // (after the last half tile of the chunk this reads a stale buffer and is not used)
 #pragma unroll
-              for (int e = 0; e < EPS; ++e) prob(diag_c, HALF, 8 + EPS * k + e, SO);
+              for (int e = 0; e < EPS; ++e) prob(diag_c, key, HALF, 8 + EPS * k + e, SO);
             }
             SB_FENCE();
             if constexpr (!LAST) {
@@ -1080,14 +1082,12 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
             half_tile(false_type(), false_type(), diag_c, H1(), buf, t);
           };
           int t = 1;
-          if (nn > 0) tile(true_type(), false_type(), 0, 0);
-          else tile(true_type(), true_type(), 0, 0);
+          tile(true_type(), true_type(), 0, 0);
           for (; t + 2 <= nn; t += 2) {
             tile(false_type(), false_type(), 1, t);
             tile(false_type(), false_type(), 0, t + 1);
           }
-          if (t < nn) { tile(false_type(), false_type(), 1, t); ++t; }
-          for (; t < ntl; ++t) tile(false_type(), true_type(), t & 1, t);  // the diagonal tiles
+          for (; t < ntl; ++t) tile(false_type(), true_type(), t & 1, t);
           half_tile(false_type(), true_type(), false_type(), H0(), ntl & 1, ntl);
           wait_vmcnt<0>();  // the loads past the last tile
         }
