@@ -675,10 +675,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64
 // moved out of the way where there is nothing to mask: with a form for each the code was a quarter longer and 16 vector and 176 scalar
 // registers were spilled around the loop, now 39 scalar ones (2039 tokens in short sequences 31.9 -> 30.9 us, long columns the same).
 // One wait per half stage for its LDS operands, instead of one before each matrix instruction: the same time.
-// D = 64 needs half the registers: there two wavefronts share a SIMD instead, a half tile is computed from start to end, and the
-// shorter tile list (8 bitmap words per chunk) lets four workgroups share a CU's LDS.  Matrix cores busy 34 -> 48 %, at a clock that
-// the chip lowers from 1.86 to 1.62 GHz for it; together with the forward kernel's second wavefront per SIMD a step of 65536 tokens,
-// 14/2 heads, selection blocks of 256: 7.66 -> 6.81 ms.
+// D = 64 needs half the registers: there two wavefronts share a SIMD instead, with a shorter pipeline that fits 256 of them, and the
+// shorter tile list (8 bitmap words per chunk) lets four workgroups share a CU's LDS.  Matrix cores busy 34 -> 48 % with half tiles computed
+// from start to end, at a clock that the chip lowers from 1.86 to 1.62 GHz for it; with the pipeline 65536 tokens, 14/2 heads, selection
+// blocks of 256: 2.92 -> 2.69 ms.
 template <int D, bool OUT_F32>
 __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2 : 1))) void attn_bwd_dkv_kernel(AttnParams P) {
   constexpr int TILE_B = 64 * D * 2;  // bytes of one Q or dO tile
@@ -812,8 +812,9 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
     loader.issue(x.rows, x.slot);
   };
 
-  f32x16 sacc[2], dpacc[2];  // [half]: scores, then (in place) probabilities; dP
-  bf16x8 pa[2][2], dsa[2];   // P [half][16 queries] and dS [16 queries] as operands
+  constexpr int PH = D == 64 ? 1 : 2;      // half tiles of dP and of P as operands that are kept
+  f32x16 sacc[2], dpacc[PH];  // [half]: scores, then (in place) probabilities; dP
+  bf16x8 pa[PH][2], dsa[2];   // P [half][16 queries] and dS [16 queries] as operands
   bf16x8 op[NOP];  // one rotating operand set: a register is refilled for the next stage right after the matrix instruction that used it
   f32x4 st_l[2], st_d[2];    // LSE and Dr of the rows 8vg + 4hf + (0..3) of a half tile, vg even / odd
   auto ld_stat = [&](unsigned so, int vg) __attribute__((always_inline)) { return lds_f4(stat_a + so + 32 * vg); };
@@ -824,16 +825,17 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
     if (decltype(diag_c)::value && key > 32 * half + c_row(v, hf)) pv = 0.f;  // causal mask inside the diagonal tile
     sacc[half][v] = pv;
     if (v & 1) {
-      pa[half][v >> 3][(v & 7) - 1] = (bf16)sacc[half][v - 1];
-      pa[half][v >> 3][v & 7] = (bf16)pv;
+      pa[half % PH][v >> 3][(v & 7) - 1] = (bf16)sacc[half][v - 1];
+      pa[half % PH][v >> 3][v & 7] = (bf16)pv;
     }
     if ((v & 3) == 3 && v < 8) st_l[(v >> 2) & 1] = ld_stat(so, (v >> 2) + 2);
   };
   auto dscore = [&](int half, int v, unsigned so) __attribute__((always_inline)) {  // dS = P (dP - Dr), likewise
-    dpacc[half][v] = sacc[half][v] * (dpacc[half][v] - st_d[(v >> 2) & 1][v & 3]);
+    f32x16& dp = dpacc[half % PH];
+    dp[v] = sacc[half][v] * (dp[v] - st_d[(v >> 2) & 1][v & 3]);
     if (v & 1) {
-      dsa[v >> 3][(v & 7) - 1] = (bf16)dpacc[half][v - 1];
-      dsa[v >> 3][v & 7] = (bf16)dpacc[half][v];
+      dsa[v >> 3][(v & 7) - 1] = (bf16)dp[v - 1];
+      dsa[v >> 3][v & 7] = (bf16)dp[v];
     }
     if ((v & 3) == 3 && v < 8) st_d[(v >> 2) & 1] = ld_stat(so + 256, (v >> 2) + 2);
   };
@@ -910,64 +912,110 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(D == 64 ? 2
       using H1 = std::integral_constant<int, 1>;
       const int nn = ntl - nd;  // tiles without a mask
       if constexpr (D == 64) {
-        // ---- D = 64: the kernel fits 256 registers, two wavefronts share a SIMD and hide each other's latencies, so a half tile
-        // is computed from start to end.  Half tile u: its loads have landed for everyone and u - 1 has been read by everyone, so
-        // u - 1's buffer takes the loads of u + 3.
+        // ---- D = 64: two wavefronts share a SIMD in 256 registers, which leaves no room for the longer pipeline below.  The stages
+        //   S(u), dK(u-1), dP(u), dV(u)
+        // of four matrix instructions need only the scores of two half tiles at a time: dS(u-1) goes beside S(u) and the start of
+        // dK(u-1), P(u) beside the rest, dP(u) and the start of dV(u); every matrix instruction is fenced with its share, as below.  The
+        // other wavefront of the SIMD fills what is left.  Half tile u-1 has been read when stage dV(u) begins: after a barrier its
+        // buffer takes the loads of half tile u+3.
         Tile newest = entry(0);  // the newest tile that loads have been issued for
         issue_half(half_of(0, 0, newest));
         issue_half(half_of(0, 1, newest));
         newest = entry(min(1, ntl - 1));
         issue_half(half_of(1, 0, newest));
-        auto half_tile = [&](auto diag_c, auto half_c, int buf, int t) __attribute__((always_inline)) {
-          constexpr bool DIAG = decltype(diag_c)::value;
-          constexpr int HALF = decltype(half_c)::value;
-          const unsigned CO = buf * BUF_B + HALF * 32 * ROW_B, SO = (2 * buf + HALF) * 512;
-          asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(2 * kLoadsPerHalf) : "memory");
-          __builtin_amdgcn_s_barrier();
-          if (HALF == 1) newest = entry(min(t + 2, ntl - 1));
-          issue_half(half_of(HALF == 0 ? 1 - buf : buf, 1 - HALF, newest));  // (past the last tile: that tile once more, never read)
-          bf16x8 rows[NOP], tr[NOP];
-          f32x4 sl[4], sd[4];
+        wait_vmcnt<2 * kLoadsPerHalf>();
+        __builtin_amdgcn_s_barrier();
 #pragma unroll
-          for (int k = 0; k < NOP; ++k) rows[k] = ld_row(k, CO);
+        for (int k = 0; k < NOP; ++k) op[k] = ld_row(k, 0);
+        auto half_tile = [&](auto first_c, auto last_c, auto diag_c, auto half_c, int buf, int t) __attribute__((always_inline)) {
+          constexpr bool FIRST = decltype(first_c)::value, LAST = decltype(last_c)::value;
+          constexpr int HALF = decltype(half_c)::value, PREV = 1 - HALF;
+          const unsigned CO = buf * BUF_B + HALF * 32 * ROW_B;                                // half tile u
+          const unsigned PO = (HALF ? buf : 1 - buf) * BUF_B + PREV * 32 * ROW_B;              // u - 1
+          const unsigned NO = (HALF ? 1 - buf : buf) * BUF_B + PREV * 32 * ROW_B;              // u + 1
+          const unsigned SO = (2 * buf + HALF) * 512, PSO = (HALF ? 2 * buf : 2 * (1 - buf) + 1) * 512;
+          const int key = t < nn ? -1 : kloc;  // (no row lies before it: nothing is masked)
+          int e2 = 0;
+#define SB_FENCE() __builtin_amdgcn_sched_barrier(0)
+          SB_FENCE();
+          if (!LAST && HALF == 1) e2 = (int)list[-min(t + 2, ntl - 1)];
 #pragma unroll
-          for (int k = 0; k < NOP; ++k) tr[k] = ld_row(k, CO + TILE_B);
+          for (int k = 0; k < NOP; ++k) {
+            if (!LAST) sacc[HALF] = mfma32(op[k], kf[k], k == 0 ? zero16() : sacc[HALF]);
+            if (!FIRST) {
+              op[k] = ld_tr(k, PO);
 #pragma unroll
-          for (int v = 0; v < 4; ++v) sl[v] = ld_stat(SO, v);
-          f32x16 s_ = zero16(), dp = zero16();
-#pragma unroll
-          for (int k = 0; k < NOP; ++k) s_ = mfma32(rows[k], kf[k], s_);
-#pragma unroll
-          for (int v = 0; v < 4; ++v) sd[v] = ld_stat(SO + 256, v);
-#pragma unroll
-          for (int k = 0; k < NOP; ++k) dp = mfma32(tr[k], vf[k], dp);
-#pragma unroll
-          for (int k = 0; k < NOP; ++k) tr[k] = ld_tr(k, CO + TILE_B);
-#pragma unroll
-          for (int k = 0; k < NOP; ++k) rows[k] = ld_tr(k, CO);
-          bf16x8 pb[2], ds[2];
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            float pv = fast_exp2(__builtin_fmaf(s_[v], P.scale_log2e, -sl[v >> 2][v & 3]));
-            if (DIAG && kloc > 32 * HALF + c_row(v, hf)) pv = 0.f;  // causal mask inside the diagonal tile
-            pb[v >> 3][v & 7] = (bf16)pv;
-            ds[v >> 3][v & 7] = (bf16)(pv * (dp[v] - sd[v >> 2][v & 3]));
+              for (int e = 0; e < 3; ++e) dscore(PREV, 3 * k + e, PSO);
+            } else {
+              op[k] = ld_row(k, CO + TILE_B);
+            }
+            SB_FENCE();
           }
+          if (!LAST) { st_l[0] = ld_stat(SO, 0); st_l[1] = ld_stat(SO, 1); }
+          SB_FENCE();
 #pragma unroll
-          for (int k = 0; k < NOP; ++k) dvacc[k % (D / 32)] = mfma32(pb[k / (D / 32)], tr[k], dvacc[k % (D / 32)]);
+          for (int k = 0; k < NOP; ++k) {
+            if (!FIRST) {
+              dkacc[k % (D / 32)] = mfma32(dsa[k / (D / 32)], op[k], dkacc[k % (D / 32)]);
+              if (!LAST) op[k] = ld_row(k, CO + TILE_B);
+              if (k == 0)
 #pragma unroll
-          for (int k = 0; k < NOP; ++k) dkacc[k % (D / 32)] = mfma32(ds[k / (D / 32)], rows[k], dkacc[k % (D / 32)]);
+                for (int v = 12; v < 16; ++v) dscore(PREV, v, PSO);
+            }
+            if (!LAST && k > 0) { prob(diag_c, key, HALF, 2 * k - 2, SO); prob(diag_c, key, HALF, 2 * k - 1, SO); }
+            SB_FENCE();
+          }
+          if constexpr (!LAST) {
+#pragma unroll
+            for (int k = 0; k < NOP; ++k) {
+              dpacc[0] = mfma32(op[k], vf[k], k == 0 ? zero16() : dpacc[0]);
+              op[k] = ld_tr(k, CO + TILE_B);
+              prob(diag_c, key, HALF, 6 + 2 * k, SO);
+              prob(diag_c, key, HALF, 7 + 2 * k, SO);
+              SB_FENCE();
+            }
+            if (HALF == 1) newest = tile_from(__builtin_amdgcn_readfirstlane(e2));
+            const Half nxt = half_of(HALF == 0 ? 1 - buf : buf, PREV, newest);
+            // half tile u - 1 has been read by this wavefront and its part of u + 1 has landed
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+            wait_vmcnt<kLoadsPerHalf>();
+            __builtin_amdgcn_s_barrier();
+            st_d[0] = ld_stat(SO + 256, 0);
+            st_d[1] = ld_stat(SO + 256, 1);
+            load_floats(nxt.stat_slot, nxt.stat, lane4);
+            SB_FENCE();
+#pragma unroll
+            for (int k = 0; k < NOP; ++k) {
+              dvacc[k % (D / 32)] = mfma32(pa[0][k / (D / 32)], op[k], dvacc[k % (D / 32)]);
+              op[k] = ld_row(k, NO);  // (after the last half tile of the chunk this reads a stale buffer and is not used)
+              if (k == 0) { prob(diag_c, key, HALF, 14, SO); prob(diag_c, key, HALF, 15, SO); }
+              SB_FENCE();
+              if (k == 0) loader.template issue2<0>(nxt.rows, nxt.slot);
+              if (k == 2) loader.template issue2<2>(nxt.rows, nxt.slot);
+              SB_FENCE();
+            }
+          }
+#undef SB_FENCE
         };
-        int t = 0;
-        for (; t < nn; ++t) {
-          half_tile(std::false_type(), H0(), t & 1, t);
-          half_tile(std::false_type(), H1(), t & 1, t);
+        {
+          using std::true_type;
+          using std::false_type;
+          auto tile = [&](auto first_c, auto diag_c, int buf, int t) __attribute__((always_inline)) {
+            half_tile(first_c, false_type(), diag_c, H0(), buf, t);
+            half_tile(false_type(), false_type(), diag_c, H1(), buf, t);
+          };
+          // (the masked form for what is not a pair of unmasked tiles, as at D = 128: with a form for each 66 vector registers were spilled,
+          // and a column of 16 tiles took 23.9 us, now 18.0; computed from start to end 21.0)
+          int t = 1;
+          tile(true_type(), true_type(), 0, 0);
+          for (; t + 2 <= nn; t += 2) {
+            tile(false_type(), false_type(), 1, t);
+            tile(false_type(), false_type(), 0, t + 1);
+          }
+          for (; t < ntl; ++t) tile(false_type(), true_type(), t & 1, t);
+          half_tile(false_type(), true_type(), false_type(), H0(), ntl & 1, ntl);
+          wait_vmcnt<0>();  // the loads past the last tile
         }
-        for (; t < ntl; ++t) {  // the diagonal tiles
-          half_tile(std::true_type(), H0(), t & 1, t);
-          half_tile(std::true_type(), H1(), t & 1, t);
-        }
-        wait_vmcnt<0>();  // the loads past the last tile
       } else {
         // ---- software pipeline over half tiles u = 0, 1, ...: four stages of NOP matrix instructions each,
         //   S(u), dP(u), dV(u-1), dK(u-1)
