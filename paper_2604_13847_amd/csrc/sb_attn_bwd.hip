@@ -1205,18 +1205,33 @@ __global__ __launch_bounds__(256) void attn_bwd_dkv_reduce_kernel(AttnParams P, 
     const int e = blockIdx.y * 16 * D + 4 * u;
     if (e >= rows * D) return;
     f32x4 dk = {0.f, 0.f, 0.f, 0.f}, dv = dk;
-    auto add = [&](const float* part) {
-      dk += *(const f32x4*)(part + e);
-      dv += *(const f32x4*)(part + 64 * D + e);
+    // n partial sums, `stride` floats apart, in order; four of them in flight (one after the other a column of eleven waited eleven times:
+    // 2039 tokens, 16/2 heads: 10.2 -> 7.5 us)
+    auto add = [&](const float* part, int n, size_t stride) {
+      int u = 0;
+      for (; u + 4 <= n; u += 4) {
+        f32x4 x[4], y[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          x[c] = *(const f32x4*)(part + (u + c) * stride + e);
+          y[c] = *(const f32x4*)(part + (u + c) * stride + 64 * D + e);
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) { dk += x[c]; dv += y[c]; }
+      }
+      for (; u < n; ++u) {
+        dk += *(const f32x4*)(part + u * stride + e);
+        dv += *(const f32x4*)(part + u * stride + 64 * D + e);
+      }
     };
-    for (int p = 0; p < np; ++p) {
-      const int it = x < extra && P.sub_slots > 0 ? P.part_item[slot0 + p] : at;
-      const int sub0 = P.sub_slots > 0 ? P.sub_base[it] : -1;
-      if (sub0 >= 0) {
-        const int n = (P.bwd_items[it].weight + P.sub_weight - 1) / P.sub_weight;
-        for (int u = 0; u < n; ++u) add(P.sub_partials + ((size_t)(sub0 + u) * P.Hkv + g) * S);
-      } else {
-        add(P.partials + (size_t)(slot0 + p) * S);
+    if (P.sub_slots == 0) {
+      add(P.partials + (size_t)slot0 * S, np, S);
+    } else {
+      for (int p = 0; p < np; ++p) {
+        const int it = x < extra ? P.part_item[slot0 + p] : at;
+        const int sub0 = P.sub_base[it];
+        if (sub0 >= 0) add(P.sub_partials + ((size_t)sub0 * P.Hkv + g) * S, (P.bwd_items[it].weight + P.sub_weight - 1) / P.sub_weight, (size_t)P.Hkv * S);
+        else add(P.partials + (size_t)(slot0 + p) * S, 1, S);
       }
     }
     const int kr = e / D, d = e % D;
