@@ -18,6 +18,7 @@
 #include <math.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "sb_geom.h"
 #include "sb_internal.h"
@@ -158,8 +159,9 @@ __global__ __launch_bounds__(256) void coverage_rows_kernel(const float* __restr
 // so that every compare-exchange puts the larger key first.  The four wavefronts of a workgroup take the heads of the
 // group in turn, keep their sums in registers and add them in wavefront order at the end: fixed summation order again.
 // Scores must be numbers (a NaN counts as -infinity); sb_block_scores writes none for finite inputs.
-// All row lengths share one kernel, so E = 32 sets the registers of all: 168 for three wavefronts per SIMD, nothing spilled (four would
-// leave 128 and 54 of them spilled).
+// Row lengths share a kernel, whose longest form sets the registers of all: 168 with E = 32 for three wavefronts per SIMD, nothing spilled
+// (four would leave 128 and 54 of them spilled: 131072 tokens 241 -> 261 us); batches without rows of more than 1024 keys take one that ends
+// with E = 16, four wavefronts (32768 tokens: 42.8 -> 40.0 us).
 constexpr int kCovRegMax = 2048;
 
 // Scores as integers of the same order (and back): integer comparisons take a partner lane's key as an operand (DPP) as it is, float
@@ -201,11 +203,12 @@ __device__ __forceinline__ void cross_stage(int (&x)[E], int lane) {
 // Rows of 512 keys and more: most of the sorting is done by a histogram.  The keys fall, by value, into 64 E bins between the row's smallest
 // and largest; a key's place is where its bin begins plus how many came before it in the bin, an LDS atomic each; what is left out of order,
 // inside bins, an odd-even transposition network puts right in as many stages as the fullest bin has keys.  A bin with kCovBin keys or more
-// (ties, outliers) or a row whose values are not finite: false, and the network below does it all.
+// (ties, heavy tails) or a row whose values are not finite: false, and the network below does it all.
 // In which order a bin's keys are counted decides nothing: the result is the sorted row.  `lds`: cov_lds<E> words, the wavefront's own; a
 // lane's E words are four words further from the next lane's than they would have to be, or all lanes would read from the same banks.
 // What bounds both: instruction issue.  For 2048 keys the network takes 4000 vector instructions, this 1200 and 100 LDS operations: 131072
-// tokens, 32 heads: 0.370 -> 0.241 ms; 65536 tokens 0.110 -> 0.083 (both with the launch saved below).
+// tokens, 32 heads: 0.370 -> 0.241 ms; 65536 tokens 0.112 -> 0.078 (both with the launch saved below), and
+// 0.367 -> 0.253 where every row has an outlier (1e4 among N(0, 1)); a row that is left to the network after the atomics: a third more than without.
 constexpr int kCovBin = 32;
 // (comparisons of all keys' places with the row's length would be kept, 64 scalar registers of them, from one phase to the next)
 __device__ __forceinline__ int opaque(int x) {
@@ -240,7 +243,14 @@ __device__ __forceinline__ bool bucket_sort(const float* __restrict__ row, int (
     lo = f > -INFINITY ? fminf(lo, f) : lo;
   }
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) { hi = fmaxf(hi, __shfl_xor(hi, off, 64)); lo = fminf(lo, __shfl_xor(lo, off, 64)); }
+  for (int off = 8; off > 0; off >>= 1) { hi = fmaxf(hi, __shfl_xor(hi, off, 64)); lo = fminf(lo, __shfl_xor(lo, off, 64)); }
+  float hi4 = hi, lo4 = lo;  // what every quarter of the lanes has a key beyond
+#pragma unroll
+  for (int off = 16; off < 64; off <<= 1) {
+    hi = fmaxf(hi, __shfl_xor(hi, off, 64)); lo = fminf(lo, __shfl_xor(lo, off, 64));
+    hi4 = fminf(hi4, __shfl_xor(hi4, off, 64)); lo4 = fmaxf(lo4, __shfl_xor(lo4, off, 64));
+  }
+  if (hi4 > lo4 && hi - lo > 2.f * (hi4 - lo4)) { hi = hi4; lo = lo4; }  // a few keys far from the others: they share the first or the last bin
   constexpr float last = 64 * E - 1;
   const float scale = last / (hi - lo);
   if (!__builtin_amdgcn_readfirstlane(hi < INFINITY && scale > 0.f && scale < 1e30f)) return false;  // (also a row without a finite key, and one of equal keys)
@@ -253,7 +263,7 @@ __device__ __forceinline__ bool bucket_sort(const float* __restrict__ row, int (
   int m = opaque(i);
 #pragma unroll
   for (int r = 0; r < E; ++r) {
-    const unsigned bin = (unsigned)fminf((hi - __int_as_float(x[r])) * scale, last);  // (no smaller for a smaller key)
+    const unsigned bin = (unsigned)fminf(fmaxf((hi - __int_as_float(x[r])) * scale, 0.f), last);  // (no smaller for a smaller key)
     const bool key = lane < m - 64 * r;
     int word = bin + bin / E * 4;
     asm volatile("" : "+v"(word));  // (or a branch round it)
@@ -410,27 +420,28 @@ __device__ __forceinline__ void coverage_row_regs(const float* __restrict__ row,
   }
 }
 
-constexpr int kCovLds = cov_lds<32>;  // words of a wavefront
-template <int E>
+template <int E, int LDS>
 __device__ __forceinline__ void coverage_rows_regs_body(const float* __restrict__ scores_s, int n, int i, int hs0, int hs1, int* lds,
                                                float* __restrict__ out) {
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   float acc[E];
 #pragma unroll
   for (int r = 0; r < E; ++r) acc[r] = 0.f;
-  for (int hs = hs0 + wave; hs < hs1; hs += 4) coverage_row_regs<E>(scores_s + ((int64_t)hs * n + i) * n, i, lane, lds + wave * kCovLds, acc);
+  for (int hs = hs0 + wave; hs < hs1; hs += 4) coverage_row_regs<E>(scores_s + ((int64_t)hs * n + i) * n, i, lane, lds + wave * LDS, acc);
   float* const part = (float*)lds;
 #pragma unroll
-  for (int r = 0; r < E; ++r) part[wave * kCovLds + lane * E + r] = acc[r];
+  for (int r = 0; r < E; ++r) part[wave * LDS + lane * E + r] = acc[r];
   __syncthreads();
   for (int p = tid; p < i; p += 256)
-    out[p] = ((part[p] + part[kCovLds + p]) + part[2 * kCovLds + p]) + part[3 * kCovLds + p];
+    out[p] = ((part[p] + part[LDS + p]) + part[2 * LDS + p]) + part[3 * LDS + p];
 }
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void coverage_rows_regs_kernel(
+template <int MAXE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAXE == 32 ? 3 : 4))) void coverage_rows_regs_kernel(
     const float* __restrict__ scores, GeomArgs ga, int Hs, int64_t slab, int32_t* qb_off, int64_t* sc_off, int32_t* qb_seq,
     float* __restrict__ pacc) {
-  __shared__ __attribute__((aligned(16))) int part[4 * kCovLds];
+  constexpr int LDS = cov_lds<MAXE>;  // words of a wavefront
+  __shared__ __attribute__((aligned(16))) int part[4 * LDS];
   const int qb = blockIdx.x;
   const BatchGeom bg(ga);
   const int s = bg.seq_of(qb);
@@ -446,12 +457,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void c
   const int hs0 = blockIdx.y * hpg, hs1 = min(Hs, hs0 + hpg);
   const float* scores_s = scores + (int64_t)Hs * sg.sc_off;
   float* out = pacc + (int64_t)blockIdx.y * slab + sg.sc_off + (int64_t)i * n;
-  if (i <= 64) coverage_rows_regs_body<1>(scores_s, n, i, hs0, hs1, part, out);
-  else if (i <= 128) coverage_rows_regs_body<2>(scores_s, n, i, hs0, hs1, part, out);
-  else if (i <= 256) coverage_rows_regs_body<4>(scores_s, n, i, hs0, hs1, part, out);
-  else if (i <= 512) coverage_rows_regs_body<8>(scores_s, n, i, hs0, hs1, part, out);
-  else if (i <= 1024) coverage_rows_regs_body<16>(scores_s, n, i, hs0, hs1, part, out);
-  else coverage_rows_regs_body<32>(scores_s, n, i, hs0, hs1, part, out);
+  auto rows = [&](auto e) __attribute__((always_inline)) { coverage_rows_regs_body<decltype(e)::value, LDS>(scores_s, n, i, hs0, hs1, part, out); };
+  if (i <= 64) rows(std::integral_constant<int, 1>());
+  else if (i <= 128) rows(std::integral_constant<int, 2>());
+  else if (i <= 256) rows(std::integral_constant<int, 4>());
+  else if (i <= 512) rows(std::integral_constant<int, 8>());
+  else if (MAXE == 16 || i <= 1024) rows(std::integral_constant<int, 16>());
+  else rows(std::integral_constant<int, MAXE>());
 }
 
 // partial column sums over slabs of kCovSlab query blocks: part[y][qb] = sum over head groups and rows i of slab y, i >= k
@@ -593,7 +605,7 @@ int sb_score_coverage(const sb_problem* p, const float* scores, float* coverage_
   KernelTimer kt(K_COVERAGE, st);
   const int groups = coverage_groups(g);
   const int64_t slab = (int64_t)coverage_slab(g);
-  hipLaunchKernelGGL(coverage_rows_regs_kernel, dim3((unsigned)g.NQB, (unsigned)groups), dim3(256), 0, st, scores,
+  hipLaunchKernelGGL(g.n_max <= 1025 ? coverage_rows_regs_kernel<16> : coverage_rows_regs_kernel<32>, dim3((unsigned)g.NQB, (unsigned)groups), dim3(256), 0, st, scores,
                      make_geom_args(g, p, t), g.Hs, slab, (int32_t*)t.qb_off, (int64_t*)t.sc_off, (int32_t*)t.qb_seq, pacc);
   SB_LAUNCH_CHECK("coverage_rows_regs_kernel");
   if (g.n_max > kCovRegMax + 1) {  // rows with more than kCovRegMax candidates
