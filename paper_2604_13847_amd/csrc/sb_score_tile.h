@@ -106,8 +106,20 @@ __device__ __forceinline__ void walk_keys(const uint32_t* keys, int lane, int m,
   }
 }
 
-// `largest`: the largest of this lane's keys lane, lane + 64, ...
-__device__ inline void select_row(const uint32_t* keys, int* hist, int lane, int m, int need, int i, int32_t* __restrict__ out, uint32_t largest) {
+// Keys in registers: key r of lane l is key 64 r + l of m, E of them to a lane, m > 0.
+template <int E, typename F>
+__device__ __forceinline__ void walk_registers(const uint32_t (&keys)[E], int lane, int m, F f) {
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    if (64 * r >= m) break;
+    const bool valid = lane < m - 64 * r;
+    f(64 * r + lane, keys[r], valid);
+  }
+}
+
+// `walk(f)`: one of the two above.  `largest`: the largest of this lane's keys lane, lane + 64, ...
+template <typename W>
+__device__ inline void select_row(W walk, int* hist, int lane, int m, int need, int i, int32_t* __restrict__ out, uint32_t largest) {
   const unsigned long long lt = (1ull << lane) - 1ull;
   uint32_t thr = 0;
   int remaining = 0;
@@ -120,7 +132,7 @@ __device__ inline void select_row(const uint32_t* keys, int* hist, int lane, int
 #pragma unroll
     for (int a = 0; a < 4; ++a) hist[lane + 64 * a] = 0;
     wave_lds_fence();
-    walk_keys(keys, lane, m, [&](int, uint32_t kk, bool valid) {
+    walk([&](int, uint32_t kk, bool valid) {
       const uint32_t d = (kmax - kk) >> kDistShift;
       if (valid && d < 255u) atomicAdd(&hist[d], 1);
     });
@@ -152,7 +164,7 @@ __device__ inline void select_row(const uint32_t* keys, int* hist, int lane, int
         wave_lds_fence();
         uint32_t* cand = (uint32_t*)hist;
         int pos = 0;
-        walk_keys(keys, lane, m, [&](int, uint32_t kk, bool valid) {
+        walk([&](int, uint32_t kk, bool valid) {
           const bool is_c = valid && ((kmax - kk) >> kDistShift) == (uint32_t)bin;
           const unsigned long long bc = __builtin_amdgcn_ballot_w64(is_c);
           if (bc == 0) return;
@@ -184,7 +196,7 @@ __device__ inline void select_row(const uint32_t* keys, int* hist, int lane, int
 #pragma unroll
       for (int a = 0; a < 4; ++a) hist[lane + 64 * a] = 0;
       wave_lds_fence();
-      walk_keys(keys, lane, m, [&](int, uint32_t kk, bool valid) {
+      walk([&](int, uint32_t kk, bool valid) {
         if (valid && (kk & mask) == prefix) atomicAdd(&hist[(kk >> shift) & 255u], 1);
       });
       wave_lds_fence();
@@ -217,7 +229,7 @@ __device__ inline void select_row(const uint32_t* keys, int* hist, int lane, int
   }
   // keys > thr are all kept; of the keys == thr the `remaining` lowest indices are kept; output in index order
   int eq_seen = 0, pos = 0;
-  walk_keys(keys, lane, m, [&](int j, uint32_t kk, bool valid) {
+  walk([&](int j, uint32_t kk, bool valid) {
     if (few && __builtin_amdgcn_ballot_w64(valid && kk >= thr) == 0) return;
     const bool is_eq = valid && kk == thr;
     const unsigned long long beq = __builtin_amdgcn_ballot_w64(is_eq);

@@ -1,7 +1,7 @@
 // Top-K block selection (paper section 2.2): per row (sequence, selection head, query block i)
 // keep the diagonal block plus the best c-1 past blocks under the total order
 // (score descending, block index ascending; -0 == +0; NaN below everything).
-// One wavefront per row: order-preserving 32-bit keys in LDS, a 4-pass radix select for the
+// One wavefront per row: order-preserving 32-bit keys in registers or LDS, a 4-pass radix select for the
 // threshold key, then an index-ordered compaction, so the result is a pure function of the scores.
 #include <mutex>
 
@@ -11,8 +11,30 @@
 
 namespace sb {
 
-// One wavefront per row (several rows per workgroup, no workgroup barrier anywhere): keys and a
-// 256-bin histogram in the wavefront's own LDS region.
+// Rows of up to 64 E past blocks (at most kRegKeys) with their keys in registers.
+constexpr int kRegKeys = 2048;
+template <int E>
+__device__ __forceinline__ void select_in_registers(const float* row, int* hist, int lane, int m, int need, int i, int32_t* __restrict__ out) {
+  // a buffer that ends with the past blocks: no branch and no address of its own for any of the loads
+  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)row, 0, 4 * m, 0x20000);
+  uint32_t keys[E], largest = 0;
+#pragma unroll
+  for (int r = 0; r < E; ++r) keys[r] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, 4 * lane, 256 * r, 0);
+#pragma unroll
+  for (int r = 0; r < E; ++r) {
+    const uint32_t key = order_key(__uint_as_float(keys[r]));
+    keys[r] = lane < m - 64 * r ? key : 0u;
+    largest = max(largest, keys[r]);
+  }
+  select_row([&](auto f) __attribute__((always_inline)) { walk_registers<E>(keys, lane, m, f); }, hist, lane, m, need, i, out, largest);
+}
+
+// One wavefront per row (several rows per workgroup, no workgroup barrier anywhere): keys in registers, or for batches with longer rows
+// (REGS = false) in the wavefront's own LDS region, which also holds a 256-bin histogram.
+// What bounds it: instruction issue, and latencies where LDS leaves few wavefronts on a CU: with 9 KB a wavefront for rows of 2048 keys four a
+// SIMD, each walk over the keys an LDS read and a wait a step; in 69 registers seven, and no reads: 131072 tokens, 32 heads 0.180 -> 0.109 ms.
+// Rows of up to 256 keys gain little (the 32768-token batch 23.1 -> 21.1 us).
+template <bool REGS>
 __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ scores, GeomArgs ga, int64_t NQB, int Hs, int64_t nnz_unit,
                                                    int region_words, int32_t* __restrict__ rowptr, int32_t* __restrict__ idx) {
   extern __shared__ uint32_t smem[];
@@ -43,6 +65,13 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ sco
     return;
   }
   const float* row = scores + (int64_t)Hs * sg.sc_off + ((int64_t)hs * n + i) * n;
+  if constexpr (REGS) {
+    if (m <= 256) select_in_registers<4>(row, hist, lane, m, need, i, out);
+    else if (m <= 512) select_in_registers<8>(row, hist, lane, m, need, i, out);
+    else if (m <= 1024) select_in_registers<16>(row, hist, lane, m, need, i, out);
+    else select_in_registers<32>(row, hist, lane, m, need, i, out);
+    return;
+  }
   uint32_t largest = 0;
   for (int j0 = lane; j0 < m; j0 += 64 * 8) {  // eight independent loads in flight per lane: the row comes from HBM
     float x[8];
@@ -57,7 +86,7 @@ __global__ __launch_bounds__(256) void topk_kernel(const float* __restrict__ sco
       }
   }
   wave_lds_fence();
-  select_row(keys, hist, lane, m, need, i, out, largest);
+  select_row([&](auto f) __attribute__((always_inline)) { walk_keys(keys, lane, m, f); }, hist, lane, m, need, i, out, largest);
 }
 
 // Scores and selection in one kernel: the scores of a row never leave the compute unit.  One
@@ -153,8 +182,9 @@ __global__ __launch_bounds__(64 * kFusedWaves) void score_select_kernel(
     if (lane == 0) out[0] = i;
   } else {
     uint32_t largest = 0;
-    walk_keys(keys + (size_t)wave * stride, lane, m, [&](int, uint32_t key, bool) { largest = max(largest, key); });
-    select_row(keys + (size_t)wave * stride, hist + 256 * wave, lane, m, need, i, out, largest);
+    auto walk = [&](auto f) __attribute__((always_inline)) { walk_keys(keys + (size_t)wave * stride, lane, m, f); };
+    walk([&](int, uint32_t key, bool) { largest = max(largest, key); });
+    select_row(walk, hist + 256 * wave, lane, m, need, i, out, largest);
   }
 }
 
@@ -162,16 +192,19 @@ __global__ __launch_bounds__(64 * kFusedWaves) void score_select_kernel(
 
 using namespace sb;
 
+constexpr size_t kLdsUnasked = 48 * 1024;  // dynamic LDS that a kernel may have without its limit being raised
+
 // launches the selection on tables that are already in device memory
 static int select_launch(const Geo& g, const GeomArgs& ga, const float* scores, int32_t* sel_rowptr_out, int32_t* sel_idx_out,
                          hipStream_t st) {
-  // every wavefront owns a region of n_max keys (rounded up to 64) plus 256 histogram bins; as many rows per workgroup
-  // (at most four) as fit in 64 KiB
-  const int region_words = (int)((g.n_max + 63) / 64 * 64 + 256);
+  // every wavefront owns 256 histogram bins and, where keys are not in registers, a region of n_max keys (rounded up to 64); as many rows
+  // per workgroup (at most four) as fit in 64 KiB
+  const bool regs = g.n_max <= kRegKeys + 1;
+  const int region_words = (regs ? 0 : (int)((g.n_max + 63) / 64 * 64)) + 256;
   int W = (int)(65536 / (sizeof(uint32_t) * (size_t)region_words));
   W = W < 1 ? 1 : (W > 4 ? 4 : W);
   const size_t smem = sizeof(uint32_t) * (size_t)region_words * W;
-  if (smem > 48 * 1024) {  // raise the kernel's dynamic LDS limit; once per device, whichever thread comes first
+  if (smem > kLdsUnasked) {  // raise the kernel's dynamic LDS limit; once per device, whichever thread comes first
     static std::mutex mu;
     static bool attr_set[kMaxDevices] = {};
     int dev = 0;
@@ -179,7 +212,7 @@ static int select_launch(const Geo& g, const GeomArgs& ga, const float* scores, 
     if (dev < 0 || dev >= kMaxDevices) { set_error("device ordinal %d out of range", dev); return SB_ERR_UNSUPPORTED; }
     std::lock_guard<std::mutex> lock(mu);
     if (!attr_set[dev]) {
-      SB_CHECK_HIP(hipFuncSetAttribute((const void*)topk_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+      SB_CHECK_HIP(hipFuncSetAttribute((const void*)topk_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)(sizeof(uint32_t) * (SB_MAX_BLOCKS_PER_SEQ + 256))));
       attr_set[dev] = true;
     }
@@ -187,7 +220,7 @@ static int select_launch(const Geo& g, const GeomArgs& ga, const float* scores, 
   const int64_t rows = (int64_t)g.Hs * g.NQB;
   dim3 grid((unsigned)((rows + W - 1) / W));
   KernelTimer kt(K_TOPK, st);
-  hipLaunchKernelGGL(topk_kernel, grid, dim3(64 * W), smem, st, scores, ga, g.NQB, g.Hs, g.nnz_unit, region_words, sel_rowptr_out,
+  hipLaunchKernelGGL(regs ? topk_kernel<true> : topk_kernel<false>, grid, dim3(64 * W), smem, st, scores, ga, g.NQB, g.Hs, g.nnz_unit, region_words, sel_rowptr_out,
                      sel_idx_out);
   SB_LAUNCH_CHECK("topk_kernel");
   return SB_OK;
@@ -222,33 +255,34 @@ static size_t fused_lds(const Geo& g, int R) { return sizeof(uint32_t) * ((size_
 // launches the kernel that scores and selects; qbar/kbar are the pooled arrays, `scores` may be null
 static int score_select_launch(const Geo& g, const GeomArgs& ga, const float* qbar, const float* kbar, float* scores, int32_t* sel_rowptr_out,
                                int32_t* sel_idx_out, hipStream_t st) {
-  static std::mutex mu;
-  static int lds_of_device[kMaxDevices] = {};  // LDS a workgroup may use, once the kernels' limit has been raised to it
-  int dev = 0;
-  SB_CHECK_HIP(hipGetDevice(&dev));
-  if (dev < 0 || dev >= kMaxDevices) { set_error("device ordinal %d out of range", dev); return SB_ERR_UNSUPPORTED; }
-  int cap = 0;
-  {
-    std::lock_guard<std::mutex> lock(mu);
-    if (!lds_of_device[dev]) {
-      int per_block = 0;
-      SB_CHECK_HIP(hipDeviceGetAttribute(&per_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
-      const void* kernels[4] = {(const void*)score_select_kernel<128, false>, (const void*)score_select_kernel<64, false>,
-                                (const void*)score_select_kernel<128, true>, (const void*)score_select_kernel<64, true>};
-      for (const void* k : kernels) SB_CHECK_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, per_block));
-      lds_of_device[dev] = per_block;
-    }
-    cap = lds_of_device[dev];
-  }
   const int stride = fused_stride(g);
   int R = kFusedWaves;
-  while (R > 1 && fused_lds(g, R) > (size_t)cap) R >>= 1;
-  const size_t smem = fused_lds(g, R);
-  if (smem > (size_t)cap) {
-    set_error("a sequence of %d blocks does not fit the fused selection (%zu bytes of LDS, %d available): pass scores_out", g.n_max,
-              smem, cap);
-    return SB_ERR_UNSUPPORTED;
+  if (fused_lds(g, R) > kLdsUnasked) {
+    static std::mutex mu;
+    static int lds_of_device[kMaxDevices] = {};  // LDS a workgroup may use, once the kernels' limit has been raised to it
+    int dev = 0;
+    SB_CHECK_HIP(hipGetDevice(&dev));
+    if (dev < 0 || dev >= kMaxDevices) { set_error("device ordinal %d out of range", dev); return SB_ERR_UNSUPPORTED; }
+    int cap = 0;
+    {
+      std::lock_guard<std::mutex> lock(mu);
+      if (!lds_of_device[dev]) {
+        int per_block = 0;
+        SB_CHECK_HIP(hipDeviceGetAttribute(&per_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev));
+        SB_CHECK_HIP(hipFuncSetAttribute((const void*)score_select_kernel<128, false>, hipFuncAttributeMaxDynamicSharedMemorySize, per_block));
+        SB_CHECK_HIP(hipFuncSetAttribute((const void*)score_select_kernel<64, false>, hipFuncAttributeMaxDynamicSharedMemorySize, per_block));
+        lds_of_device[dev] = per_block;
+      }
+      cap = lds_of_device[dev];
+    }
+    while (R > 1 && fused_lds(g, R) > (size_t)cap) R >>= 1;
+    if (fused_lds(g, R) > (size_t)cap) {
+      set_error("a sequence of %d blocks does not fit the fused selection (%zu bytes of LDS, %d available): pass scores_out", g.n_max,
+                fused_lds(g, R), cap);
+      return SB_ERR_UNSUPPORTED;
+    }
   }
+  const size_t smem = fused_lds(g, R);
   const int64_t groups = (g.NQB + R - 1) / R;
   if (groups * g.Hs > 0x7fffffffll) { set_error("too many rows for one launch of the fused selection: pass scores_out"); return SB_ERR_UNSUPPORTED; }
   KernelTimer kt(K_SCORE_SELECT, st);
@@ -263,14 +297,15 @@ static int score_select_launch(const Geo& g, const GeomArgs& ga, const float* qb
 }
 
 // Where the caller wants the score matrix too, one kernel or two?  One saves a launch and reads no scores, but gathers the pooled keys
-// for 16 rows at a time where score_kernel takes 64: up to one round of its workgroups.  Two kernels / one, with the pooling: 1000 tokens,
+// for 16 rows at a time where score_kernel takes 64: up to one round of its workgroups, and no more LDS than it has without asking (so that
+// a first call makes no runtime call that it did not make before).  Two kernels / one, with the pooling: 1000 tokens,
 // one head 15.1 / 12.9 us, 8192 tokens, 32/8 heads (256 workgroups) 34.1 / 24.8, four sequences of 2048 tokens 30.0 / 24.5.  At 512
 // workgroups the two are level (the two kernels of then took 55 us, of which score_kernel has since lost a fifth, one takes 52).  With the
 // sequences of a workgroup's rows one after the other, a barrier each, 2039 tokens in short sequences took 19.9 us in place of 12.6; their
 // tiles dealt to all wavefronts: 10.5.
 constexpr int64_t kFusedWgs = 256;
 static bool score_and_select_at_once(const Geo& g) {
-  return (g.NQB + kFusedWaves - 1) / kFusedWaves * g.Hs <= kFusedWgs && fused_lds(g, kFusedWaves) <= 64 * 1024;
+  return (g.NQB + kFusedWaves - 1) / kFusedWaves * g.Hs <= kFusedWgs && fused_lds(g, kFusedWaves) <= kLdsUnasked;
 }
 
 extern "C" int sb_score_select(const sb_problem* p, const void* q, const void* k, float* kbar_out, float* scores_out,
