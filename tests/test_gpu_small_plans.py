@@ -94,3 +94,22 @@ def test_coverage_sorted_by_a_histogram(kind, n):
     got = sb.sb_score_coverage(pb, torch.from_numpy(sc.ravel()).to(DEV)).cpu().numpy()[:n]
     ref = dst.coverage_curves(po.nblk, po.Hs, sc.ravel(), po.score_off)
     assert np.abs(got - ref).max() <= 2e-6
+
+
+@pytest.mark.parametrize("n", [257, 513, 1025, 2049, 2050])
+@pytest.mark.parametrize("k", [2, 40, 0.6])
+def test_selection_of_rows_in_registers(n, k):
+    """Rows on both sides of every register count and of the form that keeps its keys in LDS (2050 blocks), budgets on both sides of the
+    switch between the two threshold searches; ties, NaN, -infinity and signed zeros among the scores.  Bit for bit the checker's order."""
+    budget = k if isinstance(k, int) else int(k * n)
+    rng = np.random.default_rng(n + budget)
+    sc = rng.normal(size=(1, n, n)).astype(np.float32)
+    sc[:, 1::3] = np.round(sc[:, 1::3] * 4.0) / 4.0
+    sc[rng.random(sc.shape) < 0.02] = np.nan
+    sc[rng.random(sc.shape) < 0.02] = -np.inf
+    sc[rng.random(sc.shape) < 0.02] = -0.0
+    cu = np.array([0, n * 64 - 63])
+    pb = sb.Problem(cu, [budget], 1, 1, 64, 64, device=DEV)
+    rowptr, idx = sb.sb_select_topk(pb, torch.from_numpy(sc.ravel()).to(DEV))
+    rp, ix = orc.select_topk(orc.Problem(cu, 1, 1, 64, 64, 0), sc.ravel(), np.array([budget], dtype=np.int32))
+    assert np.array_equal(rowptr.cpu().numpy(), rp) and np.array_equal(idx.cpu().numpy()[: int(rp[-1])], ix)
