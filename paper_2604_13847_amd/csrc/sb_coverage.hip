@@ -9,7 +9,7 @@
 // its min(k-1, i) largest shares (pref_i[i] = 1).  C_s(k) is the mean over the sequence's rows.
 // All kernels are deterministic (fixed summation order, no atomics):
 //   coverage_rows_regs_kernel   rows of at most 2048 candidates: one wavefront per (row, selection head) sorts the row in
-//                           registers (long rows by a histogram first, short ones by a bitonic network), then softmax and prefix sums; summed over the heads of a group into
+//                           registers (long rows by a histogram, short ones by a bitonic network), then softmax and prefix sums; summed over the heads of a group into
 //                           Pacc[s][i][m-1] = sum_hs pref_{hs,i}[m], m = 1..i
 //   coverage_rows_kernel    longer rows: one workgroup per query block and group of selection heads, for every head in
 //                           turn softmax + bitonic sort + prefix sum in LDS, into the same Pacc
@@ -200,7 +200,7 @@ __device__ __forceinline__ void cross_stage(int (&x)[E], int lane) {
   }
 }
 
-// Rows of 512 keys and more: most of the sorting is done by a histogram.  The keys fall, by value, into 64 E bins between the row's smallest
+// Rows of more than 256 keys: most of the sorting is done by a histogram.  The keys fall, by value, into 64 E bins between the row's smallest
 // and largest; a key's place is where its bin begins plus how many came before it in the bin, an LDS atomic each; what is left out of order,
 // inside bins, an odd-even transposition network puts right in as many stages as the fullest bin has keys.  A bin with kCovBin keys or more
 // (ties, heavy tails) or a row whose values are not finite: false, and the network below does it all.
