@@ -15,11 +15,17 @@ namespace sb {
 constexpr int kRegKeys = 2048;
 template <int E>
 __device__ __forceinline__ void select_in_registers(const float* row, int* hist, int lane, int m, int need, int i, int32_t* __restrict__ out) {
-  // a buffer that ends with the past blocks: no branch and no address of its own for any of the loads
+  // A buffer that ends with the past blocks: no branch and no address of its own for any of the loads.  The whole offset is the lane's, a
+  // register per 4 KB and an immediate: the bounds check leaves the scalar offset out.
   const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)row, 0, 4 * m, 0x20000);
   uint32_t keys[E], largest = 0;
 #pragma unroll
-  for (int r = 0; r < E; ++r) keys[r] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, 4 * lane, 256 * r, 0);
+  for (int r0 = 0; r0 < E; r0 += 16) {
+    int at = 4 * lane + 256 * r0;
+    asm volatile("" : "+v"(at));  // (or the offsets are worked out from what the walks below need, a register each)
+#pragma unroll
+    for (int r = r0; r < r0 + 16 && r < E; ++r) keys[r] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, at + 256 * (r - r0), 0, 0);
+  }
 #pragma unroll
   for (int r = 0; r < E; ++r) {
     const uint32_t key = order_key(__uint_as_float(keys[r]));

@@ -128,13 +128,26 @@ def test_the_scan_sees_the_matrix_instructions():
     assert not scan("v_cvt_pk_bf16_f32 v9, v40, v41", "s_nop 1", other)
 
 
+def assembly(source, tmp_path):
+    out = str(tmp_path / "a.s")
+    subprocess.run(["hipcc", *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, source), "-o", out], check=True, capture_output=True)
+    return open(out).read().splitlines()
+
+
+@pytest.mark.parametrize("source", ["sb_topk.hip"])
+def test_loads_that_end_with_a_row_have_no_offset_outside_the_bounds_check(source, tmp_path):
+    """A row's keys are loaded through a buffer that ends with the row, up to 4 KB more than it has.  A buffer access is checked by its
+    lane offset and immediate; a scalar offset would not be, and the last row of a score matrix would be read past the allocation."""
+    loads = [l.split(";")[0].strip() for l in assembly(source, tmp_path) if re.match(r"\s*buffer_", l)]
+    assert len(loads) >= 60
+    assert not [l for l in loads if not re.search(r"\], 0 offen( offset:\d+)?$", l)]
+
+
 @pytest.mark.parametrize("source", ["sb_attn_fwd.hip", "sb_attn_bwd.hip"])
 def test_no_vector_write_right_before_a_load_that_reads_it(source, tmp_path):
     """... and no operand or result of a matrix instruction too close to it."""
-    out = str(tmp_path / "a.s")
-    subprocess.run(["hipcc", *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, source), "-o", out], check=True, capture_output=True)
     loads = products = 0
-    for name, code, labels in kernels(open(out).read().splitlines()):
+    for name, code, labels in kernels(assembly(source, tmp_path)):
         loads += sum(bool(re.match(r"(buffer_load\S* .* lds$|global_load_lds)", x.text)) for x in code)
         products += sum(x.matrix for x in code)
         bad = hazards(code, labels)
