@@ -220,12 +220,18 @@ template <int E>
 __device__ __forceinline__ void load_keys(const float* __restrict__ row, int i, int lane, int (&x)[E]) {
   asm volatile("" : "+s"(row));
   i = opaque(i);
-  // a buffer that ends with the row: no branch and no address of its own for any of the loads
-  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)row, 0, 4 * i, 0x20000);
+  // Buffers that end with the row: no branch and no address of its own for any of the loads.  Offsets are the lane's and an immediate, the
+  // scalar offset is zero, because the bounds check leaves it out; an immediate reaches 4 KB, so the second half of 32 keys a lane has a buffer of its own.
+  int at = 4 * lane;
+  asm volatile("" : "+v"(at));  // (or every load's offset gets a register of its own)
 #pragma unroll
-  for (int r = 0; r < E; ++r) {
-    const float f = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, 4 * lane, 256 * r, 0));
-    x[r] = __float_as_int(fmaxf(lane < i - 64 * r ? f : -INFINITY, -INFINITY));
+  for (int r0 = 0; r0 < E; r0 += 16) {
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)(row + 64 * r0), 0, 4 * max(i - 64 * r0, 0), 0x20000);
+#pragma unroll
+    for (int r = r0; r < r0 + 16 && r < E; ++r) {
+      const float f = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, at + 256 * (r - r0), 0, 0));
+      x[r] = __float_as_int(fmaxf(lane < i - 64 * r ? f : -INFINITY, -INFINITY));
+    }
   }
 }
 template <int E> constexpr int cov_lds = 64 * (E + 4);

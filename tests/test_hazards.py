@@ -134,7 +134,7 @@ def assembly(source, tmp_path):
     return open(out).read().splitlines()
 
 
-@pytest.mark.parametrize("source", ["sb_topk.hip"])
+@pytest.mark.parametrize("source", ["sb_topk.hip", "sb_coverage.hip"])
 def test_loads_that_end_with_a_row_have_no_offset_outside_the_bounds_check(source, tmp_path):
     """A row's keys are loaded through a buffer that ends with the row, up to 4 KB more than it has.  A buffer access is checked by its
     lane offset and immediate; a scalar offset would not be, and the last row of a score matrix would be read past the allocation."""
