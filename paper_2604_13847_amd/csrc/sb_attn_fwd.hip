@@ -430,9 +430,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void a
   timer.start(P);
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
-  const int pos = claim_item(blockIdx.x, P.n_items, P.ticket ? P.ticket + kTicketInts * blockIdx.y : nullptr);
+  int pos = claim_item(blockIdx.x, P.n_items, P.ticket ? P.ticket + kTicketInts * blockIdx.y : nullptr);
   if (pos < 0) return;
-  const WorkItem item = P.items[pos];  // (scalar loads make the compiler keep more in registers than there are: 1.70 -> 1.74 ms on the 32768-token batch)
+  asm volatile("" : "+v"(pos));  // (scalar loads make the compiler keep more in registers than there are: 16 of 256 spilled, with vector ones it takes 210)
+  const WorkItem item = P.items[pos];
   const int hs = item.hs, i = item.i, L = item.len, e0 = item.e0, ntiles = item.ntiles;
   const int64_t seq0 = item.seq0;
   const int strip = wave & 1;
