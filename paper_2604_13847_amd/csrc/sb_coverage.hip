@@ -200,15 +200,16 @@ __device__ __forceinline__ void cross_stage(int (&x)[E], int lane) {
   }
 }
 
-// Rows of more than 256 keys: most of the sorting is done by a histogram.  The keys fall, by value, into 64 E bins between the row's smallest
-// and largest; a key's place is where its bin begins plus how many came before it in the bin, an LDS atomic each; what is left out of order,
+// Rows of more than 256 keys: most of the sorting is done by a histogram.  The finite keys fall, by value, into 64 E bins between the smallest
+// and the largest of them; a key's place is where its bin begins plus how many came before it in the bin, an LDS atomic each; what is left out of order,
 // inside bins, an odd-even transposition network puts right in as many stages as the fullest bin has keys.  A bin with kCovBin keys or more
-// (ties, heavy tails) or a row whose values are not finite: false, and the network below does it all.
+// (ties, heavy tails), a row with +infinity or one whose finite keys are all equal: false, and the network below does it all.
+// Keys of -infinity (masked blocks, and what the row's end is filled with) take no part: their places, behind the finite keys', are filled.
 // In which order a bin's keys are counted decides nothing: the result is the sorted row.  `lds`: cov_lds<E> words, the wavefront's own; a
 // lane's E words are four words further from the next lane's than they would have to be, or all lanes would read from the same banks.
 // What bounds both: instruction issue.  For 2048 keys the network takes 4000 vector instructions, this 1200 and 100 LDS operations: 131072
-// tokens, 32 heads: 0.370 -> 0.241 ms; 65536 tokens 0.112 -> 0.078 (both with the launch saved below), and
-// 0.367 -> 0.253 where every row has an outlier (1e4 among N(0, 1)); a row that is left to the network after the atomics: a third more than without.
+// tokens, 32 heads: 0.370 -> 0.240 ms; 65536 tokens 0.113 -> 0.078 (both with the launch saved below), 0.371 -> 0.254 where every row has an
+// outlier (1e4 among N(0, 1)), 0.371 -> 0.236 where half of the keys are -infinity (0.444 where those were counted in one bin).
 constexpr int kCovBin = 32;
 // (comparisons of all keys' places with the row's length would be kept, 64 scalar registers of them, from one phase to the next)
 __device__ __forceinline__ int opaque(int x) {
@@ -234,7 +235,7 @@ __device__ __forceinline__ void load_keys(const float* __restrict__ row, int i, 
     }
   }
 }
-template <int E> constexpr int cov_lds = 64 * (E + 4);
+template <int E> constexpr int cov_lds = 64 * (E + 4) + 2 * E + 8;  // the places, and room for what has none
 // The keys are read from memory again where they are needed again: with them, their places and the sums of the heads in registers all the
 // while, a hundred were spilled.
 template <int E>
@@ -262,18 +263,20 @@ __device__ __forceinline__ bool bucket_sort(const float* __restrict__ row, int (
   if (!__builtin_amdgcn_readfirstlane(hi < INFINITY && scale > 0.f && scale < 1e30f)) return false;  // (also a row without a finite key, and one of equal keys)
   typedef int i32x4s __attribute__((ext_vector_type(4)));
   i32x4s* const own = (i32x4s*)(lds + lane * (E + 4));
+  // What is no finite key counts in a word between two lanes' that is no bin, and so far on that its place is none of the row's.
 #pragma unroll
   for (int r = 0; r < E / 4; ++r) own[r] = i32x4s{0, 0, 0, 0};
+  lds[lane * (E + 4) + E] = 32 * E;
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   int at[E], most = 0;  // word of the key's bin | keys before it << 16, then its place's word
-  int m = opaque(i);
 #pragma unroll
   for (int r = 0; r < E; ++r) {
+    asm volatile("" : "+v"(x[r]));  // (or what was compared above is kept)
     const unsigned bin = (unsigned)fminf(fmaxf((hi - __int_as_float(x[r])) * scale, 0.f), last);  // (no smaller for a smaller key)
-    const bool key = lane < m - 64 * r;
+    const bool key = __int_as_float(x[r]) > -INFINITY;
     int word = bin + bin / E * 4;
     asm volatile("" : "+v"(word));  // (or a branch round it)
-    at[r] = key ? word : lane * (E + 4) + E;  // past the row's end: a word between two lanes' that is no bin
+    at[r] = key ? word : lane * (E + 4) + E;
     const int before = atomicAdd(&lds[at[r]], 1);
     most = max(most, key ? before : 0);
     at[r] |= before << 16;
@@ -293,6 +296,7 @@ __device__ __forceinline__ bool bucket_sort(const float* __restrict__ row, int (
     const int up = __shfl_up(run, off, 64);
     if (lane >= off) run += up;
   }
+  const int finite = __builtin_amdgcn_readlane(run, 63);
   run -= sum;
   asm volatile("" ::: "memory");  // (read again instead of kept)
 #pragma unroll
@@ -303,15 +307,20 @@ __device__ __forceinline__ bool bucket_sort(const float* __restrict__ row, int (
     if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
   }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  m = opaque(m);
 #pragma unroll
   for (int r = 0; r < E; ++r) {
-    const unsigned counted = ((volatile int*)lds)[at[r] & 0xffff] + (at[r] >> 16), place = lane < m - 64 * r ? counted : r * 64 + lane;
+    const unsigned place = ((volatile int*)lds)[at[r] & 0xffff] + ((unsigned)at[r] >> 16);
     at[r] = place + place / E * 4;
     if (r % 8 == 7) __builtin_amdgcn_sched_barrier(0);
   }
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-  load_keys<E>(row, m, lane, x);
+  if ((lane + 1) * E > finite) {  // the places behind the finite keys
+    const int none = ordered(__float_as_int(-INFINITY));
+#pragma unroll
+    for (int r = 0; r < E / 4; ++r) own[r] = i32x4s{none, none, none, none};
+  }
+  asm volatile("" ::: "memory");
+  load_keys<E>(row, opaque(i), lane, x);
 #pragma unroll
   for (int r = 0; r < E; ++r)
     lds[at[r]] = ordered(x[r]);

@@ -78,22 +78,44 @@ KINDS = {
     "masked": lambda rng, s: np.where(rng.random(s) < 0.01, -np.inf, rng.normal(size=s)),
     "half masked": lambda rng, s: np.where(rng.random(s) < 0.5, -np.inf, rng.normal(size=s)),
     "tiny": lambda rng, s: rng.normal(size=s) * 1e-30,
+    "not a number": lambda rng, s: np.where(rng.random(s) < 0.01, np.nan, rng.normal(size=s)),  # counts as -infinity
 }
 
 
+def check_curves(sc):
+    """sc: [heads][n][n].  The curves against the float64 checker (2e-6, as in tests/test_gpu_dst.py: shares are at most 1 and a curve is a
+    mean of row sums)."""
+    Hs, n = sc.shape[:2]
+    cu = np.array([0, n * 64 - 5])
+    pb = sb.Problem(cu, [8], Hs, Hs, 64, 64, device=DEV)
+    po = orc.Problem(cu, Hs, Hs, 64, 64, 0)
+    got = sb.sb_score_coverage(pb, torch.from_numpy(sc.ravel()).to(DEV)).cpu().numpy()[:n]
+    with np.errstate(invalid="ignore"):
+        ref = dst.coverage_curves(po.nblk, po.Hs, np.where(np.isnan(sc), -np.inf, sc).ravel(), po.score_off)
+    np.testing.assert_allclose(got, ref, rtol=0, atol=2e-6)  # (NaN where the checker has NaN)
+    return ref
+
+
+# 1025 blocks are the most of the kernel that ends with 16 keys a lane, 2049 of the one with 32
 @pytest.mark.parametrize("kind", sorted(KINDS))
-@pytest.mark.parametrize("n", [300, 2049])
+@pytest.mark.parametrize("n", [300, 1025, 1026, 2049])
 def test_coverage_sorted_by_a_histogram(kind, n):
-    """Rows of 257 to 2048 keys: spread, tied, with outliers that leave all others in one bin, and with -infinity among them.  The curves
-    against the float64 checker (2e-6, as in tests/test_gpu_dst.py: shares are at most 1 and a curve is a mean of row sums)."""
+    """Rows of 257 to 2048 keys: spread, tied, with outliers that leave all others in one bin, and with -infinity and NaN among them."""
     Hs = 2
     sc = KINDS[kind](np.random.default_rng(n), (Hs, n, n)).astype(np.float32)
-    sc[:, :, 0] = np.where(np.isneginf(sc[:, :, 0]), 0.0, sc[:, :, 0])  # (a row without any finite score has no softmax)
-    pb = sb.Problem(np.array([0, n * 64 - 5]), [8], Hs, Hs, 64, 64, device=DEV)
-    po = orc.Problem(np.array([0, n * 64 - 5]), Hs, Hs, 64, 64, 0)
-    got = sb.sb_score_coverage(pb, torch.from_numpy(sc.ravel()).to(DEV)).cpu().numpy()[:n]
-    ref = dst.coverage_curves(po.nblk, po.Hs, sc.ravel(), po.score_off)
-    assert np.abs(got - ref).max() <= 2e-6
+    sc[:, :, 0] = np.where(np.isfinite(sc[:, :, 0]), sc[:, :, 0], 0.0)  # (a row without any finite score has no softmax)
+    check_curves(sc)
+
+
+def test_coverage_of_rows_without_a_softmax():
+    """One row with +infinity and one without a finite key, each left to the network: NaN for the budgets that they count for (up to
+    their 271 and 281 blocks), as the definition gives it, and nothing else is touched."""
+    n = 700
+    sc = np.random.default_rng(5).normal(size=(2, n, n)).astype(np.float32)
+    sc[0, 270, :270] = -np.inf
+    sc[1, 280, 17] = np.inf
+    ref = check_curves(sc)
+    assert np.isnan(ref[1:280]).all() and np.isfinite(ref[280:]).all()
 
 
 @pytest.mark.parametrize("n", [257, 513, 1025, 2049, 2050])
