@@ -171,6 +171,21 @@ template <int CTRL>
 __device__ __forceinline__ int dpp(int x) {
   return __builtin_amdgcn_mov_dpp(x, CTRL, 0xf, 0xf, true);
 }
+// A reduction over each row of 16 lanes, and over the wavefront's four rows, without LDS.
+template <typename F>
+__device__ __forceinline__ int over_row(int x, F f) {
+  x = f(x, dpp<0xB1>(x));
+  x = f(x, dpp<0x4E>(x));
+  x = f(x, dpp<0x141>(x));
+  return f(x, dpp<0x140>(x));
+}
+template <typename F>
+__device__ __forceinline__ int over_rows(int x, F f) {
+  const auto s = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  x = f((int)s[0], (int)s[1]);
+  const auto u = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return f((int)u[0], (int)u[1]);
+}
 // One stage of the network across lanes: lane l against lane l ^ d, lanes with (l & d) == 0 keep the larger key.  No LDS: at distances 1, 2
 // and 8 the partner's key is an operand of the comparison, at 4 one move away; at 16 and 32 two registers swap halves, so that each
 // then holds one side of every pair, are compared with each other and swap back.
@@ -236,11 +251,10 @@ __device__ __forceinline__ void load_keys(const float* __restrict__ row, int i, 
   }
 }
 template <int E> constexpr int cov_lds = 64 * (E + 4) + 2 * E + 8;  // the places, and room for what has none
-// The keys are read from memory again where they are needed again: with them, their places and the sums of the heads in registers all the
-// while, a hundred were spilled.
+// `x`: the keys, lane, lane + 64, ..., still there where the result is false.  Where it is true they have been read from memory again for the last step: with
+// them, their places and the sums of the heads in registers all the while, a hundred were spilled.
 template <int E>
 __device__ __forceinline__ bool bucket_sort(const float* __restrict__ row, int (&x)[E], int i, int lane, int* lds) {
-  load_keys<E>(row, i, lane, x);
   asm volatile("" : "+v"(lane));  // (what follows from the lane is not kept over the loop of rows)
   float hi = -INFINITY, lo = INFINITY;  // of the finite keys
 #pragma unroll
@@ -249,14 +263,12 @@ __device__ __forceinline__ bool bucket_sort(const float* __restrict__ row, int (
     hi = fmaxf(hi, f);
     lo = f > -INFINITY ? fminf(lo, f) : lo;
   }
-#pragma unroll
-  for (int off = 8; off > 0; off >>= 1) { hi = fmaxf(hi, __shfl_xor(hi, off, 64)); lo = fminf(lo, __shfl_xor(lo, off, 64)); }
-  float hi4 = hi, lo4 = lo;  // what every quarter of the lanes has a key beyond
-#pragma unroll
-  for (int off = 16; off < 64; off <<= 1) {
-    hi = fmaxf(hi, __shfl_xor(hi, off, 64)); lo = fminf(lo, __shfl_xor(lo, off, 64));
-    hi4 = fminf(hi4, __shfl_xor(hi4, off, 64)); lo4 = fmaxf(lo4, __shfl_xor(lo4, off, 64));
-  }
+  const auto fmax_ = [](int a, int b) __attribute__((always_inline)) { return __float_as_int(fmaxf(__int_as_float(a), __int_as_float(b))); };
+  const auto fmin_ = [](int a, int b) __attribute__((always_inline)) { return __float_as_int(fminf(__int_as_float(a), __int_as_float(b))); };
+  const int hi_row = over_row(__float_as_int(hi), fmax_), lo_row = over_row(__float_as_int(lo), fmin_);
+  hi = __int_as_float(over_rows(hi_row, fmax_)); lo = __int_as_float(over_rows(lo_row, fmin_));
+  // what every quarter of the lanes has a key beyond
+  const float hi4 = __int_as_float(over_rows(hi_row, fmin_)), lo4 = __int_as_float(over_rows(lo_row, fmax_));
   if (hi4 > lo4 && hi - lo > 2.f * (hi4 - lo4)) { hi = hi4; lo = lo4; }  // a few keys far from the others: they share the first or the last bin
   constexpr float last = 64 * E - 1;
   const float scale = last / (hi - lo);
@@ -282,10 +294,9 @@ __device__ __forceinline__ bool bucket_sort(const float* __restrict__ row, int (
     at[r] |= before << 16;
     if (r % 8 == 7) __builtin_amdgcn_sched_barrier(0);
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) most = max(most, __shfl_xor(most, off, 64));
-  most = __builtin_amdgcn_readfirstlane(most);
-  if (most + 1 >= kCovBin) return false;
+  if (__builtin_amdgcn_ballot_w64(most + 1 >= kCovBin) != 0) return false;
+  const auto imax = [](int a, int b) __attribute__((always_inline)) { return max(a, b); };
+  most = __builtin_amdgcn_readfirstlane(over_rows(over_row(most, imax), imax));
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   int sum = 0;
 #pragma unroll
@@ -398,13 +409,14 @@ __device__ __forceinline__ void bitonic_sort(int (&x)[E], int lane) {
 }
 
 template <int E>
-__device__ __forceinline__ void coverage_row_regs(const float* __restrict__ row, int i, int lane, int* lds, float (&acc)[E]) {
+__device__ __forceinline__ void coverage_row_regs(const float* __restrict__ row, int i, int lane, int* lds, bool& spread, float (&acc)[E]) {
   int x[E];
   i = opaque(i);
   bool sorted = false;
-  if constexpr (E >= 8) sorted = bucket_sort<E>(row, x, i, lane, lds);
+  load_keys<E>(row, i, lane, x);
+  if constexpr (E >= 8)
+    if (spread) spread = sorted = bucket_sort<E>(row, x, i, lane, lds);
   if (!sorted) {
-    load_keys<E>(row, i, lane, x);
 #pragma unroll
     for (int r = 0; r < E; ++r) x[r] = ordered(x[r]);
     bitonic_sort<E>(x, lane);
@@ -442,7 +454,11 @@ __device__ __forceinline__ void coverage_rows_regs_body(const float* __restrict_
   float acc[E];
 #pragma unroll
   for (int r = 0; r < E; ++r) acc[r] = 0.f;
-  for (int hs = hs0 + wave; hs < hs1; hs += 4) coverage_row_regs<E>(scores_s + ((int64_t)hs * n + i) * n, i, lane, lds + wave * LDS, acc);
+  // Once the histogram has failed for a head, it is not tried for the heads after it: what ties or far-off values these scores have, the others'
+  // are likely to have too (131072 tokens, 32 heads, 40 different values: 404 us where every head tries it and then loads its keys again, so 372 - 379,
+  // 371 with the network alone; all keys equal 382, 366 - 371 and 371).
+  bool spread = true;
+  for (int hs = hs0 + wave; hs < hs1; hs += 4) coverage_row_regs<E>(scores_s + ((int64_t)hs * n + i) * n, i, lane, lds + wave * LDS, spread, acc);
   float* const part = (float*)lds;
 #pragma unroll
   for (int r = 0; r < E; ++r) part[wave * LDS + lane * E + r] = acc[r];

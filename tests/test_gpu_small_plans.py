@@ -107,6 +107,17 @@ def test_coverage_sorted_by_a_histogram(kind, n):
     check_curves(sc)
 
 
+@pytest.mark.parametrize("Hs", [11, 40])
+def test_coverage_of_heads_that_differ(Hs):
+    """Groups of three and ten heads, of which a wavefront sorts up to three in turn: rows that the histogram
+    sorts and rows that it leaves to the network, in any order, on the same LDS."""
+    rng, n = np.random.default_rng(6), 300
+    sc = rng.normal(size=(Hs, n, n)).astype(np.float32)
+    tied = rng.random((Hs, n)) < 0.3
+    sc[tied] = np.round(sc[tied])
+    check_curves(sc)
+
+
 def test_coverage_of_rows_without_a_softmax():
     """One row with +infinity and one without a finite key, each left to the network: NaN for the budgets that they count for (up to
     their 271 and 281 blocks), as the definition gives it, and nothing else is touched."""
