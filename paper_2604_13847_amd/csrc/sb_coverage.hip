@@ -17,6 +17,7 @@
 //                           blocks, then C_s(k) = (Hs*k + sum_{i>=k} Pacc[s][i][k-2]) / (Hs*n) (the k rows i < k are fully covered)
 #include <math.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -450,7 +451,7 @@ __device__ __forceinline__ void coverage_row_regs(const float* __restrict__ row,
 template <int E, int LDS>
 __device__ __forceinline__ void coverage_rows_regs_body(const float* __restrict__ scores_s, int n, int i, int hs0, int hs1, int* lds,
                                                float* __restrict__ out) {
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, waves = (int)blockDim.x >> 6;
   float acc[E];
 #pragma unroll
   for (int r = 0; r < E; ++r) acc[r] = 0.f;
@@ -458,13 +459,16 @@ __device__ __forceinline__ void coverage_rows_regs_body(const float* __restrict_
   // are likely to have too (131072 tokens, 32 heads, 40 different values: 404 us where every head tries it and then loads its keys again, so 372 - 379,
   // 371 with the network alone; all keys equal 382, 366 - 371 and 371).
   bool spread = true;
-  for (int hs = hs0 + wave; hs < hs1; hs += 4) coverage_row_regs<E>(scores_s + ((int64_t)hs * n + i) * n, i, lane, lds + wave * LDS, spread, acc);
+  for (int hs = hs0 + wave; hs < hs1; hs += waves) coverage_row_regs<E>(scores_s + ((int64_t)hs * n + i) * n, i, lane, lds + wave * LDS, spread, acc);
   float* const part = (float*)lds;
 #pragma unroll
   for (int r = 0; r < E; ++r) part[wave * LDS + lane * E + r] = acc[r];
   __syncthreads();
-  for (int p = tid; p < i; p += 256)
-    out[p] = ((part[p] + part[LDS + p]) + part[2 * LDS + p]) + part[3 * LDS + p];
+  for (int p = tid; p < i; p += (int)blockDim.x) {
+    float sum = part[p];
+    for (int w = 1; w < waves; ++w) sum += part[w * LDS + p];
+    out[p] = sum;
+  }
 }
 
 template <int MAXE>
@@ -472,7 +476,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAXE == 32 
     const float* __restrict__ scores, GeomArgs ga, int Hs, int64_t slab, int32_t* qb_off, int64_t* sc_off, int32_t* qb_seq,
     float* __restrict__ pacc) {
   constexpr int LDS = cov_lds<MAXE>;  // words of a wavefront
-  __shared__ __attribute__((aligned(16))) int part[4 * LDS];
+  extern __shared__ __attribute__((aligned(16))) int part[];
   const int qb = blockIdx.x;
   const BatchGeom bg(ga);
   const int s = bg.seq_of(qb);
@@ -636,8 +640,13 @@ int sb_score_coverage(const sb_problem* p, const float* scores, float* coverage_
   KernelTimer kt(K_COVERAGE, st);
   const int groups = coverage_groups(g);
   const int64_t slab = (int64_t)coverage_slab(g);
-  hipLaunchKernelGGL(g.n_max <= 1025 ? coverage_rows_regs_kernel<16> : coverage_rows_regs_kernel<32>, dim3((unsigned)g.NQB, (unsigned)groups), dim3(256), 0, st, scores,
-                     make_geom_args(g, p, t), g.Hs, slab, (int32_t*)t.qb_off, (int64_t*)t.sc_off, (int32_t*)t.qb_seq, pacc);
+  // A wavefront per head of a group, four at most: one without a head would hold registers and LDS until the others are done (131072 tokens, 4
+  // heads, which are groups of one: 118 -> 63 us, keys of 40 values 155 -> 90, with the network alone 127; 8 heads 128 -> 93).
+  const int waves = std::min(4, (g.Hs + groups - 1) / groups);
+  const bool short_rows = g.n_max <= 1025;
+  hipLaunchKernelGGL(short_rows ? coverage_rows_regs_kernel<16> : coverage_rows_regs_kernel<32>, dim3((unsigned)g.NQB, (unsigned)groups), dim3(64 * waves),
+                     sizeof(int) * waves * (short_rows ? cov_lds<16> : cov_lds<32>), st, scores, make_geom_args(g, p, t), g.Hs, slab,
+                     (int32_t*)t.qb_off, (int64_t*)t.sc_off, (int32_t*)t.qb_seq, pacc);
   SB_LAUNCH_CHECK("coverage_rows_regs_kernel");
   if (g.n_max > kCovRegMax + 1) {  // rows with more than kCovRegMax candidates
     hipLaunchKernelGGL(coverage_rows_kernel, dim3((unsigned)g.NQB, (unsigned)groups), dim3(256), smem, st, scores, t.qb_off, t.sc_off,

@@ -107,9 +107,9 @@ def test_coverage_sorted_by_a_histogram(kind, n):
     check_curves(sc)
 
 
-@pytest.mark.parametrize("Hs", [11, 40])
+@pytest.mark.parametrize("Hs", [1, 3, 5, 11, 40])
 def test_coverage_of_heads_that_differ(Hs):
-    """Groups of three and ten heads, of which a wavefront sorts up to three in turn: rows that the histogram
+    """Groups of one to ten heads, of which a wavefront sorts up to three in turn (of 5, the last group has none): rows that the histogram
     sorts and rows that it leaves to the network, in any order, on the same LDS."""
     rng, n = np.random.default_rng(6), 300
     sc = rng.normal(size=(Hs, n, n)).astype(np.float32)
