@@ -648,7 +648,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64
   __shared__ __attribute__((aligned(1024))) char ring[NW][kDqRing<D>];
   BusyTimer timer;
   timer.start(P);
-  for_items<D, NW, LOOP>(P, heads, (int*)&ring[NW - 1][kDqRing<D> - 4],
+  for_items<D, NW, LOOP, !LOOP>(P, heads, (int*)&ring[NW - 1][kDqRing<D> - 4],
                 [&](const AttnParams& p, const WorkItem& item, int hh) __attribute__((always_inline)) { dq_head_item<D, OUT_F32, NW, LOOP>(p, item, hh, ring); });
   timer.stop(P);
 }
@@ -1264,14 +1264,14 @@ static int launch_bwd(const Geo& g, const AttnParams& P, hipStream_t st) {
   } else {
     if (head_ids(P.n_items, heads) > 0x7fffffffll) { set_error("too many work items for one launch"); return SB_ERR_INVALID_ARG; }
     const bool one = one_wavefront_per_item(g, items, 24);
-    const dim3 grid((unsigned)head_grid(P, heads, D, one ? 1 : 2));
+    const dim3 grid((unsigned)head_grid(P, heads, one ? 1 : 2));
     auto launch = [&](auto nw, auto loop) {
       constexpr int NW = decltype(nw)::value;
       hipLaunchKernelGGL((attn_bwd_dq_head_kernel<D, F32, NW, decltype(loop)::value>), grid, dim3(64 * NW), 0, st, P, heads);
     };
     auto with_loop = [&](auto nw) {
       if constexpr (D == 128) {
-        if (head_loop(P, D)) return launch(nw, std::true_type());
+        if (P.deal == kDealDraw) return launch(nw, std::true_type());
       }
       launch(nw, std::false_type());
     };
@@ -1366,10 +1366,11 @@ extern "C" int sb_sparse_attn_bwd(const sb_problem* p, const void* q, const void
   P.n_items = (int)n_items;
   P.ticket = nullptr;
   AttnParams Pq = P;
-  if (use_head_tickets(n_items, heads)) {
+  Pq.deal = dq_deal(g, n_items, heads);
+  if (Pq.deal != kDealPosition) {
     Pq.ticket = (int*)(wb + wo.ticket);
     // (the sub-parts of small problems are dealt by position)
-    if (P.sub_slots == 0 && use_key_tickets((int64_t)g.Hkv * (g.NQB + split_extra_max(g)))) P.ticket = Pq.ticket + kTicketInts;
+    if (P.sub_slots == 0 && use_key_tickets(g, (int64_t)g.Hkv * (g.NQB + split_extra_max(g)))) P.ticket = Pq.ticket + kTicketInts;
     if ((rc = fill_zero(Pq.ticket, sizeof(int32_t) * kTicketInts * 2, st)) != SB_OK) return rc;
   }
   if (g.D == 128) {

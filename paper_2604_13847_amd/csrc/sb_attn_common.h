@@ -40,6 +40,7 @@ struct AttnParams {
   // Work distribution (see draw_item)
   int* ticket;        // 8 counters, zero at launch (the group kernel: 8 per head plane); null: every item is taken by position
   int n_items;        // query-major items
+  int deal;           // Deal, of a launch of one query head per item
 };
 // float -> bf16 copies of one launch
 struct Conversions {
@@ -52,13 +53,21 @@ int convert_f32_to_bf16(const Conversions& c, hipStream_t st);
 // Which item does a workgroup work on?
 // Workgroup ids are dealt to the 8 XCDs in turn, so every XCD gets the same number of workgroups whatever its pace, and the XCDs do
 // differ by several percent (the L2 hit rate depends on which heads an XCD serves, and the dies themselves differ): a launch that ties
-// every item to a position ends when the slowest XCD is through its share.  So only the list's first part, the heavier items, is tied to positions
-// (*_lead).  Of the rest every eighth item is an XCD's, as if it were dealt by position, but handed out in list order by that XCD's
-// own counter, and an XCD that is through its items takes the next one of the XCD that has most left.  An item so stays on the XCD whose
-// L2 holds its head unless it is one of the launch's last, and those are the lightest.  (One counter for all, which gives that up, for one
-// item in sixteen, against this: one 131072-token sequence, top 32: forward 6.20 -> 5.75 ms, dQ 6.39 -> 6.18.  dK/dV without any, against
-// this: that sequence 10.4 -> 10.15 ms, 65536 tokens with 28/4 heads 7.3 -> 6.9, with a sink 3.47 -> 3.28, the 262144-token batch 34.2 -> 33.3.)
+// every item to a position ends when the slowest XCD is through its share.  Two ways round that (sb_internal.h has the lines between them):
+// - One item in sixteen, the last 8 of every 128 in list order, is held back: the other items are tied to the leading positions and the
+//   held-back ones handed out by one counter at the end, to whichever workgroup asks first, in twice as many workgroups (held_*).
+// - Only the list's first part, the heavier items, is tied to positions (*_lead).  Of the rest every eighth item is an XCD's, as if it
+//   were dealt by position, but handed out in list order by that XCD's own counter, and an XCD that is through its items takes the next one of the
+//   XCD that has most left (draw_item).  An item so stays on the XCD whose L2 holds its head unless it is one of the launch's last, and those
+//   are the lightest.
+// (The first against the second: one 131072-token sequence, top 32: forward 6.20 -> 5.75 ms, dQ 6.39 -> 6.18.  dK/dV without any, against
+// the second: that sequence 10.4 -> 10.15 ms, 65536 tokens with 28/4 heads 7.3 -> 6.9, with a sink 3.47 -> 3.28, the 262144-token batch 34.2 -> 33.3.)
 // Which workgroup computes an item never changes its result.
+__device__ inline int held_lead(int pos, int held) { return pos < 15 * held ? (pos / 120 << 7) + pos % 120 : pos + held; }  // item of a leading position
+__device__ inline int held_item(int held, int* counter) {  // the next one that was held back, or -1; by one thread
+  const int t = atomicAdd(counter, 1);
+  return t < held ? (t >> 3 << 7) + 120 + (t & 7) : -1;
+}
 // draw_item: an index from `lead` on, or -1 if all have been drawn; by one thread.
 __device__ inline int draw_item(int xcd, int lead, int n, int* counters) {
   for (int tries = 0; tries < 9; ++tries) {
@@ -74,13 +83,14 @@ __device__ inline int draw_item(int xcd, int lead, int n, int* counters) {
   }
   return -1;
 }
-// The item of the workgroup at position `pos`, or -1; every thread of the workgroup must call it (it has a barrier).
-__device__ inline int claim_item(int pos, int n_items, int* counters) {
-  if (!counters) return pos < n_items ? pos : -1;
-  const int lead = query_lead(n_items);
-  if (pos < lead) return pos;
+// The item of the workgroup at position `pos` of a launch that holds one in sixteen back (or, without a counter, of any), or -1; every
+// thread of the workgroup must call it (it has a barrier).
+__device__ inline int claim_item(int pos, int n_items, int* counter) {
+  if (!counter) return pos < n_items ? pos : -1;
+  const int held = (int)held_items(n_items);
+  if (pos < n_items - held) return held_lead(pos, held);
   __shared__ int sh_claim;
-  if (threadIdx.x == 0) sh_claim = draw_item(pos & 7, lead, n_items, counters);
+  if (threadIdx.x == 0) sh_claim = held_item(held, counter);
   __syncthreads();
   return __builtin_amdgcn_readfirstlane(sh_claim);
 }
@@ -95,13 +105,9 @@ __device__ inline WorkItem uniform_item(const WorkItem* items, int pos) {
 // The items of a query-major launch of one query head each: id -> (position in the work list, query head of the group).  In per-KV-group
 // mode the `heads` query heads of an item have ids that are 8 apart, so they run on the same XCD (workgroup ids are dealt to the XCDs in
 // turn) and share its L2.
-inline __host__ __device__ int64_t head_ids(int64_t n_items, int heads) { return (n_items + 7) / 8 * 8 * heads; }
-inline bool use_head_tickets(int64_t n_items, int heads) { return use_tickets(n_items) && head_ids(n_items, heads) < (1ll << 30); }
-inline bool head_loop(const AttnParams& P, int D) { return P.ticket && D == 128; }
-inline int64_t head_grid(const AttnParams& P, int heads, int D, int nw) {
+inline int64_t head_grid(const AttnParams& P, int heads, int nw) {
   const int64_t ids = head_ids(P.n_items, heads);
-  if (!P.ticket) return ids;
-  return head_loop(P, D) ? 1024 / nw : ticketed_grid(ids, true);
+  return P.deal == kDealDraw ? 1024 / nw : P.deal == kDealLast ? last_grid(ids) : P.deal == kDealHeld ? held_grid(ids) : ids;
 }
 // The items of one workgroup.  A launch without tickets: workgroup w takes item w.  With tickets at D = 128, where a wavefront fills its
 // SIMD: as many workgroups as the chip runs at a time, which draw one item after the other.  At D = 64 workgroups take one item each, the
@@ -112,17 +118,21 @@ inline int64_t head_grid(const AttnParams& P, int heads, int D, int nw) {
 // LOOP: the launch draws item after item.  A kernel of its own, because the loop costs a launch without tickets up to 1.4 us (2039 tokens,
 // 16/2 heads: forward 22.0 -> 20.7 us).
 // `sh` is an LDS word for launches of two wavefronts per item, which only wavefronts other than the first write otherwise.
-template <int D, int NW, bool LOOP>
+// HELD: the launch may hold one item in 16 back.
+template <int D, int NW, bool LOOP, bool HELD>
 struct ItemQueue {
-  static constexpr bool kDraw = LOOP || D != 128;  // a launch at D = 128 that does not loop has no tickets
   WorkItem item;
   int hh;  // query head of the group
   int id, ids, lead, heads;
   __device__ inline int pos_of(int id) const { return id / (8 * heads) * 8 + (id & 7); }
+  __device__ inline int drawn(const AttnParams& P) const {
+    if (HELD && P.deal == kDealHeld) return held_item((int)held_items(ids), P.ticket);
+    return draw_item(blockIdx.x & 7, lead, ids, P.ticket);
+  }
   __device__ inline void draw(const AttnParams& P, int* sh) {
     int t = 0;
     if (threadIdx.x == 0) {
-      do t = draw_item(blockIdx.x & 7, lead, ids, P.ticket);
+      do t = drawn(P);
       while (t >= 0 && pos_of(t) >= P.n_items);  // (the last ids may have no item)
       if (NW == 2) *sh = t;
     }
@@ -140,10 +150,16 @@ struct ItemQueue {
   __device__ inline void first(const AttnParams& P, int heads_, int* sh) {
     heads = heads_;
     ids = (int)head_ids(P.n_items, heads);
-    lead = LOOP ? (int)gridDim.x : kDraw && P.ticket ? query_lead(ids) : ids;
     id = (int)blockIdx.x;
-    if (kDraw && id >= lead) draw(P, sh);
-    else if (pos_of(id) >= P.n_items) id = -1;
+    lead = LOOP ? (int)gridDim.x : ids;
+    if (D == 64 && P.deal == kDealLast) lead = query_lead(ids);
+    if (HELD && P.deal == kDealHeld) lead = ids - (int)held_items(ids);
+    if ((LOOP || D == 64 || HELD) && id >= lead) {
+      draw(P, sh);
+    } else {
+      if (HELD && P.deal == kDealHeld) id = held_lead(id, (int)held_items(ids));
+      if (pos_of(id) >= P.n_items) id = -1;
+    }
     descriptor(P);
   }
   __device__ inline void next(const AttnParams& P, int* sh) {
@@ -164,9 +180,9 @@ __device__ inline AttnParams reloaded_params() {  // the kernel's first argument
   asm volatile("" : "+s"(p));
   return *(const AttnParams*)p;
 }
-template <int D, int NW, bool LOOP, typename F>
+template <int D, int NW, bool LOOP, bool HELD, typename F>
 __device__ __attribute__((always_inline)) inline void for_items(const AttnParams& P, int heads, int* sh, F work) {
-  ItemQueue<D, NW, LOOP> queue;
+  ItemQueue<D, NW, LOOP, HELD> queue;
   queue.first(P, heads, sh);
   if constexpr (LOOP) {
     for (; queue.id >= 0; queue.next(P, sh)) work(reloaded_params(), queue.item, queue.hh);

@@ -404,7 +404,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D == 64
   __shared__ __attribute__((aligned(1024))) char ring[NW][kFwdRing<D>];
   BusyTimer timer;
   timer.start(P);
-  for_items<D, NW, LOOP>(P, heads, (int*)&ring[NW - 1][kFwdRing<D> - 4],
+  for_items<D, NW, LOOP, false>(P, heads, (int*)&ring[NW - 1][kFwdRing<D> - 4],
                 [&](const AttnParams& p, const WorkItem& item, int hh) __attribute__((always_inline)) { fwd_head_item<D, OUT_F32, NW, LOOP>(p, item, hh, ring); });
   timer.stop(P);
 }
@@ -652,14 +652,14 @@ int convert_f32_to_bf16(const Conversions& c, hipStream_t st) {
 template <int D>
 static void launch_fwd_head(const Geo& g, const AttnParams& P, hipStream_t st, int heads) {
   const bool one = one_wavefront_per_item(g, (int64_t)g.Hq * g.NQB, D == 64 ? 24 : 16);
-  const dim3 grid((unsigned)head_grid(P, heads, D, one ? 1 : 2));
+  const dim3 grid((unsigned)head_grid(P, heads, one ? 1 : 2));
   auto launch = [&](auto f32, auto nw, auto loop) {
     constexpr int NW = decltype(nw)::value;
     hipLaunchKernelGGL((attn_fwd_head_kernel<D, decltype(f32)::value, NW, decltype(loop)::value>), grid, dim3(64 * NW), 0, st, P, heads);
   };
   auto with_loop = [&](auto f32, auto nw) {
     if constexpr (D == 128) {
-      if (head_loop(P, D)) return launch(f32, nw, std::true_type());
+      if (P.deal == kDealDraw) return launch(f32, nw, std::true_type());
     }
     launch(f32, nw, std::false_type());
   };
@@ -717,7 +717,8 @@ extern "C" int sb_sparse_attn_fwd(const sb_problem* p, const void* q, const void
   const int parts = (heads + 3) / 4, hpp = (heads + parts - 1) / parts;  // the group kernel takes `hpp` heads per workgroup
   P.n_items = (int)n_items; P.ticket = nullptr;
   const bool group = g.D == 128 && hpp >= 3 && parts * hpp == heads;
-  const bool tickets = group ? use_tickets(n_items) && parts <= kTicketPlanes : use_head_tickets(n_items, heads);
+  P.deal = group ? kDealPosition : forward_deal(g, n_items, heads);
+  const bool tickets = group ? use_tickets(n_items) && parts <= kTicketPlanes : P.deal != kDealPosition;
   KernelTimer kt(K_FWD, st);
   if (tickets) {
     P.ticket = (int*)(wb + wo.ticket);
@@ -727,7 +728,7 @@ extern "C" int sb_sparse_attn_fwd(const sb_problem* p, const void* q, const void
   // 4.58 against 4.69 ms, 262144 tokens 15.8 against 16.0; the 32768-token batch 1.78 against 1.76), but not with a head slot left idle,
   // and not at D = 64 (65536 tokens, 14/2 heads, blocks of 256: 1.49 against 1.37).
   if (group) {
-    dim3 grid((unsigned)ticketed_grid(n_items, tickets), (unsigned)parts), block(128 * hpp);
+    dim3 grid((unsigned)(tickets ? held_grid(n_items) : (n_items + 7) / 8 * 8), (unsigned)parts), block(128 * hpp);
     if (P.out_f32) hipLaunchKernelGGL((attn_fwd_group_kernel<true>), grid, block, 0, st, P, heads);
     else hipLaunchKernelGGL((attn_fwd_group_kernel<false>), grid, block, 0, st, P, heads);
   } else {

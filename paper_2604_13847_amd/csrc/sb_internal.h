@@ -214,7 +214,7 @@ struct WsOffsets {
 };
 WsOffsets fwd_ws_offsets(const Geo& g);
 WsOffsets bwd_ws_offsets(const Geo& g);
-// Launches whose list is handed out by ticket (see draw_item and ItemQueue in sb_attn_common.h): its first *_lead items are tied to workgroups,
+// Launches whose list is handed out by ticket (see sb_attn_common.h): its first *_lead items are tied to workgroups,
 // and there are more workgroups than items, for XCDs that draw more than their share.  Where the lines lie: what is drawn must be
 // enough to even out what the XCDs' paces differ by (up to 10 %).  Key-major items are columns, few and heavy: half of them; an
 // eighth or a quarter of the list by ticket is 4 and 1 % slower (65536 tokens, 28/4 heads: 7.26 and 7.08 ms against 6.97), three quarters and
@@ -225,10 +225,14 @@ constexpr int kTicketPlanes = 16;          // of 8 counters, which are cache lin
 constexpr int kTicketPitch = 64, kTicketInts = 8 * kTicketPitch;
 inline bool use_tickets(int64_t n) { return n >= kTicketMinItems; }
 inline __host__ __device__ int query_lead(int n) { return n / 32 * 24; }
-inline int64_t ticketed_grid(int64_t n, bool tickets) { return (n + (tickets ? n / 64 : 0) + 7) / 8 * 8; }
+inline __host__ __device__ int64_t held_items(int64_t n) { return n >> 7 << 3; }
+inline int64_t held_grid(int64_t n) { return (n + held_items(n) + 7) / 8 * 8; }
+inline int64_t last_grid(int64_t n) { return (n + n / 64 + 7) / 8 * 8; }
 inline __host__ __device__ int key_lead(int n) { return n / 16 * 8; }
 inline __host__ __device__ int64_t key_extra(int64_t n) { return n / 8; }
-inline bool use_key_tickets(int64_t n) { return use_tickets(n) && n + key_extra(n) < (1ll << 24); }  // (a launch has fewer than 2^32 threads)
+inline bool use_key_tickets(const Geo& tg, int64_t n) {
+  return use_tickets(n) && n + key_extra(n) < (1ll << 24);  // (a launch has fewer than 2^32 threads)
+}
 // Is a query-major item of one query head one wavefront's work, or two's?  Of `items` with at most `most` tiles, w wavefronts each, the
 // chip works on 1024 / w at a time (head_dim 64: twice as many); an item costs about `fixed` tile times of two wavefronts besides its
 // tiles (where the chip is not full and its clock is high: forward 16, dQ and head_dim 64 24), and the launch takes as long as its share
@@ -253,6 +257,36 @@ inline bool one_wavefront_per_item(const Geo& tg, int64_t items, int fixed) {
     return t;
   };
   return time(1) <= time(2);
+}
+// How the items of a query-major launch of one query head each are handed out (see ItemQueue in sb_attn_common.h): all by position, one in
+// sixteen held back, the last quarter drawn, or drawn one after the other by as many workgroups as the chip runs at a time (head_dim 128).
+// Draws keep an item near its head's L2 and end the launch evenly, but each is an atomic across the chip, 1 - 2 us of its workgroup, which
+// rows of a few tiles do not earn back unless there are many of them.  In us, alone, 32/8 heads, one sequence:
+//   forward, D = 128  position / drawn:  9024 items of 1, 4, 16, 32 tiles 105 / 123, 165 / 177, 351 / 355, 596 / 588; 20000 items of 1, 8, 16, 32 tiles 206 / 218,
+//                     525 / 524, 819 / 803, 1367 / 1360; 65536 items of 1, 2, 8 tiles 611 / 612, 805 / 797, 2071 / 1960; 16384 of 8 (8/8 heads) 557 / 537
+//   forward, D = 64   position / last:   9024 items of 1, 4, 16, 32 tiles 44 / 51, 72 / 77, 184 / 190, 334 / 330; 65536 items of 1, 4, 16, 32 tiles 284 / 311, 596 / 612,
+//                     1780 / 1693, 3175 / 3026; 20000 of 8 266 / 277, 16384 (8/8 heads) 279 / 272
+//   dQ, D = 128       held / drawn:      9024 items of 1, 4, 16, 32 tiles 169 / 180, 212 / 219, 447 / 452, 772 / 752; 20000 of 2 402 / 382
+//   dQ, D = 64        held / last:       9024 items of 1, 4, 16, 32 tiles 81 / 85, 97 / 103, 227 / 233, 428 / 418; 65536 items of 1, 4, 8 tiles 552 / 600, 769 / 779, 1226 / 1202
+// (dQ by position: 180, 232, 472 and 795; 85, 102, 242 and 433.)  What is held back are items of every weight: where the longest is not small
+// against a workgroup's share of all, they are the launch's end (head_dim 64, 7600 items of 1 - 21 tiles, 44 a workgroup: dQ 184 / 161; 6208 of 1 - 16,
+// 23 a workgroup: 106 / 96).
+enum Deal { kDealPosition, kDealHeld, kDealLast, kDealDraw };
+inline __host__ __device__ int64_t head_ids(int64_t n_items, int heads) { return (n_items + 7) / 8 * 8 * heads; }
+inline bool may_deal(int64_t n_items, int heads) { return use_tickets(n_items) && head_ids(n_items, heads) < (1ll << 30); }
+inline bool rows_of(const Geo& tg, int64_t tiles) { return tg.nnz_unit >= tiles * tg.NQB; }  // mean
+inline Deal forward_deal(const Geo& tg, int64_t n_items, int heads) {
+  if (!may_deal(n_items, heads)) return kDealPosition;
+  const int64_t items = (int64_t)tg.Hq * tg.NQB;
+  if (tg.D == 128) return rows_of(tg, 15) || (rows_of(tg, 7) && items >= 16384) || items >= 32768 ? kDealDraw : kDealPosition;
+  return rows_of(tg, 24) || (rows_of(tg, 12) && items >= 16384) ? kDealLast : kDealPosition;
+}
+inline Deal dq_deal(const Geo& tg, int64_t n_items, int heads) {
+  if (!may_deal(n_items, heads)) return kDealPosition;
+  const int64_t items = (int64_t)tg.Hq * tg.NQB;
+  const bool even = (int64_t)tg.rowT_max * (tg.D == 64 ? 3 * 2048 : 2 * 1024) <= tg.nnz_unit * tg.Hq;
+  if (tg.D == 128) return rows_of(tg, 24) || items >= 16384 || !even ? kDealDraw : kDealHeld;
+  return rows_of(tg, 24) || (rows_of(tg, 7) && items >= 32768) || !even ? kDealLast : kDealHeld;
 }
 size_t scores_ws_bytes(const Geo& g);
 size_t coverage_ws_bytes(const Geo& g);

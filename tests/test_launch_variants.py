@@ -8,6 +8,7 @@ import sys
 
 import pytest
 
+import test_gpu_deals as deals
 import test_gpu_head_rows as rows
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -24,22 +25,32 @@ pb.c.cu_seqlens_dev = pb.c.topk_dev = 4096
 b, lib, p = C.c_void_p(4096), sb.lib(), pb.ref()
 sb._check(lib.sb_sparse_attn_fwd(p, b, b, b, b, b, b, b, b, b, None))
 sb._check(lib.sb_sparse_attn_bwd(p, b, b, b, b, b, b, b, b, b, b, b, b, b, None))
-for i in range(shim.recorded_launches(np.zeros((256, 6), dtype=np.uint32).ctypes.data_as(C.c_void_p))):
-    print("kernel", shim.recorded_kernel(i).decode())
+out = np.zeros((256, 6), dtype=np.uint32)
+for i in range(shim.recorded_launches(out.ctypes.data_as(C.c_void_p))):
+    print("kernel", shim.recorded_kernel(i).decode(), out[i][0])
 """
 
 
 @pytest.fixture(scope="module")
-def query_major(tmp_path_factory):
-    """(lens, topk, mode, Hq, Hkv, D) -> wavefronts per item of the forward and of dQ (4: the kernel for few items) and whether items
-    are handed out by ticket."""
+def launches(tmp_path_factory):
+    """(lens, topk, mode, Hq, Hkv, D) -> [(kernel, workgroups)] of a forward and a backward"""
     shim = str(tmp_path_factory.mktemp("launch") / "record_launches.so")
     subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", shim, os.path.join(ROOT, "tests", "launch", "record_launches.c")], check=True)
 
     def of(*problem):
         r = subprocess.run([sys.executable, "-c", CALLS, shim, json.dumps(problem)], cwd=ROOT, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
         assert r.returncode == 0, r.stdout[-3000:]
-        names = [l.split()[1] for l in r.stdout.splitlines() if l.startswith("kernel ")]
+        return [(l.split()[1], int(l.split()[2])) for l in r.stdout.splitlines() if l.startswith("kernel ")]
+
+    return of
+
+
+@pytest.fixture(scope="module")
+def query_major(launches):
+    """(lens, topk, mode, Hq, Hkv, D) -> wavefronts per item of the forward and of dQ (4: the kernel for few items) and whether items
+    are handed out by ticket."""
+    def of(*problem):
+        names = [name for name, _ in launches(*problem)]
         fwd = [m[1] for n in names if (m := re.search(r"attn_fwd_head_kernelILi\d+ELb[01]ELi(\d)E", n))]
         dq = [m[1] for n in names if (m := re.search(r"attn_bwd_dq_head_kernelILi\d+ELb[01]ELi(\d)E", n))] + ["4" for n in names if "attn_bwd_dq_kernel" in n]
         assert len(fwd) == len(dq) == 1, names
@@ -73,3 +84,28 @@ def test_tickets_of_two_wavefronts(query_major, D):
 @pytest.mark.parametrize("lens,topk", [((64 * 300, 64 * 250 + 5), (3, 4)), ((64 * 80,) + (64 * 4,) * 120, (75,) + (2,) * 120)])
 def test_tickets_of_one_wavefront(query_major, lens, topk):
     assert query_major(lens, topk, 0, 8, 2, 128) == (1, 1, True)
+
+
+@pytest.mark.parametrize("shape,forward,dq,columns", deals.SHAPES)
+def test_how_items_are_handed_out(launches, shape, forward, dq, columns):
+    mode, Hq, Hkv, D, blocks, budget = shape
+    heads = 1 if mode == 0 else Hq // Hkv
+    items = blocks * (Hq if mode == 0 else Hkv)
+    ids = (items + 7) // 8 * 8 * heads
+    of_grid = {(ids + 7) // 8 * 8: "position", (ids + ids // 128 * 8 + 7) // 8 * 8: "held", (ids + ids // 64 + 7) // 8 * 8: "last"}
+    made = launches((64 * blocks - 59,), (budget,), mode, Hq, Hkv, D)
+    forms = {}
+    for name, workgroups in made:
+        m = re.search(r"attn_(fwd|bwd_dq)_head_kernelILi\d+ELb0ELi(\d)ELb([01])E", name)
+        if m:
+            forms[m[1]] = "draw" if m[3] == "1" else of_grid[workgroups]
+            assert m[3] == "0" or workgroups == 1024 // int(m[2])
+        elif "attn_fwd_group" in name:
+            forms["fwd"] = "group"
+            assert workgroups == (items + items // 128 * 8 + 7) // 8 * 8
+        elif "attn_bwd_dkv_kernel" in name:
+            column_workgroups = workgroups
+        elif "attn_bwd_dkv_reduce" in name:  # one workgroup for every part that a column may be cut into beyond its first
+            n = Hkv * (blocks + workgroups)
+            forms["columns"] = {n: False, n + n // 8: True}[column_workgroups]
+    assert (forms["fwd"], forms["bwd_dq"], forms["columns"]) == (forward, dq, columns)
