@@ -218,7 +218,8 @@ WsOffsets bwd_ws_offsets(const Geo& g);
 // and there are more workgroups than items, for XCDs that draw more than their share.  Where the lines lie: what is drawn must be
 // enough to even out what the XCDs' paces differ by (up to 10 %).  Key-major items are columns, few and heavy: half of them; an
 // eighth or a quarter of the list by ticket is 4 and 1 % slower (65536 tokens, 28/4 heads: 7.26 and 7.08 ms against 6.97), three quarters and
-// all of it equal or slower.  Query-major launches that do not draw item after item: a quarter, where a draw (1 us, or 5 for a
+// all of it equal or slower; and none where head_dim 64 makes columns light (by position / drawn, 32/8 heads: columns of 4 tiles 126 / 133 us, 16
+// 908 / 932, 64 2.67 / 2.67 ms; 8 tiles, 8/8 heads 207 / 219 us).  Query-major launches that do not draw item after item: a quarter, where a draw (1 us, or 5 for a
 // workgroup that finds nothing left) is to a workgroup's 20 us and more.
 constexpr int64_t kTicketMinItems = 4096;  // shorter lists are dealt by position only
 constexpr int kTicketPlanes = 16;          // of 8 counters, which are cache lines apart (in one line 8 XCDs' draws waited for each other: 15 us each)
@@ -231,7 +232,7 @@ inline int64_t last_grid(int64_t n) { return (n + n / 64 + 7) / 8 * 8; }
 inline __host__ __device__ int key_lead(int n) { return n / 16 * 8; }
 inline __host__ __device__ int64_t key_extra(int64_t n) { return n / 8; }
 inline bool use_key_tickets(const Geo& tg, int64_t n) {
-  return use_tickets(n) && n + key_extra(n) < (1ll << 24);  // (a launch has fewer than 2^32 threads)
+  return use_tickets(n) && n + key_extra(n) < (1ll << 24) && (tg.D == 128 || bwd_total_tiles(tg) >= 32 * (int64_t)tg.Hkv * tg.NQB);  // (a launch has fewer than 2^32 threads)
 }
 // Is a query-major item of one query head one wavefront's work, or two's?  Of `items` with at most `most` tiles, w wavefronts each, the
 // chip works on 1024 / w at a time (head_dim 64: twice as many); an item costs about `fixed` tile times of two wavefronts besides its
