@@ -15,7 +15,7 @@ SHAPES = [
     ((0, 8, 8, 128, 531, 2), "position", "held", True), ((0, 8, 8, 128, 531, 16), "draw", "held", True), ((0, 8, 8, 128, 531, 26), "draw", "draw", True),
     ((0, 16, 16, 64, 531, 4), "position", "held", False), ((0, 8, 8, 64, 531, 34), "last", "last", True),
     # seven query heads of a KV head: ids in groups of 56, with none for some of the last
-    ((1, 63, 9, 64, 467, 3), "position", "held", False), ((1, 63, 9, 64, 467, 8), "last", "held", True), ((1, 63, 9, 128, 467, 2), "position", "draw", True),
+    ((1, 63, 9, 64, 467, 3), "position", "held", False), ((1, 63, 9, 64, 467, 13), "last", "held", True), ((1, 63, 9, 128, 467, 2), "position", "draw", True),
     # heads that share a workgroup, in one plane and in two
     ((1, 36, 9, 128, 467, 3), "group", "draw", True), ((1, 72, 9, 128, 467, 2), "group", "draw", True),
 ]
