@@ -39,12 +39,14 @@ struct PlanArgs {
 // Plans of few tiles are all launches: geometry and fills, lists, order, 3 - 5 us each.  Up to kLaneSeqs sequences every workgroup of the
 // second can work the tables out for itself, and up to kTwoMaxTiles tiles one workgroup per KV head counts its columns from the bitmap, so
 // that nothing has to be cleared for the counting: 4.2 us less for the first launch, 1.3 more for the last (2039 tokens, 16/2 heads), a
-// step of 1024 tokens on one head 58.6 -> 56.2 us.  Larger plans keep the three: there the counting would be serial work of a few workgroups.
+// step of 1024 tokens on one head 58.6 -> 56.2 us.  What it counts grows with the square of a sequence: three launches / two, one sequence of 128 tiles on
+// 8 heads a KV head (4096 words) 15.7 / 15.5 us, 256 tiles on 2 (4096) 16.1 / 16.2, 192 on 4 (4608) 15.5 / 16.0, 384 on one (4608) 16.2 / 17.3, 192 on 8
+// (9216) 15.9 / 18.0, 512 on 4 (32768) 17.6 / 28.5; 256 tiles in 48 short sequences on 8 (2100) 22.7 / 18.5.
 constexpr int64_t kTwoMaxTiles = 512;
-constexpr int64_t kTwoMaxWords = 64;  // bitmap words of a column, over the selection heads of its KV head: eight lanes read them
+constexpr int64_t kTwoMaxWords = 4096;  // bitmap words of a KV head's columns
 inline bool plan_in_two(const Geo& tg) {
   const int64_t heads = tg.mode == SB_SELECT_PER_QHEAD ? tg.G : 1;
-  return tg.S <= kLaneSeqs && tg.NQB <= kTwoMaxTiles && heads * ((tg.n_max + 31) / 32) <= kTwoMaxWords;
+  return tg.S <= kLaneSeqs && tg.NQB <= kTwoMaxTiles && heads * tg.bm_words_unit <= kTwoMaxWords;
 }
 // the sequence of tile qb: the last one that starts at or before it
 __device__ inline int seq_of_tile(const PlanArgs& A, int qb) {

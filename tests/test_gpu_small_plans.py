@@ -31,17 +31,36 @@ def test_scores_and_selection_at_once(lens, Hq, Hkv, D, mode):
     assert torch.equal(rowptr, r.rowptr) and torch.equal(idx[:nnz], r.idx[:nnz])
 
 
-# two launches up to 512 blocks, 64 sequences and 64 bitmap words of a column; a sink fills columns and cuts them, so that sub-parts and
-# unused entries of both lists occur
-@pytest.mark.parametrize("lens,Hq,Hkv,mode", [
-    ((64 * 511 + 1,), 4, 2, 0), ((64 * 512 + 1,), 4, 2, 0), ((64 * 512,), 8, 2, 0), ((64 * 256,), 8, 1, 0), ((64 * 257,), 8, 1, 0),
-    ((0, 1, 0, 130, 0) * 13, 4, 2, 1), ((2039,), 16, 2, 0), ((1,), 1, 1, 1)])
+# (lens, Hq, Hkv, mode), in two launches: up to 512 blocks, 64 sequences and 4096 bitmap words of a KV head's columns (tests/test_launch_variants.py)
+PLANS = [((64 * 127 + 1,), 8, 1, 0, True), ((64 * 128 + 1,), 8, 1, 0, False), ((64 * 256,), 4, 2, 0, True), ((64 * 257,), 4, 2, 0, False),
+         ((64 * 363,), 2, 2, 1, False), ((64 * 341,), 2, 2, 1, True), ((64 * 20,) * 25 + (64 * 12,), 4, 2, 0, True), ((64 * 20,) * 25 + (64 * 13,), 4, 2, 0, False),
+         ((0, 1, 0, 130) * 16, 4, 2, 1, True), ((0, 1, 0, 130, 0) * 13, 4, 2, 1, False), ((700, 64 * 40, 1, 64 * 9), 8, 2, 0, True), ((2039,), 16, 2, 0, True),
+         ((1,), 1, 1, 1, True)]
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,mode", [p[:4] for p in PLANS])
 def test_plans_of_two_launches(lens, Hq, Hkv, mode):
     w = synth.small_ragged(seed=520 + Hq, lens=lens, Hq=Hq, Hkv=Hkv, D=64, ratio=(0.05, 0.2))
     r = Run(w, mode)
     check_plan(r)
     if w.T <= 4096:
         print(w, check_attention(r), flush=True)
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,mode", [p[:4] for p in PLANS if p[0][0] >= 64 * 127 or p[0][0] == 700])
+def test_plans_of_two_launches_with_a_sink(lens, Hq, Hkv, mode):
+    """Every row keeps block 0: its column is cut where it has more than 512 tiles, and walked by several workgroups, so that entries of both
+    lists are used and others are not."""
+    w = synth.Workload("sink", list(lens), Hq, Hkv, 64, topk=[3] * len(lens), seed=525 + Hq)
+    r = Run(w, mode, sel_override=synth.sink_selection(w.cu, 64, w.topk, Hq if mode == 0 else Hkv))
+    check_plan(r)
+    pv = sb.plan_views(r.pb, r.plan)
+    if Hkv * r.pb.layout.num_qblocks < 1024:  # (more columns fill the chip uncut)
+        assert pv["sub_slots_used"] > 0
+    # (cut where the tiles of its words of 32 rows but the first are 512 and more)
+    assert (len(pv["split_cols"]) > 0) == (Hq // Hkv * (-(-max(lens) // 64) - 32) >= 512)
+    items = pv["bwd_items"][:, 0]
+    assert 0 < (items >= 0).sum() <= len(items)
 
 
 def test_plan_in_a_buffer_that_held_another():

@@ -10,6 +10,7 @@ import pytest
 
 import test_gpu_deals as deals
 import test_gpu_head_rows as rows
+import test_gpu_small_plans as small
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -25,6 +26,9 @@ pb.c.cu_seqlens_dev = pb.c.topk_dev = 4096
 b, lib, p = C.c_void_p(4096), sb.lib(), pb.ref()
 sb._check(lib.sb_sparse_attn_fwd(p, b, b, b, b, b, b, b, b, b, None))
 sb._check(lib.sb_sparse_attn_bwd(p, b, b, b, b, b, b, b, b, b, b, b, b, b, None))
+if len(sys.argv) > 3:  # the plan, and scores with a selection
+    sb._check(lib.sb_plan_worklist(p, b, b, b, None))
+    sb._check(lib.sb_score_select(p, b, b, None, b, b, b, b, None))
 out = np.zeros((256, 6), dtype=np.uint32)
 for i in range(shim.recorded_launches(out.ctypes.data_as(C.c_void_p))):
     print("kernel", shim.recorded_kernel(i).decode(), out[i][0])
@@ -33,12 +37,12 @@ for i in range(shim.recorded_launches(out.ctypes.data_as(C.c_void_p))):
 
 @pytest.fixture(scope="module")
 def launches(tmp_path_factory):
-    """(lens, topk, mode, Hq, Hkv, D) -> [(kernel, workgroups)] of a forward and a backward"""
+    """(lens, topk, mode, Hq, Hkv, D) -> [(kernel, workgroups)] of a forward and a backward, and of plan and selection if asked for"""
     shim = str(tmp_path_factory.mktemp("launch") / "record_launches.so")
     subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", shim, os.path.join(ROOT, "tests", "launch", "record_launches.c")], check=True)
 
-    def of(*problem):
-        r = subprocess.run([sys.executable, "-c", CALLS, shim, json.dumps(problem)], cwd=ROOT, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    def of(*problem, before=()):
+        r = subprocess.run([sys.executable, "-c", CALLS, shim, json.dumps(problem), *before], cwd=ROOT, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
         assert r.returncode == 0, r.stdout[-3000:]
         return [(l.split()[1], int(l.split()[2])) for l in r.stdout.splitlines() if l.startswith("kernel ")]
 
@@ -109,3 +113,10 @@ def test_how_items_are_handed_out(launches, shape, forward, dq, columns):
             n = Hkv * (blocks + workgroups)
             forms["columns"] = {n: False, n + n // 8: True}[column_workgroups]
     assert (forms["fwd"], forms["bwd_dq"], forms["columns"]) == (forward, dq, columns)
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,mode,two", small.PLANS)
+def test_launches_of_a_plan(launches, lens, Hq, Hkv, mode, two):
+    names = [name for name, _ in launches(lens, [3] * len(lens), mode, Hq, Hkv, 64, before=["plan"])]
+    form = "ILb%dEE" % two
+    assert [f for n in names if (f := re.search("plan_(?:lists|bwd_order)_kernel(I.*?EE)", n))] and all(form in n for n in names if "plan_" in n), names
