@@ -85,7 +85,7 @@ class Run:
         return tuple(synth.round_to_bf16(t[n]) for n in ("q", "k", "v", "do"))
 
 
-# Tolerance of the benchmark spec's metric: bf16 outputs against the float64 checker, max-abs 2e-2 and mean-abs 2e-3.
+# Tolerance: bf16 outputs against the float64 checker, max-abs 2e-2 and mean-abs 2e-3.
 # An output stored as bf16 carries a rounding error of its own of up to half a unit in the last place, 2^-9 |x|
 # (0.016 at |x| = 8, and dV reaches 7-8 on dense rows), which the absolute bound cannot see; so every element is held to
 #     |got - ref| <= 2e-2 + 2^-8 |ref|

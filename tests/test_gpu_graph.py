@@ -12,12 +12,15 @@ from paper_2604_13847_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("case", ["small", "ticketed"])
+@pytest.mark.parametrize("case", ["small", "ticketed", "drawn"])
 def test_captured_step_replays_bitwise(case):
-    """"ticketed": more than 4096 query-major items, so the forward and dQ launches hand the tail of their work list out
-    through ticket counters that a fill kernel clears in every step; this step also scores and selects in one kernel."""
+    """"ticketed": more than 4096 query-major items, so launches hand items out
+    through ticket counters that a fill kernel clears in every step; this step also scores and selects in one kernel.  "drawn": rows of 27 to 42 tiles at head_dim 128,
+    where workgroups draw one item after the other."""
     if case == "small":
         w = synth.small_ragged(seed=2, lens=(700, 64, 1, 2100, 333), Hq=8, Hkv=2, D=128, ratio=(0.2, 0.6))
+    elif case == "drawn":
+        w = synth.small_ragged(seed=4, lens=(64 * 520 - 9, 700), Hq=8, Hkv=8, D=128, ratio=(0.053, 0.08))
     else:
         w = synth.small_ragged(seed=4, lens=(64 * 520 - 9, 700, 1), Hq=8, Hkv=2, D=64, ratio=(0.03, 0.08))
     topk = sb.sb_keep_ratio_to_topk(w.cu, w.B, w.keep_ratio)

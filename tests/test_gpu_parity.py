@@ -362,7 +362,7 @@ def test_score_select_in_one_call(mode):
 
 @pytest.mark.parametrize("mode,Hq,Hkv,lens", [(0, 8, 2, (64 * 300, 64 * 250 + 5)), (1, 8, 4, (64 * 560 - 3, 64 * 470))])
 def test_ticketed_launches_elementwise(mode, Hq, Hkv, lens):
-    """More than 4096 query-major items: the forward and dQ launches hand items out through ticket
+    """More than 4096 query-major items: launches hand items out through ticket
     counters.  Every output element is compared, so an item that no workgroup took, or that two
     took, would show; per-query-head selection with one head per workgroup, and per-KV-group selection with the group's
     two heads in one workgroup."""

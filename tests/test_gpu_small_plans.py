@@ -1,5 +1,7 @@
 """Forms that small problems take: scores and selection by one kernel that writes the matrix too, plans of two launches, and the walk of
 key-major columns of few tiles; and the histogram sort of the coverage curves.  Sizes lie at the edges of each rule."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -14,20 +16,28 @@ from test_gpu_parity import check_attention, check_plan
 pytestmark = pytest.mark.gpu
 
 
-# (groups of 16 blocks) x (selection heads) up to 256 take one kernel; 65 sequences read tables instead of lanes
-@pytest.mark.parametrize("lens,Hq,Hkv,D,mode", [
-    ((64 * 511 + 1,), 8, 8, 128, 0), ((64 * 512 + 1,), 8, 8, 128, 0), ((1,), 1, 1, 64, 0), ((64, 1, 0, 65) * 9, 6, 2, 64, 1),
-    ((1, 63, 700) * 22, 4, 2, 128, 1), ((64 * 16, 64 * 15 + 1, 64 * 17 - 1), 4, 4, 64, 0), ((100,) * 40, 16, 2, 128, 0)])
+# (lens, Hq, Hkv, D, mode), by one kernel: up to 256 workgroups (16 blocks and a selection head each) and 448 blocks a sequence, whose keys fit the
+# LDS (tests/test_launch_variants.py); from 257 blocks on a wavefront computes more than one tile, 65 sequences read tables instead of lanes
+AT_ONCE = [((64 * 447 + 1,), 8, 8, 128, 0, True), ((64 * 448 + 1,), 8, 8, 128, 0, False), ((64 * 300,), 8, 2, 64, 1, True), ((64 * 256,), 16, 2, 128, 0, True),
+           ((64 * 257,), 16, 2, 128, 0, False), ((64 * 128,), 32, 8, 64, 0, True), ((64 * 128, 1), 32, 8, 64, 0, False), ((1,), 1, 1, 64, 0, True),
+           ((64, 1, 0, 65) * 9, 6, 2, 64, 1, True), ((1, 63, 700) * 22, 4, 2, 128, 1, True), ((64 * 16, 64 * 15 + 1, 64 * 17 - 1), 4, 4, 64, 0, True),
+           ((100,) * 40, 16, 2, 128, 0, True)]
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,D,mode", [a[:5] for a in AT_ONCE])
 def test_scores_and_selection_at_once(lens, Hq, Hkv, D, mode):
-    """The same bits as sb_block_scores and sb_select_topk, -infinity included."""
+    """The same bits as sb_block_scores and sb_select_topk, -infinity included, in buffers that held NaN and -1."""
     w = synth.small_ragged(seed=500 + Hq, lens=lens, Hq=Hq, Hkv=Hkv, D=D, ratio=(0.1, 0.9))
     r = Run(w, mode, do_bwd=False)
-    n, nnz = r.pb.layout.scores_elems, int(r.rowptr_h[-1])
-    del_me = torch.full_like(r.scores, float("nan"))
-    del del_me  # (the allocator hands the same memory out again)
-    scores, rowptr, idx = sb.sb_score_select(r.pb, r.q, r.k)
+    lay, nnz = r.pb.layout, int(r.rowptr_h[-1])
+    scores = torch.full((lay.scores_elems,), float("nan"), device=DEV)
+    rowptr, idx = (torch.full((n,), -1, dtype=torch.int32, device=DEV) for n in (lay.sel_rows + 1, lay.sel_nnz))
+    ws = torch.empty(lay.scores_ws_bytes, dtype=torch.uint8, device=DEV)
+    ptr = lambda x: C.c_void_p(x.data_ptr()) if x is not None else None
+    rc = sb.lib().sb_score_select(r.pb.ref(), *map(ptr, (r.q, r.k, None, scores, rowptr, idx, ws)), C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0, sb.lib().sb_last_error().decode()
     torch.cuda.synchronize()
-    assert torch.equal(scores[:n].view(torch.int32), r.scores[:n].view(torch.int32))
+    assert torch.equal(scores.view(torch.int32), r.scores[: lay.scores_elems].view(torch.int32))
     assert torch.equal(rowptr, r.rowptr) and torch.equal(idx[:nnz], r.idx[:nnz])
 
 
@@ -124,6 +134,18 @@ def test_coverage_sorted_by_a_histogram(kind, n):
     sc = KINDS[kind](np.random.default_rng(n), (Hs, n, n)).astype(np.float32)
     sc[:, :, 0] = np.where(np.isfinite(sc[:, :, 0]), sc[:, :, 0], 0.0)  # (a row without any finite score has no softmax)
     check_curves(sc)
+
+
+# up to 64 sequences the kernel of the rows writes the tables that the column sums read, beyond them a kernel before it
+@pytest.mark.parametrize("lens", [(0, 700, 0, 1), (64 * 300, 0, 0), (0, 130, 64) * 21 + (0,), (0, 130, 64) * 22])
+def test_coverage_of_packs_with_empty_sequences(lens):
+    rng, cu = np.random.default_rng(7), np.concatenate([[0], np.cumsum(lens)])
+    po = orc.Problem(cu, 2, 1, 64, 64, 0)
+    sc = rng.normal(size=sum(2 * n * n for n in po.nblk)).astype(np.float32)
+    pb = sb.Problem(cu, [8] * len(lens), 2, 1, 64, 64, device=DEV)
+    ws = torch.full((pb.layout.coverage_ws_bytes,), 0x7f, dtype=torch.uint8, device=DEV)
+    got = sb.sb_score_coverage(pb, torch.from_numpy(sc).to(DEV), ws=ws).cpu().numpy()[: po.NQB]
+    assert np.abs(got - dst.coverage_curves(po.nblk, 2, sc, po.score_off)).max() <= 2e-6
 
 
 @pytest.mark.parametrize("Hs", [1, 3, 5, 11, 40])

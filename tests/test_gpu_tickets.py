@@ -1,5 +1,5 @@
-"""Lists that are handed out by ticket: forward and dQ launches whose workgroups draw item after item, and the key-major launch, whose
-last columns are drawn.  Every element against the float64 checker, so that an item that nobody drew shows, and the same bits from a
+"""Lists that are handed out by ticket: query-major launches that hold items back, and the key-major launch, whose
+last columns are drawn (tests/test_gpu_deals.py has every form).  Every element against the float64 checker, so that an item that nobody drew shows, and the same bits from a
 second run, whoever draws what."""
 import numpy as np
 import pytest

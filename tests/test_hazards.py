@@ -138,7 +138,8 @@ def assembly(source):
         return open(out).read().splitlines()
 
 
-@pytest.mark.parametrize("source,stated", [("sb_attn_fwd.hip", {}), ("sb_attn_bwd.hip", {"attn_bwd_dq_head_kernelILi64E": 5})])
+@pytest.mark.parametrize("source,stated", [("sb_attn_fwd.hip", {}), ("sb_attn_bwd.hip", {"attn_bwd_dq_head_kernelILi64E": 5}), ("sb_topk.hip", {}),
+                                           ("sb_scores.hip", {"score_kernelILi128ELi2E": 8}), ("sb_coverage.hip", {}), ("sb_plan.hip", {})])
 def test_no_kernel_spills_more_vector_registers_than_its_comment_says(source, stated):
     """The compiler's own count.  A spilled register costs a load or store to memory inside loops that are bound by instruction issue, and
     makes no test fail: sixteen in attn_fwd_group_kernel went unseen."""
@@ -150,7 +151,7 @@ def test_no_kernel_spills_more_vector_registers_than_its_comment_says(source, st
         elif m and m[1] == "vgpr_spill_count":
             seen += 1
             assert int(m[2]) <= max((n for k, n in stated.items() if k in name), default=0), (name, m[2])
-    assert seen >= 10
+    assert seen >= 4
 
 
 @pytest.mark.parametrize("source", ["sb_topk.hip", "sb_coverage.hip"])

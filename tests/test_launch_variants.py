@@ -120,3 +120,10 @@ def test_launches_of_a_plan(launches, lens, Hq, Hkv, mode, two):
     names = [name for name, _ in launches(lens, [3] * len(lens), mode, Hq, Hkv, 64, before=["plan"])]
     form = "ILb%dEE" % two
     assert [f for n in names if (f := re.search("plan_(?:lists|bwd_order)_kernel(I.*?EE)", n))] and all(form in n for n in names if "plan_" in n), names
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,D,mode,one", small.AT_ONCE)
+def test_launches_of_scores_with_a_selection(launches, lens, Hq, Hkv, D, mode, one):
+    names = [name for name, _ in launches(lens, [3] * len(lens), mode, Hq, Hkv, D, before=["plan"])]
+    forms = [f[0] for n in names if (f := re.search("score_select_kernel|score_kernel|topk_kernel", n))]
+    assert forms == (["score_select_kernel"] if one else ["score_kernel", "topk_kernel"])
