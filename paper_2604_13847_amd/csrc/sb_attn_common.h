@@ -37,8 +37,8 @@ struct AttnParams {
   float scale, scale_log2e;
   int out_f32;
   unsigned long long* cu_busy;  // null when instrumentation is off
-  // Work distribution (see draw_item)
-  int* ticket;        // 8 counters, zero at launch (the group kernel: 8 per head plane); null: every item is taken by position
+  // Work distribution (see held_item, draw_item and ItemQueue)
+  int* ticket;        // counters, zero at launch: 8, or one for items that are held back (the group kernel: one per head plane); null: every item is taken by position
   int n_items;        // query-major items
   int deal;           // Deal, of a launch of one query head per item
 };
@@ -109,9 +109,9 @@ inline int64_t head_grid(const AttnParams& P, int heads, int nw) {
   const int64_t ids = head_ids(P.n_items, heads);
   return P.deal == kDealDraw ? 1024 / nw : P.deal == kDealLast ? last_grid(ids) : P.deal == kDealHeld ? held_grid(ids) : ids;
 }
-// The items of one workgroup.  A launch without tickets: workgroup w takes item w.  With tickets at D = 128, where a wavefront fills its
-// SIMD: as many workgroups as the chip runs at a time, which draw one item after the other.  At D = 64 workgroups take one item each, the
-// last ones by ticket: there the next workgroup's start overlaps the end of the last (drawing all: forward of 65536 tokens, 14/2 heads,
+// The items of one workgroup.  By position: workgroup w takes item w.  Held back: one item each too, the last ones by ticket.  Drawn at D = 128, where a
+// wavefront fills its SIMD: as many workgroups as the chip runs at a time, which draw one item after the other.  At D = 64 workgroups take one item each, the
+// last quarter by ticket: there the next workgroup's start overlaps the end of the last (drawing all: forward of 65536 tokens, 14/2 heads,
 // blocks of 256 1.40 -> 1.44 ms).  At D = 128 the draw takes the place of a workgroup's start, against a quarter of the items by ticket, one a
 // workgroup: the forward of 65536 tokens whose selection is a sink and a window 1.76 -> 1.66 ms, dQ 2.13 -> 2.06, of 131072 items of one or
 // four tiles 650 -> 613 us and 1.19 -> 1.15 ms.  (The draw ahead of an item's output: 2 % faster on rows of 32 tiles, 4 % slower on short ones.)

@@ -1,6 +1,6 @@
 // Pieces shared by the score kernel, the selection kernel and the kernel that does both (paper
 // section 2.2): the 16 x 16 score tile on the fp32 matrix cores, the order-preserving key of a
-// score, and the per-row selection that one wavefront carries out on keys held in LDS.
+// score, and the per-row selection that one wavefront carries out on keys held in registers or LDS.
 // Every path that produces a score goes through score_tile16 with the same operands in the same
 // order, and every path that selects goes through select_row, so the paths agree bit for bit.
 #pragma once
@@ -68,9 +68,11 @@ __device__ inline int64_t sel_rows_before(int i, int k) {
   return (int64_t)m0 * (m0 + 1) / 2 + (int64_t)(i - m0) * k;
 }
 
-// One wavefront chooses the `need` best of keys[0..m) (0 < need < m; ties to the lower index) and
-// writes their indices in ascending order to out[0..need), then i to out[need].  keys and hist (256
-// bins) are this wavefront's own LDS; the keys must be visible to it on entry.
+// select_row: one wavefront chooses the `need` best of m keys (0 < need < m; ties to the lower index) and
+// writes their indices in ascending order to out[0..need), then i to out[need].  It sees the keys through `walk(f)`, which
+// calls f(j, key j, j < m) on every lane for its keys j = lane, lane + 64, ...: walk_registers, or walk_keys for keys in LDS, which
+// have to be visible to the wavefront on entry (a fence).  `hist`: 256 words of LDS, the wavefront's own.  `largest`: no smaller than any of
+// the lane's own keys j < m and no larger than the row's largest (distances from the row's largest key are unsigned).
 // The threshold (the need-th largest key, and how many keys equal to it are kept) comes from one of
 // two exact searches.  Small budgets: a histogram of the keys' distance from the row's largest key in
 // steps of 2^17 (keys of floats are logarithmic, so 255 such bins span the top four octaves whatever
@@ -117,7 +119,6 @@ __device__ __forceinline__ void walk_registers(const uint32_t (&keys)[E], int la
   }
 }
 
-// `walk(f)`: one of the two above.  `largest`: the largest of this lane's keys lane, lane + 64, ...
 template <typename W>
 __device__ inline void select_row(W walk, int* hist, int lane, int m, int need, int i, int32_t* __restrict__ out, uint32_t largest) {
   const unsigned long long lt = (1ull << lane) - 1ull;

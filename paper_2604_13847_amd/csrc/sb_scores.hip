@@ -69,7 +69,7 @@ __global__ __launch_bounds__(256) void pool_kernel(const void* __restrict__ Q, c
 // workgroups keeps the longest workgroup short however long the sequence is.
 // What bounds it: the matrix takes 0.11 ms to write and 0.11 ms of the fp32 matrix cores (131072 tokens, 32 heads: 537 MB), and a
 // workgroup waits between two barriers per tile, so it needs others beside it: with the query tile in LDS too two of them fitted a CU,
-// without it four, at 128 registers: 0.306 -> 0.229 ms.
+// without it four, at 128 registers, eight of them spilled (addresses, read back once a key tile): 0.306 -> 0.229 ms.
 // A key tile takes a workgroup 2 us, so where four to a workgroup make fewer workgroups than the chip runs at once, each gets one
 // (18889 tokens, 32/8 heads: 27 -> 21 us, 26565 tokens in several sequences, 16/2 heads: 22 -> 17); otherwise four, which share the query rows.
 constexpr int kScChunkLog = 2;
